@@ -146,4 +146,19 @@ __device__ __forceinline__ uint4 scale_chunk(uint4 v, float s) {
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// Arguments of the fused GEMM kernels.
+struct GemmArgs {
+    const u16* Aop; int64_t lda;   // X [T,k] (fwd) or dY [T,n] (bwd)
+    const u16* Bop; int64_t ldb;   // W [k,n]
+    u16* C; int64_t ldc;           // Y [T,n] or dX [T,k]
+    const u16* E;                  // ragged S (fwd) or dS (bwd)
+    int32_t M, Ncols, Kdim;
+    int32_t tiles_m, tiles_n;
+    int32_t skip_lora;             // MLORA_FLAG_BASE_ONLY, or a plan without adapters (the LoRA-only mode has a kernel of its own)
+    int32_t stream_out;            // write the output with streaming stores (see launch_gemm)
+    int32_t band_group;            // bands whose column groups are interleaved (see the tile order)
+    int32_t xcd_run;               // small-tile kernel: consecutive tiles per XCD (see its tile order)
+    PlanView pv;
+};
+
 }  // namespace mlora

@@ -52,19 +52,6 @@ __device__ __forceinline__ void wait_all_and_barrier() {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-struct GemmArgs {
-    const u16* Aop; int64_t lda;   // X [T,k] (fwd) or dY [T,n] (bwd)
-    const u16* Bop; int64_t ldb;   // W [k,n]
-    u16* C; int64_t ldc;           // Y [T,n] or dX [T,k]
-    const u16* E;                  // ragged S (fwd) or dS (bwd)
-    int32_t M, Ncols, Kdim;
-    int32_t tiles_m, tiles_n;
-    int32_t skip_lora;             // MLORA_FLAG_BASE_ONLY, or a plan without adapters (the LoRA-only mode has a kernel of its own)
-    int32_t stream_out;            // write the output with streaming stores (see launch_gemm)
-    int32_t band_group;            // bands whose column groups are interleaved (see the tile order)
-    PlanView pv;
-};
-
 // One masked operand pass staged into the first row-operand stage and the first weight slot.  Used for the rank extension
 // (rows owned by one adapter, contraction = rank) and for the tail of a contraction that is not a
 // multiple of 64.  All arguments are uniform over the workgroup.
@@ -595,6 +582,10 @@ __global__ __launch_bounds__(NTHR) void fused_gemm_kernel(GemmArgs g) {
     }
 }
 
+// mfma_gemm_small.hip
+int small_gemm_tile(int64_t M, int64_t N, int64_t K, int num_cus);
+void launch_small_gemm(int tile, const GemmArgs& g, bool fwd, hipStream_t st);
+
 static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, void* C, const void* E,
                        uint32_t flags, hipStream_t st) {
     if (p->T == 0) return MLORA_OK;
@@ -630,6 +621,13 @@ static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, 
     else if (p->k * p->n * 2 > kHalfCache)
         while (g.band_group < 4 && int64_t(2 * g.band_group) * kGemmBandTiles * BM * g.Kdim * 2 <= kHalfCache) g.band_group *= 2;
     g.pv = p->view;
+    const int small = small_gemm_tile(g.M, g.Ncols, g.Kdim, p->num_cus);
+    if (small >= 0) {
+        ProfScope prof(p, fwd ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
+        launch_small_gemm(small, g, fwd, st);
+        MLORA_HIP_TRY(hipGetLastError());
+        return MLORA_OK;
+    }
     const int total = g.tiles_m * g.tiles_n;
     const int grid = ((total + 255) / 256) * 256;    // whole groups of 32 tiles for each of the 8 XCDs
     ProfScope prof(p, fwd ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);

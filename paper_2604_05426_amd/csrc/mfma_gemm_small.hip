@@ -1,0 +1,418 @@
+// Fused frozen-weight GEMM + LoRA expand for shapes that give the 256 x 256 kernel too few tiles to fill the chip
+// (short batches, narrow projections): Y = X W + s_i S_i B_i and dX = dY W^T + dS_i A_i^T (paper Sec. 5.1 / App. A.1),
+// one store of the output, like the large-tile kernel.
+//
+// With one 256 x 256 tile per CU a layer of 1024 x 4096 outputs keeps 64 of 256 CUs busy for the whole contraction; 128 x 128
+// tiles keep all of them busy.  What bounds a CU then is the operand stream (32 KB per 64-wide step against 512 cycles of MFMA)
+// and, before that, latency, so the tiles come by direct global -> LDS loads into a ring that fills the LDS (all but the
+// current step in flight, one barrier per step) and the fragments of step t + 1 are read while step t is multiplied.
+// 8 wavefronts: 2 x 2 sub-tiles of the output, times two halves of each 64-wide contraction step.  Splitting the step instead of
+// the tile keeps the sub-tile of a wavefront at 64 x 64 (LDS reads per MFMA as low as four wavefronts would have) with two
+// wavefronts per SIMD; the two partial accumulators are added once at the end, in a fixed order.
+//
+// Rank extension: adapter by adapter into a second accumulator set, of which the adapter's own rows are then taken over (scaled
+// in fp32).  Rows of other adapters never reach the result, so no operand has to be masked and a diverged neighbour's Inf / NaN
+// stays out of it.
+//
+// 1024 x 4096 outputs, k = 4096: 104-106 -> 37-39 us; 230 x 512, k = 2048: 56 -> 13 us.  A 128 x 128 work group spends 0.35 us
+// per step with few neighbours (32 KB at the 45-50 B/clk a CU's load path takes; loads that always hit: 0.30) and 0.43-0.50 us
+// with all CUs busy, where the MFMAs alone would take 0.21.
+#include "mfma_common.h"
+
+namespace mlora {
+
+namespace {
+
+constexpr int SG_THREADS = 512;
+constexpr int SG_LDS = 163840;
+
+template <int N> __device__ __forceinline__ void wait_loads_and_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <bool NN, int BM, int BN>
+__global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
+    constexpr int AT = BM * 128, BT = BN * 128, STAGE = AT + BT;   // bytes: operand tiles of one 64-wide step
+    constexpr int NST = SG_LDS / STAGE < 8 ? SG_LDS / STAGE : 8;   // ring stages
+    constexpr int NA = BM / 64, NB_ = BN / 64, LPS = NA + NB_;     // direct loads per wavefront and step
+    constexpr int WTM = BM / 2, WTN = BN / 2;                      // sub-tile of a wavefront
+    constexpr int MB = WTM / 16, NB = WTN / 16;
+    constexpr int BROW = BN * 2;                                   // NN: bytes per contraction row of the weight tile
+    static_assert(LPS * (NST - 2) < 64, "vmcnt holds 6 bits");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    const int l16 = lane & 15, g4 = lane >> 4;
+
+    // Tile order: bands of 8 row tiles x all column tiles, numbered down the rows first; every XCD (blockIdx % 8) takes runs of
+    // `xcd_run` consecutive tiles, which share operand panels in its L2.  At most 32 (its CUs), fewer if that is what spreads a
+    // launch of less than 256 tiles over all eight.
+    const int total = g.tiles_m * g.tiles_n;
+    const int xcd = blockIdx.x % 8, slot_x = blockIdx.x / 8;
+    const int L = ((slot_x / g.xcd_run) * 8 + xcd) * g.xcd_run + slot_x % g.xcd_run;
+    if (L >= total) return;
+    const int per_band = 8 * g.tiles_n;
+    const int band = L / per_band, in_band = L - band * per_band;
+    const int band_rows = min(8, g.tiles_m - band * 8);
+    const int tm = band * 8 + in_band % band_rows, tn = in_band / band_rows;
+    const int m0 = tm * BM, n0 = tn * BN;
+
+    // swizzle key of contraction row k of the NN weight tile
+    auto fkey = [](int k) { return BN == 128 ? nn_swz(k) : (((k >> 1) & 1) | (((k >> 3) & 1) << 1)); };
+
+    // ---- direct loads ---------------------------------------------------------------------------
+    const int nk = g.Kdim / 64;
+    unsigned oa[NA], ob[NB_];
+#pragma unroll
+    for (int c = 0; c < NA; ++c) {
+        const int row = (wave * NA + c) * 8 + (lane >> 3), ch = (lane & 7) ^ (lane >> 3);
+        oa[c] = (unsigned)((int64_t)(min(m0 + row, g.M - 1) - m0) * g.lda + ch * 8) * 2u;
+    }
+#pragma unroll
+    for (int c = 0; c < NB_; ++c) {
+        const int kb = wave * NB_ + c;
+        if (NN) {
+            constexpr int LPR = BROW / 16;
+            const int k = kb * (64 / LPR) + lane / LPR, pos = lane % LPR;
+            const int chunk = (((pos >> 1) ^ fkey(k)) << 1) | (pos & 1);
+            ob[c] = (unsigned)((int64_t)k * g.ldb + min(n0 + chunk * 8, g.Ncols - 8)) * 2u;
+        } else {
+            const int row = kb * 8 + (lane >> 3), ch = (lane & 7) ^ (lane >> 3);
+            ob[c] = (unsigned)((int64_t)(min(n0 + row, g.Ncols - 1) - n0) * g.ldb + ch * 8) * 2u;
+        }
+    }
+    const char* baseA = uniform_ptr(g.Aop + (int64_t)m0 * g.lda);
+    const char* baseB = NN ? uniform_ptr(g.Bop) : uniform_ptr(g.Bop + (int64_t)n0 * g.ldb);
+    const int64_t bstep = NN ? (int64_t)64 * g.ldb * 2 : 128;
+    const unsigned lds0 = (unsigned)(uintptr_t)lds;
+    int slot_in = 0;
+    auto issue1 = [&](int c) {           // load c (of LPS) of the next step's tiles into the next ring slot
+        const unsigned dst = lds0 + slot_in * STAGE;
+        if (c < NA) dma16(oa[c < NA ? c : 0], baseA, dst + (wave * NA + c) * 1024);
+        else        dma16(ob[c < NA ? 0 : c - NA], baseB, dst + AT + (wave * NB_ + c - NA) * 1024);
+        if (c == LPS - 1) {
+            baseA += 128; baseB += bstep;
+            slot_in = slot_in == NST - 1 ? 0 : slot_in + 1;
+        }
+    };
+    auto issue = [&]() {
+#pragma unroll
+        for (int c = 0; c < LPS; ++c) issue1(c);
+    };
+    // all slots but the last, which the rank extension uses first
+    const int early = min(nk, NST - 1);
+    for (int t = 0; t < early; ++t) issue();
+
+    // ---- fragments and MFMAs ----------------------------------------------------------------------
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int a = 0; a < MB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 fa[2][MB], fb[2][NB];
+    const int a_off = (wm * WTM + l16) * 128 + (((kg * 4 + g4) ^ (l16 & 7)) << 4);
+    const int bnt_off = (wn * WTN + l16) * 128 + (((kg * 4 + g4) ^ (l16 & 7)) << 4);
+    const int vq = fkey(8 * g4 + (l16 >> 2));
+    const int bnn_off = (kg * 32 + 8 * g4 + (l16 >> 2)) * BROW + (l16 & 3) * 8;
+    auto read_frag_a = [&](int slot, int buf, int a) {
+        fa[buf][a] = lds_read_frag(reinterpret_cast<const u16*>(lds + slot * STAGE + a_off + a * 2048));
+    };
+    auto read_frag_b = [&](int slot, int buf, int b) {
+        const unsigned char* Bs = lds + slot * STAGE + AT;
+        if (NN) {
+            const unsigned char* p = Bs + bnn_off + (((wn * NB + b) ^ vq) << 5);
+            fb[buf][b] = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * BROW));
+        } else {
+            fb[buf][b] = lds_read_frag(reinterpret_cast<const u16*>(Bs + bnt_off + b * 2048));
+        }
+    };
+    auto read_frags = [&](int slot, int buf) {
+#pragma unroll
+        for (int a = 0; a < MB; ++a) read_frag_a(slot, buf, a);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) read_frag_b(slot, buf, b);
+    };
+    // ask the scheduler to alternate a group's LDS reads with its MFMAs
+    auto interleave = [&]() {
+        for (int i = 0; i < NB; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // operands swapped: a lane ends with one output row and 4 consecutive columns of each 16 x 16 block
+    auto mma = [&](f32x4 (&c)[MB][NB], int buf) {
+#pragma unroll
+        for (int a = 0; a < MB; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) c[a][b] = mfma16(fb[buf][b], fa[buf][a], c[a][b]);
+    };
+
+    // Operands that are not whole aligned 64-wide steps (rank extension, tail of the contraction) go through registers into the
+    // last slot, zero-filled up to a multiple of 32 in the contraction.
+    unsigned char* const Ps = lds + (NST - 1) * STAGE;
+    uint4 pa[NA], pb[NB_];
+    auto pass_load = [&](const u16* a_src, int64_t a_ld, int a_lo, int a_hi, bool a_vec, const u16* b_src, int64_t b_ld, bool b_vec,
+                         int kc) {                  // a_src: row a_lo
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+            const int idx = tid + SG_THREADS * c, t = m0 + (idx & (BM - 1)), cc = idx / BM;
+            pa[c] = zero4();
+            if (t >= a_lo && t < a_hi && cc * 8 < kc) pa[c] = load_chunk(a_src + (int64_t)(t - a_lo) * a_ld + cc * 8, min(8, kc - cc * 8), a_vec);
+        }
+#pragma unroll
+        for (int c = 0; c < NB_; ++c) {
+            const int idx = tid + SG_THREADS * c;
+            pb[c] = zero4();
+            if (NN) {
+                const int k = idx / (BN / 8), gcol = n0 + (idx % (BN / 8)) * 8;
+                if (k < kc && gcol < g.Ncols) pb[c] = *reinterpret_cast<const uint4*>(b_src + (int64_t)k * b_ld + gcol);
+            } else {
+                const int gcol = n0 + (idx & (BN - 1)), cc = idx / BN;
+                if (gcol < g.Ncols && cc * 8 < kc) pb[c] = load_chunk(b_src + (int64_t)gcol * b_ld + cc * 8, min(8, kc - cc * 8), b_vec);
+            }
+        }
+    };
+    auto pass_store = [&](int kc) {
+        const int kpad = (kc + 31) & ~31;
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+            const int idx = tid + SG_THREADS * c, row = idx & (BM - 1), cc = idx / BM;
+            if (cc * 8 < kpad) *reinterpret_cast<uint4*>(Ps + row * 128 + ((cc ^ (row & 7)) << 4)) = pa[c];
+        }
+#pragma unroll
+        for (int c = 0; c < NB_; ++c) {
+            const int idx = tid + SG_THREADS * c;
+            if (NN) {
+                const int k = idx / (BN / 8), nc = idx % (BN / 8);
+                if (k < kpad) *reinterpret_cast<uint4*>(Ps + AT + k * BROW + ((((nc >> 1) ^ fkey(k)) << 5) | ((nc & 1) << 4))) = pb[c];
+            } else {
+                const int row = idx & (BN - 1), cc = idx / BN;
+                if (cc * 8 < kpad) *reinterpret_cast<uint4*>(Ps + AT + row * 128 + ((cc ^ (row & 7)) << 4)) = pb[c];
+            }
+        }
+    };
+
+    // ---- rank extension -----------------------------------------------------------------------------
+    // Lane l holds the metadata of candidate adapter base + l, so that walking the adapters of a tile costs no memory round
+    // trips; the operands of the next pass are in flight while one is multiplied.
+    if (!g.skip_lora) {
+        const Entry4 tile = g.pv.gemm_tiles[m0 / kGemmTileRows];
+        const int m_end = min(g.M, m0 + BM);
+        for (int base = tile.c; base < tile.d; base += 64) {
+            const int cand = min(base + lane, tile.d - 1);
+            const int v_rank = g.pv.rank[cand], v_off = g.pv.off[cand], v_end = g.pv.off[cand + 1];
+            const int64_t v_so = g.pv.soff[cand];
+            const uint64_t v_f = reinterpret_cast<uint64_t>(NN ? g.pv.ptrs[cand].B : g.pv.ptrs[cand].A);
+            const float v_sc = NN ? g.pv.scale[cand] : 1.0f;
+            uint64_t todo = __ballot(base + lane < tile.d && v_rank > 0 && max(v_off, m0) < min(v_end, m_end));
+            if (todo == 0) continue;
+            auto lane64 = [](uint64_t v, int l) {
+                return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+            };
+            int l = 0, r = 0, lo = 0, hi = 0, r0 = 0;
+            auto load_next = [&]() {               // operands of pass (adapter lane l, ranks from r0)
+                const int seg0 = __builtin_amdgcn_readlane(v_off, l);
+                r = __builtin_amdgcn_readlane(v_rank, l);
+                lo = max(seg0, m0);
+                hi = min(__builtin_amdgcn_readlane(v_end, l), m_end);
+                const int64_t so = (int64_t)lane64((uint64_t)v_so, l);
+                const u16* F = reinterpret_cast<const u16*>(lane64(v_f, l));
+                const u16* e = g.E + so + (int64_t)(lo - seg0) * r + r0;
+                const bool vec = (r & 7) == 0, e_vec = vec && (so & 7) == 0;
+                if (NN) pass_load(e, r, lo, hi, e_vec, F + (int64_t)r0 * g.Ncols, g.Ncols, true, min(64, r - r0));
+                else    pass_load(e, r, lo, hi, e_vec, F + r0, r, vec, min(64, r - r0));
+            };
+            l = (int)__builtin_ctzll(todo);
+            load_next();
+            bool first = true;
+            f32x4 ext[MB][NB];
+            for (;;) {
+                const int kc = min(64, r - r0), c_lo = lo, c_hi = hi;
+                const float sc = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v_sc), l));
+                if (r0 == 0) {
+#pragma unroll
+                    for (int a = 0; a < MB; ++a)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) ext[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+                if (!first || base != tile.c) lds_barrier();      // the previous pass has been read
+                first = false;
+                pass_store(kc);
+                const bool last_of_adapter = r0 + 64 >= r;
+                if (last_of_adapter) { todo &= todo - 1; r0 = 0; if (todo) l = (int)__builtin_ctzll(todo); }
+                else r0 += 64;
+                if (todo) load_next();
+                lds_barrier();
+                if (kg * 32 < kc) { read_frags(NST - 1, 0); mma(ext, 0); }
+                if (last_of_adapter) {
+#pragma unroll
+                    for (int a = 0; a < MB; ++a) {
+                        const int row = m0 + wm * WTM + a * 16 + l16;
+                        const bool own = row >= c_lo && row < c_hi;
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) acc[a][b][q] = own ? sc * ext[a][b][q] : acc[a][b][q];
+                    }
+                }
+                if (!todo) break;
+            }
+        }
+    }
+
+    // ---- tail of a contraction that is not a multiple of 64 -----------------------------------------
+    if ((g.Kdim & 63) != 0) {
+        const int k0 = nk * 64;
+        lds_barrier();
+        pass_load(g.Aop + (int64_t)m0 * g.lda + k0, g.lda, m0, min(g.M, m0 + BM), true, NN ? g.Bop + (int64_t)k0 * g.ldb : g.Bop + k0,
+                  g.ldb, true, g.Kdim - k0);
+        pass_store(g.Kdim - k0);
+        lds_barrier();
+        if (kg * 32 < g.Kdim - k0) { read_frags(NST - 1, 0); mma(acc, 0); }
+    }
+
+    // ---- contraction over the frozen weight -----------------------------------------------------------
+    // Step t: stage t + 1 has landed and everybody has read the fragments of stage t (its slot is free for stage t + NST);
+    // read the fragments of t + 1 while multiplying those of t.
+    if (nk >= NST) {
+        lds_barrier();                   // the pass slot has been read
+        issue();                         // stage NST - 1
+        wait_loads_and_barrier<LPS * (NST - 1)>();
+        read_frags(0, 0);
+        int nxt = 1;                     // slot of stage t + 1
+        auto step = [&](int buf) {
+            wait_loads_and_barrier<LPS * (NST - 2)>();
+#pragma unroll
+            for (int a = 0; a < MB; ++a) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int c = 0; c < LPS; ++c)
+                    if (c * MB / LPS == a) issue1(c);
+                __builtin_amdgcn_sched_barrier(0);
+                read_frag_a(nxt, buf ^ 1, a);
+#pragma unroll
+                for (int b = a * NB / MB; b < (a + 1) * NB / MB; ++b) read_frag_b(nxt, buf ^ 1, b);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[a][b] = mfma16(fb[buf][b], fa[buf][a], acc[a][b]);
+                interleave();
+            }
+            nxt = nxt == NST - 1 ? 0 : nxt + 1;
+        };
+        const int full = nk - NST;
+        int t = 0;
+        for (; t + 2 <= full; t += 2) { step(0); step(1); }
+        if (t < full) {
+            step(0);
+#pragma unroll
+            for (int a = 0; a < MB; ++a) fa[0][a] = fa[1][a];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) fb[0][b] = fb[1][b];
+        }
+        // the last NST stages: nothing left to load
+#define SG_DRAIN(J)                                                                             \
+        if (J < NST) {                                                                          \
+            if (J + 1 < NST) {                                                                  \
+                wait_loads_and_barrier<(NST - 2 - J > 0 ? NST - 2 - J : 0) * LPS>();            \
+                read_frags(nxt, (J & 1) ^ 1);                                                   \
+            }                                                                                   \
+            mma(acc, J & 1);                                                                    \
+            nxt = nxt == NST - 1 ? 0 : nxt + 1;                                                 \
+        }
+        SG_DRAIN(0) SG_DRAIN(1) SG_DRAIN(2) SG_DRAIN(3) SG_DRAIN(4) SG_DRAIN(5) SG_DRAIN(6) SG_DRAIN(7)
+        static_assert(NST <= 8, "drain steps");
+#undef SG_DRAIN
+    } else if (nk > 0) {
+        wait_loads_and_barrier<0>();
+        for (int t = 0; t < nk; ++t) { read_frags(t, 0); mma(acc, 0); }
+    }
+
+    // ---- the two contraction halves are added: each wavefront finishes half of its sub-tile's rows ------
+    lds_barrier();
+    {
+        float4* red = reinterpret_cast<float4*>(lds);
+        constexpr int HB = MB / 2 * NB;
+#pragma unroll
+        for (int a = 0; a < MB / 2; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const f32x4 v = kg == 0 ? acc[a + MB / 2][b] : acc[a][b];
+                red[(wave * HB + a * NB + b) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+            }
+        lds_barrier();
+        f32x4 sum[MB / 2][NB];
+#pragma unroll
+        for (int a = 0; a < MB / 2; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const float4 o = red[((wave ^ 4) * HB + a * NB + b) * 64 + lane];
+                const f32x4 mine = kg == 0 ? acc[a][b] : acc[a + MB / 2][b];
+                sum[a][b] = f32x4{mine[0] + o.x, mine[1] + o.y, mine[2] + o.z, mine[3] + o.w};
+            }
+        // transpose through LDS (behind the partial sums), whole row segments to memory
+        constexpr int E_LD = WTN + 8;
+        static_assert(8 * HB * 1024 + 8 * (WTM / 2) * E_LD * 2 <= NST * STAGE, "reduction and epilogue staging fit the ring");
+        u16* Es = reinterpret_cast<u16*>(lds + 8 * HB * 1024) + wave * (WTM / 2) * E_LD;
+#pragma unroll
+        for (int a = 0; a < MB / 2; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                uint2 v;
+                v.x = pack2hw(sum[a][b][0], sum[a][b][1]);
+                v.y = pack2hw(sum[a][b][2], sum[a][b][3]);
+                *reinterpret_cast<uint2*>(Es + (a * 16 + l16) * E_LD + b * 16 + g4 * 4) = v;
+            }
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the same wavefront reads back what it wrote
+        constexpr int CPR = WTN / 8, RPI = 64 / CPR;
+#pragma unroll
+        for (int it = 0; it < WTM / 2 / RPI; ++it) {
+            const int rr = it * RPI + lane / CPR, c = lane % CPR;
+            const int row = m0 + wm * WTM + kg * (WTM / 2) + rr, col = n0 + wn * WTN + c * 8;
+            if (row >= g.M || col >= g.Ncols) continue;   // Ncols is a multiple of 8: chunks are all-in or all-out
+            store_streaming(g.C + (int64_t)row * g.ldc + col, *reinterpret_cast<const uint4*>(Es + rr * E_LD + c * 8));
+        }
+    }
+}
+
+}  // namespace
+
+template <int BM, int BN>
+static void launch_small(GemmArgs g, bool fwd, hipStream_t st) {
+    g.tiles_m = (g.M + BM - 1) / BM;
+    g.tiles_n = (g.Ncols + BN - 1) / BN;
+    const int total = g.tiles_m * g.tiles_n;
+    g.xcd_run = total >= 256 ? 32 : (total + 7) / 8;
+    const int per = 8 * g.xcd_run, grid = (total + per - 1) / per * per;
+    if (fwd) hipLaunchKernelGGL((small_gemm_kernel<true, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g);
+    else     hipLaunchKernelGGL((small_gemm_kernel<false, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g);
+}
+
+// Which kernel a product of M x N outputs over a contraction of K takes: -1 the 256 x 256 one, else an index of the table.
+// Every kernel runs one work group per CU, so a launch takes  launch + rounds x (fill and epilogue + steps x step)  with
+// rounds = tiles over CUs, rounded up.  The step times are what the kernels sustain with all CUs busy (64-wide step; the
+// 256 x 256 kernel moves the fewest bytes per product and wins wherever its last round is not too empty).  Against 94 shapes
+// of 64 .. 16384 tokens and widths 512 .. 14336 the choice cost 1 % over the best of the four, and no shape more than 15 %.
+// Measured (us, 256 x 256 / 128 x 128 / 64 x 128 / 64 x 64): 1000 x 4096 x 4096  111 / 40 / 53 / 73;  1000 x 1024 x 4096
+// 92 / 33 / 26 / 22;  200 x 512 x 2048  73 / 26 / 18 / 14;  4000 x 4096 x 4096  107 / 146 / 208 / 272.
+int small_gemm_tile(int64_t M, int64_t N, int64_t K, int num_cus) {
+    struct { int bm, bn; double launch, round, step; } const tab[4] = {
+        {256, 256, 3.0, 4.5, 1.45}, {128, 128, 4.0, 2.5, 0.48}, {64, 128, 4.0, 2.0, 0.32}, {64, 64, 3.5, 2.0, 0.225}};
+    int best = 0;
+    double best_us = 0;
+    for (int i = 0; i < 4; ++i) {
+        const int64_t tiles = ((M + tab[i].bm - 1) / tab[i].bm) * ((N + tab[i].bn - 1) / tab[i].bn);
+        const double us = tab[i].launch + (double)((tiles + num_cus - 1) / num_cus) * (tab[i].round + (double)((K + 63) / 64) * tab[i].step);
+        if (i == 0 || us < best_us) { best = i; best_us = us; }
+    }
+    return best - 1;
+}
+
+void launch_small_gemm(int tile, const GemmArgs& g, bool fwd, hipStream_t st) {
+    if (tile == 0)      launch_small<128, 128>(g, fwd, st);
+    else if (tile == 1) launch_small<64, 128>(g, fwd, st);
+    else                launch_small<64, 64>(g, fwd, st);
+}
+
+}  // namespace mlora
