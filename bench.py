@@ -24,6 +24,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_MFMA_TFLOPS = 2500.0   # MI355X dense bf16 matrix peak
+PEAK_F32_MFMA_TFLOPS = 157.3     # MI355X fp32 matrix peak (fp32 layers)
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 
 
@@ -299,7 +300,7 @@ def bench_power_clock(args, np, torch, ml, wl) -> int:
     return 0
 
 
-KERNEL_SOURCES = ("mfma_common.h", "mfma_gemm.hip", "mfma_lora.hip", "plan.hip", "common.h")
+KERNEL_SOURCES = ("mfma_common.h", "mfma_gemm.hip", "mfma_gemm_small.hip", "mfma_lora.hip", "plan.hip", "common.h")
 
 
 def kernel_sources_sha256() -> str:
@@ -494,7 +495,7 @@ def measure_layer(config: int, args, mods, extras: bool, lora_and_base: bool, ce
                 t = kern[name]["avg_ms"] * kern[name]["launches_per_step"] * 1e-3
                 if bound == "mfma":
                     kern[name].update(bound="mfma", achieved_tflops=work / t / 1e12,
-                                      frac=work / t / 1e12 / PEAK_BF16_MFMA_TFLOPS)
+                                      frac=work / t / 1e12 / (PEAK_F32_MFMA_TFLOPS if w.dtype == "f32" else PEAK_BF16_MFMA_TFLOPS))
                 else:
                     kern[name].update(bound="hbm", achieved_gbs=work / t / 1e9, frac=work / t / 1e9 / PEAK_HBM_GBS)
         out["kernels"] = kern
@@ -505,17 +506,13 @@ def measure_layer(config: int, args, mods, extras: bool, lora_and_base: bool, ce
             out["bwd_ms_kernels"] = float(sum(tot(nm) for nm in kern if nm not in fwd_names))
         traffic, traffic_source = committed_traffic(config)
         named = [nm for nm in kern if nm in alg]
-        if not named:
-            # fp32 / odd-width plans run every step through the grouped FMA kernel on the vector ALUs
-            out["roofline"] = {"kernel": "fma_grouped_gemm_kernel (all launches of a step)", "bound": "alu",
-                               "achieved": flops / (ms_step * 1e-3) / 1e12, "peak": 157.3, "unit": "TFLOP/s",
-                               "frac": flops / (ms_step * 1e-3) / 1e12 / 157.3, "traffic": None}
         dom = max(named, key=lambda nm: kern[nm]["avg_ms"] * kern[nm]["launches_per_step"]) if named else None
         bound, work = alg[dom] if dom else (None, 0.0)
         t = kern[dom]["avg_ms"] * kern[dom]["launches_per_step"] * 1e-3 if dom else 1.0
         if bound == "mfma":
-            out["roofline"] = {"kernel": dom, "bound": "mfma", "achieved": work / t / 1e12, "peak": PEAK_BF16_MFMA_TFLOPS,
-                               "unit": "TFLOP/s", "frac": work / t / 1e12 / PEAK_BF16_MFMA_TFLOPS, "traffic": traffic.get(dom),
+            peak = PEAK_F32_MFMA_TFLOPS if w.dtype == "f32" else PEAK_BF16_MFMA_TFLOPS
+            out["roofline"] = {"kernel": dom, "bound": "mfma", "achieved": work / t / 1e12, "peak": peak,
+                               "unit": "TFLOP/s", "frac": work / t / 1e12 / peak, "traffic": traffic.get(dom),
                                "traffic_source": traffic_source, "algorithmic_flop_per_launch": work,
                                "avg_kernel_ms": kern[dom]["avg_ms"]}
         elif bound == "hbm":

@@ -112,7 +112,7 @@ enum {
     MLORA_GEO_WGRAD_CHUNK_ROWS = 3,
     MLORA_GEO_R1_LO = 4,          /* sum_i T_i r_i, low and high 31 bits */
     MLORA_GEO_R1_HI = 5,
-    MLORA_GEO_USES_MFMA = 6,      /* 1 if the bf16 MFMA kernels serve this plan, 0 for the fp32-FMA kernels */
+    MLORA_GEO_USES_MFMA = 6,      /* 1 if the bf16 MFMA kernels serve this plan, 0 for the general kernels (fp32, or k or n not a multiple of 8) */
     MLORA_GEO_WGRAD_CHUNK_ROWS_WIDE = 7, /* token chunk of adapters with a rank above 64 */
     MLORA_GEO_BLOCK_ROWS_WIDE = 8,    /* rows per LoRA block of adapters with a rank above 64 */
     MLORA_GEO_GEMM_BAND_TILES = 9,    /* row tiles per band of the fused GEMMs' tile order */
@@ -233,7 +233,7 @@ enum {
     MLORA_K_GEMM_BWD = 3,    /* dX = dY W^T + dS_i A_i^T (fused) */
     MLORA_K_WGRAD = 4,       /* dA_i, dB_i token reductions (grouped) */
     MLORA_K_WGRAD_REDUCE = 5,/* fixed-order sum of chunk partials */
-    MLORA_K_OTHER = 6,       /* pointer upload, descriptor set-up, FMA-path launches */
+    MLORA_K_OTHER = 6,       /* pointer upload, zero fills */
     MLORA_K_ADAMW = 7        /* grouped per-adapter AdamW update */
 };
 

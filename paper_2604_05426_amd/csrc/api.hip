@@ -112,7 +112,7 @@ extern "C" int multi_lora_fwd(mlora_plan* plan, const void* X, const void* W, co
     hipStream_t st = (hipStream_t)stream;
     if (lora && (rc = upload_ptrs(plan, A, B, nullptr, nullptr, st)) != MLORA_OK) return rc;
     if (plan->use_mfma) return mfma_forward(plan, X, W, Y, S, flags, st);
-    return fma_forward(plan, X, W, Y, S, flags, st);
+    return general_forward(plan, X, W, Y, S, flags, st);
 }
 
 static int bwd_impl(mlora_plan* plan, const void* dY, const void* X, const void* W,
@@ -155,7 +155,7 @@ static int bwd_impl(mlora_plan* plan, const void* dY, const void* X, const void*
     void* dS = workspace;
     float* partials = workspace ? (float*)((char*)workspace + plan->ws_ds_bytes) : nullptr;
     if (plan->use_mfma) return mfma_backward(plan, dY, X, W, S, dX, dS, partials, flags, st);
-    return fma_backward(plan, dY, X, W, S, dX, dS, flags, st);
+    return general_backward(plan, dY, X, W, S, dX, dS, flags, st);
 }
 
 extern "C" int multi_lora_bwd(mlora_plan* plan, const void* dY, const void* X, const void* W,

@@ -111,7 +111,6 @@ struct mlora_plan {
     bool ptr_mirror_valid = false;
     bool ptr_upload_captured = false;
     hipStream_t ptr_mirror_stream = nullptr;
-    void* d_probs = nullptr;          // descriptor scratch of the FMA grouped GEMM
     void* d_adamw = nullptr;          // [N] optimizer entries (pointers + hyper-parameters), refreshed per call
     int32_t* d_reduce_list = nullptr; // adapters whose tokens are split over several weight-gradient chunks
     bool has_empty_ranked = false;    // some adapter has a rank but no tokens (its dA, dB are zero-filled)
@@ -161,11 +160,11 @@ void prepare_static_workspace();
 int upload_ptrs(mlora_plan* p, const void* const* A, const void* const* B, void* const* dA,
                 void* const* dB, hipStream_t st);
 
-// grouped_fma.hip : descriptor-driven grouped GEMM on the vector ALUs (fp32 accumulate)
-int fma_forward(mlora_plan* p, const void* X, const void* W, void* Y, void* S, uint32_t flags,
-                hipStream_t st);
-int fma_backward(mlora_plan* p, const void* dY, const void* X, const void* W, const void* S,
-                 void* dX, void* dS, uint32_t flags, hipStream_t st);
+// general.hip : fp32, and bf16 whose k or n is not a multiple of 8
+int general_forward(mlora_plan* p, const void* X, const void* W, void* Y, void* S, uint32_t flags,
+                    hipStream_t st);
+int general_backward(mlora_plan* p, const void* dY, const void* X, const void* W, const void* S,
+                     void* dX, void* dS, uint32_t flags, hipStream_t st);
 
 // mfma_*.hip : bf16 MFMA kernels
 int mfma_forward(mlora_plan* p, const void* X, const void* W, void* Y, void* S, uint32_t flags,

@@ -1,0 +1,722 @@
+// The general kernels: fp32 plans, and bf16 plans whose k or n is not a multiple of 8 (rows that start at any element).
+// Every step of the layer (paper Sec. 5.1) is one grouped launch on the matrix units, with fp32 accumulation:
+//   S_i = X_i A_i, dS_i = s_i dY_i B_i^T               general_shrink_kernel
+//   Y = X W + s_i S_i B_i, dX = dY W^T + dS_i A_i^T    general_gemm_kernel (also either term alone)
+//   dA_i = X_i^T dS_i, dB_i = s_i S_i^T dY_i           general_wgrad_kernel
+// No operand needs an alignment beyond its element: 16-byte pieces are loaded from wherever they start (global memory takes any
+// alignment), pieces that cross an edge element by element.
+//
+// fp32 goes through v_mfma_f32_16x16x4_f32 (256 FLOP per clock and CU, twice the vector ALUs without packed forms): the products of
+// a large layer are bound by it, not by memory, so a plain 64 x 64 tile with a few work groups per CU is enough.  Everything else
+// here is bound by latency (short segments, few tiles): contractions are split over the wavefronts of a work group and summed in a
+// fixed order in LDS, and loads run ahead of the MFMAs in registers.  Edges cost nothing in the main loops: the last tile of
+// rows or columns starts early enough to be whole, and only the last step of a contraction takes a mask (with a condition on every
+// load, the edge tiles alone made the bf16 products of 1500 x 1001 outputs 52 us instead of 27).
+//
+// One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
+// tokens, 256 x 256: 171 -> 26 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 394 us (its two frozen-weight products 176 us each, 98
+// TFLOP/s; 144 is what a large fp32 product reaches on this card); bf16, 1500 tokens, 2048 x 1001: 1105 -> 97 us.
+#include "mfma_common.h"
+
+namespace mlora {
+
+namespace {
+
+template <typename T> constexpr int kEpc = 16 / (int)sizeof(T);     // elements of a 16-byte piece
+
+// 16 bytes from any element boundary; the first `valid` elements are read, the rest are zero
+template <typename T> __device__ __forceinline__ uint4 load16(const T* p, int valid) {
+    uint4 v = zero4();
+    if (valid >= kEpc<T>) {
+        __builtin_memcpy(&v, p, 16);
+    } else if (valid > 0) {
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        T o[kEpc<T>];
+#pragma unroll
+        for (int e = 0; e < kEpc<T>; ++e) o[e] = p[min(e, valid - 1)];      // all in flight together
+#pragma unroll
+        for (int e = 0; e < kEpc<T>; ++e) {
+            if constexpr (sizeof(T) == 4) w[e] = e < valid ? __float_as_uint(o[e]) : 0u;
+            else w[e >> 1] |= e < valid ? (uint32_t)o[e] << ((e & 1) * 16) : 0u;
+        }
+        v = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    return v;
+}
+
+template <typename T> __device__ __forceinline__ float to_f32(T v) {
+    if constexpr (sizeof(T) == 4) return v; else return bf2f(v);
+}
+template <typename T> __device__ __forceinline__ T from_f32(float v) {
+    if constexpr (sizeof(T) == 4) return v; else return f2bf(v);
+}
+
+// One lane's share of a 16 x 16 block product over 16 (fp32) or 32 (bf16) contraction elements: 16 bytes per operand.  bf16: the
+// eight elements 8 g .. 8 g + 7 of row / column l % 16, g = l / 16; fp32: the elements 4 g .. 4 g + 3, multiplied in four steps
+// (step j takes element 4 g + j of every g: the order inside the sum is free as long as both operands agree).
+template <typename T> __device__ __forceinline__ f32x4 block_mma(uint4 a, uint4 b, f32x4 c) {
+    if constexpr (sizeof(T) == 4) {
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+        return c;
+    } else {
+        return mfma16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c);
+    }
+}
+// 2 x 2 blocks at once: the fp32 steps of the four blocks interleave, so that none waits for the one before it
+template <typename T> __device__ __forceinline__ void block_mma_2x2(const uint4 (&b)[2], const uint4 (&a)[2], f32x4 (&acc)[2][2]) {
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+                    const uint32_t av = j == 0 ? a[x].x : j == 1 ? a[x].y : j == 2 ? a[x].z : a[x].w;
+                    const uint32_t bv = j == 0 ? b[y].x : j == 1 ? b[y].y : j == 2 ? b[y].z : b[y].w;
+                    acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(bv), __uint_as_float(av), acc[x][y], 0, 0, 0);
+                }
+    } else {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = block_mma<T>(b[y], a[x], acc[x][y]);
+    }
+}
+template <typename T> constexpr int kBlockK = sizeof(T) == 4 ? 16 : 32;   // contraction of one block_mma
+
+// Four adjacent elements of a row whose columns are spread over four blocks (block x takes the columns 4 l + x).  `whole`
+// (uniform): all four are inside the row; else each is clamped to the last of `valid` (>= 1) by itself.
+template <typename T> using quad_t = uint32_t __attribute__((ext_vector_type(sizeof(T) == 4 ? 4 : 2)));
+template <typename T> __device__ __forceinline__ quad_t<T> load_quad(const T* p, bool whole, int valid) {
+    quad_t<T> v;
+    if (whole) {
+        __builtin_memcpy(&v, p, sizeof(v));
+    } else {
+        T o[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[c] = p[min(c, valid - 1)];
+        __builtin_memcpy(&v, o, sizeof(v));
+    }
+    return v;
+}
+constexpr int kQuadRows32 = 4, kQuadRows16 = 8;
+template <typename T> constexpr int kQuadRows = sizeof(T) == 4 ? kQuadRows32 : kQuadRows16;   // rows (contraction) per lane and piece
+// column x of a lane's quads as MFMA operand bytes
+template <typename T> __device__ __forceinline__ uint4 quad_column(const quad_t<T> (&q)[kQuadRows<T>], int x) {
+    uint32_t w[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        if constexpr (sizeof(T) == 4) w[p] = q[p][x];
+        else w[p] = __builtin_amdgcn_perm(q[2 * p + 1][x >> 1], q[2 * p][x >> 1], (x & 1) ? 0x07060302u : 0x05040100u);
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// the 16 bytes a lane supplies when its elements lie `ld` apart: elements k .. of a column at p
+template <typename T> __device__ __forceinline__ uint4 gather16(const T* p, int64_t ld, int valid) {
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    if (valid <= 0) return zero4();
+    T o[kEpc<T>];
+#pragma unroll
+    for (int e = 0; e < kEpc<T>; ++e) o[e] = p[min(e, valid - 1) * ld];
+#pragma unroll
+    for (int e = 0; e < kEpc<T>; ++e) {
+        if constexpr (sizeof(T) == 4) w[e] = e < valid ? __float_as_uint(o[e]) : 0u;
+        else w[e >> 1] |= e < valid ? (uint32_t)o[e] << ((e & 1) * 16) : 0u;
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// ---- shrink ------------------------------------------------------------------------------------------------------------------
+// Work group = 16 rows of one adapter x all its ranks; its eight wavefronts deal the contraction among themselves piece by piece,
+// straight from memory into MFMA operands (X / dY rows are read once; the adapter matrix comes from the caches), with the
+// operands of the next piece in flight, and the eight partial blocks are added in LDS in wavefront order.
+template <typename T> struct GenShrinkArgs {
+    const T* src; int64_t ld;     // X (ld k) or dY (ld n); the contraction has ld elements
+    T* out;                       // ragged S or dS
+    PlanView pv;
+};
+
+template <typename T, bool FWD, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void general_shrink_kernel(GenShrinkArgs<T> g) {
+    constexpr int RLD = NB * 16 + 4;
+    __shared__ float red[NW * 16 * RLD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, g4 = lane >> 4;
+    const Entry4 e = g.pv.row_blocks[blockIdx.x >> 2];
+    const int sub = (blockIdx.x & 3) * 16, rows = min(16, e.d - sub);
+    if (rows <= 0) return;
+    const int i = e.a, row0 = e.c + sub;
+    const int r = g.pv.rank[i];
+    const float s = FWD ? 1.0f : g.pv.scale[i];
+    const T* F = (const T*)(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
+    const int K = (int)g.ld;
+    const T* xrow = g.src + (int64_t)(row0 + min(l16, rows - 1)) * g.ld;    // rows past the block repeat its last one: not stored
+    // ranks of block b: 16 b + l16, or, where four blocks share one 64-rank row piece of A_i, 64 (b / 4) + 4 l16 + b % 4
+    constexpr bool QUAD = FWD && NB >= 4;
+    f32x4 acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int U = NB >= 8 ? 1 : 2;                   // neighbouring pieces a wavefront loads at a time: whole 128-byte lines of a row
+    constexpr int NQ = QUAD ? NB / 4 : 1, NF = QUAD ? 1 : NB;
+    uint4 xa[2][U], fb[2][U][NF];
+    quad_t<T> fq[2][U][NQ][kQuadRows<T>];
+    // Ranks past r_i repeat valid ones (their sums are not stored); only the end of the contraction has to read as zero, in both
+    // operands.
+    const bool r4 = (r & 3) == 0;
+    auto load = [&](int unit, int set) {
+        const bool inside = (unit + 1) * U * kBlockK<T> <= K;      // uniform over the wavefront
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = (unit * U + u) * kBlockK<T> + g4 * kEpc<T>, valid = K - k;
+            if (inside) __builtin_memcpy(&xa[set][u], xrow + k, 16);
+            else        xa[set][u] = load16<T>(xrow + k, valid);
+            if constexpr (QUAD) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    // r a multiple of 4: lanes past it repeat the last four ranks; else element by element
+                    const int rho = r4 ? min(64 * q + 4 * l16, r - 4) : min(64 * q + 4 * l16, r - 1);
+#pragma unroll
+                    for (int e = 0; e < kQuadRows<T>; ++e) {
+                        if (inside || e < valid) fq[set][u][q][e] = load_quad<T>(F + (int64_t)(k + e) * r + rho, r4, r - rho);
+                        else                     fq[set][u][q][e] = (quad_t<T>)(0u);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const int rho = min(16 * b + l16, r - 1);
+                    if (FWD)         fb[set][u][b] = gather16<T>(F + (int64_t)k * r + rho, r, inside ? kEpc<T> : valid);
+                    else if (inside) __builtin_memcpy(&fb[set][u][b], F + (int64_t)rho * g.ld + k, 16);
+                    else             fb[set][u][b] = load16<T>(F + (int64_t)rho * g.ld + k, valid);
+                }
+            }
+        }
+    };
+    auto compute = [&](int set) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if constexpr (QUAD) {
+                    if (64 * (b / 4) < r) acc[b] = block_mma<T>(xa[set][u], quad_column<T>(fq[set][u][b / 4], b % 4), acc[b]);
+                } else {
+                    if (16 * b < r) acc[b] = block_mma<T>(xa[set][u], fb[set][u][b], acc[b]);
+                }
+            }
+    };
+    const int units = (K + U * kBlockK<T> - 1) / (U * kBlockK<T>);
+    if (wave < units) load(wave, 0);
+    for (int p = wave; p < units; p += 2 * NW) {
+        if (p + NW < units) load(p + NW, 1);
+        compute(0);
+        if (p + 2 * NW < units) load(p + 2 * NW, 0);
+        if (p + NW < units) compute(1);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[(wave * 16 + 4 * g4 + q) * RLD + (QUAD ? 64 * (b / 4) + 4 * l16 + b % 4 : 16 * b + l16)] = acc[b][q];
+    __syncthreads();
+    T* out = g.out + g.pv.soff[i] + (int64_t)(row0 - g.pv.off[i]) * r;
+    for (int idx = tid; idx < rows * r; idx += 64 * NW) {
+        const int row = idx / r, col = idx - row * r;
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += red[(w * 16 + row) * RLD + col];
+        out[idx] = from_f32<T>(s * v);
+    }
+}
+
+// ---- products with the frozen weight, and the rank extension -------------------------------------------------------------------
+template <typename T> struct GenGemmArgs {
+    const T* A; const T* W;       // X (fwd) or dY (bwd); W [k][n]
+    T* C;                         // Y or dX
+    const T* E;                   // ragged S or dS
+    int64_t lda, ldw, ldc;
+    int64_t M, N, K;
+    int64_t tiles_n;
+    int32_t base, lora;           // which terms; without the base term C += LoRA term
+    PlanView pv;
+};
+
+// Tile: WK = 1: 64 x 64, four wavefronts 2 x 2;  WK = 4: 32 x 32, the four wavefronts split every step's contraction.
+// A step is WK pieces of 128 bytes per row (32 fp32 / 64 bf16 elements).  LDS rows of operands whose contraction is contiguous are
+// padded to 144 bytes (16-byte reads of 16 rows then touch every bank once); a W / B_i tile [contraction][column] keeps fp32 rows
+// padded by 4 elements, bf16 rows XOR-swizzled in 32-byte units for the transposing read.
+// Forward: B operand (W, B_i) has its columns contiguous; backward (W, A_i transposed): its contraction.
+template <typename T, bool FWD, int WK>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3 : 2))) void general_gemm_kernel(GenGemmArgs<T> g) {
+    constexpr int BT = WK == 1 ? 64 : 32;                    // tile edge
+    constexpr int KW = 128 / (int)sizeof(T), KT = KW * WK;   // contraction per wavefront and per step
+    constexpr int EPC = kEpc<T>;
+    constexpr int CPK = 8 * WK;                              // 16-byte pieces of a contraction row
+    constexpr int NCH = BT * CPK / 256;                      // pieces per thread and operand
+    constexpr int CPN = BT / EPC;                            // pieces of a column row (fwd W tile)
+    constexpr int KC_TILE = WK * BT * 144;
+    constexpr int NC_PITCH = sizeof(T) == 4 ? (BT + 4) * 4 : BT * 2;
+    constexpr int B_TILE = FWD ? KT * NC_PITCH : KC_TILE;
+    constexpr int STAGE = KC_TILE + B_TILE;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = WK == 1 ? wave >> 1 : 0, wn = WK == 1 ? wave & 1 : 0, wk = WK == 1 ? 0 : wave;
+    const int l16 = lane & 15, g4 = lane >> 4;
+    // The last tile of rows / columns starts early enough to be whole (its loads then need no conditions); what it shares with
+    // the tile before is not stored.
+    const int64_t m_own = (int64_t)(blockIdx.x / g.tiles_n) * BT, n_own = (int64_t)(blockIdx.x % g.tiles_n) * BT;
+    const int64_t m0 = max((int64_t)0, min(m_own, g.M - BT)), n0 = max((int64_t)0, min(n_own, g.N - BT));
+    auto unit = [](int k, int u) {      // swizzled 32-byte unit of a bf16 W row
+        return BT == 64 ? u ^ (((k >> 1) & 1) | (((k >> 3) & 1) << 1)) : u ^ ((k >> 3) & 1);
+    };
+
+    auto lds_off = [&](int idx) {        // where piece idx of an operand whose contraction is contiguous goes
+        const int row = idx / CPK, cc = idx % CPK;
+        return ((cc >> 3) * BT + row) * 144 + (cc & 7) * 16;
+    };
+    auto store_piece = [&](int stage, int idx, uint4 a, uint4 b) {
+        unsigned char* As = lds + stage * STAGE;
+        unsigned char* Bs = As + KC_TILE;
+        *reinterpret_cast<uint4*>(As + lds_off(idx)) = a;
+        if (FWD) {
+            const int kr = idx / CPN, cn = idx % CPN;
+            *reinterpret_cast<uint4*>(Bs + kr * NC_PITCH + (sizeof(T) == 4 ? cn * 16 : (unit(kr, cn >> 1) << 5) | ((cn & 1) << 4))) = b;
+        } else {
+            *reinterpret_cast<uint4*>(Bs + lds_off(idx)) = b;
+        }
+    };
+    auto compute = [&](f32x4 (&acc)[2][2], int stage) {
+        const unsigned char* As = lds + stage * STAGE;
+        const unsigned char* Bs = As + KC_TILE;
+        uint4 fa[2][2], fb[2][2];                        // [64-byte half of the wavefront's 128-byte piece][block]
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                fa[h][x] = *reinterpret_cast<const uint4*>(As + (wk * BT + wm * 32 + x * 16 + l16) * 144 + h * 64 + g4 * 16);
+                if (!FWD) {
+                    fb[h][x] = *reinterpret_cast<const uint4*>(Bs + (wk * BT + wn * 32 + x * 16 + l16) * 144 + h * 64 + g4 * 16);
+                } else if constexpr (sizeof(T) == 4) {
+                    const float* p = reinterpret_cast<const float*>(Bs + (wk * KW + h * 16 + 4 * g4) * NC_PITCH) + wn * 32 + x * 16 + l16;
+                    fb[h][x] = make_uint4(__float_as_uint(p[0]), __float_as_uint(p[NC_PITCH / 4]), __float_as_uint(p[2 * (NC_PITCH / 4)]),
+                                          __float_as_uint(p[3 * (NC_PITCH / 4)]));
+                } else {
+                    const int k = wk * KW + h * 32 + 8 * g4 + (l16 >> 2);
+                    const unsigned char* p = Bs + k * NC_PITCH + (unit(k, wn * 2 + x) << 5) + (l16 & 3) * 8;
+                    fb[h][x] = __builtin_bit_cast(uint4, lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * NC_PITCH)));
+                }
+            }
+        // operands swapped: a lane holds one output row and 4 consecutive columns of each block
+#pragma unroll
+        for (int h = 0; h < 2; ++h) block_mma_2x2<T>(fb[h], fa[h], acc);
+    };
+
+    // acc += A B over a contraction of K.  Element (row m0 + i, c) of A at a[i * lda + c], rows [row_lo, row_hi) exist; column
+    // n0 + j, element c of B at b[c * ldb + j] (fwd) or b[j * ldb + c] (bwd).  Any sizes, one step at a time: for short contractions.
+    auto contract_any = [&](f32x4 (&acc)[2][2], const T* a, int64_t lda, int64_t row_lo, int64_t row_hi, const T* b, int64_t ldb, int64_t K) {
+        for (int64_t k0 = 0; k0 < K; k0 += KT) {
+            const int left = (int)min((int64_t)KT, K - k0);
+            uint4 ra[NCH], rb[NCH];
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                const int idx = tid + 256 * c, row = idx / CPK, k = (idx % CPK) * EPC;
+                ra[c] = load16<T>(a + row * lda + k0 + k, m0 + row >= row_lo && m0 + row < row_hi ? min(EPC, left - k) : 0);
+                if (FWD) {
+                    const int kr = idx / CPN, col = (idx % CPN) * EPC;
+                    rb[c] = load16<T>(b + (k0 + kr) * ldb + col, kr < left ? (int)max((int64_t)0, min((int64_t)EPC, g.N - n0 - col)) : 0);
+                } else {
+                    rb[c] = load16<T>(b + row * ldb + k0 + k, n0 + row < g.N ? min(EPC, left - k) : 0);
+                }
+            }
+            __syncthreads();                             // whoever read the stage before is done
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) store_piece(0, tid + 256 * c, ra[c], rb[c]);
+            __syncthreads();
+            compute(acc, 0);
+        }
+    };
+
+    // The same for whole tiles and at least one whole step (every load is then inside its rows and takes no condition): step t
+    // travels in register set t & 1 and is computed from LDS stage t & 1, its loads run two steps ahead.  A contraction that is
+    // not a multiple of the step ends with a step that starts early; what it repeats is zeroed in both operands.
+    auto contract_whole = [&](f32x4 (&acc)[2][2], const T* a, int64_t lda, const T* b, int64_t ldb, int64_t K) {
+        uint4 ra[2][NCH], rb[2][NCH];
+        const T *pa[NCH], *pb[NCH];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int idx = tid + 256 * c, row = idx / CPK, k = (idx % CPK) * EPC;
+            pa[c] = a + row * lda + k;
+            pb[c] = FWD ? b + (idx / CPN) * ldb + (idx % CPN) * EPC : b + row * ldb + k;
+        }
+        const int64_t nt = (K + KT - 1) / KT;
+        const int again = (int)(nt * KT - K);            // elements the last step repeats
+        auto load = [&](int64_t step, int set) {
+            const int64_t k0 = step == nt - 1 ? K - KT : step * KT;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                __builtin_memcpy(&ra[set][c], pa[c] + k0, 16);
+                __builtin_memcpy(&rb[set][c], pb[c] + (FWD ? k0 * ldb : k0), 16);
+            }
+        };
+        auto zero_head = [&](uint4 v, int drop) {        // the first `drop` elements of a piece
+            uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < EPC; ++e)
+                if (e < drop) {
+                    if constexpr (sizeof(T) == 4) w[e] = 0u;
+                    else w[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
+                }
+            return make_uint4(w[0], w[1], w[2], w[3]);
+        };
+        auto store = [&](int64_t step, int set) {
+            if (step == nt - 1 && again > 0) {
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    const int idx = tid + 256 * c, k = (idx % CPK) * EPC;
+                    ra[set][c] = zero_head(ra[set][c], again - k);
+                    rb[set][c] = FWD ? (idx / CPN < again ? zero4() : rb[set][c]) : zero_head(rb[set][c], again - k);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) store_piece(set, tid + 256 * c, ra[set][c], rb[set][c]);
+        };
+        load(0, 0);
+        if (nt > 1) load(1, 1);
+        store(0, 0);
+        if (nt > 2) load(2, 0);
+        __syncthreads();
+        for (int64_t t = 0; t < nt; t += 2) {
+            if (t + 1 < nt) store(t + 1, 1);
+            if (t + 3 < nt) load(t + 3, 1);
+            compute(acc, 0);
+            __syncthreads();
+            if (t + 1 < nt) {
+                if (t + 2 < nt) store(t + 2, 0);
+                if (t + 4 < nt) load(t + 4, 0);
+                compute(acc, 1);
+                __syncthreads();
+            }
+        }
+    };
+
+    f32x4 acc[2][2];
+    bool owned[2] = {false, false};
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // lane l holds the metadata of candidate adapter first + l of this row tile; fetched ahead of the contraction that hides it
+    Entry4 tile{0, 0, 0, 0};
+    if (g.lora) {
+        tile = g.pv.gemm_tiles[m0 / kGemmTileRows];
+        tile.d = g.pv.gemm_tiles[(min(g.M, m0 + BT) - 1) / kGemmTileRows].d;      // an early last tile may reach into the next
+    }
+    int first = tile.c;
+    int c_rank = 0, c_off = 0, c_end = 0;
+    int64_t c_so = 0;
+    uint64_t c_f = 0;
+    float c_sc = 1.0f;
+    auto candidates = [&]() {
+        const int cand = min(first + lane, tile.d - 1);
+        c_rank = g.pv.rank[cand]; c_off = g.pv.off[cand]; c_end = g.pv.off[cand + 1];
+        c_so = g.pv.soff[cand];
+        c_f = reinterpret_cast<uint64_t>(FWD ? g.pv.ptrs[cand].B : g.pv.ptrs[cand].A);
+        if (FWD) c_sc = g.pv.scale[cand];
+    };
+    if (first < tile.d) candidates();
+
+    if (g.base) {
+        const T* w = FWD ? g.W + n0 : g.W + n0 * g.ldw;
+        if (g.M >= BT && g.N >= BT && g.K >= KT) contract_whole(acc, g.A + m0 * g.lda, g.lda, w, g.ldw, g.K);
+        else contract_any(acc, g.A + m0 * g.lda, g.lda, m0, g.M, w, g.ldw, g.K);
+    }
+
+    // rank extension, adapter by adapter into a second accumulator set, of which the adapter's own rows are added: another
+    // adapter's operands never touch a row, whatever they hold
+    const int lo_t = (int)m0, hi_t = (int)min(g.M, m0 + BT);
+    while (first < tile.d) {
+        uint64_t todo = __ballot(first + lane < tile.d && c_rank > 0 && max(c_off, lo_t) < min(c_end, hi_t));
+        while (todo) {
+            const int l = (int)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            auto lane64 = [&](uint64_t v) {
+                return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+            };
+            const int r = __builtin_amdgcn_readlane(c_rank, l), seg0 = __builtin_amdgcn_readlane(c_off, l);
+            const int lo = max(seg0, lo_t), hi = min(__builtin_amdgcn_readlane(c_end, l), hi_t);
+            const T* F = reinterpret_cast<const T*>(lane64(c_f));
+            const float s = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c_sc), l));
+            f32x4 ext[2][2];
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) ext[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+            contract_any(ext, g.E + (int64_t)lane64((uint64_t)c_so) + (int64_t)(lo_t - seg0) * r, r, lo, hi, FWD ? F + n0 : F + n0 * r,
+                     FWD ? g.N : r, r);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const int row = lo_t + wm * 32 + x * 16 + l16;
+                const bool own = row >= lo && row < hi;
+                owned[x] = owned[x] || own;
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[x][y][q] = own ? acc[x][y][q] + s * ext[x][y][q] : acc[x][y][q];
+            }
+        }
+        first += 64;
+        if (first < tile.d) candidates();
+    }
+
+    auto emit = [&](int x, int y, f32x4 v) {
+        const int64_t row = m0 + wm * 32 + x * 16 + l16, col = n0 + wn * 32 + y * 16 + 4 * g4;
+        if (row >= g.M || row < m_own || (!g.base && !owned[x])) return;
+        T* c = g.C + row * g.ldc + col;
+        T o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = (g.base || col + q >= g.N) ? from_f32<T>(v[q]) : from_f32<T>(v[q] + to_f32<T>(c[q]));
+        if (col >= n_own && col + 4 <= g.N) __builtin_memcpy(c, o, sizeof(o));
+        else
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (col + q >= n_own && col + q < g.N) c[q] = o[q];
+    };
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) emit(x, y, acc[x][y]);
+    } else {
+        // the wavefronts' partial tiles are added in wavefront order; wavefront w finishes block w
+        __syncthreads();
+        float4* red = reinterpret_cast<float4*>(lds);
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk) {
+            const f32x4 v = acc[blk >> 1][blk & 1];
+            red[(wave * 4 + blk) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+        }
+        __syncthreads();
+        f32x4 v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float4 o = red[(w * 4 + wave) * 64 + lane];
+            v[0] += o.x; v[1] += o.y; v[2] += o.z; v[3] += o.w;
+        }
+        if (wave & 2) emit(1, wave & 1, v); else emit(0, wave & 1, v);
+    }
+}
+
+// ---- weight gradients ------------------------------------------------------------------------------------------------------------
+// Work item = 64 columns of X (dA_i) or dY (dB_i) x 16 NB ranks of one adapter, over all its tokens; the eight wavefronts deal the
+// tokens in pieces of 16 (fp32) / 32 (bf16).  The contraction (tokens) is the row index of both operands in memory, so a lane
+// loads four adjacent columns 4 l16 .. 4 l16 + 3 of its tokens at once and those feed four different blocks (block x holds the
+// columns 4 j + x); nothing goes through LDS but the final sum over the wavefronts.
+template <typename T> struct GenWgradArgs {
+    const T* X; const T* dY; const T* S; const T* dS;
+    int32_t panels_k;
+    int32_t accumulate;
+    PlanView pv;
+};
+
+// WHOLE: k and n are at least 64, so that every panel can be whole.
+template <typename T, int NB, bool WHOLE>
+__global__ __launch_bounds__(512) void general_wgrad_kernel(GenWgradArgs<T> g) {
+    constexpr int RW = 16 * NB, RLD = RW + 1;
+    constexpr int PT = kBlockK<T>;                       // tokens per piece
+    constexpr int TPL = kQuadRows<T>;                    // tokens per lane and piece
+    __shared__ float red[4 * 64 * RLD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, g4 = lane >> 4;
+    const int i = blockIdx.y;
+    const int r = g.pv.rank[i], rho0 = blockIdx.z * RW;
+    if (rho0 >= r) return;
+    const bool isA = (int)blockIdx.x < g.panels_k;
+    const int64_t width = isA ? g.pv.k : g.pv.n;
+    // the last panel starts early enough to be whole; what it shares with the one before is not stored
+    const int64_t col_own = (int64_t)(isA ? blockIdx.x : blockIdx.x - g.panels_k) * 64, col0 = max((int64_t)0, min(col_own, width - 64));
+    const int row0 = g.pv.off[i], rows = g.pv.off[i + 1] - row0;
+    const int lcol = (int)min((int64_t)4 * l16, width - col0 - 1);      // (panels narrower than 64: lanes past the edge repeat its last column)
+    const T* big = (isA ? g.X : g.dY) + (int64_t)row0 * width + col0 + lcol;
+    const T* small = (isA ? g.dS : g.S) + g.pv.soff[i] + rho0 + l16;
+    const int cols = (int)min((int64_t)4, width - col0 - lcol);
+
+    f32x4 acc[4][NB];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[x][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    quad_t<T> wide[2][TPL];
+    T narrow[2][TPL][NB];
+    auto load = [&](int piece, int set) {
+#pragma unroll
+        for (int e = 0; e < TPL; ++e) {
+            const int t = piece * PT + (sizeof(T) == 4 ? 4 * e + g4 : 8 * g4 + e);
+            if (t < rows) wide[set][e] = load_quad<T>(big + (int64_t)t * width, WHOLE, cols);
+            else          wide[set][e] = (quad_t<T>)(0u);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                narrow[set][e][b] = (T)0;
+                if (t < rows && rho0 + 16 * b + l16 < r) narrow[set][e][b] = small[(int64_t)t * r + 16 * b];
+            }
+        }
+    };
+    auto compute = [&](int set) {
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    if (rho0 + 16 * b >= r) continue;
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        acc[x][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wide[set][e][x]), narrow[set][e][b], acc[x][b], 0, 0, 0);
+                }
+        } else {
+            uint4 fw[4], fn[NB];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) fw[x] = quad_column<T>(wide[set], x);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                uint32_t w[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) w[p] = (uint32_t)narrow[set][2 * p][b] | ((uint32_t)narrow[set][2 * p + 1][b] << 16);
+                fn[b] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) acc[x][b] = block_mma<T>(fw[x], fn[b], acc[x][b]);
+        }
+    };
+    const int pieces = (rows + PT - 1) / PT;
+    if (wave < pieces) load(wave, 0);
+    for (int p = wave; p < pieces; p += 16) {
+        if (p + 8 < pieces) load(p + 8, 1);
+        compute(0);
+        if (p + 16 < pieces) load(p + 16, 0);
+        if (p + 8 < pieces) compute(1);
+    }
+
+    // wavefronts 0 .. 3 write, 4 .. 7 add theirs; the four sums are added in order.  Lane (l16, g4) holds rank 16 b + l16 of the
+    // columns 4 (4 g4 + q) + x.
+    for (int half = 0; half < 2; ++half) {
+        if (wave >> 2 == half) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float* d = red + ((wave & 3) * 64 + 16 * g4 + 4 * q + x) * RLD + 16 * b + l16;
+                        *d = half ? *d + acc[x][b][q] : acc[x][b][q];
+                    }
+        }
+        __syncthreads();
+    }
+    const float s = isA ? 1.0f : g.pv.scale[i];
+    T* out = (T*)(isA ? g.pv.ptrs[i].dA : g.pv.ptrs[i].dB);
+    for (int idx = tid; idx < 64 * RW; idx += 512) {
+        // consecutive threads, consecutive elements of the output: ranks of a dA_i row, columns of a dB_i row
+        const int c = isA ? idx / RW : idx % 64, rho = isA ? idx % RW : idx / 64;
+        if (col0 + c < col_own || col0 + c >= width || rho0 + rho >= r) continue;
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v += red[(w * 64 + c) * RLD + rho];
+        v *= s;
+        T* o = out + (isA ? (col0 + c) * r + rho0 + rho : (int64_t)(rho0 + rho) * width + col0 + c);
+        *o = from_f32<T>(g.accumulate ? v + to_f32<T>(*o) : v);
+    }
+}
+
+// ---- launches --------------------------------------------------------------------------------------------------------------------
+
+template <typename T, bool FWD>
+int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
+    if (p->n_row_blocks == 0) return MLORA_OK;
+    GenShrinkArgs<T> a{};
+    a.src = (const T*)src; a.ld = FWD ? p->k : p->n; a.out = (T*)out; a.pv = p->view;
+    ProfScope prof(p, FWD ? MLORA_K_SHRINK : MLORA_K_DSHRINK, st);
+    const dim3 grid((unsigned)p->n_row_blocks * 4);
+    if (p->max_rank <= 16)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1, 16>), grid, dim3(1024), 0, st, a);
+    else if (p->max_rank <= 64) hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 4, 8>), grid, dim3(512), 0, st, a);
+    else                        hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 8, 8>), grid, dim3(512), 0, st, a);
+    MLORA_HIP_TRY(hipGetLastError());
+    return MLORA_OK;
+}
+
+template <typename T, bool FWD>
+int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, uint32_t flags, hipStream_t st) {
+    GenGemmArgs<T> a{};
+    a.A = (const T*)A; a.W = (const T*)W; a.C = (T*)C; a.E = (const T*)E;
+    a.M = p->T; a.K = FWD ? p->k : p->n; a.N = FWD ? p->n : p->k;
+    a.lda = a.K; a.ldw = p->n; a.ldc = a.N;
+    a.base = (flags & MLORA_FLAG_LORA_ONLY) ? 0 : 1;
+    a.lora = ((flags & MLORA_FLAG_BASE_ONLY) || p->n_row_blocks == 0) ? 0 : 1;
+    a.pv = p->view;
+    if (a.M == 0 || (!a.base && !a.lora)) return MLORA_OK;
+    ProfScope prof(p, FWD ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
+    auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
+    const bool split = tiles(64) <= p->num_cus / 2;
+    a.tiles_n = (a.N + (split ? 31 : 63)) / (split ? 32 : 64);
+    if (split) hipLaunchKernelGGL((general_gemm_kernel<T, FWD, 4>), dim3((unsigned)tiles(32)), dim3(256), 0, st, a);
+    else       hipLaunchKernelGGL((general_gemm_kernel<T, FWD, 1>), dim3((unsigned)tiles(64)), dim3(256), 0, st, a);
+    MLORA_HIP_TRY(hipGetLastError());
+    return MLORA_OK;
+}
+
+template <typename T>
+int wgrad(mlora_plan* p, const void* dY, const void* X, const void* S, const void* dS, uint32_t flags, hipStream_t st) {
+    if (p->N == 0 || p->max_rank == 0) return MLORA_OK;
+    GenWgradArgs<T> a{};
+    a.X = (const T*)X; a.dY = (const T*)dY; a.S = (const T*)S; a.dS = (const T*)dS;
+    a.panels_k = (int32_t)((p->k + 63) / 64);
+    a.accumulate = (flags & MLORA_FLAG_ACCUM_GRADS) ? 1 : 0;
+    a.pv = p->view;
+    ProfScope prof(p, MLORA_K_WGRAD, st);
+    const unsigned panels = (unsigned)(a.panels_k + (p->n + 63) / 64);
+    // ranks per work item: as many as the plan needs; bf16 keeps each rank element of a lane's eight tokens in a register of its own
+    // and would spill with 64, panels that are not whole with more than 16
+    const bool whole = p->k >= 64 && p->n >= 64;
+    const int rw = p->max_rank <= 16 || !whole ? 16 : p->max_rank <= 32 || sizeof(T) == 2 ? 32 : 64;
+    const dim3 grid(panels, (unsigned)p->N, (unsigned)((p->max_rank + rw - 1) / rw)), block(512);
+    if (!whole)        hipLaunchKernelGGL((general_wgrad_kernel<T, 1, false>), grid, block, 0, st, a);
+    else if (rw == 16) hipLaunchKernelGGL((general_wgrad_kernel<T, 1, true>), grid, block, 0, st, a);
+    else if (rw == 32) hipLaunchKernelGGL((general_wgrad_kernel<T, 2, true>), grid, block, 0, st, a);
+    else if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((general_wgrad_kernel<T, 4, true>), grid, block, 0, st, a);
+    MLORA_HIP_TRY(hipGetLastError());
+    return MLORA_OK;
+}
+
+template <typename T>
+int fwd_t(mlora_plan* p, const void* X, const void* W, void* Y, void* S, uint32_t flags, hipStream_t st) {
+    if (!(flags & MLORA_FLAG_BASE_ONLY)) {
+        const int rc = shrink<T, true>(p, X, S, st);
+        if (rc != MLORA_OK) return rc;
+    }
+    return gemm<T, true>(p, X, W, Y, S, flags, st);
+}
+
+template <typename T>
+int bwd_t(mlora_plan* p, const void* dY, const void* X, const void* W, const void* S, void* dX, void* dS, uint32_t flags, hipStream_t st) {
+    int rc;
+    if (!(flags & MLORA_FLAG_BASE_ONLY))
+        if ((rc = shrink<T, false>(p, dY, dS, st)) != MLORA_OK) return rc;
+    if ((rc = gemm<T, false>(p, dY, W, dX, dS, flags, st)) != MLORA_OK) return rc;
+    if (!(flags & MLORA_FLAG_BASE_ONLY)) return wgrad<T>(p, dY, X, S, dS, flags, st);
+    return MLORA_OK;
+}
+
+}  // namespace
+
+int general_forward(mlora_plan* p, const void* X, const void* W, void* Y, void* S, uint32_t flags, hipStream_t st) {
+    return p->dtype == MLORA_F32 ? fwd_t<float>(p, X, W, Y, S, flags, st) : fwd_t<u16>(p, X, W, Y, S, flags, st);
+}
+
+int general_backward(mlora_plan* p, const void* dY, const void* X, const void* W, const void* S, void* dX, void* dS, uint32_t flags,
+                     hipStream_t st) {
+    return p->dtype == MLORA_F32 ? bwd_t<float>(p, dY, X, W, S, dX, dS, flags, st) : bwd_t<u16>(p, dY, X, W, S, dX, dS, flags, st);
+}
+
+}  // namespace mlora

@@ -396,7 +396,7 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
         p->off.assign(1, 0);
     }
     p->build_stream = (hipStream_t)stream;
-    // bf16 with 16-byte row granularity goes to the MFMA kernels, everything else to the FMA kernels
+    // bf16 with 16-byte row granularity goes to the MFMA kernels, everything else to the general kernels
     p->use_mfma = (dtype == MLORA_BF16) && (k % 8 == 0) && (n % 8 == 0);
 
     int dev = 0;
@@ -448,7 +448,6 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     const size_t o_gt = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_gemm_tiles + 1) : 0);
     const size_t o_bo = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_bands + 1) : 0);
     const size_t o_bo_tmp = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_bands + 1) : 0);
-    const size_t o_probs = take(128 * (size_t)(5 * N + 8));
     const size_t o_adamw = take(96 * (size_t)(N + 1));
     auto block1 = std::make_shared<DeviceBlock>();
     MLORA_HIP_TRY(hipMalloc(&block1->ptr, o));
@@ -476,7 +475,6 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     Entry4* d_cb = own_seg ? (Entry4*)(base + o_cb) : const_cast<Entry4*>(lv->class_blocks);
     Entry4* d_gt = own_seg ? (Entry4*)(base + o_gt) : const_cast<Entry4*>(lv->gemm_tiles);
     Entry4* d_bo = own_seg ? (Entry4*)(base + o_bo) : const_cast<Entry4*>(lv->band_order);
-    p->d_probs = base + o_probs;
     p->d_adamw = base + o_adamw;
 
     // scheduler set-up on the library's own stream; the host waits for that stream alone
