@@ -22,6 +22,20 @@ constexpr int kWgradMinChunkRows = 512;  // smallest token chunk one weight-grad
 constexpr int kNarrowMaxRank = 64;       // ranks above it form the wide rank class (their own kernel builds)
 constexpr int kMaxSortedChunks = 16384;  // larger weight-gradient tables keep the canonical order
 constexpr int kWgradPanelCols = 128;     // columns of X / dY one weight-gradient work item covers
+constexpr int kSplitBytesNarrow = 16384, kSplitBytesWide = 65536;   // fp32 accumulators of one shrink block and split, per rank class
+
+// Work groups that share one row block's contraction in the tiled shrink kernels: as many as fill the CUs, at most 8 (the last one
+// reads all shares).  Handing the shares over costs 5-6 us (stores and loads that bypass the L2, one counter round trip) and
+// a 64-wide step 0.29 us, so a split that saves fewer than 28 steps is not made.  Measured, us without / with: 19 blocks, contraction
+// 4096: 23 / 13, 14336: 69 / 19 (8 ways); 63 blocks, 14336: 69 / 35 (3 ways); 128 blocks, 4096: 22 / 22 (2 ways: not split).
+constexpr int kMaxShrinkSplits = 8;
+inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus) {
+    if (blocks <= 0) return 1;
+    int64_t s = num_cus / blocks;
+    if (s > kMaxShrinkSplits) s = kMaxShrinkSplits;
+    const int64_t steps = contraction / 64;
+    return s > 1 && steps * (s - 1) / s >= 28 ? (int)s : 1;
+}
 
 // One entry of any plan table: 4 x int32 (meaning depends on the table).
 struct Entry4 {
@@ -112,6 +126,8 @@ struct mlora_plan {
     bool ptr_upload_captured = false;
     hipStream_t ptr_mirror_stream = nullptr;
     void* d_adamw = nullptr;          // [N] optimizer entries (pointers + hyper-parameters), refreshed per call
+    unsigned char* d_split = nullptr; // shares of split shrink contractions, and the arrival counters (two per block)
+    uint32_t* d_arrived = nullptr;
     int32_t* d_reduce_list = nullptr; // adapters whose tokens are split over several weight-gradient chunks
     bool has_empty_ranked = false;    // some adapter has a rank but no tokens (its dA, dB are zero-filled)
     size_t ws_ds_bytes = 0;           // workspace: dS

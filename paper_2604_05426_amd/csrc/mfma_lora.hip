@@ -29,6 +29,11 @@ struct ShrinkArgs {
     const u16* src; int64_t ld;   // X (ld k) or dY (ld n)
     u16* out;                     // ragged S or dS
     int32_t Kdim;                 // k or n
+    // Tiled kernels with fewer row blocks than CUs: every block's contraction is cut into `splits` work groups
+    // (blockIdx = split x blocks + block), see shrink_tiled_body.
+    int32_t splits, blocks, blocks_wide;
+    unsigned char* partials;      // plan-owned (kSplitBytesWide / kSplitBytesNarrow per block and split)
+    uint32_t* arrived;            // [2 x blocks], zero between launches
     PlanView pv;                  // one workgroup per entry of pv.class_blocks (wide rank class first: its blocks run longest)
 };
 
@@ -237,8 +242,13 @@ __global__ __launch_bounds__(64 * SNW) void shrink_kernel(ShrinkArgs g) {
 //   8 with ROWS = 128 (ranks 65..128, the wide rank class, whose row blocks are 128 rows): X / dY tile 16 KB, adapter tile 16 KB,
 //     five 32 KB stages; wavefront w owns row block w (of eight) and all eight rank blocks.  With 64-row blocks the adapter tile was
 //     twice the X tile and both go through the same load path of the CU; 128 rows halve that traffic per X byte.
+// Split contraction: a work group takes 0.3-0.35 us per 64-wide step whatever else runs, so 19 row blocks of a 1024-token batch
+// spent 68 us on a contraction of 14336 with 237 CUs idle.  With `splits` > 1 each work group of a block takes its share of the steps
+// and stores its accumulators; the one that arrives last (agent-scope counter) adds all shares in split order - so the result does
+// not depend on the order of arrival - and writes S.  Nobody waits for anybody.
 template <bool FWD, int RB16, bool DENSE = false, int ROWS = 64>
-__device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Entry4 e, unsigned char* lds) {
+__device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Entry4 e, unsigned char* lds, const int block, const int split,
+                                                  const int half = 0) {
     static_assert(FWD || !DENSE, "the dense adapter tile is a layout of A_i");
     static_assert(ROWS == 64 || (ROWS == 128 && RB16 == 8 && !DENSE), "128-row blocks: wide rank class, swizzled adapter tile");
     constexpr int ST_XT = ROWS * 128;               // X / dY tile bytes
@@ -283,10 +293,11 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
             }
         }
     }
-    const int steps = g.Kdim / 64;
-    const char* baseX = uniform_ptr(g.src + (int64_t)row0 * g.ld);
-    const char* baseF = uniform_ptr(F);
+    const int all_steps = g.Kdim / 64;
+    const int step0 = (int)((int64_t)all_steps * split / g.splits), steps = (int)((int64_t)all_steps * (split + 1) / g.splits) - step0;
     const int64_t stepF = FWD ? (int64_t)64 * __builtin_amdgcn_readfirstlane(r) * 2 : 128;
+    const char* baseX = uniform_ptr(g.src + (int64_t)row0 * g.ld + (int64_t)step0 * 64);
+    const char* baseF = uniform_ptr(reinterpret_cast<const char*>(F) + step0 * stepF);
     const unsigned lds0 = (unsigned)(uintptr_t)lds;
     int issued = 0, slot_in = 0;          // next step to load and the ring slot it goes to
     auto issue = [&]() {                  // past the last step the last one is loaded again (keeps the wait counts uniform)
@@ -347,6 +358,63 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no load may still be writing LDS when the work group ends
 
+    if (g.splits > 1) {
+        constexpr int SHARE = 8 * NCB * 1024;            // bytes of one work group's accumulators
+        static_assert(SHARE <= (ROWS == 128 ? kSplitBytesWide : RB16 == 8 ? kSplitBytesWide / 2 : kSplitBytesNarrow), "a share fits its slot");
+        const bool wide = block < g.blocks_wide;
+        unsigned char* mine = g.partials + (wide ? (int64_t)block * g.splits * kSplitBytesWide
+                                                 : (int64_t)g.blocks_wide * g.splits * kSplitBytesWide + (int64_t)(block - g.blocks_wide) * g.splits * kSplitBytesNarrow);
+        const int64_t stride = wide ? kSplitBytesWide : kSplitBytesNarrow;
+        mine += half * (kSplitBytesWide / 2);
+        auto share = [&](int s, int j) { return reinterpret_cast<uint64_t*>(mine + s * stride) + ((wave * NCB + j) * 64 + lane) * 2; };
+#pragma unroll
+        for (int j = 0; j < NCB; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint64_t v = (uint64_t)__float_as_uint(acc[j][2 * h]) | ((uint64_t)__float_as_uint(acc[j][2 * h + 1]) << 32);
+                __hip_atomic_store(share(split, j) + h, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        // The shares are written and read with agent-scope atomics only: these go through the XCD's L2 to where all XCDs see them, so
+        // that once this wavefront's stores have been acknowledged (the wait) its share is visible.  An agent-scope release would
+        // write back the whole L2 for every work group instead: 14-20 us a launch, more than the split gains.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();                                 // every wavefront's share is out, nobody reads the ring any more
+        uint32_t* flag = reinterpret_cast<uint32_t*>(lds);
+        if (tid == 0) {
+            uint32_t* ctr = g.arrived + 2 * block + half;
+            const uint32_t before = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const bool last = before + 1 == (uint32_t)g.splits;
+            if (last) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+            *flag = last ? 1u : 0u;
+        }
+        __syncthreads();
+        const bool last = *flag != 0u;
+        __syncthreads();                                 // the ring may be loaded again
+        if (!last) return;
+        // two blocks' shares at a time, all loads in flight together (slots past the last split repeat it and are not added)
+#pragma unroll
+        for (int j0 = 0; j0 < NCB; j0 += 2) {
+            uint64_t v[kMaxShrinkSplits][2][2];
+#pragma unroll
+            for (int s = 0; s < kMaxShrinkSplits; ++s)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        v[s][j][h] = __hip_atomic_load(share(min(s, g.splits - 1), j0 + j) + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                f32x4 sum{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < kMaxShrinkSplits; ++s)
+                    if (s < g.splits)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) sum[q] += __uint_as_float((uint32_t)(v[s][j][q >> 1] >> (32 * (q & 1))));
+                acc[j0 + j] = sum;
+            }
+        }
+    }
+
     // lane (l16, g4) holds rows 16 rb + 4 g4 + q, rank 16 cb + l16
     const int64_t so = g.pv.soff[i];
     const int seg0 = g.pv.off[i];
@@ -371,25 +439,26 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
 template <bool FWD, bool WIDE, bool MIXED>
 __global__ __launch_bounds__(64 * SNW) void shrink_tiled_kernel(ShrinkArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[(MIXED || WIDE) ? 163840 : 147456];
-    const Entry4 e = g.pv.class_blocks[blockIdx.x];
+    const int split = blockIdx.x / g.blocks, block = blockIdx.x - split * g.blocks;
+    const Entry4 e = g.pv.class_blocks[block];
     const int r = g.pv.rank[e.a];
     if (WIDE && r > 64) {
         if (!MIXED || (r & 7) == 0) {
-            shrink_tiled_body<FWD, 8, false, kBlockRowsWide>(g, e, lds);
+            shrink_tiled_body<FWD, 8, false, kBlockRowsWide>(g, e, lds, block, split);
         } else {
             for (int h = 0; h < e.d; h += SR) {       // (uniform)
                 const Entry4 half{e.a, e.b, e.c + h, min(SR, e.d - h)};
                 if (h) __syncthreads();               // every wavefront is done with the first half's tiles
-                if (FWD && (r & 7) == 4) shrink_tiled_body<FWD, 8, FWD>(g, half, lds);
-                else shrink_body<FWD, 4, 32, 2, 1>(g, half, reinterpret_cast<u16*>(lds));
+                if (FWD && (r & 7) == 4) shrink_tiled_body<FWD, 8, FWD>(g, half, lds, block, split, h / SR);
+                else if (split == 0) shrink_body<FWD, 4, 32, 2, 1>(g, half, reinterpret_cast<u16*>(lds));   // (takes the whole contraction)
             }
         }
     } else if (MIXED && FWD && (r & 7) == 4) {
-        shrink_tiled_body<FWD, 4, FWD>(g, e, lds);
+        shrink_tiled_body<FWD, 4, FWD>(g, e, lds, block, split);
     } else if (MIXED && (r & 7) != 0) {
-        shrink_body<FWD, 2, 64, 2, 1>(g, e, reinterpret_cast<u16*>(lds));
+        if (split == 0) shrink_body<FWD, 2, 64, 2, 1>(g, e, reinterpret_cast<u16*>(lds));
     } else {
-        shrink_tiled_body<FWD, 4>(g, e, lds);
+        shrink_tiled_body<FWD, 4>(g, e, lds, block, split);
     }
 }
 
@@ -403,7 +472,12 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
     // keep the register-staged body; B_i is read along its rows, any rank will do)
     const bool mixed = FWD && !p->ranks_mult8;
     // the tiled kernels walk the class table (wide class first, 128-row blocks); the register-staged ones the canonical 64-row blocks
-    const dim3 grid(tiled ? p->n_blocks_wide + p->n_blocks_narrow : p->n_row_blocks);
+    a.blocks = p->n_blocks_wide + p->n_blocks_narrow;
+    a.blocks_wide = p->n_blocks_wide;
+    a.splits = tiled ? shrink_splits(a.blocks, a.Kdim, p->num_cus) : 1;
+    a.partials = p->d_split;
+    a.arrived = p->d_arrived;
+    const dim3 grid(tiled ? a.blocks * a.splits : p->n_row_blocks);
     if (tiled && !mixed) {
         if (!wide) hipLaunchKernelGGL((shrink_tiled_kernel<FWD, false, false>), grid, block, 0, st, a);
         else       hipLaunchKernelGGL((shrink_tiled_kernel<FWD, true, false>), grid, block, 0, st, a);

@@ -5,6 +5,7 @@
 // offsets, masking the boundary block (App. A.1, "schedule-driven dispatch").  Here the
 // host only validates and sizes; the tables themselves are built by device kernels from
 // the offsets and ranks, once per segmentation, and shared by every layer of a step.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -449,6 +450,12 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     const size_t o_bo = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_bands + 1) : 0);
     const size_t o_bo_tmp = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_bands + 1) : 0);
     const size_t o_adamw = take(96 * (size_t)(N + 1));
+    // shrink kernels over fewer row blocks than CUs: at most num_cus shares in all (forward and backward take turns)
+    const int64_t class_blocks = rb_wide + rb_narrow;
+    const int max_splits = p->use_mfma ? std::max(shrink_splits(class_blocks, k, p->num_cus), shrink_splits(class_blocks, n, p->num_cus)) : 1;
+    const size_t n_arrived = max_splits > 1 ? sizeof(uint32_t) * 2 * (size_t)class_blocks : 0;
+    const size_t o_arrived = take(n_arrived);
+    const size_t o_split = take(max_splits > 1 ? (size_t)max_splits * ((size_t)rb_wide * kSplitBytesWide + (size_t)rb_narrow * kSplitBytesNarrow) : 0);
     auto block1 = std::make_shared<DeviceBlock>();
     MLORA_HIP_TRY(hipMalloc(&block1->ptr, o));
     p->blocks.push_back(block1);
@@ -476,6 +483,8 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     Entry4* d_gt = own_seg ? (Entry4*)(base + o_gt) : const_cast<Entry4*>(lv->gemm_tiles);
     Entry4* d_bo = own_seg ? (Entry4*)(base + o_bo) : const_cast<Entry4*>(lv->band_order);
     p->d_adamw = base + o_adamw;
+    p->d_arrived = (uint32_t*)(base + o_arrived);
+    p->d_split = (unsigned char*)(base + o_split);
 
     // scheduler set-up on the library's own stream; the host waits for that stream alone
     {
@@ -492,6 +501,7 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
                 MLORA_HIP_TRY(hipMemcpyAsync(d_scale, p->scales.data(), sizeof(float) * N, hipMemcpyHostToDevice, ss));
             }
         }
+        if (n_arrived) MLORA_HIP_TRY(hipMemsetAsync(p->d_arrived, 0, n_arrived, ss));
         const int64_t panels = ceil_div(k, kWgradPanelCols) + ceil_div(n, kWgradPanelCols);
         hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(kScanThreads), 0, ss, N, d_off, d_rank, panels, k + n,
                            (int32_t)p->num_cus, kBlockRows, kBlockRowsWide, kWgradMinChunkRows, own_seg ? d_soff : nullptr,

@@ -1,0 +1,43 @@
+"""Shrink and gradient shrink with the contraction split over work groups: rank classes, ragged last blocks and contractions that
+do not divide evenly, against the oracle; and the same bits from run to run, eagerly and replayed from a graph (the shares
+are added in a fixed order whoever comes last, and every launch leaves the arrival counters ready for the next)."""
+import pytest
+import torch
+
+from oracle import multilora_oracle as orc
+from paper_2604_05426_amd import workloads as wl
+from paper_2604_05426_amd.harness import DeviceLayer
+from util import elem_excess
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("ranks,lens", [((8, 64, 16), (1, 63, 65)), ((100, 16, 128), (130, 1, 127)), ((4, 12, 68), (70, 129, 200)),
+                                        ((7, 33, 65), (64, 100, 300)), ((32,), (5000,))])
+@pytest.mark.parametrize("k,n", [(2560, 8), (2048, 3008)])
+def test_split_contraction(ranks, lens, k, n):
+    print(f"[case] split shrink k={k} n={n} ranks={ranks} lens={lens}", flush=True)
+    w = wl.make_workload("split", "bf16", k, n, ranks, lens, [0.5] * len(ranks), seed=k + len(ranks), b_sigma=0.3)
+    dl = DeviceLayer(w)
+    dl.forward(); dl.backward(); dl.sync()
+    fw = orc.forward(w.X, w.W, w.A, w.B, w.scales, w.offsets)
+    bw = orc.backward(w.dY, w.X, w.W, w.A, w.B, w.scales, w.offsets)
+    for i in range(w.N):
+        assert elem_excess(dl.S_list()[i], fw.S[i], "bf16") <= 1 and elem_excess(dl.dS_list()[i], bw.dS[i], "bf16") <= 1, i
+    S, dS = dl.S.clone(), dl.workspace[: 2 * w.R1].clone()
+    for _ in range(20):
+        dl.S.fill_(float("nan"))
+        dl.forward(); dl.backward()
+        assert torch.equal(S.view(torch.int16), dl.S.view(torch.int16)) and torch.equal(dS, dl.workspace[: 2 * w.R1])
+    graph, side, eager = torch.cuda.CUDAGraph(), torch.cuda.Stream(), dl.stream
+    with torch.cuda.graph(graph, stream=side):
+        dl.stream = torch.cuda.current_stream().cuda_stream
+        dl.forward(); dl.backward()
+    dl.stream = eager
+    for _ in range(3):
+        dl.S.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(S.view(torch.int16), dl.S.view(torch.int16)) and torch.equal(dS, dl.workspace[: 2 * w.R1])
+        dl.forward(); dl.backward(); dl.sync()
+    dl.plan.destroy()
