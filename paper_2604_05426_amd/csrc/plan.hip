@@ -44,9 +44,10 @@ __global__ __launch_bounds__(kScanThreads) void plan_scan_kernel(
         int32_t N, const int32_t* off, const int32_t* rank, int64_t panels, int64_t kn, int32_t num_cus,
         int block_rows, int block_rows_wide, int min_chunk,
         int64_t* soff, int32_t* rb_start, int32_t* cb_start, int32_t* cb_pos,
-        int32_t* wc_start, int32_t* wc_pos, int64_t* part_off, int32_t* reduce_list, DevGeo* geo) {
+        int32_t* wc_start, int32_t* wc_pos, int64_t* part_off, int32_t* reduce_list, uint32_t* arrived, int32_t n_arrived, DevGeo* geo) {
     __shared__ int64_t red[kScanThreads];
     const int tid = threadIdx.x;
+    for (int32_t i = tid; i < n_arrived; i += kScanThreads) arrived[i] = 0u;   // arrival counters of split shrink contractions
     // items of one launch if the tokens of class `cls` (0: every adapter, 1: narrow ranks, 2: wide ranks) are cut every `chunk`
     auto count_items = [&](int64_t chunk, int cls) -> int64_t {
         int64_t mine = 0;
@@ -453,8 +454,8 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     // shrink kernels over fewer row blocks than CUs: at most num_cus shares in all (forward and backward take turns)
     const int64_t class_blocks = rb_wide + rb_narrow;
     const int max_splits = p->use_mfma ? std::max(shrink_splits(class_blocks, k, p->num_cus), shrink_splits(class_blocks, n, p->num_cus)) : 1;
-    const size_t n_arrived = max_splits > 1 ? sizeof(uint32_t) * 2 * (size_t)class_blocks : 0;
-    const size_t o_arrived = take(n_arrived);
+    const int32_t n_arrived = max_splits > 1 ? (int32_t)(2 * class_blocks) : 0;
+    const size_t o_arrived = take(sizeof(uint32_t) * (size_t)n_arrived);
     const size_t o_split = take(max_splits > 1 ? (size_t)max_splits * ((size_t)rb_wide * kSplitBytesWide + (size_t)rb_narrow * kSplitBytesNarrow) : 0);
     auto block1 = std::make_shared<DeviceBlock>();
     MLORA_HIP_TRY(hipMalloc(&block1->ptr, o));
@@ -501,11 +502,10 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
                 MLORA_HIP_TRY(hipMemcpyAsync(d_scale, p->scales.data(), sizeof(float) * N, hipMemcpyHostToDevice, ss));
             }
         }
-        if (n_arrived) MLORA_HIP_TRY(hipMemsetAsync(p->d_arrived, 0, n_arrived, ss));
         const int64_t panels = ceil_div(k, kWgradPanelCols) + ceil_div(n, kWgradPanelCols);
         hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(kScanThreads), 0, ss, N, d_off, d_rank, panels, k + n,
                            (int32_t)p->num_cus, kBlockRows, kBlockRowsWide, kWgradMinChunkRows, own_seg ? d_soff : nullptr,
-                           d_rbs, d_cbs, d_cbp, d_wcs, d_wcp, d_part, p->d_reduce_list, d_geo);
+                           d_rbs, d_cbs, d_cbp, d_wcs, d_wcp, d_part, p->d_reduce_list, p->d_arrived, n_arrived, d_geo);
         MLORA_HIP_TRY(hipGetLastError());
         MLORA_HIP_TRY(hipMemcpyAsync(&p->geo, d_geo, sizeof(DevGeo), hipMemcpyDeviceToHost, ss));
         MLORA_HIP_TRY(hipStreamSynchronize(ss));
