@@ -1,10 +1,11 @@
 // Grouped per-adapter AdamW on the LoRA matrices (fp32 state, decoupled weight decay).
 //
 // The paper keeps one optimizer instance per LoRA job (Sec. 5.2) and trains with AdamW, weight decay
-// 0.01, constant learning rate (App., training details).  Here all adapters are updated by one launch:
-// the per-adapter pointers and hyper-parameters travel to a device table through kernel arguments,
-// then grid.y enumerates (adapter, matrix) pairs and grid.x strides over the elements.  The update is
-// a pure stream (28 bytes per bf16 parameter), so it is bound by HBM bandwidth.
+// 0.01, constant learning rate (App., training details).  Here up to kBatch adapters are updated by one launch whose
+// arguments carry their pointers and hyper-parameters (no table to upload first, nothing for the next call to overwrite).
+// The update is a pure stream (28 bytes per bf16 parameter), so it is bound by HBM bandwidth: a work group takes a run of
+// kRun consecutive elements of one matrix - every group the same work, whatever the ranks - and a thread has the
+// 16-byte pieces of gradient, master, m and v of its four groups of four elements in flight together.
 #include <cmath>
 #include <cstring>
 
@@ -17,19 +18,17 @@ struct AdamwEntry {
     const void* dA; const void* dB;
     float* sA; float* sB;
     float lr, beta1, beta2, eps, wd;
-    float c1, c2;   // 1 / (1 - beta1^t), 1 / (1 - beta2^t)
-    float pad;
+    float c1, c2;          // 1 / (1 - beta1^t), 1 / (1 - beta2^t)
+    int32_t rank;
+    int32_t endA, endB;    // work groups up to the end of this adapter's A / B
 };
-static_assert(sizeof(AdamwEntry) <= 96, "plan reserves 96 bytes per optimizer entry");
 
+constexpr int kBatch = 32;
+constexpr int kRun = 4096;                  // elements per work group: 256 threads x 4 groups x 4 elements
 struct AdamwBatch {
-    AdamwEntry e[16];
+    AdamwEntry e[kBatch];
 };
-
-__global__ void adamw_upload_kernel(AdamwEntry* dst, AdamwBatch batch, int32_t base, int32_t count) {
-    const int32_t i = threadIdx.x;
-    if (i < count) dst[base + i] = batch.e[i];
-}
+static_assert(sizeof(AdamwBatch) + 64 <= 4096, "the batch travels in the kernel arguments");
 
 template <typename T> __device__ inline float ldp(const T* p);
 template <> __device__ inline float ldp<float>(const float* p) { return *p; }
@@ -43,38 +42,78 @@ template <> __device__ inline void stp<uint16_t>(uint16_t* p, float v) {
     *p = (uint16_t)(u >> 16);
 }
 
-// INIT: master <- parameter, m = v = 0.  Otherwise one AdamW step.
+// INIT: master <- parameter, m = v = 0.  Otherwise one AdamW step.  (All buffers may start at any element: a piece is loaded and
+// stored as bytes, which global memory takes at any alignment.)
 template <typename T, bool INIT>
-__global__ __launch_bounds__(256) void adamw_kernel(const AdamwEntry* __restrict__ table, const int32_t* __restrict__ rank,
-                                                    int64_t k, int64_t n) {
-    const int32_t i = blockIdx.y >> 1;
-    const bool isB = blockIdx.y & 1;
-    const int64_t r = rank[i];
-    const int64_t numel = isB ? r * n : k * r;
-    if (numel == 0) return;
-    const AdamwEntry e = table[i];
+__global__ __launch_bounds__(256) void adamw_kernel(AdamwBatch batch, int32_t count, int64_t k, int64_t n) {
+    const int32_t wg = blockIdx.x;
+    int32_t lo = 0, hi = count;              // the first adapter whose matrices end behind this work group
+    while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (batch.e[mid].endB <= wg) lo = mid + 1; else hi = mid;
+    }
+    const AdamwEntry& e = batch.e[lo];
+    const bool isB = wg >= e.endA;
+    const int64_t numel = (isB ? n : k) * (int64_t)e.rank;
+    const int32_t first = isB ? e.endA : (lo > 0 ? batch.e[lo - 1].endB : 0);
     T* param = (T*)(isB ? e.B : e.A);
     const T* grad = (const T*)(isB ? e.dB : e.dA);
     float* master = isB ? e.sB : e.sA;
-    float* m = master + numel;
-    float* v = m + numel;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < numel; idx += stride) {
-        if (INIT) {
-            master[idx] = ldp<T>(param + idx);
-            m[idx] = 0.f;
-            v[idx] = 0.f;
-        } else {
-            const float g = ldp<T>(grad + idx);
-            const float mn = e.beta1 * m[idx] + (1.0f - e.beta1) * g;
-            const float vn = e.beta2 * v[idx] + (1.0f - e.beta2) * g * g;
-            float th = master[idx];
-            th = th - e.lr * ((mn * e.c1) / (sqrtf(vn * e.c2) + e.eps) + e.wd * th);
-            m[idx] = mn;
-            v[idx] = vn;
-            master[idx] = th;
-            stp<T>(param + idx, th);
+    float* mm = master + numel;
+    float* vv = mm + numel;
+    const float lr = e.lr, beta1 = e.beta1, beta2 = e.beta2, eps = e.eps, wd = e.wd, c1 = e.c1, c2 = e.c2;
+    auto update = [&](float g, float& th, float& m, float& v) {
+        m = beta1 * m + (1.0f - beta1) * g;
+        v = beta2 * v + (1.0f - beta2) * g * g;
+        th = th - lr * ((m * c1) / (sqrtf(v * c2) + eps) + wd * th);
+    };
+    const int64_t base = (int64_t)(wg - first) * kRun + threadIdx.x * 4;
+    struct F4 { float f[4]; };
+    struct T4 { T t[4]; };
+    if (base + 3 * 1024 + 4 <= numel) {
+        T4 g[4];
+        F4 th[4], m[4], v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t idx = base + u * 1024;
+            if (INIT) {
+                __builtin_memcpy(&g[u], param + idx, sizeof(T4));
+            } else {
+                __builtin_memcpy(&g[u], grad + idx, sizeof(T4));
+                __builtin_memcpy(&th[u], master + idx, 16);
+                __builtin_memcpy(&m[u], mm + idx, 16);
+                __builtin_memcpy(&v[u], vv + idx, 16);
+            }
         }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t idx = base + u * 1024;
+            T4 p;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float x = ldp<T>(&g[u].t[c]);
+                if (INIT) { th[u].f[c] = x; m[u].f[c] = 0.f; v[u].f[c] = 0.f; }
+                else { update(x, th[u].f[c], m[u].f[c], v[u].f[c]); stp<T>(&p.t[c], th[u].f[c]); }
+            }
+            __builtin_memcpy(master + idx, &th[u], 16);
+            __builtin_memcpy(mm + idx, &m[u], 16);
+            __builtin_memcpy(vv + idx, &v[u], 16);
+            if (!INIT) __builtin_memcpy(param + idx, &p, sizeof(T4));
+        }
+    } else {
+        for (int u = 0; u < 4; ++u)
+            for (int c = 0; c < 4; ++c) {
+                const int64_t idx = base + u * 1024 + c;
+                if (idx >= numel) continue;
+                if (INIT) {
+                    master[idx] = ldp<T>(param + idx); mm[idx] = 0.f; vv[idx] = 0.f;
+                } else {
+                    float th = master[idx], m = mm[idx], v = vv[idx];
+                    update(ldp<T>(grad + idx), th, m, v);
+                    master[idx] = th; mm[idx] = m; vv[idx] = v;
+                    stp<T>(param + idx, th);
+                }
+            }
     }
 }
 
@@ -107,15 +146,25 @@ static int run(mlora_plan* p, void* const* A, void* const* B, const void* const*
             }
         }
     }
-    AdamwEntry* table = (AdamwEntry*)p->d_adamw;
-    for (int32_t base = 0; base < p->N; base += 16) {
+    auto groups = [](int64_t numel) { return (numel + kRun - 1) / kRun; };
+    for (int32_t base = 0; base < p->N;) {
         AdamwBatch batch;
         std::memset(&batch, 0, sizeof(batch));
-        const int32_t cnt = (p->N - base) < 16 ? (p->N - base) : 16;
-        for (int32_t j = 0; j < cnt; ++j) {
-            const int32_t i = base + j;
-            AdamwEntry& e = batch.e[j];
+        int32_t cnt = 0;
+        int64_t total = 0;
+        for (; base < p->N && cnt < kBatch; ++base) {
+            const int32_t i = base;
+            if (p->ranks[i] == 0) continue;
+            const int64_t endA = total + groups(p->k * p->ranks[i]), endB = endA + groups(p->n * p->ranks[i]);
+            if (endB > INT32_MAX) {
+                if (cnt > 0) break;                        // the next launch takes it
+                set_error("AdamW: an adapter's matrices exceed 2^43 elements");
+                return MLORA_ERR_SHAPE;
+            }
+            AdamwEntry& e = batch.e[cnt++];
             e.A = A[i]; e.B = B[i]; e.sA = sA[i]; e.sB = sB[i];
+            e.rank = p->ranks[i]; e.endA = (int32_t)endA; e.endB = (int32_t)endB;
+            total = endB;
             if (!init) {
                 e.dA = dA[i]; e.dB = dB[i];
                 const mlora_adamw_hparams& h = hp[i];
@@ -124,21 +173,14 @@ static int run(mlora_plan* p, void* const* A, void* const* B, const void* const*
                 e.c2 = (float)(1.0 / (1.0 - std::pow((double)h.beta2, (double)h.step)));
             }
         }
-        ProfScope prof(p, MLORA_K_OTHER, st);
-        hipLaunchKernelGGL(adamw_upload_kernel, dim3(1), dim3(16), 0, st, table, batch, base, cnt);
-    }
-    const int64_t big = (p->k > p->n ? p->k : p->n) * (int64_t)(p->max_rank > 0 ? p->max_rank : 1);
-    int64_t gx = (big + 256 * 4 - 1) / (256 * 4);
-    if (gx < 1) gx = 1;
-    if (gx > 256) gx = 256;
-    const dim3 grid((unsigned)gx, (unsigned)(2 * p->N));
-    {
+        if (cnt == 0) break;
         ProfScope prof(p, MLORA_K_ADAMW, st);
         const bool f32 = p->dtype == MLORA_F32;
-        if (init && f32)       hipLaunchKernelGGL((adamw_kernel<float, true>), grid, dim3(256), 0, st, table, p->view.rank, p->k, p->n);
-        else if (init)         hipLaunchKernelGGL((adamw_kernel<uint16_t, true>), grid, dim3(256), 0, st, table, p->view.rank, p->k, p->n);
-        else if (f32)          hipLaunchKernelGGL((adamw_kernel<float, false>), grid, dim3(256), 0, st, table, p->view.rank, p->k, p->n);
-        else                   hipLaunchKernelGGL((adamw_kernel<uint16_t, false>), grid, dim3(256), 0, st, table, p->view.rank, p->k, p->n);
+        const dim3 grid((unsigned)total);
+        if (init && f32)       hipLaunchKernelGGL((adamw_kernel<float, true>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
+        else if (init)         hipLaunchKernelGGL((adamw_kernel<uint16_t, true>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
+        else if (f32)          hipLaunchKernelGGL((adamw_kernel<float, false>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
+        else                   hipLaunchKernelGGL((adamw_kernel<uint16_t, false>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
     }
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;

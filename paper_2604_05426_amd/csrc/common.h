@@ -125,7 +125,6 @@ struct mlora_plan {
     bool ptr_mirror_valid = false;
     bool ptr_upload_captured = false;
     hipStream_t ptr_mirror_stream = nullptr;
-    void* d_adamw = nullptr;          // [N] optimizer entries (pointers + hyper-parameters), refreshed per call
     unsigned char* d_split = nullptr; // shares of split shrink contractions, and the arrival counters (two per block)
     uint32_t* d_arrived = nullptr;
     int32_t* d_reduce_list = nullptr; // adapters whose tokens are split over several weight-gradient chunks

@@ -450,7 +450,6 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     const size_t o_gt = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_gemm_tiles + 1) : 0);
     const size_t o_bo = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_bands + 1) : 0);
     const size_t o_bo_tmp = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_bands + 1) : 0);
-    const size_t o_adamw = take(96 * (size_t)(N + 1));
     // shrink kernels over fewer row blocks than CUs: at most num_cus shares in all (forward and backward take turns)
     const int64_t class_blocks = rb_wide + rb_narrow;
     const int max_splits = p->use_mfma ? std::max(shrink_splits(class_blocks, k, p->num_cus), shrink_splits(class_blocks, n, p->num_cus)) : 1;
@@ -483,7 +482,6 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     Entry4* d_cb = own_seg ? (Entry4*)(base + o_cb) : const_cast<Entry4*>(lv->class_blocks);
     Entry4* d_gt = own_seg ? (Entry4*)(base + o_gt) : const_cast<Entry4*>(lv->gemm_tiles);
     Entry4* d_bo = own_seg ? (Entry4*)(base + o_bo) : const_cast<Entry4*>(lv->band_order);
-    p->d_adamw = base + o_adamw;
     p->d_arrived = (uint32_t*)(base + o_arrived);
     p->d_split = (unsigned char*)(base + o_split);
 
