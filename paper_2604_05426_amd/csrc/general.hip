@@ -152,10 +152,12 @@ __global__ __launch_bounds__(64 * NW) void general_shrink_kernel(GenShrinkArgs<T
     const int i = e.a, row0 = e.c + sub;
     const int r = g.pv.rank[i];
     const float s = FWD ? 1.0f : g.pv.scale[i];
-    const T* F = (const T*)(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
+    const T* F = global_ptr<const T>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
     const int K = (int)g.ld;
     const T* xrow = g.src + (int64_t)(row0 + min(l16, rows - 1)) * g.ld;    // rows past the block repeat its last one: not stored
-    // ranks of block b: 16 b + l16, or, where four blocks share one 64-rank row piece of A_i, 64 (b / 4) + 4 l16 + b % 4
+    // Ranks of block b: 16 b + l16, or, where four blocks share one 64-rank row piece of A_i, quad(b / 4) + b % 4: four adjacent
+    // ranks per lane.  The lane that would cross r_i takes the last four ranks instead (what it repeats comes out the same, bit for
+    // bit, from the lane before), so that any rank from 4 on is read in whole quads.
     constexpr bool QUAD = FWD && NB >= 4;
     f32x4 acc[NB];
 #pragma unroll
@@ -165,33 +167,58 @@ __global__ __launch_bounds__(64 * NW) void general_shrink_kernel(GenShrinkArgs<T
     uint4 xa[2][U], fb[2][U][NF];
     quad_t<T> fq[2][U][NQ][kQuadRows<T>];
     // Ranks past r_i repeat valid ones (their sums are not stored); only the end of the contraction has to read as zero, in both
-    // operands.
-    const bool r4 = (r & 3) == 0;
+    // operands.  The plain loads of a whole unit stand in one branch: a condition per load would make each wait for itself.
+    const bool quads = r >= 4;
+    auto quad = [&](int q) { return min(64 * q + 4 * l16, r - 4); };
     auto load = [&](int unit, int set) {
-        const bool inside = (unit + 1) * U * kBlockK<T> <= K;      // uniform over the wavefront
+        const int k0 = unit * U * kBlockK<T> + g4 * kEpc<T>;
+        if ((unit + 1) * U * kBlockK<T> <= K && (quads || !QUAD)) {     // uniform over the wavefront
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = (unit * U + u) * kBlockK<T> + g4 * kEpc<T>, valid = K - k;
-            if (inside) __builtin_memcpy(&xa[set][u], xrow + k, 16);
-            else        xa[set][u] = load16<T>(xrow + k, valid);
-            if constexpr (QUAD) {
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * kBlockK<T>;
+                __builtin_memcpy(&xa[set][u], xrow + k, 16);
+                if constexpr (QUAD) {
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    // r a multiple of 4: lanes past it repeat the last four ranks; else element by element
-                    const int rho = r4 ? min(64 * q + 4 * l16, r - 4) : min(64 * q + 4 * l16, r - 1);
+                    for (int q = 0; q < NQ; ++q)
 #pragma unroll
-                    for (int e = 0; e < kQuadRows<T>; ++e) {
-                        if (inside || e < valid) fq[set][u][q][e] = load_quad<T>(F + (int64_t)(k + e) * r + rho, r4, r - rho);
-                        else                     fq[set][u][q][e] = (quad_t<T>)(0u);
+                        for (int e = 0; e < kQuadRows<T>; ++e)
+                            __builtin_memcpy(&fq[set][u][q][e], F + (int64_t)(k + e) * r + quad(q), sizeof(quad_t<T>));
+                } else {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const int rho = min(16 * b + l16, r - 1);
+                        if constexpr (FWD) {
+                            T* o = reinterpret_cast<T*>(&fb[set][u][b]);
+#pragma unroll
+                            for (int e = 0; e < kEpc<T>; ++e) o[e] = F[(int64_t)(k + e) * r + rho];
+                        } else {
+                            __builtin_memcpy(&fb[set][u][b], F + (int64_t)rho * g.ld + k, 16);
+                        }
                     }
                 }
-            } else {
+            }
+        } else {
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const int rho = min(16 * b + l16, r - 1);
-                    if (FWD)         fb[set][u][b] = gather16<T>(F + (int64_t)k * r + rho, r, inside ? kEpc<T> : valid);
-                    else if (inside) __builtin_memcpy(&fb[set][u][b], F + (int64_t)rho * g.ld + k, 16);
-                    else             fb[set][u][b] = load16<T>(F + (int64_t)rho * g.ld + k, valid);
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * kBlockK<T>, valid = K - k;
+                xa[set][u] = load16<T>(xrow + k, valid);
+                if constexpr (QUAD) {
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) {
+                        const int rho = quads ? quad(q) : min(4 * l16, r - 1);
+#pragma unroll
+                        for (int e = 0; e < kQuadRows<T>; ++e) {
+                            fq[set][u][q][e] = (quad_t<T>)(0u);
+                            if (e < valid) fq[set][u][q][e] = load_quad<T>(F + (int64_t)(k + e) * r + rho, quads, r - rho);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const int rho = min(16 * b + l16, r - 1);
+                        if (FWD) fb[set][u][b] = gather16<T>(F + (int64_t)k * r + rho, r, valid);
+                        else     fb[set][u][b] = load16<T>(F + (int64_t)rho * g.ld + k, valid);
+                    }
                 }
             }
         }
@@ -219,7 +246,10 @@ __global__ __launch_bounds__(64 * NW) void general_shrink_kernel(GenShrinkArgs<T
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) red[(wave * 16 + 4 * g4 + q) * RLD + (QUAD ? 64 * (b / 4) + 4 * l16 + b % 4 : 16 * b + l16)] = acc[b][q];
+        for (int q = 0; q < 4; ++q) {
+            const int rho = !QUAD ? 16 * b + l16 : quads ? quad(b / 4) + b % 4 : 4 * l16 + b;
+            if (!QUAD || (64 * (b / 4) < r && rho < r)) red[(wave * 16 + 4 * g4 + q) * RLD + rho] = acc[b][q];
+        }
     __syncthreads();
     T* out = g.out + g.pv.soff[i] + (int64_t)(row0 - g.pv.off[i]) * r;
     for (int idx = tid; idx < rows * r; idx += 64 * NW) {
@@ -287,30 +317,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
             *reinterpret_cast<uint4*>(Bs + lds_off(idx)) = b;
         }
     };
-    auto compute = [&](f32x4 (&acc)[2][2], int stage) {
+    struct Frags { uint4 a[2][2], b[2][2]; };            // [64-byte half of the wavefront's 128-byte piece][block]
+    auto read_frags = [&](Frags& f, int stage) {
         const unsigned char* As = lds + stage * STAGE;
         const unsigned char* Bs = As + KC_TILE;
-        uint4 fa[2][2], fb[2][2];                        // [64-byte half of the wavefront's 128-byte piece][block]
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int x = 0; x < 2; ++x) {
-                fa[h][x] = *reinterpret_cast<const uint4*>(As + (wk * BT + wm * 32 + x * 16 + l16) * 144 + h * 64 + g4 * 16);
+                f.a[h][x] = *reinterpret_cast<const uint4*>(As + (wk * BT + wm * 32 + x * 16 + l16) * 144 + h * 64 + g4 * 16);
                 if (!FWD) {
-                    fb[h][x] = *reinterpret_cast<const uint4*>(Bs + (wk * BT + wn * 32 + x * 16 + l16) * 144 + h * 64 + g4 * 16);
+                    f.b[h][x] = *reinterpret_cast<const uint4*>(Bs + (wk * BT + wn * 32 + x * 16 + l16) * 144 + h * 64 + g4 * 16);
                 } else if constexpr (sizeof(T) == 4) {
                     const float* p = reinterpret_cast<const float*>(Bs + (wk * KW + h * 16 + 4 * g4) * NC_PITCH) + wn * 32 + x * 16 + l16;
-                    fb[h][x] = make_uint4(__float_as_uint(p[0]), __float_as_uint(p[NC_PITCH / 4]), __float_as_uint(p[2 * (NC_PITCH / 4)]),
-                                          __float_as_uint(p[3 * (NC_PITCH / 4)]));
+                    f.b[h][x] = make_uint4(__float_as_uint(p[0]), __float_as_uint(p[NC_PITCH / 4]), __float_as_uint(p[2 * (NC_PITCH / 4)]),
+                                           __float_as_uint(p[3 * (NC_PITCH / 4)]));
                 } else {
                     const int k = wk * KW + h * 32 + 8 * g4 + (l16 >> 2);
                     const unsigned char* p = Bs + k * NC_PITCH + (unit(k, wn * 2 + x) << 5) + (l16 & 3) * 8;
-                    fb[h][x] = __builtin_bit_cast(uint4, lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * NC_PITCH)));
+                    f.b[h][x] = __builtin_bit_cast(uint4, lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * NC_PITCH)));
                 }
             }
-        // operands swapped: a lane holds one output row and 4 consecutive columns of each block
+    };
+    // operands swapped: a lane holds one output row and 4 consecutive columns of each block
+    auto multiply = [&](f32x4 (&acc)[2][2], const Frags& f) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) block_mma_2x2<T>(fb[h], fa[h], acc);
+        for (int h = 0; h < 2; ++h) block_mma_2x2<T>(f.b[h], f.a[h], acc);
     };
 
     // acc += A B over a contraction of K.  Element (row m0 + i, c) of A at a[i * lda + c], rows [row_lo, row_hi) exist; column
@@ -334,13 +366,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
 #pragma unroll
             for (int c = 0; c < NCH; ++c) store_piece(0, tid + 256 * c, ra[c], rb[c]);
             __syncthreads();
-            compute(acc, 0);
+            Frags f;
+            read_frags(f, 0);
+            multiply(acc, f);
         }
     };
 
-    // The same for whole tiles and at least one whole step (every load is then inside its rows and takes no condition): step t
-    // travels in register set t & 1 and is computed from LDS stage t & 1, its loads run two steps ahead.  A contraction that is
-    // not a multiple of the step ends with a step that starts early; what it repeats is zeroed in both operands.
+    // The same for whole tiles and at least one whole step: every load is inside its rows and takes no condition.  Step t travels
+    // in register set t & 1 and LDS stage t & 1 (loads past the last step fetch it again); products may
+    // be scheduled across the barrier.  What is left of a contraction that is not a multiple of the step is the end of one more step that starts early;
+    // what that repeats is zeroed in both operands.
     auto contract_whole = [&](f32x4 (&acc)[2][2], const T* a, int64_t lda, const T* b, int64_t ldb, int64_t K) {
         uint4 ra[2][NCH], rb[2][NCH];
         const T *pa[NCH], *pb[NCH];
@@ -350,54 +385,68 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
             pa[c] = a + row * lda + k;
             pb[c] = FWD ? b + (idx / CPN) * ldb + (idx % CPN) * EPC : b + row * ldb + k;
         }
-        const int64_t nt = (K + KT - 1) / KT;
-        const int again = (int)(nt * KT - K);            // elements the last step repeats
-        auto load = [&](int64_t step, int set) {
-            const int64_t k0 = step == nt - 1 ? K - KT : step * KT;
+        const int64_t nt = K / KT;
+        const int again = (int)((nt + 1) * KT - K);      // elements the early step repeats (KT: there is none)
+        auto load = [&](int64_t k0, uint4 (&va)[NCH], uint4 (&vb)[NCH]) {
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
-                __builtin_memcpy(&ra[set][c], pa[c] + k0, 16);
-                __builtin_memcpy(&rb[set][c], pb[c] + (FWD ? k0 * ldb : k0), 16);
+                __builtin_memcpy(&va[c], pa[c] + k0, 16);
+                __builtin_memcpy(&vb[c], pb[c] + (FWD ? k0 * ldb : k0), 16);
             }
         };
-        auto zero_head = [&](uint4 v, int drop) {        // the first `drop` elements of a piece
-            uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        auto load_step = [&](int64_t step, int set) { load(min(step, nt - 1) * KT, ra[set], rb[set]); };
+        auto store = [&](int stage, const uint4 (&va)[NCH], const uint4 (&vb)[NCH]) {
 #pragma unroll
-            for (int e = 0; e < EPC; ++e)
-                if (e < drop) {
-                    if constexpr (sizeof(T) == 4) w[e] = 0u;
-                    else w[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
-                }
-            return make_uint4(w[0], w[1], w[2], w[3]);
+            for (int c = 0; c < NCH; ++c) store_piece(stage, tid + 256 * c, va[c], vb[c]);
         };
-        auto store = [&](int64_t step, int set) {
-            if (step == nt - 1 && again > 0) {
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) {
-                    const int idx = tid + 256 * c, k = (idx % CPK) * EPC;
-                    ra[set][c] = zero_head(ra[set][c], again - k);
-                    rb[set][c] = FWD ? (idx / CPN < again ? zero4() : rb[set][c]) : zero_head(rb[set][c], again - k);
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) store_piece(set, tid + 256 * c, ra[set][c], rb[set][c]);
-        };
-        load(0, 0);
-        if (nt > 1) load(1, 1);
-        store(0, 0);
-        if (nt > 2) load(2, 0);
+        Frags f;
+        load_step(0, 0);
+        load_step(1, 1);
+        store(0, ra[0], rb[0]);
+        load_step(2, 0);
         __syncthreads();
-        for (int64_t t = 0; t < nt; t += 2) {
-            if (t + 1 < nt) store(t + 1, 1);
-            if (t + 3 < nt) load(t + 3, 1);
-            compute(acc, 0);
+        int64_t t = 0;
+        for (; t + 1 < nt; t += 2) {
+            store(1, ra[1], rb[1]);
+            load_step(t + 3, 1);
+            read_frags(f, 0);
+            __builtin_amdgcn_sched_barrier(0);           // all reads are on their way before the first product
+            multiply(acc, f);
             __syncthreads();
-            if (t + 1 < nt) {
-                if (t + 2 < nt) store(t + 2, 0);
-                if (t + 4 < nt) load(t + 4, 0);
-                compute(acc, 1);
-                __syncthreads();
+            store(0, ra[0], rb[0]);
+            load_step(t + 4, 0);
+            read_frags(f, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(acc, f);
+            __syncthreads();
+        }
+        if (t < nt) {
+            read_frags(f, 0);
+            multiply(acc, f);
+        }
+        if (again < KT) {
+            auto zero_head = [&](uint4 v, int drop) {    // the first `drop` elements of a piece
+                uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < EPC; ++e)
+                    if (e < drop) {
+                        if constexpr (sizeof(T) == 4) w[e] = 0u;
+                        else w[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
+                    }
+                return make_uint4(w[0], w[1], w[2], w[3]);
+            };
+            load(K - KT, ra[0], rb[0]);
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                const int idx = tid + 256 * c, k = (idx % CPK) * EPC;
+                ra[0][c] = zero_head(ra[0][c], again - k);
+                rb[0][c] = FWD ? (idx / CPN < again ? zero4() : rb[0][c]) : zero_head(rb[0][c], again - k);
             }
+            __syncthreads();                             // the fragments of stage 0 have been read
+            store(0, ra[0], rb[0]);
+            __syncthreads();
+            read_frags(f, 0);
+            multiply(acc, f);
         }
     };
 
@@ -446,7 +495,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
             };
             const int r = __builtin_amdgcn_readlane(c_rank, l), seg0 = __builtin_amdgcn_readlane(c_off, l);
             const int lo = max(seg0, lo_t), hi = min(__builtin_amdgcn_readlane(c_end, l), hi_t);
-            const T* F = reinterpret_cast<const T*>(lane64(c_f));
+            const T* F = global_ptr<const T>(reinterpret_cast<const void*>(lane64(c_f)));
             const float s = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c_sc), l));
             f32x4 ext[2][2];
 #pragma unroll
@@ -616,7 +665,7 @@ __global__ __launch_bounds__(512) void general_wgrad_kernel(GenWgradArgs<T> g) {
         __syncthreads();
     }
     const float s = isA ? 1.0f : g.pv.scale[i];
-    T* out = (T*)(isA ? g.pv.ptrs[i].dA : g.pv.ptrs[i].dB);
+    T* out = global_ptr<T>(isA ? g.pv.ptrs[i].dA : g.pv.ptrs[i].dB);
     for (int idx = tid; idx < 64 * RW; idx += 512) {
         // consecutive threads, consecutive elements of the output: ranks of a dA_i row, columns of a dB_i row
         const int c = isA ? idx / RW : idx % 64, rho = isA ? idx % RW : idx / 64;

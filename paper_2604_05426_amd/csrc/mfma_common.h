@@ -48,6 +48,13 @@ __device__ __forceinline__ uint32_t pack2hw(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2v));
 }
 
+// A pointer read from memory (the adapters' pointer table) that is known to point to device memory.  Without this the compiler
+// has to use flat loads and stores through it, which count as LDS accesses too and return in no order it can rely on: every
+// wait for one becomes a wait for everything.
+template <typename T> __device__ __forceinline__ T* global_ptr(const void* p) {
+    return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p);
+}
+
 // A pointer the compiler may keep in vector registers although it is the same in every lane, moved to scalar registers.
 __device__ __forceinline__ const char* uniform_ptr(const void* p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);

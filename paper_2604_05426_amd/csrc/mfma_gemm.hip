@@ -354,7 +354,7 @@ __global__ __launch_bounds__(NTHR) void fused_gemm_kernel(GemmArgs g) {
             const int r = g.pv.rank[i];
             const int npass = (r + BK - 1) / BK;                       // 1 or 2
             const char* sb = reinterpret_cast<const char*>(g.E + g.pv.soff[i] + (int64_t)(m0 - g.pv.off[i]) * r);
-            const u16* F = (const u16*)(NN ? g.pv.ptrs[i].B : g.pv.ptrs[i].A);
+            const u16* F = global_ptr<const u16>(NN ? g.pv.ptrs[i].B : g.pv.ptrs[i].A);
             // pass 0 goes to row stage 1 / weight slot 2, pass 1 to row stage 0 / weight slot 0 (the buffers tile 0 of the main
             // loop uses: with two passes it is requested after them)
             if (npass == 1 && nk > 0) {
@@ -437,7 +437,7 @@ __global__ __launch_bounds__(NTHR) void fused_gemm_kernel(GemmArgs g) {
                 const int lo = max(seg0, m0), hi = min(seg1, m0 + BM);
                 if (lo >= hi) continue;
                 const int64_t so = g.pv.soff[i];
-                const u16* F = (const u16*)(NN ? g.pv.ptrs[i].B : g.pv.ptrs[i].A);
+                const u16* F = global_ptr<const u16>(NN ? g.pv.ptrs[i].B : g.pv.ptrs[i].A);
                 for (int r0 = 0; r0 < r; r0 += BK) {
                     PassDesc d;
                     d.a_src = g.E + so + r0; d.a_ld = r; d.a_row_base = seg0; d.a_row_lo = lo; d.a_row_hi = hi;

@@ -219,7 +219,7 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
                 lo = max(seg0, m0);
                 hi = min(__builtin_amdgcn_readlane(v_end, l), m_end);
                 const int64_t so = (int64_t)lane64((uint64_t)v_so, l);
-                const u16* F = reinterpret_cast<const u16*>(lane64(v_f, l));
+                const u16* F = global_ptr<const u16>(reinterpret_cast<const void*>(lane64(v_f, l)));
                 const u16* e = g.E + so + (int64_t)(lo - seg0) * r + r0;
                 const bool vec = (r & 7) == 0, e_vec = vec && (so & 7) == 0;
                 if (NN) pass_load(e, r, lo, hi, e_vec, F + (int64_t)r0 * g.Ncols, g.Ncols, true, min(64, r - r0));

@@ -63,7 +63,7 @@ __device__ __forceinline__ void shrink_body(const ShrinkArgs& g, const Entry4 e,
     const int r = g.pv.rank[i];
     const int rpad = (r + 31) & ~31;
     const int nblk = rpad / 32;
-    const u16* F = (const u16*)(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
+    const u16* F = global_ptr<const u16>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
     const bool f_vec = FWD ? ((r & 7) == 0) : true;
     const float s = FWD ? 1.0f : g.pv.scale[i];
     u16* Xs = lds + wave * S_WAVE;
@@ -264,7 +264,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     const int l16 = lane & 15, g4 = lane >> 4;
     const int i = e.a, row0 = e.c, rows = e.d;
     const int r = g.pv.rank[i];
-    const u16* F = (const u16*)(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
+    const u16* F = global_ptr<const u16>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
     const float s = FWD ? 1.0f : g.pv.scale[i];
     // swizzle key of contraction row k of the A_i tile
     auto fkey = [](int k) { return RB16 == 8 ? nn_swz(k) : (((k >> 1) & 1) | (((k >> 3) & 1) << 1)); };
@@ -294,7 +294,11 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
         }
     }
     const int all_steps = g.Kdim / 64;
-    const int step0 = (int)((int64_t)all_steps * split / g.splits), steps = (int)((int64_t)all_steps * (split + 1) / g.splits) - step0;
+    int step0 = 0, steps = all_steps;
+    if (g.splits > 1) {
+        step0 = all_steps / g.splits * split;
+        steps = split == g.splits - 1 ? all_steps - step0 : all_steps / g.splits;
+    }
     const int64_t stepF = FWD ? (int64_t)64 * __builtin_amdgcn_readfirstlane(r) * 2 : 128;
     const char* baseX = uniform_ptr(g.src + (int64_t)row0 * g.ld + (int64_t)step0 * 64);
     const char* baseF = uniform_ptr(reinterpret_cast<const char*>(F) + step0 * stepF);
@@ -439,7 +443,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
 template <bool FWD, bool WIDE, bool MIXED>
 __global__ __launch_bounds__(64 * SNW) void shrink_tiled_kernel(ShrinkArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[(MIXED || WIDE) ? 163840 : 147456];
-    const int split = blockIdx.x / g.blocks, block = blockIdx.x - split * g.blocks;
+    const int split = g.splits > 1 ? blockIdx.x / g.blocks : 0, block = blockIdx.x - split * g.blocks;
     const Entry4 e = g.pv.class_blocks[block];
     const int r = g.pv.rank[e.a];
     if (WIDE && r > 64) {
@@ -672,7 +676,7 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs& g, u16* lds, const i
     //   dA_i item (transposed block): rows = ranks, lane column = panel column: out[c][rho], 4 consecutive rho
     // so every lane stores 8-byte (bf16) or 16-byte (fp32 partial) pieces; ranks that are not multiples of 4 and
     // the ragged edge go element by element.
-    u16* out = (u16*)(isA ? g.pv.ptrs[i].dA : g.pv.ptrs[i].dB);
+    u16* out = global_ptr<u16>(isA ? g.pv.ptrs[i].dA : g.pv.ptrs[i].dB);
     float* part = nchunks == 1 ? nullptr
                                : g.partials + g.pv.part_off[i] + (int64_t)chunk * (kk + nn) * r + (isA ? 0 : kk * r);
     const bool vec = isA ? ((r & 3) == 0) : ((nn & 3) == 0);
@@ -746,7 +750,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs g, const in
         const float4 t = *reinterpret_cast<const float4*>(part + (int64_t)c * per);
         v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
     }
-    uint2* out = reinterpret_cast<uint2*>(idx < kk * r ? (u16*)g.pv.ptrs[i].dA + idx : (u16*)g.pv.ptrs[i].dB + (idx - kk * r));
+    uint2* out = reinterpret_cast<uint2*>(idx < kk * r ? global_ptr<u16>(g.pv.ptrs[i].dA) + idx : global_ptr<u16>(g.pv.ptrs[i].dB) + (idx - kk * r));
     if (g.accumulate) {
         const uint2 old = *out;
         v.x += __uint_as_float(old.x << 16); v.y += __uint_as_float(old.x & 0xffff0000u);
@@ -763,8 +767,8 @@ __global__ void wgrad_zero_empty_kernel(PlanView pv) {
     const int64_t kk = pv.k, nn = pv.n;
     const int64_t per = (kk + nn) * r;
     for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < per; idx += (int64_t)gridDim.x * 256) {
-        if (idx < kk * r) ((u16*)pv.ptrs[i].dA)[idx] = 0;
-        else ((u16*)pv.ptrs[i].dB)[idx - kk * r] = 0;
+        if (idx < kk * r) global_ptr<u16>(pv.ptrs[i].dA)[idx] = 0;
+        else global_ptr<u16>(pv.ptrs[i].dB)[idx - kk * r] = 0;
     }
 }
 
@@ -831,7 +835,7 @@ __global__ __launch_bounds__(128 * XCW) void expand_add_kernel(ExpandArgs g) {
     const int64_t so = g.pv.soff[i];
     const int seg0 = g.pv.off[i];
     const float s = FWD ? g.pv.scale[i] : 1.0f;
-    const u16* F = (const u16*)(FWD ? g.pv.ptrs[i].B : g.pv.ptrs[i].A);
+    const u16* F = global_ptr<const u16>(FWD ? g.pv.ptrs[i].B : g.pv.ptrs[i].A);
     const int colw = ct * XC + wc * 64;          // first column of this wavefront
     const bool stream_in = g.stream_in != 0;
 
