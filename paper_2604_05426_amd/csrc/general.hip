@@ -707,6 +707,8 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
     if (a.M == 0 || (!a.base && !a.lora)) return MLORA_OK;
     ProfScope prof(p, FWD ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
     auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
+    // 32 x 32 tiles where 64 x 64 ones would leave half the chip idle.  fp32, us 32 x 32 / 64 x 64: 500 x 513 (72 tiles) 16 / 20,
+    // 700 x 1001 (176) 56 / 55, 1000 x 1001 (256) 46 / 34; bf16 12.3 / 11.6, 29 / 20, 28 / 16; 256 x 257 (20): 11 / 14 and 9.6 / 9.9.
     const bool split = tiles(64) <= p->num_cus / 2;
     a.tiles_n = (a.N + (split ? 31 : 63)) / (split ? 32 : 64);
     if (split) hipLaunchKernelGGL((general_gemm_kernel<T, FWD, 4>), dim3((unsigned)tiles(32)), dim3(256), 0, st, a);

@@ -5,6 +5,8 @@
 // S_i = X_i A_i are computed.  App. A.1: blocks map to token ranges through the per-adapter
 // offsets, the boundary block is masked at the segment end, ranks are masked (columns beyond
 // r_i contribute zero).
+#include <type_traits>
+
 #include "mfma_common.h"
 
 namespace mlora {
@@ -246,7 +248,7 @@ __global__ __launch_bounds__(64 * SNW) void shrink_kernel(ShrinkArgs g) {
 // spent 68 us on a contraction of 14336 with 237 CUs idle.  With `splits` > 1 each work group of a block takes its share of the steps
 // and stores its accumulators; the one that arrives last (agent-scope counter) adds all shares in split order - so the result does
 // not depend on the order of arrival - and writes S.  Nobody waits for anybody.
-template <bool FWD, int RB16, bool DENSE = false, int ROWS = 64>
+template <bool FWD, int RB16, bool SPLIT, bool DENSE = false, int ROWS = 64>
 __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Entry4 e, unsigned char* lds, const int block, const int split,
                                                   const int half = 0) {
     static_assert(FWD || !DENSE, "the dense adapter tile is a layout of A_i");
@@ -295,7 +297,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     }
     const int all_steps = g.Kdim / 64;
     int step0 = 0, steps = all_steps;
-    if (g.splits > 1) {
+    if (SPLIT) {
         step0 = all_steps / g.splits * split;
         steps = split == g.splits - 1 ? all_steps - step0 : all_steps / g.splits;
     }
@@ -362,7 +364,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no load may still be writing LDS when the work group ends
 
-    if (g.splits > 1) {
+    if constexpr (SPLIT) {
         constexpr int SHARE = 8 * NCB * 1024;            // bytes of one work group's accumulators
         static_assert(SHARE <= (ROWS == 128 ? kSplitBytesWide : RB16 == 8 ? kSplitBytesWide / 2 : kSplitBytesNarrow), "a share fits its slot");
         const bool wide = block < g.blocks_wide;
@@ -440,29 +442,29 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
 // dense in LDS (rows of 2 r bytes: 8-byte granules, which is what one lane of the transposing load reads), any other rank
 // the register-staged body.  Uniform branches per work group.
 // Row blocks of the wide class have 128 rows (kBlockRowsWide); the bodies built for 64 rows take such a block as two halves.
-template <bool FWD, bool WIDE, bool MIXED>
+template <bool FWD, bool WIDE, bool MIXED, bool SPLIT>
 __global__ __launch_bounds__(64 * SNW) void shrink_tiled_kernel(ShrinkArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[(MIXED || WIDE) ? 163840 : 147456];
-    const int split = g.splits > 1 ? blockIdx.x / g.blocks : 0, block = blockIdx.x - split * g.blocks;
+    const int split = SPLIT ? blockIdx.x / g.blocks : 0, block = blockIdx.x - split * g.blocks;
     const Entry4 e = g.pv.class_blocks[block];
     const int r = g.pv.rank[e.a];
     if (WIDE && r > 64) {
         if (!MIXED || (r & 7) == 0) {
-            shrink_tiled_body<FWD, 8, false, kBlockRowsWide>(g, e, lds, block, split);
+            shrink_tiled_body<FWD, 8, SPLIT, false, kBlockRowsWide>(g, e, lds, block, split);
         } else {
             for (int h = 0; h < e.d; h += SR) {       // (uniform)
                 const Entry4 half{e.a, e.b, e.c + h, min(SR, e.d - h)};
                 if (h) __syncthreads();               // every wavefront is done with the first half's tiles
-                if (FWD && (r & 7) == 4) shrink_tiled_body<FWD, 8, FWD>(g, half, lds, block, split, h / SR);
+                if (FWD && (r & 7) == 4) shrink_tiled_body<FWD, 8, SPLIT, FWD>(g, half, lds, block, split, h / SR);
                 else if (split == 0) shrink_body<FWD, 4, 32, 2, 1>(g, half, reinterpret_cast<u16*>(lds));   // (takes the whole contraction)
             }
         }
     } else if (MIXED && FWD && (r & 7) == 4) {
-        shrink_tiled_body<FWD, 4, FWD>(g, e, lds, block, split);
+        shrink_tiled_body<FWD, 4, SPLIT, FWD>(g, e, lds, block, split);
     } else if (MIXED && (r & 7) != 0) {
         if (split == 0) shrink_body<FWD, 2, 64, 2, 1>(g, e, reinterpret_cast<u16*>(lds));
     } else {
-        shrink_tiled_body<FWD, 4>(g, e, lds, block, split);
+        shrink_tiled_body<FWD, 4, SPLIT>(g, e, lds, block, split);
     }
 }
 
@@ -482,12 +484,17 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
     a.partials = p->d_split;
     a.arrived = p->d_arrived;
     const dim3 grid(tiled ? a.blocks * a.splits : p->n_row_blocks);
-    if (tiled && !mixed) {
-        if (!wide) hipLaunchKernelGGL((shrink_tiled_kernel<FWD, false, false>), grid, block, 0, st, a);
-        else       hipLaunchKernelGGL((shrink_tiled_kernel<FWD, true, false>), grid, block, 0, st, a);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, a); };
+    // (the split build by itself: its handing-over costs the plain one 1 us of 16 in registers and code even where it is not taken)
+    auto tiled_build = [&](auto split) {
+        constexpr bool SP = decltype(split)::value;
+        if (!mixed) { if (!wide) go(shrink_tiled_kernel<FWD, false, false, SP>); else go(shrink_tiled_kernel<FWD, true, false, SP>); }
+        else        { if (!wide) go(shrink_tiled_kernel<FWD, false, true, SP>);  else go(shrink_tiled_kernel<FWD, true, true, SP>); }
+    };
+    if (tiled && a.splits > 1) {
+        tiled_build(std::true_type{});
     } else if (tiled) {
-        if (!wide) hipLaunchKernelGGL((shrink_tiled_kernel<FWD, false, true>), grid, block, 0, st, a);
-        else       hipLaunchKernelGGL((shrink_tiled_kernel<FWD, true, true>), grid, block, 0, st, a);
+        tiled_build(std::false_type{});
     } else {
         if (!wide) hipLaunchKernelGGL((shrink_kernel<FWD, false>), grid, block, 0, st, a);
         else       hipLaunchKernelGGL((shrink_kernel<FWD, true>), grid, block, 0, st, a);
