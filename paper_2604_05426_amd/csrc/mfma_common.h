@@ -164,7 +164,7 @@ struct GemmArgs {
     int32_t skip_lora;             // MLORA_FLAG_BASE_ONLY, or a plan without adapters (the LoRA-only mode has a kernel of its own)
     int32_t stream_out;            // write the output with streaming stores (see launch_gemm)
     int32_t band_group;            // bands whose column groups are interleaved (see the tile order)
-    int32_t xcd_run;               // small-tile kernel: consecutive tiles per XCD (see its tile order)
+    int32_t xcd_run;               // consecutive tiles per XCD (see the kernels' tile orders; large-tile kernel: 0 = groups of 32)
     PlanView pv;
 };
 

@@ -18,7 +18,8 @@ RANKS, SCALES = (8, 0, 128, 33, 70, 16), (2.0, 1.0, 0.25, 0.5, 1.0, 3.0)
 SHAPES = [(70, 40, 72), (130, 64, 448), (230, 512, 136), (333, 576, 584),             # 64 x 64 tiles; ring of 8 stages
           (1100, 320, 1096), (1100, 384, 1096), (1100, 456, 1096), (1100, 1096, 392),   # 64 x 128; ring of 6
           (2900, 256, 1096), (2900, 328, 1096), (2900, 384, 1096), (2900, 1096, 328),   # 128 x 128; ring of 5
-          (8100, 72, 2048), (8100, 2048, 64)]                                         # 256 x 256 forward / backward
+          (8100, 72, 2048), (8100, 2048, 64),                                         # 256 x 256 forward / backward
+          (6900, 72, 1800), (6900, 1800, 72)]                                         # the same, fewer tiles than CUs
 
 
 @pytest.mark.parametrize("T,k,n", SHAPES)
