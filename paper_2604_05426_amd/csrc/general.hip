@@ -14,8 +14,8 @@
 // load, the edge tiles alone made the bf16 products of 1500 x 1001 outputs 52 us instead of 27).
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
-// tokens, 256 x 256: 171 -> 26 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 394 us (its two frozen-weight products 176 us each, 98
-// TFLOP/s; 144 is what a large fp32 product reaches on this card); bf16, 1500 tokens, 2048 x 1001: 1105 -> 97 us.
+// tokens, 256 x 256: 171 -> 26 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 383 us (its two frozen-weight products 176 us each, 98
+// TFLOP/s; 144 is what a large fp32 product reaches on this card); bf16, 1500 tokens, 2048 x 1001: 1105 -> 83 us.
 #include "mfma_common.h"
 
 namespace mlora {
