@@ -5,18 +5,23 @@
 // With one 256 x 256 tile per CU a layer of 1024 x 4096 outputs keeps 64 of 256 CUs busy for the whole contraction; 128 x 128
 // tiles keep all of them busy.  What bounds a CU then is the operand stream (32 KB per 64-wide step against 512 cycles of MFMA)
 // and, before that, latency, so the tiles come by direct global -> LDS loads into a ring that fills the LDS (all but the
-// current step in flight, one barrier per step) and the fragments of step t + 1 are read while step t is multiplied.
-// 8 wavefronts: 2 x 2 sub-tiles of the output, times two halves of each 64-wide contraction step.  Splitting the step instead of
-// the tile keeps the sub-tile of a wavefront at 64 x 64 (LDS reads per MFMA as low as four wavefronts would have) with two
-// wavefronts per SIMD; the two partial accumulators are added once at the end, in a fixed order.
+// current step in flight, one barrier per step) and the fragments of each 32-wide half step are read while the one before it is
+// multiplied.
+//
+// Order of the sum: every output element is one chain of MFMAs - rank extension, contraction in ascending order, tail - exactly as in
+// the 256 x 256 kernel, so that a row has the same bits whichever tile its batch is given: the tile follows from the number of tokens
+// of the whole batch, and a job's results must not change when a neighbour joins or leaves it.  That is why the 8 wavefronts
+// (2 x 4 sub-tiles of the output, two per SIMD) do not share a step's contraction among themselves; with 2 x 2 sub-tiles and the
+// two halves of a step summed apart the LDS reads per MFMA were a third fewer; over 190 products the mean time moved by -2.5 %
+// (128 x 128), 0 (64 x 128) and +5 % (64 x 64).
 //
 // Rank extension: adapter by adapter into a second accumulator set, of which the adapter's own rows are then taken over (scaled
 // in fp32).  Rows of other adapters never reach the result, so no operand has to be masked and a diverged neighbour's Inf / NaN
 // stays out of it.
 //
-// 1024 x 4096 outputs, k = 4096: 104-106 -> 37-39 us; 230 x 512, k = 2048: 56 -> 13 us.  A 128 x 128 work group spends 0.35 us
-// per step with few neighbours (32 KB at the 45-50 B/clk a CU's load path takes; loads that always hit: 0.30) and 0.43-0.50 us
-// with all CUs busy, where the MFMAs alone would take 0.21.
+// 1000 x 4096 outputs, k = 4096: 85 us with 256 x 256 tiles, 40 with 128 x 128; 200 x 512, k = 2048: 67 and, with 64 x 64, 14.  A
+// 128 x 128 work group spends about 0.5 us per step with all CUs busy (32 KB of operands at the 45-50 B/clk a CU's load path takes
+// are 0.3), where the MFMAs alone would take 0.21.
 #include "mfma_common.h"
 
 namespace mlora {
@@ -36,14 +41,14 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
     constexpr int AT = BM * 128, BT = BN * 128, STAGE = AT + BT;   // bytes: operand tiles of one 64-wide step
     constexpr int NST = SG_LDS / STAGE < 8 ? SG_LDS / STAGE : 8;   // ring stages
     constexpr int NA = BM / 64, NB_ = BN / 64, LPS = NA + NB_;     // direct loads per wavefront and step
-    constexpr int WTM = BM / 2, WTN = BN / 2;                      // sub-tile of a wavefront
+    constexpr int WTM = BM / 2, WTN = BN / 4;                      // sub-tile of a wavefront
     constexpr int MB = WTM / 16, NB = WTN / 16;
     constexpr int BROW = BN * 2;                                   // NN: bytes per contraction row of the weight tile
     static_assert(LPS * (NST - 2) < 64, "vmcnt holds 6 bits");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    const int wm = wave >> 2, wn = wave & 3;
     const int l16 = lane & 15, g4 = lane >> 4;
 
     // Tile order: bands of 8 row tiles x all column tiles, numbered down the rows first; every XCD (blockIdx % 8) takes runs of
@@ -112,42 +117,42 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
     bf16x8 fa[2][MB], fb[2][NB];
-    const int a_off = (wm * WTM + l16) * 128 + (((kg * 4 + g4) ^ (l16 & 7)) << 4);
-    const int bnt_off = (wn * WTN + l16) * 128 + (((kg * 4 + g4) ^ (l16 & 7)) << 4);
+    // a step is two 32-wide halves h; the fragments of one are read while the other is multiplied
+    const int a_off = (wm * WTM + l16) * 128, bnt_off = (wn * WTN + l16) * 128;
     const int vq = fkey(8 * g4 + (l16 >> 2));
-    const int bnn_off = (kg * 32 + 8 * g4 + (l16 >> 2)) * BROW + (l16 & 3) * 8;
-    auto read_frag_a = [&](int slot, int buf, int a) {
-        fa[buf][a] = lds_read_frag(reinterpret_cast<const u16*>(lds + slot * STAGE + a_off + a * 2048));
+    const int bnn_off = (8 * g4 + (l16 >> 2)) * BROW + (l16 & 3) * 8;
+    auto read_frag_a = [&](int slot, int h, int a) {
+        fa[h][a] = lds_read_frag(reinterpret_cast<const u16*>(lds + slot * STAGE + a_off + (((h * 4 + g4) ^ (l16 & 7)) << 4) + a * 2048));
     };
-    auto read_frag_b = [&](int slot, int buf, int b) {
+    auto read_frag_b = [&](int slot, int h, int b) {
         const unsigned char* Bs = lds + slot * STAGE + AT;
         if (NN) {
-            const unsigned char* p = Bs + bnn_off + (((wn * NB + b) ^ vq) << 5);
-            fb[buf][b] = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * BROW));
+            const unsigned char* p = Bs + bnn_off + h * 32 * BROW + (((wn * NB + b) ^ vq) << 5);
+            fb[h][b] = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * BROW));
         } else {
-            fb[buf][b] = lds_read_frag(reinterpret_cast<const u16*>(Bs + bnt_off + b * 2048));
+            fb[h][b] = lds_read_frag(reinterpret_cast<const u16*>(Bs + bnt_off + (((h * 4 + g4) ^ (l16 & 7)) << 4) + b * 2048));
         }
     };
-    auto read_frags = [&](int slot, int buf) {
+    auto read_frags = [&](int slot, int h) {
 #pragma unroll
-        for (int a = 0; a < MB; ++a) read_frag_a(slot, buf, a);
+        for (int a = 0; a < MB; ++a) read_frag_a(slot, h, a);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) read_frag_b(slot, buf, b);
+        for (int b = 0; b < NB; ++b) read_frag_b(slot, h, b);
     };
     // ask the scheduler to alternate a group's LDS reads with its MFMAs
     auto interleave = [&]() {
         for (int i = 0; i < NB; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, NB == 1 ? 3 : 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
     // operands swapped: a lane ends with one output row and 4 consecutive columns of each 16 x 16 block
-    auto mma = [&](f32x4 (&c)[MB][NB], int buf) {
+    auto mma = [&](f32x4 (&c)[MB][NB], int h) {
 #pragma unroll
         for (int a = 0; a < MB; ++a)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) c[a][b] = mfma16(fb[buf][b], fa[buf][a], c[a][b]);
+            for (int b = 0; b < NB; ++b) c[a][b] = mfma16(fb[h][b], fa[h][a], c[a][b]);
     };
 
     // Operands that are not whole aligned 64-wide steps (rank extension, tail of the contraction) go through registers into the
@@ -246,7 +251,9 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
                 else r0 += 64;
                 if (todo) load_next();
                 lds_barrier();
-                if (kg * 32 < kc) { read_frags(NST - 1, 0); mma(ext, 0); }
+                read_frags(NST - 1, 0);
+                mma(ext, 0);
+                if (kc > 32) { read_frags(NST - 1, 1); mma(ext, 1); }
                 if (last_of_adapter) {
 #pragma unroll
                     for (int a = 0; a < MB; ++a) {
@@ -263,6 +270,64 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
         }
     }
 
+    // ---- contraction over the frozen weight -----------------------------------------------------------
+    // Step t starts with the fragments of its first half in registers: the second half's are read while the first is multiplied.  Then
+    // stage t + 1 has landed and everybody has read stage t (its slot is free for stage t + NST); the first half of t + 1 is
+    // read while the second of t is multiplied.
+    if (nk >= NST) {
+        lds_barrier();                   // the pass slot has been read
+        issue();                         // stage NST - 1
+        wait_loads_and_barrier<LPS * (NST - 1)>();
+        read_frags(0, 0);
+        int cur = 0, nxt = 1;            // slots of stages t and t + 1
+        auto half = [&](int h, int slot, bool load) {    // multiply half h, read the other half from `slot`
+#pragma unroll
+            for (int a = 0; a < MB; ++a) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (load) {
+#pragma unroll
+                    for (int c = 0; c < LPS; ++c)
+                        if (c * MB / LPS == a) issue1(c);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                read_frag_a(slot, h ^ 1, a);
+#pragma unroll
+                for (int b = a * NB / MB; b < (a + 1) * NB / MB; ++b) read_frag_b(slot, h ^ 1, b);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[a][b] = mfma16(fb[h][b], fa[h][a], acc[a][b]);
+                interleave();
+            }
+        };
+        auto advance = [&]() {
+            cur = nxt;
+            nxt = nxt == NST - 1 ? 0 : nxt + 1;
+        };
+        for (int t = 0; t < nk - NST; ++t) {
+            half(0, cur, false);
+            wait_loads_and_barrier<LPS * (NST - 2)>();
+            half(1, nxt, true);
+            advance();
+        }
+        // the last NST stages: nothing left to load
+#define SG_DRAIN(J)                                                                             \
+        if (J < NST) {                                                                          \
+            half(0, cur, false);                                                                \
+            if (J + 1 < NST) {                                                                  \
+                wait_loads_and_barrier<(NST - 2 - J > 0 ? NST - 2 - J : 0) * LPS>();            \
+                half(1, nxt, false);                                                            \
+            } else {                                                                            \
+                mma(acc, 1);                                                                    \
+            }                                                                                   \
+            advance();                                                                          \
+        }
+        SG_DRAIN(0) SG_DRAIN(1) SG_DRAIN(2) SG_DRAIN(3) SG_DRAIN(4) SG_DRAIN(5) SG_DRAIN(6) SG_DRAIN(7)
+        static_assert(NST <= 8, "drain steps");
+#undef SG_DRAIN
+    } else if (nk > 0) {
+        wait_loads_and_barrier<0>();
+        for (int t = 0; t < nk; ++t) { read_frags(t, 0); read_frags(t, 1); mma(acc, 0); mma(acc, 1); }
+    }
+
     // ---- tail of a contraction that is not a multiple of 64 -----------------------------------------
     if ((g.Kdim & 63) != 0) {
         const int k0 = nk * 64;
@@ -271,108 +336,33 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
                   g.ldb, true, g.Kdim - k0);
         pass_store(g.Kdim - k0);
         lds_barrier();
-        if (kg * 32 < g.Kdim - k0) { read_frags(NST - 1, 0); mma(acc, 0); }
+        read_frags(NST - 1, 0);
+        mma(acc, 0);
+        if (g.Kdim - k0 > 32) { read_frags(NST - 1, 1); mma(acc, 1); }
     }
 
-    // ---- contraction over the frozen weight -----------------------------------------------------------
-    // Step t: stage t + 1 has landed and everybody has read the fragments of stage t (its slot is free for stage t + NST);
-    // read the fragments of t + 1 while multiplying those of t.
-    if (nk >= NST) {
-        lds_barrier();                   // the pass slot has been read
-        issue();                         // stage NST - 1
-        wait_loads_and_barrier<LPS * (NST - 1)>();
-        read_frags(0, 0);
-        int nxt = 1;                     // slot of stage t + 1
-        auto step = [&](int buf) {
-            wait_loads_and_barrier<LPS * (NST - 2)>();
-#pragma unroll
-            for (int a = 0; a < MB; ++a) {
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int c = 0; c < LPS; ++c)
-                    if (c * MB / LPS == a) issue1(c);
-                __builtin_amdgcn_sched_barrier(0);
-                read_frag_a(nxt, buf ^ 1, a);
-#pragma unroll
-                for (int b = a * NB / MB; b < (a + 1) * NB / MB; ++b) read_frag_b(nxt, buf ^ 1, b);
-#pragma unroll
-                for (int b = 0; b < NB; ++b) acc[a][b] = mfma16(fb[buf][b], fa[buf][a], acc[a][b]);
-                interleave();
-            }
-            nxt = nxt == NST - 1 ? 0 : nxt + 1;
-        };
-        const int full = nk - NST;
-        int t = 0;
-        for (; t + 2 <= full; t += 2) { step(0); step(1); }
-        if (t < full) {
-            step(0);
-#pragma unroll
-            for (int a = 0; a < MB; ++a) fa[0][a] = fa[1][a];
-#pragma unroll
-            for (int b = 0; b < NB; ++b) fb[0][b] = fb[1][b];
-        }
-        // the last NST stages: nothing left to load
-#define SG_DRAIN(J)                                                                             \
-        if (J < NST) {                                                                          \
-            if (J + 1 < NST) {                                                                  \
-                wait_loads_and_barrier<(NST - 2 - J > 0 ? NST - 2 - J : 0) * LPS>();            \
-                read_frags(nxt, (J & 1) ^ 1);                                                   \
-            }                                                                                   \
-            mma(acc, J & 1);                                                                    \
-            nxt = nxt == NST - 1 ? 0 : nxt + 1;                                                 \
-        }
-        SG_DRAIN(0) SG_DRAIN(1) SG_DRAIN(2) SG_DRAIN(3) SG_DRAIN(4) SG_DRAIN(5) SG_DRAIN(6) SG_DRAIN(7)
-        static_assert(NST <= 8, "drain steps");
-#undef SG_DRAIN
-    } else if (nk > 0) {
-        wait_loads_and_barrier<0>();
-        for (int t = 0; t < nk; ++t) { read_frags(t, 0); mma(acc, 0); }
-    }
-
-    // ---- the two contraction halves are added: each wavefront finishes half of its sub-tile's rows ------
+    // ---- the tile goes through LDS, whole rows of it to memory ----------------------------------------
     lds_barrier();
-    {
-        float4* red = reinterpret_cast<float4*>(lds);
-        constexpr int HB = MB / 2 * NB;
+    constexpr int E_LD = BN + 8;
+    static_assert(BM * E_LD * 2 <= NST * STAGE, "epilogue staging fits the ring");
+    u16* Es = reinterpret_cast<u16*>(lds);
 #pragma unroll
-        for (int a = 0; a < MB / 2; ++a)
+    for (int a = 0; a < MB; ++a)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const f32x4 v = kg == 0 ? acc[a + MB / 2][b] : acc[a][b];
-                red[(wave * HB + a * NB + b) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
-            }
-        lds_barrier();
-        f32x4 sum[MB / 2][NB];
-#pragma unroll
-        for (int a = 0; a < MB / 2; ++a)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const float4 o = red[((wave ^ 4) * HB + a * NB + b) * 64 + lane];
-                const f32x4 mine = kg == 0 ? acc[a][b] : acc[a + MB / 2][b];
-                sum[a][b] = f32x4{mine[0] + o.x, mine[1] + o.y, mine[2] + o.z, mine[3] + o.w};
-            }
-        // transpose through LDS (behind the partial sums), whole row segments to memory
-        constexpr int E_LD = WTN + 8;
-        static_assert(8 * HB * 1024 + 8 * (WTM / 2) * E_LD * 2 <= NST * STAGE, "reduction and epilogue staging fit the ring");
-        u16* Es = reinterpret_cast<u16*>(lds + 8 * HB * 1024) + wave * (WTM / 2) * E_LD;
-#pragma unroll
-        for (int a = 0; a < MB / 2; ++a)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                uint2 v;
-                v.x = pack2hw(sum[a][b][0], sum[a][b][1]);
-                v.y = pack2hw(sum[a][b][2], sum[a][b][3]);
-                *reinterpret_cast<uint2*>(Es + (a * 16 + l16) * E_LD + b * 16 + g4 * 4) = v;
-            }
-        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the same wavefront reads back what it wrote
-        constexpr int CPR = WTN / 8, RPI = 64 / CPR;
-#pragma unroll
-        for (int it = 0; it < WTM / 2 / RPI; ++it) {
-            const int rr = it * RPI + lane / CPR, c = lane % CPR;
-            const int row = m0 + wm * WTM + kg * (WTM / 2) + rr, col = n0 + wn * WTN + c * 8;
-            if (row >= g.M || col >= g.Ncols) continue;   // Ncols is a multiple of 8: chunks are all-in or all-out
-            store_streaming(g.C + (int64_t)row * g.ldc + col, *reinterpret_cast<const uint4*>(Es + rr * E_LD + c * 8));
+        for (int b = 0; b < NB; ++b) {
+            uint2 v;
+            v.x = pack2hw(acc[a][b][0], acc[a][b][1]);
+            v.y = pack2hw(acc[a][b][2], acc[a][b][3]);
+            *reinterpret_cast<uint2*>(Es + (wm * WTM + a * 16 + l16) * E_LD + wn * WTN + b * 16 + g4 * 4) = v;
         }
+    lds_barrier();
+    constexpr int CPR = BN / 8;
+#pragma unroll
+    for (int it = 0; it < BM * CPR / SG_THREADS; ++it) {
+        const int idx = tid + SG_THREADS * it, rr = idx / CPR, c = idx % CPR;
+        const int row = m0 + rr, col = n0 + c * 8;
+        if (row >= g.M || col >= g.Ncols) continue;   // Ncols is a multiple of 8: chunks are all-in or all-out
+        store_streaming(g.C + (int64_t)row * g.ldc + col, *reinterpret_cast<const uint4*>(Es + rr * E_LD + c * 8));
     }
 }
 
@@ -392,10 +382,10 @@ static void launch_small(GemmArgs g, bool fwd, hipStream_t st) {
 // Which kernel a product of M x N outputs over a contraction of K takes: -1 the 256 x 256 one, else an index of the table.
 // Every kernel runs one work group per CU, so a launch takes  launch + rounds x (fill and epilogue + steps x step)  with
 // rounds = tiles over CUs, rounded up.  The step times are what the kernels sustain with all CUs busy (64-wide step; the
-// 256 x 256 kernel moves the fewest bytes per product and wins wherever its last round is not too empty).  Against 94 shapes
-// of 64 .. 16384 tokens and widths 512 .. 14336 the choice cost 1 % over the best of the four, and no shape more than 15 %.
-// Measured (us, 256 x 256 / 128 x 128 / 64 x 128 / 64 x 64): 1000 x 4096 x 4096  111 / 40 / 53 / 73;  1000 x 1024 x 4096
-// 92 / 33 / 26 / 22;  200 x 512 x 2048  73 / 26 / 18 / 14;  4000 x 4096 x 4096  107 / 146 / 208 / 272.
+// 256 x 256 kernel moves the fewest bytes per product and wins wherever its last round is not too empty).  Over 192 products
+// (64 .. 16384 tokens, widths 512 .. 14336, both directions) the choice takes 0.1 % longer in all than the best of the four, 11 % at worst.
+// Measured (us, 256 x 256 / 128 x 128 / 64 x 128 / 64 x 64, tokens x outputs x contraction): 1000 x 4096 x 4096  86 / 41 / 56 / 81;
+// 1000 x 1024 x 4096  81 / 34 / 28 / 23;  200 x 512 x 2048  67 / 25 / 18 / 14;  4000 x 4096 x 4096  110 / 157 / 220 / 300.
 int small_gemm_tile(int64_t M, int64_t N, int64_t K, int num_cus) {
     struct { int bm, bn; double launch, round, step; } const tab[4] = {
         {256, 256, 3.0, 4.5, 1.45}, {128, 128, 4.0, 2.5, 0.48}, {64, 128, 4.0, 2.0, 0.32}, {64, 64, 3.5, 2.0, 0.225}};

@@ -1,0 +1,46 @@
+"""An adapter's rows of S, Y, dS and dX have the same bits whoever shares its batch: every kernel and tile that the layer may choose
+for a batch sums a row in one order, which the adapter's own rank and the layer's widths fix.  One adapter's segment is run alone
+and among neighbours whose tokens and ranks send the same layer to other tiles, splits and builds."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_05426_amd import workloads as wl
+from paper_2604_05426_amd.harness import DeviceLayer
+
+pytestmark = pytest.mark.gpu
+
+ROWS = 150      # tokens of the adapter under test
+
+
+def _run(dtype, k, n, rank, before, after, seed=11):
+    """(S, Y, dS, dX) bits of the adapter with `before` / `after` = (rank, tokens) of its neighbours; its own data depend on `seed` alone."""
+    own = wl.make_workload("own", dtype, k, n, [rank], [ROWS], [0.7], seed=seed, b_sigma=0.3)
+    ranks = [r for r, _ in before] + [rank] + [r for r, _ in after]
+    lens = [t for _, t in before] + [ROWS] + [t for _, t in after]
+    i = len(before)
+    w = wl.make_workload("batch", dtype, k, n, ranks, lens, [0.7] * len(ranks), seed=seed + 1, b_sigma=0.3)
+    lo = w.offsets[i]
+    w.W[...], w.A[i], w.B[i] = own.W, own.A[0], own.B[0]
+    w.X[lo:lo + ROWS], w.dY[lo:lo + ROWS] = own.X, own.dY
+    dl = DeviceLayer(w)
+    dl.forward(); dl.backward(); dl.sync()
+    got = [dl.S_list()[i], dl.Y[lo:lo + ROWS].clone(), dl.dS_list()[i], dl.dX[lo:lo + ROWS].clone()]
+    dl.plan.destroy()
+    return [np.asarray(g) if isinstance(g, np.ndarray) else g.view(torch.int16 if dtype == "bf16" else torch.int32).cpu().numpy() for g in got]
+
+
+def _same_bits(dtype, k, n, rank, batches):
+    want = _run(dtype, k, n, rank, [], [])
+    for before, after in batches:
+        print(f"[case] {dtype} k={k} n={n} rank={rank} before={before} after={after}", flush=True)
+        for name, a, b in zip(("S", "Y", "dS", "dX"), want, _run(dtype, k, n, rank, before, after)):
+            assert np.array_equal(a, b), (name, before, after, int((a != b).sum()), a.size)
+
+
+@pytest.mark.parametrize("k,n", [(520, 1096), (1096, 520), (1800, 72)])
+@pytest.mark.parametrize("rank", [16, 33, 100])
+def test_tiles_of_the_fused_products(k, n, rank):
+    """Every tile of the bf16 products (64 x 64 alone; 64 x 128, 128 x 128, 256 x 256 with more rows), contractions with and without a
+    tail; ranks of one and two passes, one that is not a multiple of 8."""
+    _same_bits("bf16", k, n, rank, [([(16, 37)], [(16, 930)]), ([(8, 1301)], [(64, 1500)]), ([(128, 5003)], [(16, 3000)])])
