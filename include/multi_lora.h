@@ -73,7 +73,8 @@ typedef enum {
 #define MLORA_FLAG_GROUP_BANDS 8u /* bf16 tile order only, results unchanged bit for bit: sweep the frozen weight once
                                    per group of four 2048-row bands instead of once per band.  The library does this by
                                    itself when W is larger than half the Infinity Cache and the bands' rows fit the other
-                                   half; the flag forces it for any shape (tuning, tests).  Ignored by the fp32 path. */
+                                   half; the flag forces it, and with it the 256 x 256 tiles that have such bands, for any shape,
+                                   also for those that would take smaller tiles (tuning, tests).  Ignored by the fp32 path. */
 
 /* which table multi_lora_plan_dump copies out */
 typedef enum {

@@ -624,7 +624,7 @@ static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, 
         while (g.band_group < 4 && int64_t(2 * g.band_group) * kGemmBandTiles * BM * g.Kdim * 2 <= kHalfCache) g.band_group *= 2;
     g.pv = p->view;
     g.xcd_run = g.tiles_m * g.tiles_n < 256 ? (g.tiles_m * g.tiles_n + 7) / 8 : 0;
-    const int small = small_gemm_tile(g.M, g.Ncols, g.Kdim, p->num_cus);
+    const int small = (flags & MLORA_FLAG_GROUP_BANDS) ? -1 : small_gemm_tile(g.M, g.Ncols, g.Kdim, p->num_cus);
     if (small >= 0) {
         ProfScope prof(p, fwd ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
         launch_small_gemm(small, g, fwd, st);

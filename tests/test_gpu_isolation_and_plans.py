@@ -21,19 +21,22 @@ def _bits(t):
 
 @pytest.mark.parametrize("poison", ["B_inf", "A_nan", "B_inf_second_rank_pass"])
 @pytest.mark.parametrize("decoupled", [False, True])
-def test_non_finite_weights_of_one_adapter_do_not_reach_its_neighbours(poison, decoupled):
-    # segments 300 / 1200 / 77 rows: the 256-row tiles of the fused GEMM straddle both boundaries of adapter 1
+@pytest.mark.parametrize("large_tiles", [False, True])
+def test_non_finite_weights_of_one_adapter_do_not_reach_its_neighbours(poison, decoupled, large_tiles):
+    # segments 300 / 1200 / 77 rows: the tiles of the fused GEMM straddle both boundaries of adapter 1 - the smaller ones this
+    # shape takes and, with the flag, those of 256 rows, which keep the neighbours apart in a way of their own
+    flag = ml.FLAG_GROUP_BANDS if large_tiles else 0
     w = wl.small_case(seed=65, dtype="bf16", k=512, n=512, ranks=(8, 128, 16), seg_lens=(300, 1200, 77),
                       scales=(2.0, 0.25, 1.0), b_sigma=0.3)
-    print(f"[case] isolation poison={poison} decoupled={decoupled}", flush=True)
+    print(f"[case] isolation poison={poison} decoupled={decoupled} large_tiles={large_tiles}", flush=True)
     dl = DeviceLayer(w)
 
     def step():
         if decoupled:
-            dl.forward(ml.FLAG_BASE_ONLY); dl.forward(ml.FLAG_LORA_ONLY)
-            dl.backward(ml.FLAG_BASE_ONLY); dl.backward(ml.FLAG_LORA_ONLY)
+            dl.forward(ml.FLAG_BASE_ONLY | flag); dl.forward(ml.FLAG_LORA_ONLY)
+            dl.backward(ml.FLAG_BASE_ONLY | flag); dl.backward(ml.FLAG_LORA_ONLY)
         else:
-            dl.forward(); dl.backward()
+            dl.forward(flag); dl.backward(flag)
         dl.sync()
 
     step()
@@ -60,6 +63,8 @@ def test_non_finite_weights_of_one_adapter_do_not_reach_its_neighbours(poison, d
         others = [c for c in range(w.n) if c != ycol]
         assert torch.equal(_bits(clean[0][lo:hi][:, others]), _bits(dl.Y[lo:hi][:, others]))
         assert not bool(torch.isfinite(dl.dX[lo:hi]).any())
+        if not decoupled:      # which kernel ran: in a tile that adapters share, the one of 256 rows flags such a column (NaN), the smaller ones keep Inf
+            assert bool((torch.isnan if large_tiles else torch.isinf)(dl.Y[lo:512, ycol]).all())
     else:                      # A_1[xcol, rho] = NaN: every column of its Y rows (through S); column xcol of its dX rows
         assert not bool(torch.isfinite(dl.Y[lo:hi]).any())
         assert not bool(torch.isfinite(dl.dX[lo:hi, xcol]).any())
@@ -152,8 +157,9 @@ def test_grouped_row_bands_change_the_tile_order_and_no_bit(k, n, total):
     four 2048-row bands by groups of four column tiles.  The shapes put every branch of that numbering on trial: five full
     bands and a short one (one group of four and a single band behind it), column counts that are not multiples of four tiles
     (one whole group plus three tiles, one of them ragged; fewer than four tiles: no whole group at all), exactly four bands
-    and a 77-row one.  Every tile must be computed exactly once: same bits as the ungrouped order, which the parity tests
-    hold against the oracle, and the sampled rows are held against the oracle here as well."""
+    and a 77-row one.  Every tile must be computed exactly once: same bits as without the flag (the ungrouped order, or smaller
+    tiles where a direction takes those by itself), which the parity tests hold against the oracle, and the sampled rows are
+    held against the oracle here as well."""
     lens = [1500, 2300, 700, total - 1500 - 2300 - 700 - 1300, 1300]
     ranks, scales = [16, 128, 0, 40, 64], [2.0, 0.25, 1.0, 0.5, 1.0]
     w = wl.make_workload("bands", "bf16", k, n, ranks, lens, scales, seed=91, b_sigma=0.3)

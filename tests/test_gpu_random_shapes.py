@@ -1,7 +1,7 @@
-"""Seeded random layers against the oracle: widths that are and are not multiples of 8 (MFMA and FMA kernels) and of 64, ranks
+"""Seeded random layers against the oracle: widths that are and are not multiples of 8 (MFMA and general kernels) and of 64, ranks
 from 0 to 128 including odd ones and the class boundaries, segment lengths around the 64-row block and 256-row tile
 boundaries including empty ones, in the fused mode, the decoupled mode (frozen-weight pass, then LoRA-only pass in
-place) and with gradient accumulation."""
+place) and with gradient accumulation; and the 256 x 256 tiles against the ones the shape takes, bit for bit."""
 import numpy as np
 import pytest
 
@@ -9,7 +9,7 @@ from oracle import multilora_oracle as orc
 from paper_2604_05426_amd import binding as ml
 from paper_2604_05426_amd import workloads as wl
 from paper_2604_05426_amd.harness import DeviceLayer, to_host
-from util import rel_fro
+from util import large_tiles_leave_every_bit_alone, rel_fro
 
 pytestmark = pytest.mark.gpu
 
@@ -51,4 +51,6 @@ def test_random_layers(block):
             assert rel_fro(to_host(dl.Y), fw.Y) <= two * tol and rel_fro(to_host(dl.dX), bw.dX) <= two * tol, case
         for i in range(w.N):
             assert rel_fro(to_host(dl.dA[i]), bw.dA[i]) <= tol and rel_fro(to_host(dl.dB[i]), bw.dB[i]) <= tol, (case, i)
+        dl.forward(); dl.backward()
+        large_tiles_leave_every_bit_alone(dl)
         dl.plan.destroy()

@@ -63,6 +63,24 @@ def elem_excess(G: np.ndarray, O: np.ndarray, dtype: str, c: float = 4.0) -> flo
     return float(np.max(diff / np.where(bound == 0.0, 1.0, bound)))
 
 
+def large_tiles_leave_every_bit_alone(dl):
+    """The bf16 layer `dl` has just run fused: the same pass with MLORA_FLAG_GROUP_BANDS, i.e. its frozen-weight products through the
+    256 x 256 kernel whatever the shape would take by itself, gives the same bits.  (Small layers take smaller tiles; this is what
+    puts the large kernel to the same test.)"""
+    import torch
+    from paper_2604_05426_amd import binding as ml
+    if not dl.plan.geometry()[ml.GEO_USES_MFMA] or dl.w.T == 0:
+        return
+    dl.sync()
+    outs = (dl.Y, dl.dX, *dl.dA, *dl.dB)
+    want = [t.clone() for t in outs]
+    for t in outs:
+        t.fill_(-3.0)
+    dl.forward(ml.FLAG_GROUP_BANDS); dl.backward(ml.FLAG_GROUP_BANDS); dl.sync()
+    for i, (a, b) in enumerate(zip(want, outs)):
+        assert torch.equal(a.contiguous().view(torch.int16), b.contiguous().view(torch.int16)), i
+
+
 def sample_rows(offsets, T, tile_rows, count, seed):
     """First and last row of every segment, rows on both sides of every tile boundary,
     and random rows up to `count`."""
