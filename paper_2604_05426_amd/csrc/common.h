@@ -24,19 +24,26 @@ constexpr int kMaxSortedChunks = 16384;  // larger weight-gradient tables keep t
 constexpr int kWgradPanelCols = 128;     // columns of X / dY one weight-gradient work item covers
 constexpr int kSplitBytesNarrow = 16384, kSplitBytesWide = 65536;   // fp32 accumulators of one shrink block and split, per rank class
 
-// Work groups that share one row block's contraction in the tiled shrink kernels: as many as fill the CUs, at most 8 (the last one
-// reads all shares).  Handing the shares over costs 5-6 us (stores and loads that bypass the L2, one counter round trip) and
-// a 64-wide step 0.29 us, so a split that saves fewer than 28 steps is not made.  Measured, us without / with: 19 blocks, contraction
-// 4096: 23 / 13, 14336: 69 / 19 (8 ways); 6 blocks, 2048: 10.5 / 8.7 (8 ways); 63 blocks, 14336: 69 / 35 (3 ways).  Two ways fill the chip
-// and the stream of X then bounds the launch: 128 blocks, 4096: 22 / 22, so that takes 96 steps.
+// Tiled shrink kernels.  A contraction of 32 steps (64 elements each) or more is summed in 8 pieces whoever does it (see
+// shrink_tiled_body): below, even the split launches would gain no more than 1 us, and the pieces cost the others 0.5-1 us.
 constexpr int kMaxShrinkSplits = 8;
-inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus) {
-    if (blocks <= 0) return 1;
-    int64_t s = num_cus / blocks;
-    if (s > kMaxShrinkSplits) s = kMaxShrinkSplits;
+constexpr int shrink_log_pieces(int steps) { return steps < 32 ? 0 : 3; }
+
+// Work groups that share one row block's contraction (`wide`: some block belongs to the wide rank class): the most that find room
+// on the CUs, where the steps they save are more than the handing-over (stores and loads that bypass the L2, one counter round trip, and
+// the last one reads all shares; four times the bytes in the wide class).  Measured on both sides of each line, us, blocks x contraction:
+//   8 ways rather than 4: 19 x 3072  12.2 / 12.2, x 4096  12.8 / 13.3, x 14336  17.2 / 23.0; of few blocks always: 4 x 2048  10.6 / 11.6
+//   4 ways rather than 1: 64 x 1792  12.8 / 13.2, x 2048  13.0 / 14.3, x 4096  17.0 / 22.4; wide: 32 x 2048  29.2 / 30.5,
+//     64 x 2048  33.9 / 31.0, x 3072  37.1 / 41.7
+//   2 ways rather than 1: 66 x 2560  14.7 / 15.9, x 3072  15.6 / 18.0; 128 x 2560  17.9 / 17.0, x 3072  19.0 / 19.2; wide: 128 x 4096  52.3 / 54.5 forward,
+//     58.5 / 53.0 backward, x 5120  58.4 / 66.4 and 60.2 / 65.4
+inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus, bool wide) {
     const int64_t steps = contraction / 64;
-    if (s == 2 && steps < 96) return 1;
-    return s > 1 && steps * (s - 1) / s >= 28 ? (int)s : 1;
+    if (blocks <= 0 || shrink_log_pieces((int)steps) == 0) return 1;
+    if (8 * blocks <= num_cus && (steps >= 64 || blocks <= 8)) return 8;
+    if (4 * blocks <= num_cus) return steps >= (wide && blocks > 32 ? 48 : 32) ? 4 : 1;
+    if (2 * blocks <= num_cus) return steps >= (wide ? 80 : 48) ? 2 : 1;
+    return 1;
 }
 
 // One entry of any plan table: 4 x int32 (meaning depends on the table).

@@ -33,7 +33,7 @@ struct ShrinkArgs {
     int32_t Kdim;                 // k or n
     // Tiled kernels with fewer row blocks than CUs: every block's contraction is cut into `splits` work groups
     // (blockIdx = split x blocks + block), see shrink_tiled_body.
-    int32_t splits, blocks, blocks_wide;
+    int32_t splits, log_splits, blocks, blocks_wide;
     unsigned char* partials;      // plan-owned (kSplitBytesWide / kSplitBytesNarrow per block and split)
     uint32_t* arrived;            // [2 x blocks], zero between launches
     PlanView pv;                  // one workgroup per entry of pv.class_blocks (wide rank class first: its blocks run longest)
@@ -244,10 +244,17 @@ __global__ __launch_bounds__(64 * SNW) void shrink_kernel(ShrinkArgs g) {
 //   8 with ROWS = 128 (ranks 65..128, the wide rank class, whose row blocks are 128 rows): X / dY tile 16 KB, adapter tile 16 KB,
 //     five 32 KB stages; wavefront w owns row block w (of eight) and all eight rank blocks.  With 64-row blocks the adapter tile was
 //     twice the X tile and both go through the same load path of the CU; 128 rows halve that traffic per X byte.
+// Order of the sum: a contraction of 32 steps or more is summed in 8 pieces (piece q ends before step steps (q + 1) / 8) and the
+// pieces pairwise, ((0 1) (2 3)) ((4 5) (6 7)); a shorter one is a single chain.  That is fixed by the contraction alone, so that a row of S
+// has the same bits whatever work groups its batch gives it: were the division taken from the number of row blocks, a job's
+// results would change when a neighbour joins or leaves the batch.
 // Split contraction: a work group takes 0.3-0.35 us per 64-wide step whatever else runs, so 19 row blocks of a 1024-token batch
-// spent 68 us on a contraction of 14336 with 237 CUs idle.  With `splits` > 1 each work group of a block takes its share of the steps
-// and stores its accumulators; the one that arrives last (agent-scope counter) adds all shares in split order - so the result does
-// not depend on the order of arrival - and writes S.  Nobody waits for anybody.
+// spent 68 us on a contraction of 14336 with 237 CUs idle.  With `splits` (2, 4 or 8) > 1 each work group of a block takes 8 / splits
+// neighbouring pieces, a whole subtree of the sum, and stores its accumulators; the one that arrives last (agent-scope counter) adds the
+// shares up the rest of the tree - so the result does not depend on the order of arrival either - and writes S.  Nobody waits for anybody.
+// The handing-over is correct by what this hardware does, not by the language's memory model: shares and counter are relaxed
+// agent-scope atomics, and the only order between a work group's shares and its counter increment is the s_waitcnt between them.  Such
+// stores are written through to where every XCD sees them and are acknowledged from there; such loads do not hit a stale line.
 template <bool FWD, int RB16, bool SPLIT, bool DENSE = false, int ROWS = 64>
 __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Entry4 e, unsigned char* lds, const int block, const int split,
                                                   const int half = 0) {
@@ -265,7 +272,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g4 = lane >> 4;
     const int i = e.a, row0 = e.c, rows = e.d;
-    const int r = g.pv.rank[i];
+    const int r = __builtin_amdgcn_readfirstlane(g.pv.rank[i]);      // (scalar branches on it in the loop below)
     const u16* F = global_ptr<const u16>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
     const float s = FWD ? 1.0f : g.pv.scale[i];
     // swizzle key of contraction row k of the A_i tile
@@ -296,11 +303,10 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
         }
     }
     const int all_steps = g.Kdim / 64;
-    int step0 = 0, steps = all_steps;
-    if (SPLIT) {
-        step0 = all_steps / g.splits * split;
-        steps = split == g.splits - 1 ? all_steps - step0 : all_steps / g.splits;
-    }
+    const int log_pieces = shrink_log_pieces(all_steps);
+    const int pieces = 1 << (SPLIT ? log_pieces - g.log_splits : log_pieces), piece0 = SPLIT ? split * pieces : 0;   // of this work group
+    auto piece_end = [&](int q) { return (all_steps * q) >> log_pieces; };
+    const int step0 = SPLIT ? piece_end(piece0) : 0, steps = SPLIT ? piece_end(piece0 + pieces) - step0 : all_steps;
     const int64_t stepF = FWD ? (int64_t)64 * __builtin_amdgcn_readfirstlane(r) * 2 : 128;
     const char* baseX = uniform_ptr(g.src + (int64_t)row0 * g.ld + (int64_t)step0 * 64);
     const char* baseF = uniform_ptr(reinterpret_cast<const char*>(F) + step0 * stepF);
@@ -319,8 +325,6 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
 
     const int rb = ROWS == 128 ? wave : (wave & 3), ch = ROWS == 128 ? 0 : (wave >> 2);
     f32x4 acc[NCB];
-#pragma unroll
-    for (int j = 0; j < NCB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int xrow = 16 * rb + l16;
     const int vq = fkey(8 * g4 + (l16 >> 2));      // key of the A_i tile rows this lane reads (rows +4, +32 share it)
     auto compute = [&](int slot) {
@@ -332,8 +336,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
 #pragma unroll
             for (int j = 0; j < NCB; ++j) {
                 const int cb = ch * NCB + j;
-                if (cb * 16 >= r) continue;
-                bf16x8 b;
+                bf16x8 b;      // (also of blocks past r_i: a condition per block makes every LDS read a wait of its own)
                 if (DENSE) {   // rows of 2 r bytes, unswizzled; a lane past r_i reads ranks 0..3 again (output not stored)
                     const int rk = 16 * cb + (l16 & 3) * 4;
                     const unsigned char* p = Fs + (k32 * 32 + 8 * g4 + (l16 >> 2)) * (2 * r) + (rk < r ? rk * 2 : 0);
@@ -352,16 +355,46 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
 
     for (int t = 0; t < NST - 1; ++t) issue();
     int slot = 0;
-    for (int t = 0; t < steps; ++t) {
-        // step t has landed (only the loads of the NST - 2 later steps may be in flight) and every wavefront is past
-        // step t-1, whose slot the next load overwrites
-        if (RB16 == 8) asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::: "memory");
-        else           asm volatile("s_waitcnt vmcnt(14)\n\ts_barrier" ::: "memory");
-        static_assert((NX + NF) * (NST - 2) == (RB16 == 8 ? 12 : 14), "wait count = loads of the steps that may still be in flight");
-        issue();
-        compute(slot);
-        slot = slot == NST - 1 ? 0 : slot + 1;
+    // Piece by piece; sum[l] collects two sums of 2^l pieces.  All start at zero and none can become -0, so adding to zero is exact: a
+    // level that this work group does not have, whose loop runs once, passes its child's sum on as it is.  (A binary counter with a
+    // branch per level costs 1 us more: the branches leave every accumulator behind copies.)
+    int t = 0, piece = piece0;
+    f32x4 sum[3][NCB];
+    auto clear = [&](f32x4 (&v)[NCB]) {
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto add = [&](f32x4 (&v)[NCB], const f32x4 (&w)[NCB]) {
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) v[j] += w[j];
+    };
+    static_assert(kMaxShrinkSplits == 8, "levels");
+    clear(sum[2]);
+    for (int c = 0; c < (pieces >= 8 ? 2 : 1); ++c) {
+        clear(sum[1]);
+        for (int b = 0; b < (pieces >= 4 ? 2 : 1); ++b) {
+            clear(sum[0]);
+            for (int a = 0; a < (pieces >= 2 ? 2 : 1); ++a) {
+                clear(acc);
+                const int end = piece_end(++piece) - step0;
+                do {
+                    // step t has landed (only the loads of the NST - 2 later steps may be in flight) and every wavefront is past
+                    // step t-1, whose slot the next load overwrites
+                    if (RB16 == 8) asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::: "memory");
+                    else           asm volatile("s_waitcnt vmcnt(14)\n\ts_barrier" ::: "memory");
+                    static_assert((NX + NF) * (NST - 2) == (RB16 == 8 ? 12 : 14), "wait count = loads of the steps that may still be in flight");
+                    issue();
+                    compute(slot);
+                    slot = slot == NST - 1 ? 0 : slot + 1;
+                } while (++t < end);
+                add(sum[0], acc);
+            }
+            add(sum[1], sum[0]);
+        }
+        add(sum[2], sum[1]);
     }
+#pragma unroll
+    for (int j = 0; j < NCB; ++j) acc[j] = sum[2][j];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no load may still be writing LDS when the work group ends
 
     if constexpr (SPLIT) {
@@ -410,13 +443,17 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
                         v[s][j][h] = __hip_atomic_load(share(min(s, g.splits - 1), j0 + j) + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                f32x4 sum{0.f, 0.f, 0.f, 0.f};
+                f32x4 sum[kMaxShrinkSplits];
 #pragma unroll
                 for (int s = 0; s < kMaxShrinkSplits; ++s)
-                    if (s < g.splits)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) sum[q] += __uint_as_float((uint32_t)(v[s][j][q >> 1] >> (32 * (q & 1))));
-                acc[j0 + j] = sum;
+                    for (int q = 0; q < 4; ++q) sum[s][q] = __uint_as_float((uint32_t)(v[s][j][q >> 1] >> (32 * (q & 1))));
+#pragma unroll
+                for (int w = 1; w < kMaxShrinkSplits; w *= 2)
+#pragma unroll
+                    for (int s = 0; s < kMaxShrinkSplits; s += 2 * w)
+                        if (w < g.splits) sum[s] += sum[s + w];
+                acc[j0 + j] = sum[0];
             }
         }
     }
@@ -480,7 +517,8 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
     // the tiled kernels walk the class table (wide class first, 128-row blocks); the register-staged ones the canonical 64-row blocks
     a.blocks = p->n_blocks_wide + p->n_blocks_narrow;
     a.blocks_wide = p->n_blocks_wide;
-    a.splits = tiled ? shrink_splits(a.blocks, a.Kdim, p->num_cus) : 1;
+    a.splits = tiled ? shrink_splits(a.blocks, a.Kdim, p->num_cus, wide) : 1;
+    a.log_splits = a.splits == 8 ? 3 : a.splits == 4 ? 2 : a.splits == 2 ? 1 : 0;
     a.partials = p->d_split;
     a.arrived = p->d_arrived;
     const dim3 grid(tiled ? a.blocks * a.splits : p->n_row_blocks);

@@ -19,10 +19,17 @@ def _run(dtype, k, n, rank, before, after, seed=11):
     ranks = [r for r, _ in before] + [rank] + [r for r, _ in after]
     lens = [t for _, t in before] + [ROWS] + [t for _, t in after]
     i = len(before)
-    w = wl.make_workload("batch", dtype, k, n, ranks, lens, [0.7] * len(ranks), seed=seed + 1, b_sigma=0.3)
-    lo = w.offsets[i]
-    w.W[...], w.A[i], w.B[i] = own.W, own.A[0], own.B[0]
-    w.X[lo:lo + ROWS], w.dY[lo:lo + ROWS] = own.X, own.dY
+    off = [0]
+    for t in lens:
+        off.append(off[-1] + t)
+    lo, rng = off[i], np.random.default_rng(seed)
+    A = [own.A[0] if j == i else np.resize(own.A[0], (k, r)) for j, r in enumerate(ranks)]
+    B = [own.B[0] if j == i else np.resize(own.B[0], (r, n)) for j, r in enumerate(ranks)]
+    other = rng.permutation(ROWS)               # the neighbours' tokens: this adapter's in another order, again and again
+    X, dY = np.resize(own.X[other], (off[-1], k)), np.resize(own.dY[other], (off[-1], n))
+    X[lo:lo + ROWS], dY[lo:lo + ROWS] = own.X, own.dY
+    w = wl.Workload(name="batch", dtype=dtype, T=off[-1], k=k, n=n, ranks=ranks, scales=[0.7] * len(ranks), offsets=off,
+                    X=X, W=own.W, A=A, B=B, dY=dY)
     dl = DeviceLayer(w)
     dl.forward(); dl.backward(); dl.sync()
     got = [dl.S_list()[i], dl.Y[lo:lo + ROWS].clone(), dl.dS_list()[i], dl.dX[lo:lo + ROWS].clone()]
@@ -44,3 +51,12 @@ def test_tiles_of_the_fused_products(k, n, rank):
     """Every tile of the bf16 products (64 x 64 alone; 64 x 128, 128 x 128, 256 x 256 with more rows), contractions with and without a
     tail; ranks of one and two passes, one that is not a multiple of 8."""
     _same_bits("bf16", k, n, rank, [([(16, 37)], [(16, 930)]), ([(8, 1301)], [(64, 1500)]), ([(128, 5003)], [(16, 3000)])])
+
+
+@pytest.mark.parametrize("k,n,rank", [(2048, 5120, 16), (5120, 2048, 104), (2112, 4160, 36), (2048, 2048, 100), (3072, 2048, 33)])
+def test_splits_of_the_shrink(k, n, rank):
+    """A contraction shared by 8, 4 and 2 work groups or done by one (3 row blocks alone, 36, 53, 110 and 150 with the neighbours), and with
+    a neighbour of the wide rank class or of an odd rank, which send the layer to other builds; contractions of 32 to 80 steps, some
+    that do not divide into equal pieces."""
+    _same_bits("bf16", k, n, rank, [([(16, 37)], [(16, 2100)]), ([(8, 1301)], [(33, 1900)]), ([(16, 3003)], [(64, 3800)]),
+                                    ([(128, 500)], [(16, 1500)]), ([(64, 5003)], [(4, 4500)])])
