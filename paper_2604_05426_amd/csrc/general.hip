@@ -8,10 +8,13 @@
 //
 // fp32 goes through v_mfma_f32_16x16x4_f32 (256 FLOP per clock and CU, twice the vector ALUs without packed forms): the products of
 // a large layer are bound by it, not by memory, so a plain 64 x 64 tile with a few work groups per CU is enough.  Everything else
-// here is bound by latency (short segments, few tiles): contractions are split over the wavefronts of a work group and summed in a
-// fixed order in LDS, and loads run ahead of the MFMAs in registers.  Edges cost nothing in the main loops: the last tile of
-// rows or columns starts early enough to be whole, and only the last step of a contraction takes a mask (with a condition on every
-// load, the edge tiles alone made the bf16 products of 1500 x 1001 outputs 52 us instead of 27).
+// here is bound by latency (short segments, few tiles): the contractions of shrink and weight gradients are split over the wavefronts of a
+// work group and summed in a fixed order in LDS, and loads run ahead of the MFMAs in registers.  Edges cost nothing in the main loops:
+// the last tile of rows or columns starts early enough to be whole, and only the last step of a contraction takes a mask (with a
+// condition on every load, the edge tiles alone made the bf16 products of 1500 x 1001 outputs 52 us instead of 27).
+//
+// Order of the sums: it follows from the contraction alone, not from the tile or the build that a batch is given, so that an adapter's rows
+// of S, Y, dS and dX have the same bits whatever its neighbours' tokens and ranks are.
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
 // tokens, 256 x 256: 171 -> 26 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 383 us (its two frozen-weight products 176 us each, 98
@@ -131,17 +134,19 @@ template <typename T> __device__ __forceinline__ uint4 gather16(const T* p, int6
 }
 
 // ---- shrink ------------------------------------------------------------------------------------------------------------------
-// Work group = 16 rows of one adapter x all its ranks; its eight wavefronts deal the contraction among themselves piece by piece,
-// straight from memory into MFMA operands (X / dY rows are read once; the adapter matrix comes from the caches), with the
-// operands of the next piece in flight, and the eight partial blocks are added in LDS in wavefront order.
+// Work group = 16 rows of one adapter x all its ranks; its eight wavefronts deal the contraction among themselves two neighbouring pieces at
+// a time (whole 128-byte lines of a row), straight from memory into MFMA operands (X / dY rows are read once; the adapter matrix
+// comes from the caches), with the operands of the next load in flight.  A wavefront's pairs of pieces take turns on two accumulator sets
+// (half the rounding error of one chain); their sums are added in LDS in wavefront order.
 template <typename T> struct GenShrinkArgs {
     const T* src; int64_t ld;     // X (ld k) or dY (ld n); the contraction has ld elements
     T* out;                       // ragged S or dS
     PlanView pv;
 };
 
-template <typename T, bool FWD, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) void general_shrink_kernel(GenShrinkArgs<T> g) {
+template <typename T, bool FWD, int NB>
+__global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g) {
+    constexpr int NW = 8;
     constexpr int RLD = NB * 16 + 4;
     __shared__ float red[NW * 16 * RLD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -159,10 +164,10 @@ __global__ __launch_bounds__(64 * NW) void general_shrink_kernel(GenShrinkArgs<T
     // ranks per lane.  The lane that would cross r_i takes the last four ranks instead (what it repeats comes out the same, bit for
     // bit, from the lane before), so that any rank from 4 on is read in whole quads.
     constexpr bool QUAD = FWD && NB >= 4;
-    f32x4 acc[NB];
+    f32x4 acc[2][NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int U = NB >= 8 ? 1 : 2;                   // neighbouring pieces a wavefront loads at a time: whole 128-byte lines of a row
+    for (int b = 0; b < NB; ++b) acc[0][b] = acc[1][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int U = NB >= 8 ? 1 : 2;                   // pieces a wavefront loads at a time (two would spill)
     constexpr int NQ = QUAD ? NB / 4 : 1, NF = QUAD ? 1 : NB;
     uint4 xa[2][U], fb[2][U][NF];
     quad_t<T> fq[2][U][NQ][kQuadRows<T>];
@@ -223,32 +228,52 @@ __global__ __launch_bounds__(64 * NW) void general_shrink_kernel(GenShrinkArgs<T
             }
         }
     };
-    auto compute = [&](int set) {
+    auto compute = [&](int set, f32x4 (&to)[NB]) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 if constexpr (QUAD) {
-                    if (64 * (b / 4) < r) acc[b] = block_mma<T>(xa[set][u], quad_column<T>(fq[set][u][b / 4], b % 4), acc[b]);
+                    if (64 * (b / 4) < r) to[b] = block_mma<T>(xa[set][u], quad_column<T>(fq[set][u][b / 4], b % 4), to[b]);
                 } else {
-                    if (16 * b < r) acc[b] = block_mma<T>(xa[set][u], fb[set][u][b], acc[b]);
+                    if (16 * b < r) to[b] = block_mma<T>(xa[set][u], fb[set][u][b], to[b]);
                 }
             }
     };
     const int units = (K + U * kBlockK<T> - 1) / (U * kBlockK<T>);
-    if (wave < units) load(wave, 0);
-    for (int p = wave; p < units; p += 2 * NW) {
-        if (p + NW < units) load(p + NW, 1);
-        compute(0);
-        if (p + 2 * NW < units) load(p + 2 * NW, 0);
-        if (p + NW < units) compute(1);
+    // wavefront w takes the pairs of pieces w, w + 8, w + 16, ..., in turn into acc[0] and acc[1]
+    if constexpr (U == 2) {
+        if (wave < units) load(wave, 0);
+        for (int p = wave; p < units; p += 2 * NW) {
+            if (p + NW < units) load(p + NW, 1);
+            compute(0, acc[0]);
+            if (p + 2 * NW < units) load(p + 2 * NW, 0);
+            if (p + NW < units) compute(1, acc[1]);
+        }
+    } else {
+        // the same sums, all of acc[0] first: both sets in one loop spill
+#pragma unroll 1
+        for (int turn = 0; turn < 2; ++turn) {
+            const int first = 2 * (wave + NW * turn);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) { acc[1][b] = acc[0][b]; acc[0][b] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+            if (first < units) load(first, 0);
+            for (int p = first; p < units; p += 4 * NW) {
+                if (p + 1 < units) load(p + 1, 1);
+                compute(0, acc[0]);
+                if (p + 4 * NW < units) load(p + 4 * NW, 0);
+                if (p + 1 < units) compute(1, acc[0]);
+            }
+        }
     }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[0][b] += acc[1][b];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int rho = !QUAD ? 16 * b + l16 : quads ? quad(b / 4) + b % 4 : 4 * l16 + b;
-            if (!QUAD || (64 * (b / 4) < r && rho < r)) red[(wave * 16 + 4 * g4 + q) * RLD + rho] = acc[b][q];
+            if (!QUAD || (64 * (b / 4) < r && rho < r)) red[(wave * 16 + 4 * g4 + q) * RLD + rho] = acc[0][b][q];
         }
     __syncthreads();
     T* out = g.out + g.pv.soff[i] + (int64_t)(row0 - g.pv.off[i]) * r;
@@ -273,26 +298,33 @@ template <typename T> struct GenGemmArgs {
     PlanView pv;
 };
 
-// Tile: WK = 1: 64 x 64, four wavefronts 2 x 2;  WK = 4: 32 x 32, the four wavefronts split every step's contraction.
-// A step is WK pieces of 128 bytes per row (32 fp32 / 64 bf16 elements).  LDS rows of operands whose contraction is contiguous are
+// Tile: KC = 1: 64 x 64, KC = 4: 32 x 32; four wavefronts 2 x 2, each 2 x 2 blocks or one.
+// A step is KC chunks of 128 bytes per row (32 fp32 / 64 bf16 elements).  LDS rows of operands whose contraction is contiguous are
 // padded to 144 bytes (16-byte reads of 16 rows then touch every bank once); a W / B_i tile [contraction][column] keeps fp32 rows
 // padded by 4 elements, bf16 rows XOR-swizzled in 32-byte units for the transposing read.
 // Forward: B operand (W, B_i) has its columns contiguous; backward (W, A_i transposed): its contraction.
-template <typename T, bool FWD, int WK>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3 : 2))) void general_gemm_kernel(GenGemmArgs<T> g) {
-    constexpr int BT = WK == 1 ? 64 : 32;                    // tile edge
-    constexpr int KW = 128 / (int)sizeof(T), KT = KW * WK;   // contraction per wavefront and per step
+// Order of the sum, in both tiles and both loops below (the tile follows from the number of tokens, and a row's bits must not): groups of 16
+// (fp32) / 32 (bf16) elements that start at multiples of that, zero-filled at the end, in ascending order, then each adapter's term.  bf16:
+// one chain of MFMAs; fp32: a chain per pair of chunks (64 elements), or per chunk where the contraction is shorter than 256, added up one
+// by one.  Relative error of a product against one chain throughout: 256 elements 2.7e-7 -> 1.5e-7, 2048 elements 7.9e-7 -> 1.8e-7; time,
+// 2048 x 2048 x 2048: 176 -> 175-177 us (a chain per chunk throughout: 189).  Splitting the 32 x 32 tile's contraction over its wavefronts
+// instead of the tile takes the same time (256 x 256 x 256: 10.2 us both ways).
+template <typename T, bool FWD, int KC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3 : 2))) void general_gemm_kernel(GenGemmArgs<T> g) {
+    constexpr int BT = KC == 1 ? 64 : 32;                    // tile edge
+    constexpr int NB = BT / 32;                              // blocks of a wavefront, each way
+    constexpr int KW = 128 / (int)sizeof(T), KT = KW * KC;   // contraction per chunk and per step
     constexpr int EPC = kEpc<T>;
-    constexpr int CPK = 8 * WK;                              // 16-byte pieces of a contraction row
+    constexpr int CPK = 8 * KC;                              // 16-byte pieces of a contraction row
     constexpr int NCH = BT * CPK / 256;                      // pieces per thread and operand
     constexpr int CPN = BT / EPC;                            // pieces of a column row (fwd W tile)
-    constexpr int KC_TILE = WK * BT * 144;
+    constexpr int A_TILE = KC * BT * 144;
     constexpr int NC_PITCH = sizeof(T) == 4 ? (BT + 4) * 4 : BT * 2;
-    constexpr int B_TILE = FWD ? KT * NC_PITCH : KC_TILE;
-    constexpr int STAGE = KC_TILE + B_TILE;
+    constexpr int B_TILE = FWD ? KT * NC_PITCH : A_TILE;
+    constexpr int STAGE = A_TILE + B_TILE;
     __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = WK == 1 ? wave >> 1 : 0, wn = WK == 1 ? wave & 1 : 0, wk = WK == 1 ? 0 : wave;
+    const int wm = wave >> 1, wn = wave & 1;
     const int l16 = lane & 15, g4 = lane >> 4;
     // The last tile of rows / columns starts early enough to be whole (its loads then need no conditions); what it shares with
     // the tile before is not stored.
@@ -308,7 +340,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
     };
     auto store_piece = [&](int stage, int idx, uint4 a, uint4 b) {
         unsigned char* As = lds + stage * STAGE;
-        unsigned char* Bs = As + KC_TILE;
+        unsigned char* Bs = As + A_TILE;
         *reinterpret_cast<uint4*>(As + lds_off(idx)) = a;
         if (FWD) {
             const int kr = idx / CPN, cn = idx % CPN;
@@ -317,38 +349,74 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
             *reinterpret_cast<uint4*>(Bs + lds_off(idx)) = b;
         }
     };
-    struct Frags { uint4 a[2][2], b[2][2]; };            // [64-byte half of the wavefront's 128-byte piece][block]
-    auto read_frags = [&](Frags& f, int stage) {
+    struct Frags { uint4 a[2][NB], b[2][NB]; };          // [64-byte half of the chunk][block]
+    auto read_frags = [&](Frags (&fr)[KC], int stage) {
         const unsigned char* As = lds + stage * STAGE;
-        const unsigned char* Bs = As + KC_TILE;
+        const unsigned char* Bs = As + A_TILE;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                f.a[h][x] = *reinterpret_cast<const uint4*>(As + (wk * BT + wm * 32 + x * 16 + l16) * 144 + h * 64 + g4 * 16);
-                if (!FWD) {
-                    f.b[h][x] = *reinterpret_cast<const uint4*>(Bs + (wk * BT + wn * 32 + x * 16 + l16) * 144 + h * 64 + g4 * 16);
-                } else if constexpr (sizeof(T) == 4) {
-                    const float* p = reinterpret_cast<const float*>(Bs + (wk * KW + h * 16 + 4 * g4) * NC_PITCH) + wn * 32 + x * 16 + l16;
-                    f.b[h][x] = make_uint4(__float_as_uint(p[0]), __float_as_uint(p[NC_PITCH / 4]), __float_as_uint(p[2 * (NC_PITCH / 4)]),
-                                           __float_as_uint(p[3 * (NC_PITCH / 4)]));
-                } else {
-                    const int k = wk * KW + h * 32 + 8 * g4 + (l16 >> 2);
-                    const unsigned char* p = Bs + k * NC_PITCH + (unit(k, wn * 2 + x) << 5) + (l16 & 3) * 8;
-                    f.b[h][x] = __builtin_bit_cast(uint4, lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * NC_PITCH)));
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int x = 0; x < NB; ++x) {
+                    Frags& f = fr[kc];
+                    f.a[h][x] = *reinterpret_cast<const uint4*>(As + (kc * BT + (wm * NB + x) * 16 + l16) * 144 + h * 64 + g4 * 16);
+                    if (!FWD) {
+                        f.b[h][x] = *reinterpret_cast<const uint4*>(Bs + (kc * BT + (wn * NB + x) * 16 + l16) * 144 + h * 64 + g4 * 16);
+                    } else if constexpr (sizeof(T) == 4) {
+                        const float* p = reinterpret_cast<const float*>(Bs + (kc * KW + h * 16 + 4 * g4) * NC_PITCH) + (wn * NB + x) * 16 + l16;
+                        f.b[h][x] = make_uint4(__float_as_uint(p[0]), __float_as_uint(p[NC_PITCH / 4]), __float_as_uint(p[2 * (NC_PITCH / 4)]),
+                                               __float_as_uint(p[3 * (NC_PITCH / 4)]));
+                    } else {
+                        const int k = kc * KW + h * 32 + 8 * g4 + (l16 >> 2);
+                        const unsigned char* p = Bs + k * NC_PITCH + (unit(k, wn * NB + x) << 5) + (l16 & 3) * 8;
+                        f.b[h][x] = __builtin_bit_cast(uint4, lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * NC_PITCH)));
+                    }
                 }
-            }
     };
     // operands swapped: a lane holds one output row and 4 consecutive columns of each block
-    auto multiply = [&](f32x4 (&acc)[2][2], const Frags& f) {
+    using Acc = f32x4[NB][NB];
+    auto clear = [&](Acc& acc) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) block_mma_2x2<T>(f.b[h], f.a[h], acc);
+        for (int x = 0; x < NB; ++x)
+#pragma unroll
+            for (int y = 0; y < NB; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto add = [&](Acc& acc, const Acc& part) {
+#pragma unroll
+        for (int x = 0; x < NB; ++x)
+#pragma unroll
+            for (int y = 0; y < NB; ++y) acc[x][y] += part[x][y];
+    };
+    // the products of one step; `odd`: it ends a pair of (one-chunk) steps
+    enum Chains { PER_CHUNK, PER_PAIR };
+    auto chains_of = [](int64_t K) { return K < 256 ? PER_CHUNK : PER_PAIR; };
+    auto multiply = [&](Acc& acc, Acc& part, const Frags (&fr)[KC], Chains chains, bool odd) {
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) {
+            constexpr bool PARTS = sizeof(T) == 4;
+            const bool second = KC == 1 ? odd : (kc & 1) != 0;
+            if (PARTS && (chains == PER_CHUNK || !second)) clear(part);
+            Acc& to = PARTS ? part : acc;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if constexpr (NB == 2) block_mma_2x2<T>(fr[kc].b[h], fr[kc].a[h], to);
+                else                   to[0][0] = block_mma<T>(fr[kc].b[h][0], fr[kc].a[h][0], to[0][0]);
+            }
+            if (PARTS && (chains == PER_CHUNK || second)) add(acc, part);
+        }
+    };
+    auto finish = [&](Acc& acc, const Acc& part, Chains chains, int64_t steps) {      // a last pair with only one chunk
+        if (sizeof(T) == 4 && KC == 1 && chains == PER_PAIR && (steps & 1)) add(acc, part);
     };
 
     // acc += A B over a contraction of K.  Element (row m0 + i, c) of A at a[i * lda + c], rows [row_lo, row_hi) exist; column
     // n0 + j, element c of B at b[c * ldb + j] (fwd) or b[j * ldb + c] (bwd).  Any sizes, one step at a time: for short contractions.
-    auto contract_any = [&](f32x4 (&acc)[2][2], const T* a, int64_t lda, int64_t row_lo, int64_t row_hi, const T* b, int64_t ldb, int64_t K) {
-        for (int64_t k0 = 0; k0 < K; k0 += KT) {
+    auto contract_any = [&](Acc& acc, const T* a, int64_t lda, int64_t row_lo, int64_t row_hi, const T* b, int64_t ldb, int64_t K, Chains chains) {
+        Acc part;
+        clear(part);
+        int64_t step = 0;
+        for (int64_t k0 = 0; k0 < K; k0 += KT, ++step) {
             const int left = (int)min((int64_t)KT, K - k0);
             uint4 ra[NCH], rb[NCH];
 #pragma unroll
@@ -366,17 +434,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
 #pragma unroll
             for (int c = 0; c < NCH; ++c) store_piece(0, tid + 256 * c, ra[c], rb[c]);
             __syncthreads();
-            Frags f;
+            Frags f[KC];
             read_frags(f, 0);
-            multiply(acc, f);
+            multiply(acc, part, f, chains, step & 1);
         }
+        finish(acc, part, chains, step);
     };
 
     // The same for whole tiles and at least one whole step: every load is inside its rows and takes no condition.  Step t travels
     // in register set t & 1 and LDS stage t & 1 (loads past the last step fetch it again); products may
-    // be scheduled across the barrier.  What is left of a contraction that is not a multiple of the step is the end of one more step that starts early;
-    // what that repeats is zeroed in both operands.
-    auto contract_whole = [&](f32x4 (&acc)[2][2], const T* a, int64_t lda, const T* b, int64_t ldb, int64_t K) {
+    // be scheduled across the barrier.  What is left of a contraction that is not a multiple of the step is one more, zero-filled step: a piece that
+    // reaches past the end is loaded from where it still fits into its row and shifted into place.
+    auto contract_whole = [&](Acc& acc, const T* a, int64_t lda, const T* b, int64_t ldb, int64_t K) {
         uint4 ra[2][NCH], rb[2][NCH];
         const T *pa[NCH], *pb[NCH];
 #pragma unroll
@@ -386,76 +455,85 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
             pb[c] = FWD ? b + (idx / CPN) * ldb + (idx % CPN) * EPC : b + row * ldb + k;
         }
         const int64_t nt = K / KT;
-        const int again = (int)((nt + 1) * KT - K);      // elements the early step repeats (KT: there is none)
-        auto load = [&](int64_t k0, uint4 (&va)[NCH], uint4 (&vb)[NCH]) {
+        auto load_step = [&](int64_t step, int set) {
+            const int64_t k0 = min(step, nt - 1) * KT;
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
-                __builtin_memcpy(&va[c], pa[c] + k0, 16);
-                __builtin_memcpy(&vb[c], pb[c] + (FWD ? k0 * ldb : k0), 16);
+                __builtin_memcpy(&ra[set][c], pa[c] + k0, 16);
+                __builtin_memcpy(&rb[set][c], pb[c] + (FWD ? k0 * ldb : k0), 16);
             }
         };
-        auto load_step = [&](int64_t step, int set) { load(min(step, nt - 1) * KT, ra[set], rb[set]); };
         auto store = [&](int stage, const uint4 (&va)[NCH], const uint4 (&vb)[NCH]) {
 #pragma unroll
             for (int c = 0; c < NCH; ++c) store_piece(stage, tid + 256 * c, va[c], vb[c]);
         };
-        Frags f;
+        Frags f[KC];
+        Acc part;
+        clear(part);
         load_step(0, 0);
         load_step(1, 1);
         store(0, ra[0], rb[0]);
         load_step(2, 0);
         __syncthreads();
         int64_t t = 0;
-        for (; t + 1 < nt; t += 2) {
+        auto two_steps = [&](Chains chains) {
             store(1, ra[1], rb[1]);
             load_step(t + 3, 1);
             read_frags(f, 0);
             __builtin_amdgcn_sched_barrier(0);           // all reads are on their way before the first product
-            multiply(acc, f);
+            multiply(acc, part, f, chains, false);
             __syncthreads();
             store(0, ra[0], rb[0]);
             load_step(t + 4, 0);
             read_frags(f, 1);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(acc, f);
+            multiply(acc, part, f, chains, true);
             __syncthreads();
-        }
+            t += 2;
+        };
+        if (sizeof(T) == 4 && K < 256)                   // (a branch inside the loop costs 6 %)
+            while (t + 1 < nt) two_steps(PER_CHUNK);
+        else
+            while (t + 1 < nt) two_steps(PER_PAIR);
         if (t < nt) {
             read_frags(f, 0);
-            multiply(acc, f);
+            multiply(acc, part, f, chains_of(K), false);
         }
-        if (again < KT) {
-            auto zero_head = [&](uint4 v, int drop) {    // the first `drop` elements of a piece
-                uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < EPC; ++e)
-                    if (e < drop) {
-                        if constexpr (sizeof(T) == 4) w[e] = 0u;
-                        else w[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
-                    }
-                return make_uint4(w[0], w[1], w[2], w[3]);
+        const int left = (int)(K - nt * KT);
+        if (left > 0) {
+            auto drop = [&](uint4 v, int d) {            // the piece without its first d elements, zeros behind it
+                uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+                const int sh = min(d * (int)sizeof(T) * 8, 128);
+                const uint64_t up = sh == 0 ? lo : sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : sh < 128 ? hi >> (sh - 64) : 0;
+                hi = sh < 64 ? hi >> sh : 0;
+                return make_uint4((uint32_t)up, (uint32_t)(up >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
             };
-            load(K - KT, ra[0], rb[0]);
+            int miss[NCH];                               // elements by which a piece of this step reaches past the end
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
-                const int idx = tid + 256 * c, k = (idx % CPK) * EPC;
-                ra[0][c] = zero_head(ra[0][c], again - k);
-                rb[0][c] = FWD ? (idx / CPN < again ? zero4() : rb[0][c]) : zero_head(rb[0][c], again - k);
+                const int idx = tid + 256 * c, k = (idx % CPK) * EPC, kr = idx / CPN;
+                miss[c] = max(0, k + EPC - left);
+                __builtin_memcpy(&ra[0][c], pa[c] + nt * KT - miss[c], 16);
+                if (FWD) __builtin_memcpy(&rb[0][c], pb[c] + (nt * KT - max(0, kr + 1 - left)) * ldb, 16);
+                else     __builtin_memcpy(&rb[0][c], pb[c] + nt * KT - miss[c], 16);
+            }
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                ra[0][c] = drop(ra[0][c], miss[c]);
+                rb[0][c] = FWD ? ((tid + 256 * c) / CPN < left ? rb[0][c] : zero4()) : drop(rb[0][c], miss[c]);
             }
             __syncthreads();                             // the fragments of stage 0 have been read
             store(0, ra[0], rb[0]);
             __syncthreads();
             read_frags(f, 0);
-            multiply(acc, f);
+            multiply(acc, part, f, chains_of(K), nt & 1);
         }
+        finish(acc, part, chains_of(K), nt + (left > 0));
     };
 
-    f32x4 acc[2][2];
-    bool owned[2] = {false, false};
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Acc acc;
+    bool owned[NB] = {};
+    clear(acc);
     // lane l holds the metadata of candidate adapter first + l of this row tile; fetched ahead of the contraction that hides it
     Entry4 tile{0, 0, 0, 0};
     if (g.lora) {
@@ -479,7 +557,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
     if (g.base) {
         const T* w = FWD ? g.W + n0 : g.W + n0 * g.ldw;
         if (g.M >= BT && g.N >= BT && g.K >= KT) contract_whole(acc, g.A + m0 * g.lda, g.lda, w, g.ldw, g.K);
-        else contract_any(acc, g.A + m0 * g.lda, g.lda, m0, g.M, w, g.ldw, g.K);
+        else contract_any(acc, g.A + m0 * g.lda, g.lda, m0, g.M, w, g.ldw, g.K, chains_of(g.K));
     }
 
     // rank extension, adapter by adapter into a second accumulator set, of which the adapter's own rows are added: another
@@ -497,20 +575,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
             const int lo = max(seg0, lo_t), hi = min(__builtin_amdgcn_readlane(c_end, l), hi_t);
             const T* F = global_ptr<const T>(reinterpret_cast<const void*>(lane64(c_f)));
             const float s = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c_sc), l));
-            f32x4 ext[2][2];
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y) ext[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+            Acc ext;
+            clear(ext);
             contract_any(ext, g.E + (int64_t)lane64((uint64_t)c_so) + (int64_t)(lo_t - seg0) * r, r, lo, hi, FWD ? F + n0 : F + n0 * r,
-                     FWD ? g.N : r, r);
+                     FWD ? g.N : r, r, PER_CHUNK);
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const int row = lo_t + wm * 32 + x * 16 + l16;
+            for (int x = 0; x < NB; ++x) {
+                const int row = lo_t + (wm * NB + x) * 16 + l16;
                 const bool own = row >= lo && row < hi;
                 owned[x] = owned[x] || own;
 #pragma unroll
-                for (int y = 0; y < 2; ++y)
+                for (int y = 0; y < NB; ++y)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) acc[x][y][q] = own ? acc[x][y][q] + s * ext[x][y][q] : acc[x][y][q];
             }
@@ -519,42 +594,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK == 1 ? 3
         if (first < tile.d) candidates();
     }
 
-    auto emit = [&](int x, int y, f32x4 v) {
-        const int64_t row = m0 + wm * 32 + x * 16 + l16, col = n0 + wn * 32 + y * 16 + 4 * g4;
-        if (row >= g.M || row < m_own || (!g.base && !owned[x])) return;
-        T* c = g.C + row * g.ldc + col;
-        T o[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = (g.base || col + q >= g.N) ? from_f32<T>(v[q]) : from_f32<T>(v[q] + to_f32<T>(c[q]));
-        if (col >= n_own && col + 4 <= g.N) __builtin_memcpy(c, o, sizeof(o));
-        else
+    for (int x = 0; x < NB; ++x)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (col + q >= n_own && col + q < g.N) c[q] = o[q];
-    };
-    if constexpr (WK == 1) {
+        for (int y = 0; y < NB; ++y) {
+            const f32x4 v = acc[x][y];
+            const int64_t row = m0 + (wm * NB + x) * 16 + l16, col = n0 + (wn * NB + y) * 16 + 4 * g4;
+            if (row >= g.M || row < m_own || (!g.base && !owned[x])) continue;
+            T* c = g.C + row * g.ldc + col;
+            T o[4];
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+            for (int q = 0; q < 4; ++q) o[q] = (g.base || col + q >= g.N) ? from_f32<T>(v[q]) : from_f32<T>(v[q] + to_f32<T>(c[q]));
+            if (col >= n_own && col + 4 <= g.N) __builtin_memcpy(c, o, sizeof(o));
+            else
 #pragma unroll
-            for (int y = 0; y < 2; ++y) emit(x, y, acc[x][y]);
-    } else {
-        // the wavefronts' partial tiles are added in wavefront order; wavefront w finishes block w
-        __syncthreads();
-        float4* red = reinterpret_cast<float4*>(lds);
-#pragma unroll
-        for (int blk = 0; blk < 4; ++blk) {
-            const f32x4 v = acc[blk >> 1][blk & 1];
-            red[(wave * 4 + blk) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+                for (int q = 0; q < 4; ++q)
+                    if (col + q >= n_own && col + q < g.N) c[q] = o[q];
         }
-        __syncthreads();
-        f32x4 v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float4 o = red[(w * 4 + wave) * 64 + lane];
-            v[0] += o.x; v[1] += o.y; v[2] += o.z; v[3] += o.w;
-        }
-        if (wave & 2) emit(1, wave & 1, v); else emit(0, wave & 1, v);
-    }
 }
 
 // ---- weight gradients ------------------------------------------------------------------------------------------------------------
@@ -688,9 +744,9 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     a.src = (const T*)src; a.ld = FWD ? p->k : p->n; a.out = (T*)out; a.pv = p->view;
     ProfScope prof(p, FWD ? MLORA_K_SHRINK : MLORA_K_DSHRINK, st);
     const dim3 grid((unsigned)p->n_row_blocks * 4);
-    if (p->max_rank <= 16)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1, 16>), grid, dim3(1024), 0, st, a);
-    else if (p->max_rank <= 64) hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 4, 8>), grid, dim3(512), 0, st, a);
-    else                        hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 8, 8>), grid, dim3(512), 0, st, a);
+    if (p->max_rank <= 16)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1>), grid, dim3(512), 0, st, a);
+    else if (p->max_rank <= 64) hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 4>), grid, dim3(512), 0, st, a);
+    else                        hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 8>), grid, dim3(512), 0, st, a);
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;
 }

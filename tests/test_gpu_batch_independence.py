@@ -13,11 +13,11 @@ pytestmark = pytest.mark.gpu
 ROWS = 150      # tokens of the adapter under test
 
 
-def _run(dtype, k, n, rank, before, after, seed=11):
+def _run(dtype, k, n, rank, before, after, rows=ROWS, seed=11):
     """(S, Y, dS, dX) bits of the adapter with `before` / `after` = (rank, tokens) of its neighbours; its own data depend on `seed` alone."""
-    own = wl.make_workload("own", dtype, k, n, [rank], [ROWS], [0.7], seed=seed, b_sigma=0.3)
+    own = wl.make_workload("own", dtype, k, n, [rank], [rows], [0.7], seed=seed, b_sigma=0.3)
     ranks = [r for r, _ in before] + [rank] + [r for r, _ in after]
-    lens = [t for _, t in before] + [ROWS] + [t for _, t in after]
+    lens = [t for _, t in before] + [rows] + [t for _, t in after]
     i = len(before)
     off = [0]
     for t in lens:
@@ -25,23 +25,23 @@ def _run(dtype, k, n, rank, before, after, seed=11):
     lo, rng = off[i], np.random.default_rng(seed)
     A = [own.A[0] if j == i else np.resize(own.A[0], (k, r)) for j, r in enumerate(ranks)]
     B = [own.B[0] if j == i else np.resize(own.B[0], (r, n)) for j, r in enumerate(ranks)]
-    other = rng.permutation(ROWS)               # the neighbours' tokens: this adapter's in another order, again and again
+    other = rng.permutation(rows)               # the neighbours' tokens: this adapter's in another order, again and again
     X, dY = np.resize(own.X[other], (off[-1], k)), np.resize(own.dY[other], (off[-1], n))
-    X[lo:lo + ROWS], dY[lo:lo + ROWS] = own.X, own.dY
+    X[lo:lo + rows], dY[lo:lo + rows] = own.X, own.dY
     w = wl.Workload(name="batch", dtype=dtype, T=off[-1], k=k, n=n, ranks=ranks, scales=[0.7] * len(ranks), offsets=off,
                     X=X, W=own.W, A=A, B=B, dY=dY)
     dl = DeviceLayer(w)
     dl.forward(); dl.backward(); dl.sync()
-    got = [dl.S_list()[i], dl.Y[lo:lo + ROWS].clone(), dl.dS_list()[i], dl.dX[lo:lo + ROWS].clone()]
+    got = [dl.S_list()[i], dl.Y[lo:lo + rows].clone(), dl.dS_list()[i], dl.dX[lo:lo + rows].clone()]
     dl.plan.destroy()
     return [np.asarray(g) if isinstance(g, np.ndarray) else g.view(torch.int16 if dtype == "bf16" else torch.int32).cpu().numpy() for g in got]
 
 
-def _same_bits(dtype, k, n, rank, batches):
-    want = _run(dtype, k, n, rank, [], [])
+def _same_bits(dtype, k, n, rank, batches, rows=ROWS):
+    want = _run(dtype, k, n, rank, [], [], rows)
     for before, after in batches:
         print(f"[case] {dtype} k={k} n={n} rank={rank} before={before} after={after}", flush=True)
-        for name, a, b in zip(("S", "Y", "dS", "dX"), want, _run(dtype, k, n, rank, before, after)):
+        for name, a, b in zip(("S", "Y", "dS", "dX"), want, _run(dtype, k, n, rank, before, after, rows)):
             assert np.array_equal(a, b), (name, before, after, int((a != b).sum()), a.size)
 
 
@@ -60,3 +60,11 @@ def test_splits_of_the_shrink(k, n, rank):
     that do not divide into equal pieces."""
     _same_bits("bf16", k, n, rank, [([(16, 37)], [(16, 2100)]), ([(8, 1301)], [(33, 1900)]), ([(16, 3003)], [(64, 3800)]),
                                     ([(128, 500)], [(16, 1500)]), ([(64, 5003)], [(4, 4500)])])
+
+
+@pytest.mark.parametrize("dtype,k,n", [("f32", 256, 264), ("f32", 1000, 515), ("f32", 31, 700), ("bf16", 1000, 515), ("bf16", 513, 260), ("bf16", 2050, 96)])
+@pytest.mark.parametrize("rank,rows", [(8, 20), (16, 150), (33, 150), (100, 40)])
+def test_tiles_and_builds_of_the_general_kernels(dtype, k, n, rank, rows):
+    """Both tiles of the general products (32 x 32 alone, 64 x 64 with the neighbours), fewer rows than a tile, contractions with
+    and without a remainder and shorter than a step, and neighbours whose ranks send the shrink to its builds for 16, 64 and 128."""
+    _same_bits(dtype, k, n, rank, [([(4, 9)], [(16, 30)]), ([(64, 37)], [(8, 300)]), ([(8, 1301)], [(64, 1500)]), ([(128, 700)], [(16, 3000)])], rows)
