@@ -126,7 +126,11 @@ enum {
 /*
  * Build the per-segmentation plan (App. A.1: the schedule table is built once per step
  * from the per-adapter offsets and shared by every layer).  Validates the arguments,
- * allocates the small device tables and builds them with a device kernel on `stream`.
+ * allocates the device tables and builds them with a device kernel on `stream`.  Beside the tables, which are small, a
+ * bf16 plan whose row blocks leave CUs idle holds scratch for the shrink kernels' shared contractions: at most one share
+ * per CU, of 4 KB per 16 ranks (of the largest rank up to 64; 8 KB per 16 where some rank is above 64), i.e. on 256 CUs at
+ * most 1 MB with ranks up to 16, 4 MB up to 64, 16 MB up to 128.  Every plan has its own, as it may run on a stream of its own;
+ * multi_lora_workspace_bytes() does not count it.
  *   out          host, receives the plan
  *   T, k, n      token count (>= 0), input width (>= 1), output width (>= 1)
  *   N            number of adapters, 0..MLORA_MAX_ADAPTERS.  With N = 0 all T rows are plain X W rows

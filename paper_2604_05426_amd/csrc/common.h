@@ -22,7 +22,6 @@ constexpr int kWgradMinChunkRows = 512;  // smallest token chunk one weight-grad
 constexpr int kNarrowMaxRank = 64;       // ranks above it form the wide rank class (their own kernel builds)
 constexpr int kMaxSortedChunks = 16384;  // larger weight-gradient tables keep the canonical order
 constexpr int kWgradPanelCols = 128;     // columns of X / dY one weight-gradient work item covers
-constexpr int kSplitBytesNarrow = 16384, kSplitBytesWide = 65536;   // fp32 accumulators of one shrink block and split, per rank class
 
 // Tiled shrink kernels.  A contraction of 32 steps (64 elements each) or more is summed in 8 pieces whoever does it (see
 // shrink_tiled_body): below, even the split launches would gain no more than 1 us, and the pieces cost the others 0.5-1 us.
@@ -37,6 +36,9 @@ constexpr int shrink_log_pieces(int steps) { return steps < 32 ? 0 : 3; }
 //     64 x 2048  33.9 / 31.0, x 3072  37.1 / 41.7
 //   2 ways rather than 1: 66 x 2560  14.7 / 15.9, x 3072  15.6 / 18.0; 128 x 2560  17.9 / 17.0, x 3072  19.0 / 19.2; wide: 128 x 4096  52.3 / 54.5 forward,
 //     58.5 / 53.0 backward, x 5120  58.4 / 66.4 and 60.2 / 65.4
+// Bytes of one work group's share (fp32 accumulators) where the largest rank of the block's class is `rank`: as many 16-wide rank blocks
+// as that takes, of 64 rows (ranks up to 64) or 128.
+constexpr int shrink_share_bytes(int rank) { return (rank + 15) / 16 * (rank > kNarrowMaxRank ? 8192 : 4096); }
 inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus, bool wide) {
     const int64_t steps = contraction / 64;
     if (blocks <= 0 || shrink_log_pieces((int)steps) == 0) return 1;
@@ -117,7 +119,7 @@ struct mlora_plan {
     // ones launch the items of the two classes as two launches over their own parts of the table, each through the
     // kernel build - and so at the workgroups per CU - its class allows, and chunk the tokens per class.
     mlora::DevGeo geo{};
-    int32_t max_rank_narrow = 0;      // largest rank <= 64 among adapters with tokens
+    int32_t max_rank_narrow = 0, max_rank_wide = 0;      // largest rank <= 64 and largest rank above it among adapters with tokens
     bool ranks_mult8 = true;          // every rank of an adapter with tokens is a multiple of 8
     // Device allocations: the plan's own blocks, and every block of other plans its view points into (a plan made by
     // multi_lora_plan_create_like uses the segmentation tables of its base in place - and through it those of the

@@ -34,7 +34,8 @@ struct ShrinkArgs {
     // Tiled kernels with fewer row blocks than CUs: every block's contraction is cut into `splits` work groups
     // (blockIdx = split x blocks + block), see shrink_tiled_body.
     int32_t splits, log_splits, blocks, blocks_wide;
-    unsigned char* partials;      // plan-owned (kSplitBytesWide / kSplitBytesNarrow per block and split)
+    int32_t share_wide, share_narrow;   // bytes of one share, per rank class (shrink_share_bytes)
+    unsigned char* partials;      // plan-owned: the shares of the wide class's blocks, then of the narrow one's
     uint32_t* arrived;            // [2 x blocks], zero between launches
     PlanView pv;                  // one workgroup per entry of pv.class_blocks (wide rank class first: its blocks run longest)
 };
@@ -398,21 +399,26 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no load may still be writing LDS when the work group ends
 
     if constexpr (SPLIT) {
-        constexpr int SHARE = 8 * NCB * 1024;            // bytes of one work group's accumulators
-        static_assert(SHARE <= (ROWS == 128 ? kSplitBytesWide : RB16 == 8 ? kSplitBytesWide / 2 : kSplitBytesNarrow), "a share fits its slot");
-        const bool wide = block < g.blocks_wide;
-        unsigned char* mine = g.partials + (wide ? (int64_t)block * g.splits * kSplitBytesWide
-                                                 : (int64_t)g.blocks_wide * g.splits * kSplitBytesWide + (int64_t)(block - g.blocks_wide) * g.splits * kSplitBytesNarrow);
-        const int64_t stride = wide ? kSplitBytesWide : kSplitBytesNarrow;
-        mine += half * (kSplitBytesWide / 2);
-        auto share = [&](int s, int j) { return reinterpret_cast<uint64_t*>(mine + s * stride) + ((wave * NCB + j) * 64 + lane) * 2; };
+        // A share is a kilobyte per 16 x 16 block, [rank block][row block]; of the wide class's 128 rows the 64-row bodies take a half each.
+        constexpr bool CLASS_WIDE = RB16 == 8;
+        constexpr int ROW_BLOCKS = ROWS / 16;
+        const int64_t stride = CLASS_WIDE ? g.share_wide : g.share_narrow;
+        const int rank_blocks = (int)stride / (CLASS_WIDE ? 8192 : 4096);
+        unsigned char* mine = g.partials + (CLASS_WIDE ? block * stride : g.blocks_wide * (int64_t)g.share_wide + (block - g.blocks_wide) * stride) * g.splits +
+                              half * (stride / 2);
+        auto share = [&](int s, int j) {
+            const int cb = min(ch * NCB + j, rank_blocks - 1);
+            return reinterpret_cast<uint64_t*>(mine + s * stride) + ((cb * ROW_BLOCKS + rb) * 64 + lane) * 2;
+        };
 #pragma unroll
-        for (int j = 0; j < NCB; ++j)
+        for (int j = 0; j < NCB; ++j) {
+            if (ch * NCB + j >= rank_blocks) continue;   // (uniform)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const uint64_t v = (uint64_t)__float_as_uint(acc[j][2 * h]) | ((uint64_t)__float_as_uint(acc[j][2 * h + 1]) << 32);
                 __hip_atomic_store(share(split, j) + h, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+        }
         // The shares are written and read with agent-scope atomics only: these go through the XCD's L2 to where all XCDs see them, so
         // that once this wavefront's stores have been acknowledged (the wait) its share is visible.  An agent-scope release would
         // write back the whole L2 for every work group instead: 14-20 us a launch, more than the split gains.
@@ -433,6 +439,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
         // two blocks' shares at a time, all loads in flight together (slots past the last split repeat it and are not added)
 #pragma unroll
         for (int j0 = 0; j0 < NCB; j0 += 2) {
+            if (ch * NCB + j0 >= rank_blocks) break;     // (uniform; nothing of these blocks is stored)
             uint64_t v[kMaxShrinkSplits][2][2];
 #pragma unroll
             for (int s = 0; s < kMaxShrinkSplits; ++s)
@@ -519,6 +526,8 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
     a.blocks_wide = p->n_blocks_wide;
     a.splits = tiled ? shrink_splits(a.blocks, a.Kdim, p->num_cus, wide) : 1;
     a.log_splits = a.splits == 8 ? 3 : a.splits == 4 ? 2 : a.splits == 2 ? 1 : 0;
+    a.share_wide = shrink_share_bytes(p->max_rank_wide);
+    a.share_narrow = shrink_share_bytes(p->max_rank_narrow);
     a.partials = p->d_split;
     a.arrived = p->d_arrived;
     const dim3 grid(tiled ? a.blocks * a.splits : p->n_row_blocks);

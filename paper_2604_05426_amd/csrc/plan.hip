@@ -422,6 +422,7 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
         if (ranks[i] % 8) p->ranks_mult8 = false;
         if (ranks[i] > kNarrowMaxRank) {
             rb_wide += ceil_div(Ti, kBlockRowsWide);
+            if (ranks[i] > p->max_rank_wide) p->max_rank_wide = ranks[i];
         } else {
             rb_narrow += ceil_div(Ti, kBlockRows);
             if (ranks[i] > p->max_rank_narrow) p->max_rank_narrow = ranks[i];
@@ -455,7 +456,8 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     const int max_splits = p->use_mfma ? std::max(shrink_splits(class_blocks, k, p->num_cus, rb_wide > 0), shrink_splits(class_blocks, n, p->num_cus, rb_wide > 0)) : 1;
     const int32_t n_arrived = max_splits > 1 ? (int32_t)(2 * class_blocks) : 0;
     const size_t o_arrived = take(sizeof(uint32_t) * (size_t)n_arrived);
-    const size_t o_split = take(max_splits > 1 ? (size_t)max_splits * ((size_t)rb_wide * kSplitBytesWide + (size_t)rb_narrow * kSplitBytesNarrow) : 0);
+    const size_t o_split = take(max_splits > 1 ? (size_t)max_splits * ((size_t)rb_wide * shrink_share_bytes(p->max_rank_wide) +
+                                                                       (size_t)rb_narrow * shrink_share_bytes(p->max_rank_narrow)) : 0);
     auto block1 = std::make_shared<DeviceBlock>();
     MLORA_HIP_TRY(hipMalloc(&block1->ptr, o));
     p->blocks.push_back(block1);

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from oracle import multilora_oracle as orc
+from paper_2604_05426_amd import binding as ml
 from paper_2604_05426_amd import workloads as wl
 from paper_2604_05426_amd.harness import DeviceLayer
 from util import elem_excess
@@ -41,3 +42,19 @@ def test_split_contraction(ranks, lens, k, n):
         assert torch.equal(S.view(torch.int16), dl.S.view(torch.int16)) and torch.equal(dS, dl.workspace[: 2 * w.R1])
         dl.forward(); dl.backward(); dl.sync()
     dl.plan.destroy()
+
+
+def test_scratch_of_a_plan_follows_its_ranks():
+    """A plan whose shrink is shared by work groups holds a share per row block and work group: with ranks up to 16 a quarter of
+    what ranks of 64 take (here 128 shares of 4 KB, 0.5 MB a plan)."""
+    off = [0, 512, 1024]
+    make = lambda: ml.Plan(ml.BF16, 1024, 4096, 4096, [8, 16], [1.0, 1.0], off)
+    make().destroy()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    plans = [make() for _ in range(64)]
+    used = before - torch.cuda.mem_get_info()[0]
+    print(f"[case] 64 plans of 1024 tokens, ranks 8 and 16: {used / 64 / 2**20:.2f} MB each", flush=True)
+    for p in plans:
+        p.destroy()
+    assert used <= 64 * (1 << 20)
