@@ -151,8 +151,10 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
     __shared__ float red[NW * 16 * RLD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g4 = lane >> 4;
-    const Entry4 e = g.pv.row_blocks[blockIdx.x >> 2];
-    const int sub = (blockIdx.x & 3) * 16, rows = min(16, e.d - sub);
+    const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (wg >= (int64_t)g.pv.n_row_blocks * 4) return;
+    const Entry4 e = g.pv.row_blocks[wg >> 2];
+    const int sub = (wg & 3) * 16, rows = min(16, e.d - sub);
     if (rows <= 0) return;
     const int i = e.a, row0 = e.c + sub;
     const int r = g.pv.rank[i];
@@ -620,7 +622,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
 // columns 4 j + x); nothing goes through LDS but the final sum over the wavefronts.
 template <typename T> struct GenWgradArgs {
     const T* X; const T* dY; const T* S; const T* dS;
-    int32_t panels_k;
+    int32_t panels_k, panels;     // 64-column panels of X, and of X and dY
+    uint32_t rank_items;          // work items along the ranks
     int32_t accumulate;
     PlanView pv;
 };
@@ -635,12 +638,13 @@ __global__ __launch_bounds__(512) void general_wgrad_kernel(GenWgradArgs<T> g) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g4 = lane >> 4;
     const int i = blockIdx.y;
-    const int r = g.pv.rank[i], rho0 = blockIdx.z * RW;
-    if (rho0 >= r) return;
-    const bool isA = (int)blockIdx.x < g.panels_k;
+    const int r = g.pv.rank[i], rho0 = (int)(blockIdx.z % g.rank_items) * RW;
+    const int panel = (int)(blockIdx.z / g.rank_items * gridDim.x + blockIdx.x);
+    if (rho0 >= r || panel >= g.panels) return;
+    const bool isA = panel < g.panels_k;
     const int64_t width = isA ? g.pv.k : g.pv.n;
     // the last panel starts early enough to be whole; what it shares with the one before is not stored
-    const int64_t col_own = (int64_t)(isA ? blockIdx.x : blockIdx.x - g.panels_k) * 64, col0 = max((int64_t)0, min(col_own, width - 64));
+    const int64_t col_own = (int64_t)(isA ? panel : panel - g.panels_k) * 64, col0 = max((int64_t)0, min(col_own, width - 64));
     const int row0 = g.pv.off[i], rows = g.pv.off[i + 1] - row0;
     const int lcol = (int)min((int64_t)4 * l16, width - col0 - 1);      // (panels narrower than 64: lanes past the edge repeat its last column)
     const T* big = (isA ? g.X : g.dY) + (int64_t)row0 * width + col0 + lcol;
@@ -737,13 +741,17 @@ __global__ __launch_bounds__(512) void general_wgrad_kernel(GenWgradArgs<T> g) {
 
 // ---- launches --------------------------------------------------------------------------------------------------------------------
 
+// Work groups along x; a dimension of a launch holds fewer than 2^32 work items (2^23 work groups of 512), the rest goes along y.
+constexpr int64_t kGridX = 1 << 20;
+dim3 two_dims(int64_t groups) { return dim3((unsigned)(groups < kGridX ? groups : kGridX), (unsigned)((groups + kGridX - 1) / kGridX)); }
+
 template <typename T, bool FWD>
 int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     if (p->n_row_blocks == 0) return MLORA_OK;
     GenShrinkArgs<T> a{};
     a.src = (const T*)src; a.ld = FWD ? p->k : p->n; a.out = (T*)out; a.pv = p->view;
     ProfScope prof(p, FWD ? MLORA_K_SHRINK : MLORA_K_DSHRINK, st);
-    const dim3 grid((unsigned)p->n_row_blocks * 4);
+    const dim3 grid = two_dims((int64_t)p->n_row_blocks * 4);
     if (p->max_rank <= 16)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1>), grid, dim3(512), 0, st, a);
     else if (p->max_rank <= 64) hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 4>), grid, dim3(512), 0, st, a);
     else                        hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 8>), grid, dim3(512), 0, st, a);
@@ -782,12 +790,13 @@ int wgrad(mlora_plan* p, const void* dY, const void* X, const void* S, const voi
     a.accumulate = (flags & MLORA_FLAG_ACCUM_GRADS) ? 1 : 0;
     a.pv = p->view;
     ProfScope prof(p, MLORA_K_WGRAD, st);
-    const unsigned panels = (unsigned)(a.panels_k + (p->n + 63) / 64);
+    a.panels = (int32_t)(a.panels_k + (p->n + 63) / 64);
     // ranks per work item: as many as the plan needs; bf16 keeps each rank element of a lane's eight tokens in a register of its own
     // and would spill with 64, panels that are not whole with more than 16
     const bool whole = p->k >= 64 && p->n >= 64;
     const int rw = p->max_rank <= 16 || !whole ? 16 : p->max_rank <= 32 || sizeof(T) == 2 ? 32 : 64;
-    const dim3 grid(panels, (unsigned)p->N, (unsigned)((p->max_rank + rw - 1) / rw)), block(512);
+    a.rank_items = (uint32_t)((p->max_rank + rw - 1) / rw);
+    const dim3 xy = two_dims(a.panels), grid(xy.x, (unsigned)p->N, xy.y * a.rank_items), block(512);
     if (!whole)        hipLaunchKernelGGL((general_wgrad_kernel<T, 1, false>), grid, block, 0, st, a);
     else if (rw == 16) hipLaunchKernelGGL((general_wgrad_kernel<T, 1, true>), grid, block, 0, st, a);
     else if (rw == 32) hipLaunchKernelGGL((general_wgrad_kernel<T, 2, true>), grid, block, 0, st, a);
