@@ -1,6 +1,7 @@
 """Shrink and gradient shrink with the contraction split over work groups: rank classes, ragged last blocks and contractions that
 do not divide evenly, against the oracle; and the same bits from run to run, eagerly and replayed from a graph (the shares
-are added in a fixed order whoever comes last, and every launch leaves the arrival counters ready for the next)."""
+are added in a fixed order whoever comes last, and every launch leaves the arrival counters ready for the next: S and dS are
+poisoned before each run, so a block that nobody finished shows)."""
 import pytest
 import torch
 
@@ -17,6 +18,19 @@ pytestmark = pytest.mark.gpu
                                         ((7, 33, 65), (64, 100, 300)), ((32,), (5000,))])
 @pytest.mark.parametrize("k,n", [(2560, 8), (2048, 3008)])
 def test_split_contraction(ranks, lens, k, n):
+    _check(ranks, lens, k, n)
+
+
+@pytest.mark.parametrize("ranks,lens,k,n", [((16, 64), (3000, 3100), 3136, 8), ((64, 8), (3000, 3100), 8, 3136),        # 2 ways, 49 steps
+                                             ((128, 100), (5000, 5100), 5184, 8), ((104, 16), (5000, 400), 8, 5184),      # 2 and 4 ways, 81 steps, wide
+                                             ((16, 33), (1700, 1500), 4160, 8), ((104,), (6000,), 8, 3200),               # 4 ways, 65 and 50 steps
+                                             ((36, 12), (700, 900), 4416, 8)])                                          # 8 ways, 69 steps, dense tiles
+def test_every_number_of_shares(ranks, lens, k, n):
+    """2, 4 and 8 work groups per row block in both rank classes, steps that do not divide into equal pieces."""
+    _check(ranks, lens, k, n)
+
+
+def _check(ranks, lens, k, n):
     print(f"[case] split shrink k={k} n={n} ranks={ranks} lens={lens}", flush=True)
     w = wl.make_workload("split", "bf16", k, n, ranks, lens, [0.5] * len(ranks), seed=k + len(ranks), b_sigma=0.3)
     dl = DeviceLayer(w)
@@ -26,8 +40,12 @@ def test_split_contraction(ranks, lens, k, n):
     for i in range(w.N):
         assert elem_excess(dl.S_list()[i], fw.S[i], "bf16") <= 1 and elem_excess(dl.dS_list()[i], bw.dS[i], "bf16") <= 1, i
     S, dS = dl.S.clone(), dl.workspace[: 2 * w.R1].clone()
-    for _ in range(20):
+    def poison():
         dl.S.fill_(float("nan"))
+        dl.workspace[: 2 * w.R1].fill_(0xFF)
+
+    for _ in range(20):
+        poison()
         dl.forward(); dl.backward()
         assert torch.equal(S.view(torch.int16), dl.S.view(torch.int16)) and torch.equal(dS, dl.workspace[: 2 * w.R1])
     graph, side, eager = torch.cuda.CUDAGraph(), torch.cuda.Stream(), dl.stream
@@ -36,10 +54,11 @@ def test_split_contraction(ranks, lens, k, n):
         dl.forward(); dl.backward()
     dl.stream = eager
     for _ in range(3):
-        dl.S.fill_(float("nan"))
+        poison()
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(S.view(torch.int16), dl.S.view(torch.int16)) and torch.equal(dS, dl.workspace[: 2 * w.R1])
+        poison()
         dl.forward(); dl.backward(); dl.sync()
     dl.plan.destroy()
 
