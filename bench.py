@@ -300,7 +300,7 @@ def bench_power_clock(args, np, torch, ml, wl) -> int:
     return 0
 
 
-KERNEL_SOURCES = ("mfma_common.h", "mfma_gemm.hip", "mfma_gemm_small.hip", "mfma_lora.hip", "plan.hip", "common.h")
+KERNEL_SOURCES = ("mfma_common.h", "mfma_gemm.hip", "mfma_gemm_small.hip", "mfma_lora.hip", "general.hip", "adamw.hip", "plan.hip", "common.h")
 
 
 def kernel_sources_sha256() -> str:

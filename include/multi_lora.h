@@ -20,6 +20,11 @@
  * is [T_i, r_i] dense.  dtype is one of MLORA_F32 / MLORA_BF16 for all tensors;
  * accumulation is always fp32 and each output is rounded once from the accumulator.
  *
+ * Repeated calls give the same bits.  An adapter's rows of S, Y, dS and dX have the same bits
+ * whoever shares its batch: they follow from its own tokens, matrices, rank and scale and from W.
+ * dA_i and dB_i of the bf16 kernels are summed in token chunks whose length follows from the
+ * whole batch (MLORA_GEO_WGRAD_CHUNK_ROWS): a neighbour that joins or leaves may move their last bits.
+ *
  * Pointers: "device" = device memory the caller owns (for example torch tensors),
  * "host" = ordinary host memory read during the call and free to reuse once the call
  * returns.  `stream` is a hipStream_t passed as void* (NULL = the null stream).

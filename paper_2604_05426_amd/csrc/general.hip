@@ -17,7 +17,7 @@
 // of S, Y, dS and dX have the same bits whatever its neighbours' tokens and ranks are.
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
-// tokens, 256 x 256: 171 -> 26 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 383 us (its two frozen-weight products 176 us each, 98
+// tokens, 256 x 256: 171 -> 26 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 387 us (its two frozen-weight products 176 us each, 98
 // TFLOP/s; 144 is what a large fp32 product reaches on this card); bf16, 1500 tokens, 2048 x 1001: 1105 -> 83 us.
 #include "mfma_common.h"
 
@@ -771,8 +771,10 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
     if (a.M == 0 || (!a.base && !a.lora)) return MLORA_OK;
     ProfScope prof(p, FWD ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
     auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
-    // 32 x 32 tiles where 64 x 64 ones would leave half the chip idle.  fp32, us 32 x 32 / 64 x 64: 500 x 513 (72 tiles) 16 / 20,
-    // 700 x 1001 (176) 56 / 55, 1000 x 1001 (256) 46 / 34; bf16 12.3 / 11.6, 29 / 20, 28 / 16; 256 x 257 (20): 11 / 14 and 9.6 / 9.9.
+    // 32 x 32 tiles where 64 x 64 ones would leave half the chip idle.  us, 32 x 32 / 64 x 64, by the number of 64 x 64 tiles: fp32, 20 (256 x
+    // 257, contraction 256) 10.3 / 13.5, 72 (500 x 513, 1000) 24 / 32, 128 (512 x 1024, 1024) 25 / 31, 136 (500 x 1025, 4096) 97 / 99, 176
+    // (700 x 1001, 1001) 38 / 34; bf16, the same shapes: 8.4 / 9.6, 14.2 / 14.1, 20 / 14 (136 tiles, 1024), 44 / 31, 23 / 15.  The results are
+    // the same bit for bit.
     const bool split = tiles(64) <= p->num_cus / 2;
     a.tiles_n = (a.N + (split ? 31 : 63)) / (split ? 32 : 64);
     if (split) hipLaunchKernelGGL((general_gemm_kernel<T, FWD, 4>), dim3((unsigned)tiles(32)), dim3(256), 0, st, a);

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2604_05426_amd import binding as ml
 from paper_2604_05426_amd import workloads as wl
 from paper_2604_05426_amd.harness import DeviceLayer
 
@@ -14,7 +15,8 @@ ROWS = 150      # tokens of the adapter under test
 
 
 def _run(dtype, k, n, rank, before, after, rows=ROWS, seed=11):
-    """(S, Y, dS, dX) bits of the adapter with `before` / `after` = (rank, tokens) of its neighbours; its own data depend on `seed` alone."""
+    """Bits of the adapter's S, Y, dS, dX, and Y, dX of the decoupled form, with `before` / `after` = (rank, tokens) of its neighbours; its own
+    data depend on `seed` alone."""
     own = wl.make_workload("own", dtype, k, n, [rank], [rows], [0.7], seed=seed, b_sigma=0.3)
     ranks = [r for r, _ in before] + [rank] + [r for r, _ in after]
     lens = [t for _, t in before] + [rows] + [t for _, t in after]
@@ -33,6 +35,11 @@ def _run(dtype, k, n, rank, before, after, rows=ROWS, seed=11):
     dl = DeviceLayer(w)
     dl.forward(); dl.backward(); dl.sync()
     got = [dl.S_list()[i], dl.Y[lo:lo + rows].clone(), dl.dS_list()[i], dl.dX[lo:lo + rows].clone()]
+    for t in (dl.Y, dl.dX):
+        t.fill_(float("nan"))
+    dl.forward(ml.FLAG_BASE_ONLY); dl.forward(ml.FLAG_LORA_ONLY)
+    dl.backward(ml.FLAG_BASE_ONLY); dl.backward(ml.FLAG_LORA_ONLY); dl.sync()
+    got += [dl.Y[lo:lo + rows].clone(), dl.dX[lo:lo + rows].clone()]
     dl.plan.destroy()
     return [np.asarray(g) if isinstance(g, np.ndarray) else g.view(torch.int16 if dtype == "bf16" else torch.int32).cpu().numpy() for g in got]
 
@@ -41,7 +48,7 @@ def _same_bits(dtype, k, n, rank, batches, rows=ROWS):
     want = _run(dtype, k, n, rank, [], [], rows)
     for before, after in batches:
         print(f"[case] {dtype} k={k} n={n} rank={rank} before={before} after={after}", flush=True)
-        for name, a, b in zip(("S", "Y", "dS", "dX"), want, _run(dtype, k, n, rank, before, after, rows)):
+        for name, a, b in zip(("S", "Y", "dS", "dX", "decoupled Y", "decoupled dX"), want, _run(dtype, k, n, rank, before, after, rows)):
             assert np.array_equal(a, b), (name, before, after, int((a != b).sum()), a.size)
 
 
