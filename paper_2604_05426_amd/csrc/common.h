@@ -39,6 +39,7 @@ constexpr int shrink_log_pieces(int steps) { return steps < 32 ? 0 : 3; }
 // Bytes of one work group's share (fp32 accumulators) where the largest rank of the block's class is `rank`: as many 16-wide rank blocks
 // as that takes, of 64 rows (ranks up to 64) or 128.
 constexpr int shrink_share_bytes(int rank) { return (rank + 15) / 16 * (rank > kNarrowMaxRank ? 8192 : 4096); }
+constexpr int kSplitChunks = 3, kSplitChunkBytes = (2 << 20) - (128 << 10);
 inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus, bool wide) {
     const int64_t steps = contraction / 64;
     if (blocks <= 0 || shrink_log_pieces((int)steps) == 0) return 1;
@@ -136,8 +137,13 @@ struct mlora_plan {
     bool ptr_mirror_valid = false;
     bool ptr_upload_captured = false;
     hipStream_t ptr_mirror_stream = nullptr;
-    unsigned char* d_split = nullptr; // shares of split shrink contractions, and the arrival counters (two per block)
-    uint32_t* d_arrived = nullptr;
+    // Shares of split shrink contractions.  Up to kSplitChunks allocations of less than 2 MB, each for as many whole row blocks as
+    // fit at `split_slot` bytes a share (both rank classes alike): those come from memory the runtime keeps at hand (1 us for an
+    // allocation and its release, 24 us from 2 MB on, which a plan made for every step would pay every step; more than three of them
+    // cost 100 us).  What does not fit is one allocation with shares of each class's own size (split_slot 0).
+    std::vector<std::shared_ptr<mlora::DeviceBlock>> split_blocks;
+    int32_t split_slot = 0, split_chunk_shares = 0;      // shares in every allocation but the last
+    uint32_t* d_arrived = nullptr;    // arrival counters of the split contractions (two per block)
     int32_t* d_reduce_list = nullptr; // adapters whose tokens are split over several weight-gradient chunks
     bool has_empty_ranked = false;    // some adapter has a rank but no tokens (its dA, dB are zero-filled)
     size_t ws_ds_bytes = 0;           // workspace: dS

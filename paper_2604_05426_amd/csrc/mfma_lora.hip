@@ -35,7 +35,11 @@ struct ShrinkArgs {
     // (blockIdx = split x blocks + block), see shrink_tiled_body.
     int32_t splits, log_splits, blocks, blocks_wide;
     int32_t share_wide, share_narrow;   // bytes of one share, per rank class (shrink_share_bytes)
-    unsigned char* partials;      // plan-owned: the shares of the wide class's blocks, then of the narrow one's
+    // Plan-owned: the shares of the wide class's blocks, then of the narrow one's, one every slot_wide / slot_narrow bytes.  Blocks from
+    // chunk_blocks on are in the second allocation, from 2 chunk_blocks on in the third (split_slot of the plan).
+    int32_t slot_wide, slot_narrow, slots_wide;      // slots_wide: blocks before the first of slot_narrow
+    int32_t chunk_blocks;
+    unsigned char* partials[kSplitChunks];
     uint32_t* arrived;            // [2 x blocks], zero between launches
     PlanView pv;                  // one workgroup per entry of pv.class_blocks (wide rank class first: its blocks run longest)
 };
@@ -402,10 +406,11 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
         // A share is a kilobyte per 16 x 16 block, [rank block][row block]; of the wide class's 128 rows the 64-row bodies take a half each.
         constexpr bool CLASS_WIDE = RB16 == 8;
         constexpr int ROW_BLOCKS = ROWS / 16;
-        const int64_t stride = CLASS_WIDE ? g.share_wide : g.share_narrow;
-        const int rank_blocks = (int)stride / (CLASS_WIDE ? 8192 : 4096);
-        unsigned char* mine = g.partials + (CLASS_WIDE ? block * stride : g.blocks_wide * (int64_t)g.share_wide + (block - g.blocks_wide) * stride) * g.splits +
-                              half * (stride / 2);
+        const int bytes = CLASS_WIDE ? g.share_wide : g.share_narrow, rank_blocks = bytes / (CLASS_WIDE ? 8192 : 4096);
+        const int64_t stride = CLASS_WIDE ? g.slot_wide : g.slot_narrow;
+        const int chunk = (block >= g.chunk_blocks) + (block >= 2 * g.chunk_blocks), in = block - chunk * g.chunk_blocks;
+        unsigned char* mine = (chunk == 0 ? g.partials[0] : chunk == 1 ? g.partials[1] : g.partials[2]) + half * (bytes / 2) +
+                              (CLASS_WIDE ? in * stride : g.slots_wide * (int64_t)g.slot_wide + (in - g.slots_wide) * stride) * g.splits;
         auto share = [&](int s, int j) {
             const int cb = min(ch * NCB + j, rank_blocks - 1);
             return reinterpret_cast<uint64_t*>(mine + s * stride) + ((cb * ROW_BLOCKS + rb) * 64 + lane) * 2;
@@ -528,7 +533,14 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
     a.log_splits = a.splits == 8 ? 3 : a.splits == 4 ? 2 : a.splits == 2 ? 1 : 0;
     a.share_wide = shrink_share_bytes(p->max_rank_wide);
     a.share_narrow = shrink_share_bytes(p->max_rank_narrow);
-    a.partials = p->d_split;
+    if (a.splits > 1) {
+        const bool chunks = p->split_slot != 0;
+        a.slot_wide = chunks ? p->split_slot : a.share_wide;
+        a.slot_narrow = chunks ? p->split_slot : a.share_narrow;
+        a.slots_wide = chunks ? 0 : a.blocks_wide;
+        a.chunk_blocks = chunks ? p->split_chunk_shares / a.splits : 1 << 29;      // (splits are powers of two: it divides)
+        for (size_t i = 0; i < p->split_blocks.size(); ++i) a.partials[i] = (unsigned char*)p->split_blocks[i]->ptr;
+    }
     a.arrived = p->d_arrived;
     const dim3 grid(tiled ? a.blocks * a.splits : p->n_row_blocks);
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, a); };

@@ -456,11 +456,27 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     const int max_splits = p->use_mfma ? std::max(shrink_splits(class_blocks, k, p->num_cus, rb_wide > 0), shrink_splits(class_blocks, n, p->num_cus, rb_wide > 0)) : 1;
     const int32_t n_arrived = max_splits > 1 ? (int32_t)(2 * class_blocks) : 0;
     const size_t o_arrived = take(sizeof(uint32_t) * (size_t)n_arrived);
-    const size_t o_split = take(max_splits > 1 ? (size_t)max_splits * ((size_t)rb_wide * shrink_share_bytes(p->max_rank_wide) +
-                                                                       (size_t)rb_narrow * shrink_share_bytes(p->max_rank_narrow)) : 0);
     auto block1 = std::make_shared<DeviceBlock>();
     MLORA_HIP_TRY(hipMalloc(&block1->ptr, o));
     p->blocks.push_back(block1);
+    if (max_splits > 1) {
+        auto scratch = [&](size_t bytes) -> int {
+            auto b = std::make_shared<DeviceBlock>();
+            MLORA_HIP_TRY(hipMalloc(&b->ptr, bytes));
+            p->split_blocks.push_back(b);
+            return MLORA_OK;
+        };
+        const int share_wide = shrink_share_bytes(p->max_rank_wide), share_narrow = shrink_share_bytes(p->max_rank_narrow);
+        const int64_t slot = std::max(share_wide, share_narrow), per_chunk = kSplitChunkBytes / (slot * max_splits);
+        if (per_chunk * kSplitChunks >= class_blocks) {
+            p->split_slot = (int32_t)slot;
+            p->split_chunk_shares = (int32_t)(per_chunk * max_splits);
+            for (int64_t left = class_blocks; left > 0; left -= per_chunk)
+                if (const int rc = scratch((size_t)(std::min(left, per_chunk) * slot * max_splits))) return rc;
+        } else if (const int rc = scratch((size_t)max_splits * ((size_t)rb_wide * share_wide + (size_t)rb_narrow * share_narrow))) {
+            return rc;
+        }
+    }
     if (like) {      // every block the shared tables live in, whoever allocated it
         p->shared_blocks = like->shared_blocks;
         p->shared_blocks.insert(p->shared_blocks.end(), like->blocks.begin(), like->blocks.end());
@@ -485,7 +501,6 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     Entry4* d_gt = own_seg ? (Entry4*)(base + o_gt) : const_cast<Entry4*>(lv->gemm_tiles);
     Entry4* d_bo = own_seg ? (Entry4*)(base + o_bo) : const_cast<Entry4*>(lv->band_order);
     p->d_arrived = (uint32_t*)(base + o_arrived);
-    p->d_split = (unsigned char*)(base + o_split);
 
     // scheduler set-up on the library's own stream; the host waits for that stream alone
     {

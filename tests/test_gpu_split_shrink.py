@@ -2,6 +2,9 @@
 do not divide evenly, against the oracle; and the same bits from run to run, eagerly and replayed from a graph (the shares
 are added in a fixed order whoever comes last, and every launch leaves the arrival counters ready for the next: S and dS are
 poisoned before each run, so a block that nobody finished shows)."""
+import time
+
+import numpy as np
 import pytest
 import torch
 
@@ -77,3 +80,23 @@ def test_scratch_of_a_plan_follows_its_ranks():
     for p in plans:
         p.destroy()
     assert used <= 64 * (1 << 20)
+
+
+def test_a_plan_with_scratch_is_made_as_quickly_as_one_without():
+    """Plans are made for every step of a job with ragged batches: making and destroying one that holds 2 to 4 MB of shares costs what one
+    without shares costs (allocations of 2 MB and more would add half of it again)."""
+    def median_us(T, ranks):
+        times = []
+        for _ in range(200):
+            t0 = time.perf_counter()
+            plan = ml.Plan(ml.BF16, T, 4096, 4096, ranks, [1.0] * 8, [T // 8 * i for i in range(9)])
+            plan.destroy()
+            times.append(time.perf_counter() - t0)
+            torch.cuda.synchronize()
+        return 1e6 * float(np.median(times))
+
+    for T, ranks in ((1024, [64] * 8), (4096, [16, 64] * 4), (2048, [32, 64] * 4)):
+        # (the least of three ratios: 1.0 here, 1.5 with one allocation of 2 MB or more; 256 row blocks fill the CUs: nothing is shared)
+        ratio = min(median_us(T, ranks) / median_us(16384, ranks) for _ in range(3))
+        print(f"[case] T={T} ranks={ranks[:2]}: {ratio:.2f} of the time without shares", flush=True)
+        assert ratio <= 1.3
