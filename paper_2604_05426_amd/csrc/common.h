@@ -28,18 +28,20 @@ constexpr int kWgradPanelCols = 128;     // columns of X / dY one weight-gradien
 constexpr int kMaxShrinkSplits = 8;
 constexpr int shrink_log_pieces(int steps) { return steps < 32 ? 0 : 3; }
 
+// Bytes of one work group's share (fp32 accumulators) where the largest rank of the block's class is `rank`: as many 16-wide rank blocks
+// as that takes, of 64 rows (ranks up to 64) or 128.
+constexpr int shrink_share_bytes(int rank) { return (rank + 15) / 16 * (rank > kNarrowMaxRank ? 8192 : 4096); }
+// Allocations that hold a plan's shares, and the bytes of one (see mlora_plan::split_blocks).
+constexpr int kSplitChunks = 3, kSplitChunkBytes = (2 << 20) - (128 << 10);
+
 // Work groups that share one row block's contraction (`wide`: some block belongs to the wide rank class): the most that find room
 // on the CUs, where the steps they save are more than the handing-over (stores and loads that bypass the L2, one counter round trip, and
 // the last one reads all shares; four times the bytes in the wide class).  Measured on both sides of each line, us, blocks x contraction:
 //   8 ways rather than 4: 19 x 3072  12.2 / 12.2, x 4096  12.8 / 13.3, x 14336  17.2 / 23.0; of few blocks always: 4 x 2048  10.6 / 11.6
 //   4 ways rather than 1: 64 x 1792  12.8 / 13.2, x 2048  13.0 / 14.3, x 4096  17.0 / 22.4; wide: 32 x 2048  29.2 / 30.5,
 //     64 x 2048  33.9 / 31.0, x 3072  37.1 / 41.7
-//   2 ways rather than 1: 66 x 2560  14.7 / 15.9, x 3072  15.6 / 18.0; 128 x 2560  17.9 / 17.0, x 3072  19.0 / 19.2; wide: 128 x 4096  52.3 / 54.5 forward,
-//     58.5 / 53.0 backward, x 5120  58.4 / 66.4 and 60.2 / 65.4
-// Bytes of one work group's share (fp32 accumulators) where the largest rank of the block's class is `rank`: as many 16-wide rank blocks
-// as that takes, of 64 rows (ranks up to 64) or 128.
-constexpr int shrink_share_bytes(int rank) { return (rank + 15) / 16 * (rank > kNarrowMaxRank ? 8192 : 4096); }
-constexpr int kSplitChunks = 3, kSplitChunkBytes = (2 << 20) - (128 << 10);
+//   2 ways rather than 1: 66 x 2560  14.7 / 15.9, x 3072  15.6 / 18.0; 128 x 2560  17.9 / 17.0, x 3072  19.0 / 19.2; wide: 128 x 4096
+//     52.3 / 54.5 forward, 58.5 / 53.0 backward, x 5120  58.4 / 66.4 and 60.2 / 65.4
 inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus, bool wide) {
     const int64_t steps = contraction / 64;
     if (blocks <= 0 || shrink_log_pieces((int)steps) == 0) return 1;

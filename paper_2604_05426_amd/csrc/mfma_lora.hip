@@ -253,7 +253,7 @@ __global__ __launch_bounds__(64 * SNW) void shrink_kernel(ShrinkArgs g) {
 // pieces pairwise, ((0 1) (2 3)) ((4 5) (6 7)); a shorter one is a single chain.  That is fixed by the contraction alone, so that a row of S
 // has the same bits whatever work groups its batch gives it: were the division taken from the number of row blocks, a job's
 // results would change when a neighbour joins or leaves the batch.
-// Split contraction: a work group takes 0.3-0.35 us per 64-wide step whatever else runs, so 19 row blocks of a 1024-token batch
+// Split contraction: a work group takes 0.28-0.35 us per 64-wide step whatever else runs, so 19 row blocks of a 1024-token batch
 // spent 68 us on a contraction of 14336 with 237 CUs idle.  With `splits` (2, 4 or 8) > 1 each work group of a block takes 8 / splits
 // neighbouring pieces, a whole subtree of the sum, and stores its accumulators; the one that arrives last (agent-scope counter) adds the
 // shares up the rest of the tree - so the result does not depend on the order of arrival either - and writes S.  Nobody waits for anybody.
@@ -277,7 +277,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g4 = lane >> 4;
     const int i = e.a, row0 = e.c, rows = e.d;
-    const int r = __builtin_amdgcn_readfirstlane(g.pv.rank[i]);      // (scalar branches on it in the loop below)
+    const int r = __builtin_amdgcn_readfirstlane(g.pv.rank[i]);
     const u16* F = global_ptr<const u16>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
     const float s = FWD ? 1.0f : g.pv.scale[i];
     // swizzle key of contraction row k of the A_i tile
@@ -312,7 +312,7 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     const int pieces = 1 << (SPLIT ? log_pieces - g.log_splits : log_pieces), piece0 = SPLIT ? split * pieces : 0;   // of this work group
     auto piece_end = [&](int q) { return (all_steps * q) >> log_pieces; };
     const int step0 = SPLIT ? piece_end(piece0) : 0, steps = SPLIT ? piece_end(piece0 + pieces) - step0 : all_steps;
-    const int64_t stepF = FWD ? (int64_t)64 * __builtin_amdgcn_readfirstlane(r) * 2 : 128;
+    const int64_t stepF = FWD ? (int64_t)64 * r * 2 : 128;
     const char* baseX = uniform_ptr(g.src + (int64_t)row0 * g.ld + (int64_t)step0 * 64);
     const char* baseF = uniform_ptr(reinterpret_cast<const char*>(F) + step0 * stepF);
     const unsigned lds0 = (unsigned)(uintptr_t)lds;
