@@ -148,7 +148,8 @@ template <typename T> __device__ __forceinline__ uint4 gather16(const T* p, int6
 // Work group = 16 rows of one adapter x all its ranks; its eight wavefronts deal the contraction among themselves two neighbouring pieces at
 // a time (whole 128-byte lines of a row), straight from memory into MFMA operands (X / dY rows are read once; the adapter matrix
 // comes from the caches), with the operands of the next load in flight.  In fp32 a wavefront's pairs of pieces take turns on two accumulator
-// sets (less rounding error than one chain); the wavefronts' sums are added in LDS in wavefront order.
+// sets (less rounding error than one chain) and a contraction of up to eight pieces is dealt singly; the wavefronts' sums are added in
+// LDS in wavefront order.
 template <typename T> struct GenShrinkArgs {
     const T* src; int64_t ld;     // X (ld k) or dY (ld n); the contraction has ld elements
     T* out;                       // ragged S or dS
@@ -246,21 +247,31 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
             }
         }
     };
+    auto compute_piece = [&](int set, int u, f32x4 (&to)[NB]) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if constexpr (QUAD) {
+                if (64 * (b / 4) < r) to[b] = block_mma<T>(xa[set][u], quad_column<T>(fq[set][u][b / 4], b % 4), to[b]);
+            } else {
+                if (16 * b < r) to[b] = block_mma<T>(xa[set][u], fb[set][u][b], to[b]);
+            }
+        }
+    };
     auto compute = [&](int set, f32x4 (&to)[NB]) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                if constexpr (QUAD) {
-                    if (64 * (b / 4) < r) to[b] = block_mma<T>(xa[set][u], quad_column<T>(fq[set][u][b / 4], b % 4), to[b]);
-                } else {
-                    if (16 * b < r) to[b] = block_mma<T>(xa[set][u], fb[set][u][b], to[b]);
-                }
-            }
+        for (int u = 0; u < U; ++u) compute_piece(set, u, to);
     };
     const int units = (K + U * kBlockK<T> - 1) / (U * kBlockK<T>);
     // wavefront w takes the pairs of pieces w, w + 8, w + 16, ..., in fp32 in turn into acc and other
-    if constexpr (U == 2) {
+    if (TWO && K <= NW * kBlockK<T>) {
+        // up to 128 elements of fp32, one piece a wavefront: S is off by 0.8 of what it is with pairs (1.07e-7 -> 8.4e-8 relative at 64
+        // elements), in the same time
+        if (wave / U < units) {
+            load(wave / U, 0);
+            if (U == 1 || wave % 2 == 0) compute_piece(0, 0, acc);
+            else                         compute_piece(0, U - 1, acc);
+        }
+    } else if constexpr (U == 2) {
         if (wave < units) load(wave, 0);
         for (int p = wave; p < units; p += 2 * NW) {
             if (p + NW < units) load(p + NW, 1);

@@ -69,7 +69,7 @@ def test_splits_of_the_shrink(k, n, rank):
                                     ([(128, 500)], [(16, 1500)]), ([(64, 5003)], [(4, 4500)])])
 
 
-@pytest.mark.parametrize("dtype,k,n", [("f32", 256, 264), ("f32", 1000, 515), ("f32", 31, 700), ("bf16", 1000, 515), ("bf16", 513, 260), ("bf16", 2050, 96)])
+@pytest.mark.parametrize("dtype,k,n", [("f32", 256, 264), ("f32", 1000, 515), ("f32", 31, 700), ("f32", 128, 100), ("bf16", 1000, 515), ("bf16", 513, 260), ("bf16", 2050, 96)])
 @pytest.mark.parametrize("rank,rows", [(8, 20), (16, 150), (33, 150), (100, 40)])
 def test_tiles_and_builds_of_the_general_kernels(dtype, k, n, rank, rows):
     """Both tiles of the general products (32 x 32 alone, 64 x 64 with the neighbours), fewer rows than a tile, contractions with
