@@ -1,148 +1,26 @@
 // The general kernels: fp32 plans, and bf16 plans whose k or n is not a multiple of 8 (rows that start at any element).
 // Every step of the layer (paper Sec. 5.1) is one grouped launch on the matrix units, with fp32 accumulation:
 //   S_i = X_i A_i, dS_i = s_i dY_i B_i^T               general_shrink_kernel
-//   Y = X W + s_i S_i B_i, dX = dY W^T + dS_i A_i^T    general_gemm_kernel (also either term alone)
+//   Y = X W + s_i S_i B_i, dX = dY W^T + dS_i A_i^T    general_gemm_kernel in bf16 (also either term alone); fp32: f32_gemm.hip
 //   dA_i = X_i^T dS_i, dB_i = s_i S_i^T dY_i           general_wgrad_kernel
 // No operand needs an alignment beyond its element: 16-byte pieces are loaded from wherever they start (global memory takes any
 // alignment), pieces that cross an edge element by element.
 //
-// fp32 goes through v_mfma_f32_16x16x4_f32 (256 FLOP per clock and CU, twice the vector ALUs without packed forms): the products of
-// a large layer are bound by it, not by memory, so a plain 64 x 64 tile with a few work groups per CU is enough.  Everything else
-// here is bound by latency (short segments, few tiles): the contractions of shrink and weight gradients are split over the wavefronts of a
-// work group and summed in a fixed order in LDS, and loads run ahead of the MFMAs in registers.  Edges cost nothing in the main loops:
-// the last tile of rows or columns starts early enough to be whole, and only the last step of a contraction takes a mask (with a
+// Everything here is bound by latency (short segments, few tiles): the contractions of shrink and weight gradients are split over the
+// wavefronts of a work group and summed in a fixed order in LDS, and loads run ahead of the MFMAs in registers.  Edges cost nothing in the main
+// loops: the last tile of rows or columns starts early enough to be whole, and only the last step of a contraction takes a mask (with a
 // condition on every load, the edge tiles alone made the bf16 products of 1500 x 1001 outputs 52 us instead of 27).
 //
 // Order of the sums: it follows from the contraction alone, not from the tile or the build that a batch is given, so that an adapter's rows
 // of S, Y, dS and dX have the same bits whatever its neighbours' tokens and ranks are.
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
-// tokens, 256 x 256: 171 -> 26 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 387 us (its two frozen-weight products 176 us each, 98
-// TFLOP/s; 144 is what a large fp32 product reaches on this card); bf16, 1500 tokens, 2048 x 1001: 1105 -> 83 us.
-#include "mfma_common.h"
+// tokens, 256 x 256: 171 -> 24 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 264 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 83 us.
+#include "general_common.h"
 
 namespace mlora {
 
 namespace {
-
-template <typename T> constexpr int kEpc = 16 / (int)sizeof(T);     // elements of a 16-byte piece
-
-// 16 bytes from any element boundary; the first `valid` elements are read, the rest are zero
-template <typename T> __device__ __forceinline__ uint4 load16(const T* p, int valid) {
-    uint4 v = zero4();
-    if (valid >= kEpc<T>) {
-        __builtin_memcpy(&v, p, 16);
-    } else if (valid > 0) {
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        T o[kEpc<T>];
-#pragma unroll
-        for (int e = 0; e < kEpc<T>; ++e) o[e] = p[min(e, valid - 1)];      // all in flight together
-#pragma unroll
-        for (int e = 0; e < kEpc<T>; ++e) {
-            if constexpr (sizeof(T) == 4) w[e] = e < valid ? __float_as_uint(o[e]) : 0u;
-            else w[e >> 1] |= e < valid ? (uint32_t)o[e] << ((e & 1) * 16) : 0u;
-        }
-        v = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-    return v;
-}
-
-template <typename T> __device__ __forceinline__ float to_f32(T v) {
-    if constexpr (sizeof(T) == 4) return v; else return bf2f(v);
-}
-template <typename T> __device__ __forceinline__ T from_f32(float v) {
-    if constexpr (sizeof(T) == 4) return v; else return f2bf(v);
-}
-
-// One lane's share of a 16 x 16 block product over 16 (fp32) or 32 (bf16) contraction elements: 16 bytes per operand.  bf16: the
-// eight elements 8 g .. 8 g + 7 of row / column l % 16, g = l / 16; fp32: the elements 4 g .. 4 g + 3, multiplied in four steps
-// (step j takes element 4 g + j of every g: the order inside the sum is free as long as both operands agree).
-template <typename T> __device__ __forceinline__ f32x4 block_mma(uint4 a, uint4 b, f32x4 c) {
-    if constexpr (sizeof(T) == 4) {
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
-        return c;
-    } else {
-        return mfma16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c);
-    }
-}
-// 2 x 2 blocks at once: the fp32 steps of the four blocks interleave, so that none waits for the one before it
-template <typename T> __device__ __forceinline__ void block_mma_2x2(const uint4 (&b)[2], const uint4 (&a)[2], f32x4 (&acc)[2][2]) {
-    if constexpr (sizeof(T) == 4) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y) {
-                    const uint32_t av = j == 0 ? a[x].x : j == 1 ? a[x].y : j == 2 ? a[x].z : a[x].w;
-                    const uint32_t bv = j == 0 ? b[y].x : j == 1 ? b[y].y : j == 2 ? b[y].z : b[y].w;
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(bv), __uint_as_float(av), acc[x][y], 0, 0, 0);
-                }
-    } else {
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int y = 0; y < 2; ++y) acc[x][y] = block_mma<T>(b[y], a[x], acc[x][y]);
-    }
-}
-// N chains of fp32 blocks at once
-template <int N> __device__ __forceinline__ void block_mma_n(const uint4 (&b)[N], const uint4 (&a)[N], f32x4* c) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const uint32_t av = j == 0 ? a[i].x : j == 1 ? a[i].y : j == 2 ? a[i].z : a[i].w;
-            const uint32_t bv = j == 0 ? b[i].x : j == 1 ? b[i].y : j == 2 ? b[i].z : b[i].w;
-            c[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(bv), __uint_as_float(av), c[i], 0, 0, 0);
-        }
-}
-template <typename T> constexpr int kBlockK = sizeof(T) == 4 ? 16 : 32;   // contraction of one block_mma
-
-// Four adjacent elements of a row whose columns are spread over four blocks (block x takes the columns 4 l + x).  `whole`
-// (uniform): all four are inside the row; else each is clamped to the last of `valid` (>= 1) by itself.
-template <typename T> using quad_t = uint32_t __attribute__((ext_vector_type(sizeof(T) == 4 ? 4 : 2)));
-template <typename T> __device__ __forceinline__ quad_t<T> load_quad(const T* p, bool whole, int valid) {
-    quad_t<T> v;
-    if (whole) {
-        __builtin_memcpy(&v, p, sizeof(v));
-    } else {
-        T o[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) o[c] = p[min(c, valid - 1)];
-        __builtin_memcpy(&v, o, sizeof(v));
-    }
-    return v;
-}
-constexpr int kQuadRows32 = 4, kQuadRows16 = 8;
-template <typename T> constexpr int kQuadRows = sizeof(T) == 4 ? kQuadRows32 : kQuadRows16;   // rows (contraction) per lane and piece
-// column x of a lane's quads as MFMA operand bytes
-template <typename T> __device__ __forceinline__ uint4 quad_column(const quad_t<T> (&q)[kQuadRows<T>], int x) {
-    uint32_t w[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        if constexpr (sizeof(T) == 4) w[p] = q[p][x];
-        else w[p] = __builtin_amdgcn_perm(q[2 * p + 1][x >> 1], q[2 * p][x >> 1], (x & 1) ? 0x07060302u : 0x05040100u);
-    }
-    return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-// the 16 bytes a lane supplies when its elements lie `ld` apart: elements k .. of a column at p
-template <typename T> __device__ __forceinline__ uint4 gather16(const T* p, int64_t ld, int valid) {
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-    if (valid <= 0) return zero4();
-    T o[kEpc<T>];
-#pragma unroll
-    for (int e = 0; e < kEpc<T>; ++e) o[e] = p[min(e, valid - 1) * ld];
-#pragma unroll
-    for (int e = 0; e < kEpc<T>; ++e) {
-        if constexpr (sizeof(T) == 4) w[e] = e < valid ? __float_as_uint(o[e]) : 0u;
-        else w[e >> 1] |= e < valid ? (uint32_t)o[e] << ((e & 1) * 16) : 0u;
-    }
-    return make_uint4(w[0], w[1], w[2], w[3]);
-}
 
 // ---- shrink ------------------------------------------------------------------------------------------------------------------
 // Work group = 16 rows of one adapter x all its ranks; its eight wavefronts deal the contraction among themselves two neighbouring pieces at
@@ -321,8 +199,9 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
     }
 }
 
-// ---- products with the frozen weight, and the rank extension -------------------------------------------------------------------
-template <typename T> struct GenGemmArgs {
+// ---- bf16 products with the frozen weight, and the rank extension (fp32: f32_gemm.hip) -------------------------------------------------------------------
+struct GenGemmArgs {
+    typedef u16 T;
     const T* A; const T* W;       // X (fwd) or dY (bwd); W [k][n]
     T* C;                         // Y or dX
     const T* E;                   // ragged S or dS
@@ -334,18 +213,15 @@ template <typename T> struct GenGemmArgs {
 };
 
 // Tile: KC = 1: 64 x 64, KC = 4: 32 x 32; four wavefronts 2 x 2, each 2 x 2 blocks or one.
-// A step is KC chunks of 128 bytes per row (32 fp32 / 64 bf16 elements).  LDS rows of operands whose contraction is contiguous are
-// padded to 144 bytes (16-byte reads of 16 rows then touch every bank once); a W / B_i tile [contraction][column] keeps fp32 rows
-// padded by 4 elements, bf16 rows XOR-swizzled in 32-byte units for the transposing read.
+// A step is KC chunks of 128 bytes per row (64 elements).  LDS rows of operands whose contraction is contiguous are padded to 144 bytes
+// (16-byte reads of 16 rows then touch every bank once); a W / B_i tile [contraction][column] is XOR-swizzled in 32-byte units for the
+// transposing read.
 // Forward: B operand (W, B_i) has its columns contiguous; backward (W, A_i transposed): its contraction.
-// Order of the sum, in both tiles and both loops below (the tile follows from the number of tokens, and a row's bits must not): groups of 16
-// (fp32) / 32 (bf16) elements that start at multiples of that, zero-filled at the end, in ascending order, then each adapter's term.  bf16:
-// one chain of MFMAs; fp32: a chain per pair of chunks (64 elements), or per chunk where the contraction is shorter than 256, added up one
-// by one.  Relative error of a product against one chain throughout: 256 elements 2.7e-7 -> 1.5e-7, 2048 elements 7.9e-7 -> 1.8e-7; time,
-// 2048 x 2048 x 2048: 176 -> 175-177 us (a chain per chunk throughout: 189).  Splitting the 32 x 32 tile's contraction over its wavefronts
-// instead of the tile takes the same time (256 x 256 x 256: 10.2 us both ways).
-template <typename T, bool FWD, int KC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3 : 2))) void general_gemm_kernel(GenGemmArgs<T> g) {
+// Order of the sum, in both tiles and both loops below (the tile follows from the number of tokens, and a row's bits must not): one chain of
+// MFMAs over groups of 32 elements that start at multiples of that, zero-filled at the end, in ascending order, then each adapter's term.
+template <bool FWD, int KC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3 : 2))) void general_gemm_kernel(GenGemmArgs g) {
+    typedef u16 T;
     constexpr int BT = KC == 1 ? 64 : 32;                    // tile edge
     constexpr int NB = BT / 32;                              // blocks of a wavefront, each way
     constexpr int KW = 128 / (int)sizeof(T), KT = KW * KC;   // contraction per chunk and per step
@@ -354,7 +230,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
     constexpr int NCH = BT * CPK / 256;                      // pieces per thread and operand
     constexpr int CPN = BT / EPC;                            // pieces of a column row (fwd W tile)
     constexpr int A_TILE = KC * BT * 144;
-    constexpr int NC_PITCH = sizeof(T) == 4 ? (BT + 4) * 4 : BT * 2;
+    constexpr int NC_PITCH = BT * 2;
     constexpr int B_TILE = FWD ? KT * NC_PITCH : A_TILE;
     constexpr int STAGE = A_TILE + B_TILE;
     __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE];
@@ -379,7 +255,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
         *reinterpret_cast<uint4*>(As + lds_off(idx)) = a;
         if (FWD) {
             const int kr = idx / CPN, cn = idx % CPN;
-            *reinterpret_cast<uint4*>(Bs + kr * NC_PITCH + (sizeof(T) == 4 ? cn * 16 : (unit(kr, cn >> 1) << 5) | ((cn & 1) << 4))) = b;
+            *reinterpret_cast<uint4*>(Bs + kr * NC_PITCH + ((unit(kr, cn >> 1) << 5) | ((cn & 1) << 4))) = b;
         } else {
             *reinterpret_cast<uint4*>(Bs + lds_off(idx)) = b;
         }
@@ -398,10 +274,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
                     f.a[h][x] = *reinterpret_cast<const uint4*>(As + (kc * BT + (wm * NB + x) * 16 + l16) * 144 + h * 64 + g4 * 16);
                     if (!FWD) {
                         f.b[h][x] = *reinterpret_cast<const uint4*>(Bs + (kc * BT + (wn * NB + x) * 16 + l16) * 144 + h * 64 + g4 * 16);
-                    } else if constexpr (sizeof(T) == 4) {
-                        const float* p = reinterpret_cast<const float*>(Bs + (kc * KW + h * 16 + 4 * g4) * NC_PITCH) + (wn * NB + x) * 16 + l16;
-                        f.b[h][x] = make_uint4(__float_as_uint(p[0]), __float_as_uint(p[NC_PITCH / 4]), __float_as_uint(p[2 * (NC_PITCH / 4)]),
-                                               __float_as_uint(p[3 * (NC_PITCH / 4)]));
                     } else {
                         const int k = kc * KW + h * 32 + 8 * g4 + (l16 >> 2);
                         const unsigned char* p = Bs + k * NC_PITCH + (unit(k, wn * NB + x) << 5) + (l16 & 3) * 8;
@@ -417,64 +289,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
 #pragma unroll
             for (int y = 0; y < NB; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    auto add = [&](Acc& acc, const Acc& part) {
+    auto multiply = [&](Acc& acc, const Frags (&fr)[KC]) {
 #pragma unroll
-        for (int x = 0; x < NB; ++x)
+        for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-            for (int y = 0; y < NB; ++y) acc[x][y] += part[x][y];
-    };
-    // the products of one step; `odd`: it ends a pair of (one-chunk) steps
-    enum Chains { PER_CHUNK, PER_PAIR };
-    auto chains_of = [](int64_t K) { return K < 256 ? PER_CHUNK : PER_PAIR; };
-    auto multiply = [&](Acc& acc, Acc& part, const Frags (&fr)[KC], Chains chains, bool odd) {
-        // Here the chains of a step interleave, so that none waits for its last product: 25.7 -> 24.2 us (142 x 720 x 600, 24 adapters),
-        // 13.8 -> 13.3 us (888 x 368 x 152).  Not in the backward, whose launches did not get faster.
-        if constexpr (sizeof(T) == 4 && KC == 4 && FWD) {
-            f32x4 sum[KC];
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int kc = 0; kc < KC; ++kc) sum[kc] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (chains == PER_PAIR) {
+                for (int x = 0; x < NB; ++x)
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) block_mma_n<2>({fr[c].b[h][0], fr[2 + c].b[h][0]}, {fr[c].a[h][0], fr[2 + c].a[h][0]}, sum);
-                acc[0][0] += sum[0];
-                acc[0][0] += sum[1];
-            } else {
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    block_mma_n<4>({fr[0].b[h][0], fr[1].b[h][0], fr[2].b[h][0], fr[3].b[h][0]},
-                                   {fr[0].a[h][0], fr[1].a[h][0], fr[2].a[h][0], fr[3].a[h][0]}, sum);
-#pragma unroll
-                for (int kc = 0; kc < KC; ++kc) acc[0][0] += sum[kc];
-            }
-            return;
-        }
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-            constexpr bool PARTS = sizeof(T) == 4;
-            const bool second = KC == 1 ? odd : (kc & 1) != 0;
-            if (PARTS && (chains == PER_CHUNK || !second)) clear(part);
-            Acc& to = PARTS ? part : acc;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if constexpr (NB == 2) block_mma_2x2<T>(fr[kc].b[h], fr[kc].a[h], to);
-                else                   to[0][0] = block_mma<T>(fr[kc].b[h][0], fr[kc].a[h][0], to[0][0]);
-            }
-            if (PARTS && (chains == PER_CHUNK || second)) add(acc, part);
-        }
-    };
-    auto finish = [&](Acc& acc, const Acc& part, Chains chains, int64_t steps) {      // a last pair with only one chunk
-        if (sizeof(T) == 4 && KC == 1 && chains == PER_PAIR && (steps & 1)) add(acc, part);
+                    for (int y = 0; y < NB; ++y) acc[x][y] = block_mma<T>(fr[kc].b[h][y], fr[kc].a[h][x], acc[x][y]);
     };
 
     // acc += A B over a contraction of K.  Element (row m0 + i, c) of A at a[i * lda + c], rows [row_lo, row_hi) exist; column
     // n0 + j, element c of B at b[c * ldb + j] (fwd) or b[j * ldb + c] (bwd).  Any sizes, one step at a time: for short contractions.
-    auto contract_any = [&](Acc& acc, const T* a, int64_t lda, int64_t row_lo, int64_t row_hi, const T* b, int64_t ldb, int64_t K, Chains chains) {
-        Acc part;
-        clear(part);
-        int64_t step = 0;
-        for (int64_t k0 = 0; k0 < K; k0 += KT, ++step) {
+    auto contract_any = [&](Acc& acc, const T* a, int64_t lda, int64_t row_lo, int64_t row_hi, const T* b, int64_t ldb, int64_t K) {
+        for (int64_t k0 = 0; k0 < K; k0 += KT) {
             const int left = (int)min((int64_t)KT, K - k0);
             uint4 ra[NCH], rb[NCH];
 #pragma unroll
@@ -494,9 +323,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
             __syncthreads();
             Frags f[KC];
             read_frags(f, 0);
-            multiply(acc, part, f, chains, step & 1);
+            multiply(acc, f);
         }
-        finish(acc, part, chains, step);
     };
 
     // The same for whole tiles and at least one whole step: every load is inside its rows and takes no condition.  Step t travels
@@ -526,36 +354,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
             for (int c = 0; c < NCH; ++c) store_piece(stage, tid + 256 * c, va[c], vb[c]);
         };
         Frags f[KC];
-        Acc part;
-        clear(part);
         load_step(0, 0);
         load_step(1, 1);
         store(0, ra[0], rb[0]);
         load_step(2, 0);
         __syncthreads();
         int64_t t = 0;
-        auto two_steps = [&](Chains chains) {
+        auto two_steps = [&]() {
             store(1, ra[1], rb[1]);
             load_step(t + 3, 1);
             read_frags(f, 0);
             __builtin_amdgcn_sched_barrier(0);           // all reads are on their way before the first product
-            multiply(acc, part, f, chains, false);
+            multiply(acc, f);
             __syncthreads();
             store(0, ra[0], rb[0]);
             load_step(t + 4, 0);
             read_frags(f, 1);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(acc, part, f, chains, true);
+            multiply(acc, f);
             __syncthreads();
             t += 2;
         };
-        if (sizeof(T) == 4 && K < 256)                   // (a branch inside the loop costs 6 %)
-            while (t + 1 < nt) two_steps(PER_CHUNK);
-        else
-            while (t + 1 < nt) two_steps(PER_PAIR);
+        while (t + 1 < nt) two_steps();
         if (t < nt) {
             read_frags(f, 0);
-            multiply(acc, part, f, chains_of(K), false);
+            multiply(acc, f);
         }
         const int left = (int)(K - nt * KT);
         if (left > 0) {
@@ -584,9 +407,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
             store(0, ra[0], rb[0]);
             __syncthreads();
             read_frags(f, 0);
-            multiply(acc, part, f, chains_of(K), nt & 1);
+            multiply(acc, f);
         }
-        finish(acc, part, chains_of(K), nt + (left > 0));
     };
 
     Acc acc;
@@ -615,7 +437,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
     if (g.base) {
         const T* w = FWD ? g.W + n0 : g.W + n0 * g.ldw;
         if (g.M >= BT && g.N >= BT && g.K >= KT) contract_whole(acc, g.A + m0 * g.lda, g.lda, w, g.ldw, g.K);
-        else contract_any(acc, g.A + m0 * g.lda, g.lda, m0, g.M, w, g.ldw, g.K, chains_of(g.K));
+        else contract_any(acc, g.A + m0 * g.lda, g.lda, m0, g.M, w, g.ldw, g.K);
     }
 
     // rank extension, adapter by adapter into a second accumulator set, of which the adapter's own rows are added: another
@@ -636,7 +458,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
             Acc ext;
             clear(ext);
             contract_any(ext, g.E + (int64_t)lane64((uint64_t)c_so) + (int64_t)(lo_t - seg0) * r, r, lo, hi, FWD ? F + n0 : F + n0 * r,
-                     FWD ? g.N : r, r, PER_CHUNK);
+                     FWD ? g.N : r, r);
 #pragma unroll
             for (int x = 0; x < NB; ++x) {
                 const int row = lo_t + (wm * NB + x) * 16 + l16;
@@ -815,10 +637,10 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     return MLORA_OK;
 }
 
-template <typename T, bool FWD>
+template <bool FWD>
 int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, uint32_t flags, hipStream_t st) {
-    GenGemmArgs<T> a{};
-    a.A = (const T*)A; a.W = (const T*)W; a.C = (T*)C; a.E = (const T*)E;
+    GenGemmArgs a{};
+    a.A = (const u16*)A; a.W = (const u16*)W; a.C = (u16*)C; a.E = (const u16*)E;
     a.M = p->T; a.K = FWD ? p->k : p->n; a.N = FWD ? p->n : p->k;
     a.lda = a.K; a.ldw = p->n; a.ldc = a.N;
     a.base = (flags & MLORA_FLAG_LORA_ONLY) ? 0 : 1;
@@ -827,14 +649,13 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
     if (a.M == 0 || (!a.base && !a.lora)) return MLORA_OK;
     ProfScope prof(p, FWD ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
     auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
-    // 32 x 32 tiles where 64 x 64 ones would leave half the chip idle.  us, 32 x 32 / 64 x 64, by the number of 64 x 64 tiles: fp32, 20 (256 x
-    // 257, contraction 256) 10.3 / 13.5, 72 (500 x 513, 1000) 24 / 32, 128 (512 x 1024, 1024) 25 / 31, 136 (500 x 1025, 4096) 97 / 99, 176
-    // (700 x 1001, 1001) 38 / 34; bf16, the same shapes: 8.4 / 9.6, 14.2 / 14.1, 20 / 14 (136 tiles, 1024), 44 / 31, 23 / 15.  The results are
-    // the same bit for bit.
+    // 32 x 32 tiles where 64 x 64 ones would leave half the chip idle.  us, 32 x 32 / 64 x 64, by the number of 64 x 64 tiles: 20 (256 x 257,
+    // contraction 256) 8.4 / 9.6, 72 (500 x 513, 1000) 14.2 / 14.1, 128 (512 x 1024, 1024) 20 / 14, 136 (500 x 1025, 4096) 44 / 31, 176
+    // (700 x 1001, 1001) 23 / 15.  The results are the same bit for bit.
     const bool split = tiles(64) <= p->num_cus / 2;
     a.tiles_n = (a.N + (split ? 31 : 63)) / (split ? 32 : 64);
-    if (split) hipLaunchKernelGGL((general_gemm_kernel<T, FWD, 4>), dim3((unsigned)tiles(32)), dim3(256), 0, st, a);
-    else       hipLaunchKernelGGL((general_gemm_kernel<T, FWD, 1>), dim3((unsigned)tiles(64)), dim3(256), 0, st, a);
+    if (split) hipLaunchKernelGGL((general_gemm_kernel<FWD, 4>), dim3((unsigned)tiles(32)), dim3(256), 0, st, a);
+    else       hipLaunchKernelGGL((general_gemm_kernel<FWD, 1>), dim3((unsigned)tiles(64)), dim3(256), 0, st, a);
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;
 }
@@ -863,13 +684,19 @@ int wgrad(mlora_plan* p, const void* dY, const void* X, const void* S, const voi
     return MLORA_OK;
 }
 
+template <typename T, bool FWD>
+int product(mlora_plan* p, const void* A, const void* W, void* C, const void* E, uint32_t flags, hipStream_t st) {
+    if constexpr (sizeof(T) == 4) return f32_gemm(p, FWD, A, W, C, E, flags, st);
+    else                          return gemm<FWD>(p, A, W, C, E, flags, st);
+}
+
 template <typename T>
 int fwd_t(mlora_plan* p, const void* X, const void* W, void* Y, void* S, uint32_t flags, hipStream_t st) {
     if (!(flags & MLORA_FLAG_BASE_ONLY)) {
         const int rc = shrink<T, true>(p, X, S, st);
         if (rc != MLORA_OK) return rc;
     }
-    return gemm<T, true>(p, X, W, Y, S, flags, st);
+    return product<T, true>(p, X, W, Y, S, flags, st);
 }
 
 template <typename T>
@@ -877,7 +704,7 @@ int bwd_t(mlora_plan* p, const void* dY, const void* X, const void* W, const voi
     int rc;
     if (!(flags & MLORA_FLAG_BASE_ONLY))
         if ((rc = shrink<T, false>(p, dY, dS, st)) != MLORA_OK) return rc;
-    if ((rc = gemm<T, false>(p, dY, W, dX, dS, flags, st)) != MLORA_OK) return rc;
+    if ((rc = product<T, false>(p, dY, W, dX, dS, flags, st)) != MLORA_OK) return rc;
     if (!(flags & MLORA_FLAG_BASE_ONLY)) return wgrad<T>(p, dY, X, S, dS, flags, st);
     return MLORA_OK;
 }

@@ -1,0 +1,75 @@
+"""The fp32 products (three bf16 parts per value) against float64: every tile with whole and partial stages, and rows and columns
+whose values the parts do not hold - close to the largest fp32 number, below 2^-90, infinite, NaN - beside ordinary ones."""
+import pytest
+import torch
+
+from paper_2604_05426_amd import binding as ml
+
+pytestmark = pytest.mark.gpu
+
+# tokens, k, n: 32 x 32, 64 x 64 and 128 x 128 tiles forward and backward; contractions that are whole stages, end inside one, or are one element
+SHAPES = [(40, 64, 96), (70, 33, 1), (33, 7, 40), (700, 500, 515), (1000, 512, 720), (2100, 520, 1100), (2051, 1111, 514)]
+
+
+def _products(X, W, dY):
+    """(Y, dX) of a plan without adapters."""
+    T, k, n = X.shape[0], X.shape[1], W.shape[1]
+    plan = ml.Plan(ml.F32, T, k, n, [], [], [0])
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+    Y, dX = torch.full((T, n), float("nan"), device="cuda"), torch.full((T, k), float("nan"), device="cuda")
+    ml.multi_lora_fwd(plan, X, W, [], [], Y, None, ws)
+    ml.multi_lora_bwd(plan, dY, X, W, [], [], None, dX, [], [], ws)
+    torch.cuda.synchronize()
+    plan.destroy()
+    return Y.cpu(), dX.cpu()
+
+
+def _check(got, a, b):
+    """got against a @ b.  An element's error is at most that of a sum of K rounded products in any order, (K + 8) 2^-24 of the sum of
+    magnitudes, and one denormal step per product; observed is a tenth of it."""
+    a, b = a.double().cpu(), b.double().cpu()
+    want, K = a @ b, a.shape[1]
+    f32max = torch.finfo(torch.float32).max
+    bound = (K + 8) * 2.0 ** -24 * (a.abs() @ b.abs()) + K * 2.0 ** -149
+    ordinary = want.isfinite() & (want.abs() < f32max / 2)
+    assert torch.equal(got[ordinary].isfinite(), torch.ones(int(ordinary.sum()), dtype=torch.bool))
+    assert bool(((got.double() - want).abs()[ordinary] <= bound[ordinary]).all())
+    assert torch.equal(got.isnan()[~want.isfinite()], want.isnan()[~want.isfinite()])
+    inf = want.isinf()
+    assert torch.equal(got[inf].double(), want[inf])
+
+
+@pytest.mark.parametrize("T,k,n", SHAPES)
+def test_products_and_their_range(T, k, n):
+    g = torch.Generator().manual_seed(T + k + n)
+    X, W, dY = (torch.randn(s, generator=g) for s in ((T, k), (k, n), (T, n)))
+    print(f"[case] fp32 products T={T} k={k} n={n}", flush=True)
+    Y, dX = _products(X.cuda(), W.cuda(), dY.cuda())
+    _check(Y, X, W)
+    _check(dX, dY, W.T)
+    plain = Y.clone(), dX.clone()
+    # rows of X and dY by turns: tiny, near the largest number, one Inf, one NaN, zero; the others keep their bits
+    for M in (X, dY):
+        M[3] *= 2.0 ** -120
+        M[5] *= 2.0 ** -140
+        M[9] = torch.sign(M[9]) * 3.4e38 * 2.0 ** -12
+        M[10, 0] = 3.4028234e38
+        M[17, -1] = float("inf")
+        M[18, 0] = float("nan")
+        M[T - 1] = 0.0
+    W[:, 0] *= 2.0 ** -10                   # (keeps the products with the largest numbers finite here and there)
+    Y, dX = _products(X.cuda(), W.cuda(), dY.cuda())
+    _check(Y, X, W)
+    _check(dX, dY, W.T)
+    same = [r for r in range(T) if r not in (3, 5, 9, 10, 17, 18, T - 1)]
+    assert torch.equal(Y[same][:, 1:], plain[0][same][:, 1:])
+    # a weight with an infinite, a NaN, a tiny and a huge entry
+    X, dY = torch.randn((T, k), generator=g), torch.randn((T, n), generator=g)
+    W[k // 2, n // 2] = float("inf")
+    W[0, n - 1] = float("nan")
+    W[:, n // 3] *= 2.0 ** -100
+    W[k // 3] *= 2.0 ** -130
+    W[k - 1, 0] = -3.0e38
+    Y, dX = _products(X.cuda(), W.cuda(), dY.cuda())
+    _check(Y, X, W)
+    _check(dX, dY, W.T)
