@@ -29,7 +29,7 @@
 // The MFMA operands are swapped (C^T blocks) so that each lane ends up with 4 consecutive output columns,
 // which lets the epilogue transpose each wavefront's sub-tile through LDS with 64-bit writes and store
 // full 128-byte row segments.
-#include "mfma_common.h"
+#include "mfma_wgrad.h"
 
 namespace mlora {
 
@@ -584,12 +584,19 @@ __global__ __launch_bounds__(NTHR) void fused_gemm_kernel(GemmArgs g) {
     }
 }
 
-// mfma_gemm_small.hip
-int small_gemm_tile(int64_t M, int64_t N, int64_t K, int num_cus);
-void launch_small_gemm(int tile, const GemmArgs& g, bool fwd, hipStream_t st);
+// Whether the weight gradients run beside the small tiles of a backward product (one launch less, and one begins where the other leaves CUs
+// idle): while both together are two rounds of work groups at most.  Beyond, the items get fewer work groups a CU here than in their own
+// launch, and the two ways are equal within 1 %.  us a step, apart / together, tokens x k x n (work groups of both in CUs): 600 x 1024 x 1024
+// (0.6) 36.2 / 30.3, 230 x 2048 x 512 (0.7) 33.4 / 28.9, 6000 x 512 x 768 (1.0) 55.1 / 47.4, 1000 x 512 x 4096 (1.6) 56.9 / 51.4, 1024 x 4096 x
+// 1024 (1.6) 61.1 / 60.0, 1024 x 4096 x 4096 (2.0) 103.0 / 102.5, 1024 x 4096 x 14336 (3.2) 267 / 266.
+static bool side_by_side(int tile, const GemmArgs& g, int items, int num_cus) {
+    const int64_t bm = tile == 0 ? 128 : 64, bn = tile == 2 ? 64 : 128;
+    const int64_t groups = ((g.M + bm - 1) / bm) * ((g.Ncols + bn - 1) / bn);
+    return groups + items / 2 <= 2 * num_cus;
+}
 
 static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, void* C, const void* E,
-                       uint32_t flags, hipStream_t st) {
+                       uint32_t flags, const WgradArgs* w, int items, int max_nb, bool* with_w, hipStream_t st) {
     if (p->T == 0) return MLORA_OK;
     // the direct tile loads address a tile with 32-bit byte offsets from its first row: 256 rows of k or n elements
     if (p->k > (int64_t(1) << 22) || p->n > (int64_t(1) << 22)) {
@@ -627,7 +634,9 @@ static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, 
     const int small = (flags & MLORA_FLAG_GROUP_BANDS) ? -1 : small_gemm_tile(g.M, g.Ncols, g.Kdim, p->num_cus);
     if (small >= 0) {
         ProfScope prof(p, fwd ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
-        launch_small_gemm(small, g, fwd, st);
+        const WgradArgs* beside = w && side_by_side(small, g, items, p->num_cus) ? w : nullptr;
+        launch_small_gemm(small, g, fwd, beside, items, max_nb, st);
+        if (beside) *with_w = true;
         MLORA_HIP_TRY(hipGetLastError());
         return MLORA_OK;
     }
@@ -642,12 +651,12 @@ static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, 
 
 int mfma_gemm_fwd(mlora_plan* p, const void* X, const void* W, void* Y, const void* S, uint32_t flags,
                   hipStream_t st) {
-    return launch_gemm(p, true, X, W, Y, S, flags, st);
+    return launch_gemm(p, true, X, W, Y, S, flags, nullptr, 0, 0, nullptr, st);
 }
 
-int mfma_gemm_bwd(mlora_plan* p, const void* dY, const void* W, void* dX, const void* dS, uint32_t flags,
-                  hipStream_t st) {
-    return launch_gemm(p, false, dY, W, dX, dS, flags, st);
+int mfma_gemm_bwd(mlora_plan* p, const void* dY, const void* W, void* dX, const void* dS, uint32_t flags, const WgradArgs* w, int items,
+                  int max_nb, bool* with_w, hipStream_t st) {
+    return launch_gemm(p, false, dY, W, dX, dS, flags, w, items, max_nb, with_w, st);
 }
 
 }  // namespace mlora

@@ -22,7 +22,7 @@
 // 1000 x 4096 outputs, k = 4096: 85 us with 256 x 256 tiles, 40 with 128 x 128; 200 x 512, k = 2048: 67 and, with 64 x 64, 14.  A
 // 128 x 128 work group spends about 0.5 us per step with all CUs busy (32 KB of operands at the 45-50 B/clk a CU's load path takes
 // are 0.3), where the MFMAs alone would take 0.21.
-#include "mfma_common.h"
+#include "mfma_wgrad.h"
 
 namespace mlora {
 
@@ -36,16 +36,19 @@ template <int N> __device__ __forceinline__ void wait_loads_and_barrier() {
 }
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// bytes of LDS: ring stages of the operand tiles of one 64-wide step
+template <int BM, int BN> constexpr int kStages = SG_LDS / ((BM + BN) * 128) < 8 ? SG_LDS / ((BM + BN) * 128) : 8;
+template <int BM, int BN> constexpr int kRing = kStages<BM, BN> * (BM + BN) * 128;
+
 template <bool NN, int BM, int BN>
-__global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
+__device__ __forceinline__ void small_gemm_body(const GemmArgs& g, unsigned char* const lds) {
     constexpr int AT = BM * 128, BT = BN * 128, STAGE = AT + BT;   // bytes: operand tiles of one 64-wide step
-    constexpr int NST = SG_LDS / STAGE < 8 ? SG_LDS / STAGE : 8;   // ring stages
+    constexpr int NST = kStages<BM, BN>;                           // ring stages
     constexpr int NA = BM / 64, NB_ = BN / 64, LPS = NA + NB_;     // direct loads per wavefront and step
     constexpr int WTM = BM / 2, WTN = BN / 4;                      // sub-tile of a wavefront
     constexpr int MB = WTM / 16, NB = WTN / 16;
     constexpr int BROW = BN * 2;                                   // NN: bytes per contraction row of the weight tile
     static_assert(LPS * (NST - 2) < 64, "vmcnt holds 6 bits");
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
@@ -366,17 +369,60 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
     }
 }
 
+template <bool NN, int BM, int BN>
+__global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kRing<BM, BN>];
+    small_gemm_body<NN, BM, BN>(g, lds);
+}
+
+// The backward product and the weight gradients of a batch that fills the chip with neither: both need dS alone and run side by side, the first
+// `gemm_groups` work groups on the tiles of dX, the others on two weight-gradient items each (four wavefronts an item).
+template <int BM, int BN, int MAXNB>
+__global__ __launch_bounds__(SG_THREADS) void small_bwd_kernel(GemmArgs g, WgradArgs w, int gemm_groups, int items) {
+    constexpr int ITEM = 2 * (WX_TILE + WT * MAXNB * 32);            // elements of LDS an item takes
+    constexpr int BYTES = kRing<BM, BN> > 4 * ITEM ? kRing<BM, BN> : 4 * ITEM;
+    static_assert(BYTES <= SG_LDS, "two items fit");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[BYTES];
+    if ((int)blockIdx.x < gemm_groups) {
+        small_gemm_body<false, BM, BN>(g, lds);
+        return;
+    }
+    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int panels = w.panels_k + w.panels_n;
+    const int item = 2 * (int)(blockIdx.x - gemm_groups) + half, other = item ^ 1;
+    const Entry4 none{0, 0, 0, 0};
+    const Entry4 e = item < items ? w.pv.wgrad_chunks[w.chunk_base + item / panels] : none;
+    const Entry4 o = other < items ? w.pv.wgrad_chunks[w.chunk_base + other / panels] : none;
+    const int steps = max(wgrad_steps(e), wgrad_steps(o));           // both halves pass the same barriers
+    if (item >= items) {
+        for (int t = 0; t <= steps; ++t) __syncthreads();
+        return;
+    }
+    u16* mine = reinterpret_cast<u16*>(lds) + half * ITEM;
+    const int panel = item % panels, tid = threadIdx.x & 255;
+    if (panel < w.panels_k) wgrad_body<MAXNB, true>(w, mine, tid, e, panel, steps);
+    else                    wgrad_body<MAXNB, false>(w, mine, tid, e, panel - w.panels_k, steps);
+}
+
 }  // namespace
 
+// `w` (backward only, may be null): the weight-gradient items that run beside the product, `items` of them, built for max_nb 32-wide rank blocks
 template <int BM, int BN>
-static void launch_small(GemmArgs g, bool fwd, hipStream_t st) {
+static void launch_small(GemmArgs g, bool fwd, const WgradArgs* w, int items, int max_nb, hipStream_t st) {
     g.tiles_m = (g.M + BM - 1) / BM;
     g.tiles_n = (g.Ncols + BN - 1) / BN;
     const int total = g.tiles_m * g.tiles_n;
     g.xcd_run = total >= 256 ? 32 : (total + 7) / 8;
     const int per = 8 * g.xcd_run, grid = (total + per - 1) / per * per;
-    if (fwd) hipLaunchKernelGGL((small_gemm_kernel<true, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g);
-    else     hipLaunchKernelGGL((small_gemm_kernel<false, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g);
+    if (w) {
+        const dim3 both(grid + (items + 1) / 2);
+        if (max_nb == 1) hipLaunchKernelGGL((small_bwd_kernel<BM, BN, 1>), both, dim3(SG_THREADS), 0, st, g, *w, grid, items);
+        else             hipLaunchKernelGGL((small_bwd_kernel<BM, BN, 2>), both, dim3(SG_THREADS), 0, st, g, *w, grid, items);
+    } else if (fwd) {
+        hipLaunchKernelGGL((small_gemm_kernel<true, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g);
+    } else {
+        hipLaunchKernelGGL((small_gemm_kernel<false, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g);
+    }
 }
 
 // Which kernel a product of M x N outputs over a contraction of K takes: -1 the 256 x 256 one, else an index of the table.
@@ -399,10 +445,10 @@ int small_gemm_tile(int64_t M, int64_t N, int64_t K, int num_cus) {
     return best - 1;
 }
 
-void launch_small_gemm(int tile, const GemmArgs& g, bool fwd, hipStream_t st) {
-    if (tile == 0)      launch_small<128, 128>(g, fwd, st);
-    else if (tile == 1) launch_small<64, 128>(g, fwd, st);
-    else                launch_small<64, 64>(g, fwd, st);
+void launch_small_gemm(int tile, const GemmArgs& g, bool fwd, const WgradArgs* w, int items, int max_nb, hipStream_t st) {
+    if (tile == 0)      launch_small<128, 128>(g, fwd, w, items, max_nb, st);
+    else if (tile == 1) launch_small<64, 128>(g, fwd, w, items, max_nb, st);
+    else                launch_small<64, 64>(g, fwd, w, items, max_nb, st);
 }
 
 }  // namespace mlora

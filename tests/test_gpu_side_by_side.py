@@ -1,0 +1,51 @@
+"""The backward product and the weight gradients in one launch (small batches): an odd number of weight-gradient items (a work group with
+one), items of different lengths that share a work group, segments without tokens, every tile, both rank builds, split segments
+with partial sums, accumulation; and a batch on the other side of the rule."""
+import pytest
+import torch
+
+from oracle import multilora_oracle as orc
+from paper_2604_05426_amd import binding as ml
+from paper_2604_05426_amd import workloads as wl
+from paper_2604_05426_amd.harness import DeviceLayer, to_host
+from util import elem_excess, rel_fro, row_rel_max
+
+pytestmark = pytest.mark.gpu
+
+# k, n, ranks, tokens of each adapter
+CASES = [(128, 256, [16, 8, 32], [70, 1, 200]),             # 9 items; 1, 2 and 4 steps
+         (384, 128, [64, 40], [129, 640]),                  # 4 panels; a segment of two chunks (partial sums)
+         (264, 136, [33, 4, 0, 12, 64], [64, 65, 10, 0, 63]),   # edges of a panel, a rank of 0, no tokens
+         (1024, 520, [16] * 3, [300, 250, 90]),             # 64 x 128 tiles
+         (2048, 640, [24, 64], [900, 700]),                 # 128 x 128 tiles
+         (512, 1032, [8] * 40, [30 + i for i in range(40)])]     # 13 panels x 40 adapters: more than two rounds of work groups
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_backward_of_small_batches(case):
+    k, n, ranks, lens = CASES[case]
+    w = wl.make_workload(f"beside_{case}", "bf16", k, n, ranks, lens, [1.0 + 0.5 * (i % 3) for i in range(len(ranks))], seed=case, b_sigma=0.3)
+    print(f"[case] side by side k={k} n={n} ranks={ranks[:6]} tokens={lens[:6]}", flush=True)
+    dl = DeviceLayer(w)
+    bw = orc.backward(w.dY, w.X, w.W, w.A, w.B, w.scales, w.offsets)
+
+    def check(times):
+        # bf16: tolerances of the parity tests (one rounding of dS, one of the result; accumulated: one more of the stored value)
+        assert rel_fro(to_host(dl.dX), bw.dX) <= 1e-2 and row_rel_max(to_host(dl.dX), bw.dX) <= 4e-2
+        for i in range(w.N):
+            if w.ranks[i] and w.seg_lens[i]:
+                assert rel_fro(to_host(dl.dA[i]), times * bw.dA[i]) <= 1e-2 and rel_fro(to_host(dl.dB[i]), times * bw.dB[i]) <= 1e-2
+                if times == 1:
+                    assert elem_excess(to_host(dl.dA[i]), bw.dA[i], "bf16") <= 1 and elem_excess(to_host(dl.dB[i]), bw.dB[i], "bf16") <= 1
+
+    dl.forward(); dl.backward(); dl.sync()
+    check(1)
+    once = [t.clone() for t in dl.dA + dl.dB]
+    # the decoupled form launches the weight gradients by themselves: the same bits
+    dl.backward(ml.FLAG_BASE_ONLY); dl.backward(ml.FLAG_LORA_ONLY); dl.sync()
+    for a, b in zip(once, dl.dA + dl.dB):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    dl.backward(ml.FLAG_ACCUM_GRADS); dl.sync()
+    check(2)
+    dl.check_guards()
+    dl.plan.destroy()
