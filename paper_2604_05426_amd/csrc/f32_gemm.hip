@@ -23,7 +23,7 @@
 // term.  The rank extension stays with fp32 MFMAs: its operands are other adapters' neighbours, and whatever they hold stays out.
 #include <type_traits>
 
-#include "general_common.h"
+#include "general_wgrad.h"
 
 namespace mlora {
 
@@ -59,8 +59,11 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t& p0, uint32_t&
 
 // Tile BT x BT, eight wavefronts: 2 x 2 sub-tiles times the two wavefront groups kg that share the contraction.
 // EDGE: the forward of a layer narrower than the tile.
+// lds: kF32Lds<BT> bytes; wg: the work group's number in the launch.
+template <int BT> constexpr int kF32Ring = (BT == 128 ? 3 : 2) * (BT == 128 ? 1 : 2) * BT * 384;
+template <int BT> constexpr int kF32Lds = kF32Ring<BT> + 2 * BT * 4;
 template <bool FWD, int BT, bool EDGE>
-__global__ __launch_bounds__(FG_THREADS) __attribute__((amdgpu_waves_per_eu(BT == 32 ? 4 : 2))) void f32_gemm_kernel(F32GemmArgs g) {
+__device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned char* const lds, const int64_t wg) {
     constexpr int KU = 32;                                   // contraction of a unit: one 16x16x32 MFMA, 64 bytes of a row of parts
     constexpr int Q = BT == 128 ? 1 : 2;                     // units of a stage
     constexpr int KS = Q * KU;
@@ -74,15 +77,16 @@ __global__ __launch_bounds__(FG_THREADS) __attribute__((amdgpu_waves_per_eu(BT =
     constexpr int MB = BT / 32, NB = BT / 32;                // 16 x 16 blocks of a wavefront
     constexpr int HB = MB > 1 ? MB / 2 : 1;                  // row blocks of a half
     constexpr int NT = 6;                                    // products of parts
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[SLOTS * STAGE];
-    __shared__ uint32_t row_max[BT], col_max[BT];
+    static_assert(SLOTS * STAGE == kF32Ring<BT>, "ring");
+    uint32_t* const row_max = reinterpret_cast<uint32_t*>(lds + SLOTS * STAGE);
+    uint32_t* const col_max = row_max + BT;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
     const int l16 = lane & 15, g4 = lane >> 4;
 
     const int64_t total = (int64_t)g.tiles_m * g.tiles_n;
-    const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, slot_x = wg / 8;
+    const int64_t slot_x = wg / 8;
     const int64_t L = (slot_x / g.xcd_run * 8 + wg % 8) * g.xcd_run + slot_x % g.xcd_run;
     if (L >= total) return;
     const int64_t per_band = (int64_t)8 * g.tiles_n;
@@ -581,16 +585,60 @@ __global__ __launch_bounds__(FG_THREADS) __attribute__((amdgpu_waves_per_eu(BT =
         }
 }
 
-template <bool FWD, int BT, bool EDGE = false>
-void launch(F32GemmArgs a, hipStream_t st) {
+template <bool FWD, int BT, bool EDGE>
+__global__ __launch_bounds__(FG_THREADS) __attribute__((amdgpu_waves_per_eu(BT == 32 ? 4 : 2))) void f32_gemm_kernel(F32GemmArgs g) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kF32Lds<BT>];
+    f32_gemm_body<FWD, BT, EDGE>(g, lds, (int64_t)blockIdx.y * gridDim.x + blockIdx.x);
+}
+
+// The backward product and the weight gradients of a small batch: both need dS alone.  The first `gemm_groups` work groups take the
+// tiles of dX, the others a weight-gradient item each.
+template <int BT, int NB, bool WHOLE>
+__global__ __launch_bounds__(FG_THREADS) __attribute__((amdgpu_waves_per_eu(BT == 32 ? 4 : 2)))
+void f32_bwd_kernel(F32GemmArgs g, GenWgradArgs<float> w, int gemm_groups) {
+    constexpr int BYTES = kF32Lds<BT> > kGenWgradFloats<NB> * 4 ? kF32Lds<BT> : kGenWgradFloats<NB> * 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[BYTES];
+    const int wg = blockIdx.x;
+    if (wg < gemm_groups) {
+        f32_gemm_body<false, BT, false>(g, lds, wg);
+        return;
+    }
+    const int item = wg - gemm_groups, i = item / w.panels % w.pv.N;
+    general_wgrad_body<float, NB, WHOLE>(w, reinterpret_cast<float*>(lds), item % w.panels, i, item / w.panels / w.pv.N);
+}
+
+template <int BT> int64_t set_tiles(F32GemmArgs& a) {        // work groups
     a.tiles_m = (int32_t)((a.M + BT - 1) / BT);
     a.tiles_n = (int32_t)((a.N + BT - 1) / BT);
     const int64_t total = (int64_t)a.tiles_m * a.tiles_n;
     a.xcd_run = total >= 256 ? 32 : (int32_t)((total + 7) / 8);
-    const int64_t per = 8 * a.xcd_run, groups = (total + per - 1) / per * per;
+    const int64_t per = 8 * a.xcd_run;
+    return (total + per - 1) / per * per;
+}
+
+template <bool FWD, int BT, bool EDGE = false>
+void launch(F32GemmArgs a, hipStream_t st) {
+    const int64_t groups = set_tiles<BT>(a);
     constexpr int64_t GX = 1 << 20;      // (a dimension of a launch holds fewer than 2^32 work items)
     hipLaunchKernelGGL((f32_gemm_kernel<FWD, BT, EDGE>), dim3((unsigned)(groups < GX ? groups : GX), (unsigned)((groups + GX - 1) / GX)),
                        dim3(FG_THREADS), 0, st, a);
+}
+
+// Weight gradients beside the product: up to eight rounds of work groups (beyond, equal within 1 %), and not where they need more registers than
+// the two work groups a CU of the 32 x 32 tile leave (ranks above 32).  us a step, apart / together, tokens x k x n (work groups of both in
+// CUs): 4 x 64 tokens, 256 x 256 (0.4) 25.1 / 21.3, 600 x 512 x 512 (2.3) 37.4 / 33.6, 1000 x 300 x 700 (3.3) 46.5 / 42.1, 4000 x 128 x 256 (4)
+// 40.1 / 37.4, 2048 x 2048 x 2048 (3) 278 / 267, 8000 x 512 x 512 (2.5) 104.5 / 101.9; 32 x 32 tiles and ranks of 64, 500 x 1024 x 512 (2.2)
+// 54.9 / 57.7.
+template <int BT>
+bool launch_with_wgrad(F32GemmArgs a, const GenWgradArgs<float>& w, int nb, bool whole, int num_cus, hipStream_t st) {
+    const int64_t groups = set_tiles<BT>(a), items = (int64_t)w.panels * w.pv.N * w.rank_items;
+    if (groups + items > 8 * num_cus || (BT == 32 && nb == 4)) return false;
+    const dim3 grid((unsigned)(groups + items)), block(FG_THREADS);
+    if (!whole)       hipLaunchKernelGGL((f32_bwd_kernel<BT, 1, false>), grid, block, 0, st, a, w, (int)groups);
+    else if (nb == 1) hipLaunchKernelGGL((f32_bwd_kernel<BT, 1, true>), grid, block, 0, st, a, w, (int)groups);
+    else if (nb == 2) hipLaunchKernelGGL((f32_bwd_kernel<BT, 2, true>), grid, block, 0, st, a, w, (int)groups);
+    else if constexpr (BT != 32) hipLaunchKernelGGL((f32_bwd_kernel<BT, 4, true>), grid, block, 0, st, a, w, (int)groups);
+    return true;
 }
 
 // Tile edge for M x N outputs over a contraction of K, the one that the times measured give the least for:
@@ -608,19 +656,22 @@ int tile_edge(int64_t M, int64_t N, int64_t K, int num_cus) {
     return t128 < t64 && t128 < t32 ? 128 : t64 < t32 ? 64 : 32;
 }
 
-template <bool FWD>
-void gemm(mlora_plan* p, const F32GemmArgs& a, hipStream_t st) {
-    const int edge = tile_edge(a.M, a.N, a.K, p->num_cus);
-    if (FWD && a.N < 32)                launch<FWD, 32, true>(a, st);
-    else if (FWD && a.N < edge)         launch<FWD, 32>(a, st);
-    else if (edge == 128)               launch<FWD, 128>(a, st);
-    else if (edge == 64)                launch<FWD, 64>(a, st);
-    else                                launch<FWD, 32>(a, st);
+void forward(const F32GemmArgs& a, int edge, hipStream_t st) {
+    if (a.N < 32)                       launch<true, 32, true>(a, st);
+    else if (edge == 128 && a.N >= 128) launch<true, 128>(a, st);
+    else if (edge == 64 && a.N >= 64)   launch<true, 64>(a, st);
+    else                                launch<true, 32>(a, st);
+}
+void backward(const F32GemmArgs& a, int edge, hipStream_t st) {
+    if (edge == 128)     launch<false, 128>(a, st);
+    else if (edge == 64) launch<false, 64>(a, st);
+    else                 launch<false, 32>(a, st);
 }
 
 }  // namespace
 
-int f32_gemm(mlora_plan* p, bool fwd, const void* A, const void* W, void* C, const void* E, uint32_t flags, hipStream_t st) {
+int f32_gemm(mlora_plan* p, bool fwd, const void* A, const void* W, void* C, const void* E, uint32_t flags, const GenWgradArgs<float>* w, int nb,
+             bool whole, bool* with_w, hipStream_t st) {
     F32GemmArgs a{};
     a.A = (const float*)A; a.W = (const float*)W; a.C = (float*)C; a.E = (const float*)E;
     a.M = p->T; a.K = fwd ? p->k : p->n; a.N = fwd ? p->n : p->k;
@@ -630,8 +681,15 @@ int f32_gemm(mlora_plan* p, bool fwd, const void* A, const void* W, void* C, con
     a.pv = p->view;
     if (a.M == 0 || (!a.base && !a.lora)) return MLORA_OK;
     ProfScope prof(p, fwd ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
-    if (fwd) gemm<true>(p, a, st);
-    else     gemm<false>(p, a, st);
+    const int edge = tile_edge(a.M, a.N, a.K, p->num_cus);
+    if (fwd) {
+        forward(a, edge, st);
+    } else {
+        if (w) *with_w = edge == 128   ? launch_with_wgrad<128>(a, *w, nb, whole, p->num_cus, st)
+                         : edge == 64  ? launch_with_wgrad<64>(a, *w, nb, whole, p->num_cus, st)
+                                       : launch_with_wgrad<32>(a, *w, nb, whole, p->num_cus, st);
+        if (!w || !*with_w) backward(a, edge, st);
+    }
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;
 }

@@ -93,7 +93,4 @@ template <typename T> __device__ __forceinline__ uint4 gather16(const T* p, int6
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// f32_gemm.hip : Y = X W + s_i S_i B_i (fwd) or dX = dY W^T + dS_i A_i^T in fp32, or either term alone
-int f32_gemm(mlora_plan* p, bool fwd, const void* A, const void* W, void* C, const void* E, uint32_t flags, hipStream_t st);
-
 }  // namespace mlora

@@ -49,3 +49,33 @@ def test_backward_of_small_batches(case):
     check(2)
     dl.check_guards()
     dl.plan.destroy()
+
+
+# fp32: k, n, ranks, tokens; 32 x 32, 64 x 64 and 128 x 128 tiles; 16, 32 and 64 ranks per item; panels narrower than 64; more ranks than an item
+F32_CASES = [(64, 96, [5, 16, 0, 3], [40, 1, 9, 0]), (40, 200, [33, 100], [70, 130]), (300, 700, [16, 32], [500, 517]), (700, 512, [64, 17, 128], [400, 16, 300]),
+             (1100, 520, [48], [2100]), (130, 129, [128], [17])]
+
+
+@pytest.mark.parametrize("case", range(len(F32_CASES)))
+def test_fp32_backward_of_small_batches(case):
+    k, n, ranks, lens = F32_CASES[case]
+    w = wl.make_workload(f"beside_f32_{case}", "f32", k, n, ranks, lens, [1.0 + 0.5 * (i % 3) for i in range(len(ranks))], seed=case, b_sigma=0.3)
+    print(f"[case] fp32 side by side k={k} n={n} ranks={ranks} tokens={lens}", flush=True)
+    dl = DeviceLayer(w)
+    fw, bw = orc.forward(w.X, w.W, w.A, w.B, w.scales, w.offsets), orc.backward(w.dY, w.X, w.W, w.A, w.B, w.scales, w.offsets)
+    dl.forward(); dl.backward(); dl.sync()
+    for got, want in ((dl.Y, fw.Y), (dl.dX, bw.dX)):
+        assert rel_fro(to_host(got), want) <= 1e-5 and row_rel_max(to_host(got), want) <= 4e-5
+    for i in range(w.N):
+        assert rel_fro(to_host(dl.dA[i]), bw.dA[i]) <= 1e-5 and rel_fro(to_host(dl.dB[i]), bw.dB[i]) <= 1e-5
+        if w.ranks[i] and w.seg_lens[i]:
+            assert rel_fro(dl.S_list()[i], fw.S[i]) <= 1e-5 and rel_fro(dl.dS_list()[i], bw.dS[i]) <= 1e-5
+    once = [t.clone() for t in dl.dA + dl.dB]
+    dl.backward(ml.FLAG_BASE_ONLY); dl.backward(ml.FLAG_LORA_ONLY); dl.sync()
+    for a, b in zip(once, dl.dA + dl.dB):
+        assert torch.equal(a, b)
+    dl.backward(ml.FLAG_ACCUM_GRADS); dl.sync()
+    for i in range(w.N):
+        assert rel_fro(to_host(dl.dA[i]), 2 * bw.dA[i]) <= 1e-5 and rel_fro(to_host(dl.dB[i]), 2 * bw.dB[i]) <= 1e-5
+    dl.check_guards()
+    dl.plan.destroy()
