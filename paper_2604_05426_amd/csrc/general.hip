@@ -23,7 +23,7 @@ namespace mlora {
 namespace {
 
 // ---- shrink ------------------------------------------------------------------------------------------------------------------
-// Work group = 16 rows of one adapter x all its ranks; its eight wavefronts deal the contraction among themselves two neighbouring pieces at
+// Work group = 16 rows of one adapter x 16 NB of its ranks (see `shrink`); its eight wavefronts deal the contraction among themselves two neighbouring pieces at
 // a time (whole 128-byte lines of a row), straight from memory into MFMA operands (X / dY rows are read once; the adapter matrix
 // comes from the caches), with the operands of the next load in flight.  In fp32 a wavefront's pairs of pieces take turns on two accumulator
 // sets (less rounding error than one chain) and a contraction of up to eight pieces is dealt singly; the wavefronts' sums are added in
@@ -31,6 +31,7 @@ namespace {
 template <typename T> struct GenShrinkArgs {
     const T* src; int64_t ld;     // X (ld k) or dY (ld n); the contraction has ld elements
     T* out;                       // ragged S or dS
+    int32_t rank_items;           // work groups along the ranks, 16 NB each
     PlanView pv;
 };
 
@@ -41,18 +42,19 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
     __shared__ float red[NW * 16 * RLD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g4 = lane >> 4;
-    const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, wg = item / g.rank_items;
     if (wg >= (int64_t)g.pv.n_row_blocks * 4) return;
     const Entry4 e = g.pv.row_blocks[wg >> 2];
     const int sub = (wg & 3) * 16, rows = min(16, e.d - sub);
     if (rows <= 0) return;
     const int i = e.a, row0 = e.c + sub;
-    const int r = g.pv.rank[i];
+    const int r = g.pv.rank[i], rho0 = (int)(item % g.rank_items) * (16 * NB), rl = min(r - rho0, 16 * NB);      // this work group's ranks
+    if (rl <= 0) return;
     const float s = FWD ? 1.0f : g.pv.scale[i];
-    const T* F = global_ptr<const T>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B);
+    const T* F = global_ptr<const T>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B) + (FWD ? (int64_t)rho0 : rho0 * g.ld);
     const int K = (int)g.ld;
     const T* xrow = g.src + (int64_t)(row0 + min(l16, rows - 1)) * g.ld;    // rows past the block repeat its last one: not stored
-    // Ranks of block b: 16 b + l16, or, where four blocks share one 64-rank row piece of A_i, quad(b / 4) + b % 4: four adjacent
+    // Ranks of block b, from rho0 on: 16 b + l16, or, where four blocks share one 64-rank row piece of A_i, quad(b / 4) + b % 4: four adjacent
     // ranks per lane.  The lane that would cross r_i takes the last four ranks instead (what it repeats comes out the same, bit for
     // bit, from the lane before), so that any rank from 4 on is read in whole quads.
     constexpr bool QUAD = FWD && NB >= 4;
@@ -70,8 +72,8 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
     quad_t<T> fq[2][U][NQ][kQuadRows<T>];
     // Ranks past r_i repeat valid ones (their sums are not stored); only the end of the contraction has to read as zero, in both
     // operands.  The plain loads of a whole unit stand in one branch: a condition per load would make each wait for itself.
-    const bool quads = r >= 4;
-    auto quad = [&](int q) { return min(64 * q + 4 * l16, r - 4); };
+    const bool quads = rl >= 4;
+    auto quad = [&](int q) { return min(64 * q + 4 * l16, rl - 4); };
     auto load = [&](int unit, int set) {
         const int k0 = unit * U * kBlockK<T> + g4 * kEpc<T>;
         if ((unit + 1) * U * kBlockK<T> <= K && (quads || !QUAD)) {     // uniform over the wavefront
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
                 } else {
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
-                        const int rho = min(16 * b + l16, r - 1);
+                        const int rho = min(16 * b + l16, rl - 1);
                         if constexpr (FWD) {
                             T* o = reinterpret_cast<T*>(&fb[set][u][b]);
 #pragma unroll
@@ -107,17 +109,17 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
                 if constexpr (QUAD) {
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
-                        const int rho = quads ? quad(q) : min(4 * l16, r - 1);
+                        const int rho = quads ? quad(q) : min(4 * l16, rl - 1);
 #pragma unroll
                         for (int e = 0; e < kQuadRows<T>; ++e) {
                             fq[set][u][q][e] = (quad_t<T>)(0u);
-                            if (e < valid) fq[set][u][q][e] = load_quad<T>(F + (int64_t)(k + e) * r + rho, quads, r - rho);
+                            if (e < valid) fq[set][u][q][e] = load_quad<T>(F + (int64_t)(k + e) * r + rho, quads, rl - rho);
                         }
                     }
                 } else {
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
-                        const int rho = min(16 * b + l16, r - 1);
+                        const int rho = min(16 * b + l16, rl - 1);
                         if (FWD) fb[set][u][b] = gather16<T>(F + (int64_t)k * r + rho, r, valid);
                         else     fb[set][u][b] = load16<T>(F + (int64_t)rho * g.ld + k, valid);
                     }
@@ -129,9 +131,9 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             if constexpr (QUAD) {
-                if (64 * (b / 4) < r) to[b] = block_mma<T>(xa[set][u], quad_column<T>(fq[set][u][b / 4], b % 4), to[b]);
+                if (64 * (b / 4) < rl) to[b] = block_mma<T>(xa[set][u], quad_column<T>(fq[set][u][b / 4], b % 4), to[b]);
             } else {
-                if (16 * b < r) to[b] = block_mma<T>(xa[set][u], fb[set][u][b], to[b]);
+                if (16 * b < rl) to[b] = block_mma<T>(xa[set][u], fb[set][u][b], to[b]);
             }
         }
     };
@@ -186,16 +188,16 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int rho = !QUAD ? 16 * b + l16 : quads ? quad(b / 4) + b % 4 : 4 * l16 + b;
-            if (!QUAD || (64 * (b / 4) < r && rho < r)) red[(wave * 16 + 4 * g4 + q) * RLD + rho] = acc[b][q];
+            if (!QUAD || (64 * (b / 4) < rl && rho < rl)) red[(wave * 16 + 4 * g4 + q) * RLD + rho] = acc[b][q];
         }
     __syncthreads();
-    T* out = g.out + g.pv.soff[i] + (int64_t)(row0 - g.pv.off[i]) * r;
-    for (int idx = tid; idx < rows * r; idx += 64 * NW) {
-        const int row = idx / r, col = idx - row * r;
+    T* out = g.out + g.pv.soff[i] + (int64_t)(row0 - g.pv.off[i]) * r + rho0;
+    for (int idx = tid; idx < rows * rl; idx += 64 * NW) {
+        const int row = idx / rl, col = idx - row * rl;
         float v = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) v += red[(w * 16 + row) * RLD + col];
-        out[idx] = from_f32<T>(s * v);
+        out[(int64_t)row * r + col] = from_f32<T>(s * v);
     }
 }
 
@@ -512,10 +514,20 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     GenShrinkArgs<T> a{};
     a.src = (const T*)src; a.ld = FWD ? p->k : p->n; a.out = (T*)out; a.pv = p->view;
     ProfScope prof(p, FWD ? MLORA_K_SHRINK : MLORA_K_DSHRINK, st);
-    const dim3 grid = two_dims((int64_t)p->n_row_blocks * 4);
-    if (p->max_rank <= 16)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1>), grid, dim3(512), 0, st, a);
-    else if (p->max_rank <= 64) hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 4>), grid, dim3(512), 0, st, a);
-    else                        hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 8>), grid, dim3(512), 0, st, a);
+    const int64_t groups = (int64_t)p->n_row_blocks * 4;
+    // Ranks per work group: 16, 64 or all.  With all of them a few row blocks of wide ranks kept a few CUs busy with the whole adapter matrix
+    // each; with 16 the rows are read once per 16 ranks (from the caches).  us, all / 64 / 16, work groups in CUs with 16 (64) ranks each:
+    // fp32 333 tokens, contraction 4000, rank 128 (0.7) 68.6 / - / 18.5; 100, 3000, rank 100 (0.9) 42.8 / - / 12.9; 2048, 2048, ranks to 64 (2.3)
+    // - / 23.7 / 19.0; 4000, 1000, ranks to 100 (6.9) 27.8 / 27.4 / 16.1; 8000, 2000, rank 128 (15.8; 3.9) 59 / 66 / 96; bf16 1500, 2048, ranks to 33
+    // (1.2) - / 13.0 / 8.4; 2000, 4095, ranks to 100 (3.5; 1) 99 / 66 / 100; 6000, 1001, rank 64 (6) - / 25.1 / 28.4.
+    auto items = [&](int nb) { return (p->max_rank + 16 * nb - 1) / (16 * nb); };
+    const int lim = (sizeof(T) == 4 ? 8 : 2) * p->num_cus;
+    const int nb = p->max_rank <= 16 || groups * items(1) <= lim ? 1 : p->max_rank <= 64 || groups * items(4) <= 2 * p->num_cus ? 4 : 8;
+    a.rank_items = items(nb);
+    const dim3 grid = two_dims(groups * a.rank_items);
+    if (nb == 1)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1>), grid, dim3(512), 0, st, a);
+    else if (nb == 4) hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 4>), grid, dim3(512), 0, st, a);
+    else              hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 8>), grid, dim3(512), 0, st, a);
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;
 }
