@@ -15,7 +15,7 @@
 // of S, Y, dS and dX have the same bits whatever its neighbours' tokens and ranks are.
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
-// tokens, 256 x 256: 171 -> 24 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 264 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 83 us.
+// tokens, 256 x 256: 171 -> 21 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 258 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 67 us.
 #include "general_wgrad.h"
 
 namespace mlora {
@@ -221,8 +221,9 @@ struct GenGemmArgs {
 // Forward: B operand (W, B_i) has its columns contiguous; backward (W, A_i transposed): its contraction.
 // Order of the sum, in both tiles and both loops below (the tile follows from the number of tokens, and a row's bits must not): one chain of
 // MFMAs over groups of 32 elements that start at multiples of that, zero-filled at the end, in ascending order, then each adapter's term.
+template <bool FWD, int KC> constexpr int kGenGemmLds = 2 * KC * (KC == 1 ? 64 : 32) * (144 + (FWD ? 128 : 144));      // bytes of LDS
 template <bool FWD, int KC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3 : 2))) void general_gemm_kernel(GenGemmArgs g) {
+__device__ __forceinline__ void general_gemm_body(const GenGemmArgs& g, unsigned char* const lds, const uint32_t wg) {
     typedef u16 T;
     constexpr int BT = KC == 1 ? 64 : 32;                    // tile edge
     constexpr int NB = BT / 32;                              // blocks of a wavefront, each way
@@ -235,13 +236,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
     constexpr int NC_PITCH = BT * 2;
     constexpr int B_TILE = FWD ? KT * NC_PITCH : A_TILE;
     constexpr int STAGE = A_TILE + B_TILE;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE];
+    static_assert(2 * STAGE == kGenGemmLds<FWD, KC>);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l16 = lane & 15, g4 = lane >> 4;
     // The last tile of rows / columns starts early enough to be whole (its loads then need no conditions); what it shares with
     // the tile before is not stored.
-    const int64_t m_own = (int64_t)(blockIdx.x / g.tiles_n) * BT, n_own = (int64_t)(blockIdx.x % g.tiles_n) * BT;
+    const int64_t m_own = (int64_t)(wg / g.tiles_n) * BT, n_own = (int64_t)(wg % g.tiles_n) * BT;
     const int64_t m0 = max((int64_t)0, min(m_own, g.M - BT)), n0 = max((int64_t)0, min(n_own, g.N - BT));
     auto unit = [](int k, int u) {      // swizzled 32-byte unit of a bf16 W row
         return BT == 64 ? u ^ (((k >> 1) & 1) | (((k >> 3) & 1) << 1)) : u ^ ((k >> 3) & 1);
@@ -495,6 +496,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3
         }
 }
 
+template <bool FWD, int KC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3 : 2))) void general_gemm_kernel(GenGemmArgs g) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kGenGemmLds<FWD, KC>];
+    general_gemm_body<FWD, KC>(g, lds, blockIdx.x);
+}
+
+// The backward product and the weight gradients of a small batch: both need dS alone.  The first `gemm_groups` work groups take the
+// tiles of dX, the others a weight-gradient item of 16 ranks each (32 would leave the product fewer work groups a CU).
+template <int KC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3 : 2)))
+void general_bwd_kernel(GenGemmArgs g, GenWgradArgs<u16> w, uint32_t gemm_groups) {
+    static_assert(kGenWgradFloats<1> * 4 <= kGenGemmLds<false, KC>);
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kGenGemmLds<false, KC>];
+    const uint32_t wg = blockIdx.x;
+    if (wg < gemm_groups) {
+        general_gemm_body<false, KC>(g, lds, wg);
+        return;
+    }
+    const int item = (int)(wg - gemm_groups), i = item / w.panels % w.pv.N;
+    general_wgrad_body<u16, 1, true, 4>(w, reinterpret_cast<float*>(lds), item % w.panels, i, item / w.panels / w.pv.N);
+}
+
 // ---- weight gradients --------------------------------------------------------------------------------------------------------------
 template <typename T, int NB, bool WHOLE>
 __global__ __launch_bounds__(512) void general_wgrad_kernel(GenWgradArgs<T> g) {
@@ -532,8 +555,23 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     return MLORA_OK;
 }
 
+// Whether the weight gradients go with the backward product (one launch less).  A work group of four wavefronts takes twice as long for an item as
+// the eight of a launch of its own, so the longest adapter decides: its tokens times the work groups of both in CUs, or a contraction of
+// the product twice its tokens.  us a step, apart / together, tokens x k x n (longest adapter, work groups of both in CUs): 1500 x 2048 x 1001
+// (about 400, 6.4) 74.2 / 67.3, 256 x 257 x 256 (100, 0.4) 27.8 / 24.1, 1024 x 1001 x 3000 (60, 8.9) 79 / 70.6, 6000 x 1001 x 2048 (1000, 7.4) 154.5 /
+// 149.7, 6000 x 300 x 777 (1000, 2.7) 77.3 / 74.0, 2000 x 100 x 333 (2000, 1.0) 35.9 / 30.6; not: 2000 x 1001 x 300 (2000, 2.1) 45.9 / 46.9,
+// 6000 x 1001 x 300 (1000, 6.9) 73.1 / 77.4, 6000 x 100 x 333 (3000, 1.0) 56.0 / 60.1, 8000 x 1001 x 300 (4000, 8.5) 98.9 / 120.5.
+bool beside_product(const mlora_plan* p, const GenWgradArgs<u16>& w, int64_t groups, int64_t K) {
+    int64_t longest = 0;
+    for (int32_t i = 0; i < p->N; ++i)
+        if (p->ranks[i] > 0) longest = std::max(longest, p->off[i + 1] - p->off[i]);
+    const int64_t all = groups + (int64_t)w.panels * p->N * ((p->max_rank + 15) / 16);
+    return all <= 10 * p->num_cus && longest <= 2000 && (longest * all <= 4000 * p->num_cus || 2 * longest <= K);
+}
+
 template <bool FWD>
-int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, uint32_t flags, hipStream_t st) {
+int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, uint32_t flags, const GenWgradArgs<u16>* w, bool* with_w,
+         hipStream_t st) {
     GenGemmArgs a{};
     a.A = (const u16*)A; a.W = (const u16*)W; a.C = (u16*)C; a.E = (const u16*)E;
     a.M = p->T; a.K = FWD ? p->k : p->n; a.N = FWD ? p->n : p->k;
@@ -549,8 +587,21 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
     // (700 x 1001, 1001) 23 / 15.  The results are the same bit for bit.
     const bool split = tiles(64) <= p->num_cus / 2;
     a.tiles_n = (a.N + (split ? 31 : 63)) / (split ? 32 : 64);
-    if (split) hipLaunchKernelGGL((general_gemm_kernel<FWD, 4>), dim3((unsigned)tiles(32)), dim3(256), 0, st, a);
-    else       hipLaunchKernelGGL((general_gemm_kernel<FWD, 1>), dim3((unsigned)tiles(64)), dim3(256), 0, st, a);
+    const int64_t groups = tiles(split ? 32 : 64);
+    if constexpr (!FWD) {
+        if (w && beside_product(p, *w, groups, a.K)) {
+            GenWgradArgs<u16> b = *w;
+            b.rank_items = (uint32_t)((p->max_rank + 15) / 16);
+            const dim3 grid((unsigned)(groups + (int64_t)b.panels * p->N * b.rank_items));
+            if (split) hipLaunchKernelGGL((general_bwd_kernel<4>), grid, dim3(256), 0, st, a, b, (uint32_t)groups);
+            else       hipLaunchKernelGGL((general_bwd_kernel<1>), grid, dim3(256), 0, st, a, b, (uint32_t)groups);
+            *with_w = true;
+            MLORA_HIP_TRY(hipGetLastError());
+            return MLORA_OK;
+        }
+    }
+    if (split) hipLaunchKernelGGL((general_gemm_kernel<FWD, 4>), dim3((unsigned)groups), dim3(256), 0, st, a);
+    else       hipLaunchKernelGGL((general_gemm_kernel<FWD, 1>), dim3((unsigned)groups), dim3(256), 0, st, a);
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;
 }
@@ -594,7 +645,7 @@ int fwd_t(mlora_plan* p, const void* X, const void* W, void* Y, void* S, uint32_
         if (rc != MLORA_OK) return rc;
     }
     if constexpr (sizeof(T) == 4) return f32_gemm(p, true, X, W, Y, S, flags, nullptr, 0, false, nullptr, st);
-    else                          return gemm<true>(p, X, W, Y, S, flags, st);
+    else                          return gemm<true>(p, X, W, Y, S, flags, nullptr, nullptr, st);
 }
 
 template <typename T>
@@ -605,7 +656,7 @@ int bwd_t(mlora_plan* p, const void* dY, const void* X, const void* W, const voi
     const GenWgrad<T> w = wgrad_of<T>(p, dY, X, S, dS, flags);
     bool joined = false;
     if constexpr (sizeof(T) == 4) rc = f32_gemm(p, false, dY, W, dX, dS, flags, grads ? &w.args : nullptr, w.nb, w.whole, &joined, st);
-    else                          rc = gemm<false>(p, dY, W, dX, dS, flags, st);
+    else                          rc = gemm<false>(p, dY, W, dX, dS, flags, grads && w.whole ? &w.args : nullptr, &joined, st);
     if (rc != MLORA_OK || !grads || joined) return rc;
     return launch_wgrad<T>(p, w, st);
 }

@@ -19,9 +19,10 @@ template <typename T> struct GenWgradArgs {
     PlanView pv;
 };
 
-// WHOLE: k and n are at least 64, so that every panel can be whole.  red: kGenWgradFloats<NB> floats of LDS.
+// WHOLE: k and n are at least 64, so that every panel can be whole.  red: kGenWgradFloats<NB> floats of LDS.  NW: wavefronts of the work group, 8,
+// or 4 that each do the part of two, one after the other (the same sums in the same order).
 template <int NB> constexpr int kGenWgradFloats = 4 * 64 * (16 * NB + 1);
-template <typename T, int NB, bool WHOLE>
+template <typename T, int NB, bool WHOLE, int NW = 8>
 __device__ __forceinline__ void general_wgrad_body(const GenWgradArgs<T>& g, float* const red, const int panel, const int i, const int rank_item) {
     constexpr int RW = 16 * NB, RLD = RW + 1;
     constexpr int PT = kBlockK<T>;                       // tokens per piece
@@ -85,69 +86,77 @@ __device__ __forceinline__ void general_wgrad_body(const GenWgradArgs<T>& g, flo
     // Wavefront w takes the pieces w, w + 8, ...  Whole ones are loaded without conditions, D ahead (past the last one it is loaded again): with a
     // condition per load, even one that always holds, the loop waited for all its loads in every turn.  us before / now, two adapters:
     // bf16 8000 tokens x (300 + 777) 42 / 30, 3000 x (1001 + 2048) 18 / 13; fp32 8000 x (128 + 128) 37 / 30, 3000 x (512 + 512) 17 / 14.
-    const int whole = rows / PT, mine = whole > wave ? (whole - wave + 7) / 8 : 0;
-    const bool rest = rows % PT != 0 && whole % 8 == wave;
-    if (rest) {                                          // what is left of the tokens, zero-filled; multiplied last
-#pragma unroll
-        for (int e = 0; e < TPL; ++e) {
-            const int t = whole * PT + T0 + TE * e, tc = min(t, rows - 1);
-            const quad_t<T> v = load_quad<T>(big + (int64_t)tc * width, WHOLE, cols);
-            wide[D][e] = t < rows ? v : (quad_t<T>)(0u);
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const T n = small[(int64_t)tc * r + rho[b]];
-                narrow[D][e][b] = t < rows ? n : (T)0;
-            }
-        }
-    }
-    if (mine > 0) {
-        const T* pw = big + (int64_t)(wave * PT + T0) * width;
-        const T* pn = small + (int64_t)(wave * PT + T0) * r;
-        int next = 0;
-        auto load = [&](int set) __attribute__((always_inline)) {
+    const int whole = rows / PT;
+#pragma nounroll
+    for (int part = 0; part < 8 / NW; ++part) {
+        const int w8 = wave + NW * part;                     // of eight
+        const int mine = whole > w8 ? (whole - w8 + 7) / 8 : 0;
+        const bool rest = rows % PT != 0 && whole % 8 == w8;
+        if (rest) {                                          // what is left of the tokens, zero-filled; multiplied last
 #pragma unroll
             for (int e = 0; e < TPL; ++e) {
-                wide[set][e] = load_quad<T>(pw + (int64_t)(TE * e) * width, WHOLE, cols);
+                const int t = whole * PT + T0 + TE * e, tc = min(t, rows - 1);
+                const quad_t<T> v = load_quad<T>(big + (int64_t)tc * width, WHOLE, cols);
+                wide[D][e] = t < rows ? v : (quad_t<T>)(0u);
 #pragma unroll
-                for (int b = 0; b < NB; ++b) narrow[set][e][b] = pn[(int64_t)(TE * e) * r + rho[b]];
+                for (int b = 0; b < NB; ++b) {
+                    const T n = small[(int64_t)tc * r + rho[b]];
+                    narrow[D][e][b] = t < rows ? n : (T)0;
+                }
             }
-            const bool more = ++next < mine;
-            pw += more ? (int64_t)(8 * PT) * width : 0;
-            pn += more ? (int64_t)(8 * PT) * r : 0;
-        };
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-            if (d < mine) load(d);                       // (uniform)
-        int p = 0;
-        for (; p + D <= mine; p += D) {
-#pragma unroll
-            for (int d = 0; d < D; ++d) { compute(d); load(d); }
         }
+        if (mine > 0) {
+            const T* pw = big + (int64_t)(w8 * PT + T0) * width;
+            const T* pn = small + (int64_t)(w8 * PT + T0) * r;
+            int next = 0;
+            auto load = [&](int set) __attribute__((always_inline)) {
 #pragma unroll
-        for (int d = 0; d + 1 < D; ++d)
-            if (p + d < mine) compute(d);
-    }
-    if (rest) compute(D);
+                for (int e = 0; e < TPL; ++e) {
+                    wide[set][e] = load_quad<T>(pw + (int64_t)(TE * e) * width, WHOLE, cols);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) narrow[set][e][b] = pn[(int64_t)(TE * e) * r + rho[b]];
+                }
+                const bool more = ++next < mine;
+                pw += more ? (int64_t)(8 * PT) * width : 0;
+                pn += more ? (int64_t)(8 * PT) * r : 0;
+            };
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+                if (d < mine) load(d);                       // (uniform)
+            int p = 0;
+            for (; p + D <= mine; p += D) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) { compute(d); load(d); }
+            }
+#pragma unroll
+            for (int d = 0; d + 1 < D; ++d)
+                if (p + d < mine) compute(d);
+        }
+        if (rest) compute(D);
 
-    // wavefronts 0 .. 3 write, 4 .. 7 add theirs; the four sums are added in order.  Lane (l16, g4) holds rank 16 b + l16 of the
-    // columns 4 (4 g4 + q) + x.
-    for (int half = 0; half < 2; ++half) {
-        if (wave >> 2 == half) {
+        // wavefronts 0 .. 3 of the eight write, 4 .. 7 add theirs; the four sums are added in order.  Lane (l16, g4) holds rank 16 b + l16 of
+        // the columns 4 (4 g4 + q) + x.
+        for (int half = 0; half < 2; ++half) {
+            if (w8 >> 2 == half) {
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
+                for (int x = 0; x < 4; ++x)
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
+                    for (int b = 0; b < NB; ++b) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float* d = red + ((wave & 3) * 64 + 16 * g4 + 4 * q + x) * RLD + 16 * b + l16;
-                        *d = half ? *d + acc[x][b][q] : acc[x][b][q];
+                        for (int q = 0; q < 4; ++q) {
+                            float* d = red + ((wave & 3) * 64 + 16 * g4 + 4 * q + x) * RLD + 16 * b + l16;
+                            *d = half ? *d + acc[x][b][q] : acc[x][b][q];
+                        }
+                        if constexpr (NW == 4) acc[x][b] = f32x4{0.f, 0.f, 0.f, 0.f};
                     }
+            }
+            if (NW == 8) __syncthreads();
         }
-        __syncthreads();
     }
+    if (NW == 4) __syncthreads();
     const float s = isA ? 1.0f : g.pv.scale[i];
     T* out = global_ptr<T>(isA ? g.pv.ptrs[i].dA : g.pv.ptrs[i].dB);
-    for (int idx = tid; idx < 64 * RW; idx += 512) {
+    for (int idx = tid; idx < 64 * RW; idx += 64 * NW) {
         // consecutive threads, consecutive elements of the output: ranks of a dA_i row, columns of a dB_i row
         const int c = isA ? idx / RW : idx % 64, rho = isA ? idx % RW : idx / 64;
         if (col0 + c < col_own || col0 + c >= width || rho0 + rho >= r) continue;

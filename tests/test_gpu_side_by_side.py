@@ -79,3 +79,42 @@ def test_fp32_backward_of_small_batches(case):
         assert rel_fro(to_host(dl.dA[i]), 2 * bw.dA[i]) <= 1e-5 and rel_fro(to_host(dl.dB[i]), 2 * bw.dB[i]) <= 1e-5
     dl.check_guards()
     dl.plan.destroy()
+
+
+# bf16 rows that start at any element: k, n, ranks, tokens; 32 x 32 and 64 x 64 tiles, one and several rank items, panels with a remainder
+ODD_CASES = [(65, 129, [5, 16, 0, 3], [40, 1, 9, 0]), (300, 77, [33, 100], [70, 257]), (2048, 1001, [4, 7, 33], [310, 500, 96]), (1001, 515, [16], [1100]),
+             (100, 333, [64, 8], [1999, 31])]
+
+
+@pytest.mark.parametrize("case", range(len(ODD_CASES)))
+def test_odd_width_backward_of_small_batches(case):
+    """Against the oracle, and the same bits as with a neighbour whose tokens are too many for the one launch."""
+    k, n, ranks, lens = ODD_CASES[case]
+    ranks, lens = ranks + [8], lens + [2100]
+    big = wl.make_workload(f"beside_odd_{case}", "bf16", k, n, ranks, lens, [1.0 + 0.5 * (i % 3) for i in range(len(ranks))], seed=case, b_sigma=0.3)
+    print(f"[case] odd widths side by side k={k} n={n} ranks={ranks} tokens={lens}", flush=True)
+    N, T = big.N - 1, big.offsets[-2]
+    w = wl.Workload(name="part", dtype="bf16", T=T, k=k, n=n, ranks=ranks[:N], scales=big.scales[:N], offsets=big.offsets[:-1], X=big.X[:T], W=big.W,
+                    A=big.A[:N], B=big.B[:N], dY=big.dY[:T])
+    dl, db = DeviceLayer(w), DeviceLayer(big)
+    for d in (dl, db):
+        d.forward(); d.backward(); d.sync()
+    bw = orc.backward(w.dY, w.X, w.W, w.A, w.B, w.scales, w.offsets)
+    # bf16: tolerances of the parity tests, as above
+    assert rel_fro(to_host(dl.dX), bw.dX) <= 1e-2 and row_rel_max(to_host(dl.dX), bw.dX) <= 4e-2
+    assert torch.equal(dl.dX.view(torch.int16), db.dX[:T].view(torch.int16))
+
+    def check(times):
+        for i in range(N):
+            if w.ranks[i]:
+                assert rel_fro(to_host(dl.dA[i]), times * bw.dA[i]) <= 1e-2 and rel_fro(to_host(dl.dB[i]), times * bw.dB[i]) <= 1e-2
+                for a, b in ((dl.dA[i], db.dA[i]), (dl.dB[i], db.dB[i])):
+                    assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+    check(1)
+    for d in (dl, db):
+        d.backward(ml.FLAG_ACCUM_GRADS); d.sync()
+    check(2)
+    for d in (dl, db):
+        d.check_guards()
+        d.plan.destroy()
