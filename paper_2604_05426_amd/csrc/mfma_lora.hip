@@ -269,6 +269,8 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     constexpr int FT = RB16 * 2048;                 // adapter tile bytes
     constexpr int STAGE = ST_XT + FT;
     constexpr int NST = ROWS == 128 ? 5 : RB16 == 8 ? 6 : 9;   // ring stages (144 KB; 160 KB with 128-row blocks)
+    constexpr bool PAIRS = ROWS == 64;              // two steps per barrier (128-row blocks: too few stages)
+    constexpr int AHEAD = PAIRS ? NST - 2 : NST - 1;            // steps loaded ahead of the one that is waited for
     constexpr int NX = ROWS / 64;                   // X-tile loads per wavefront per step
     constexpr int NF = RB16 / 4;                    // adapter-tile loads per wavefront per step
     constexpr int NCB = ROWS == 128 ? RB16 : RB16 / 2;   // rank blocks per wavefront
@@ -332,33 +334,56 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     f32x4 acc[NCB];
     const int xrow = 16 * rb + l16;
     const int vq = fkey(8 * g4 + (l16 >> 2));      // key of the A_i tile rows this lane reads (rows +4, +32 share it)
-    auto compute = [&](int slot) {
-        const unsigned char* Xs = lds + slot * STAGE;
-        const unsigned char* Fs = Xs + ST_XT;
+    // the products of the steps in `STEPS` neighbouring slots: all their fragments are read before the first one
+    auto compute = [&](auto count, int slot) {
+        constexpr int STEPS = decltype(count)::value;
+        bf16x8 a[STEPS][2], b[STEPS][2][NCB];
 #pragma unroll
-        for (int k32 = 0; k32 < 2; ++k32) {
-            const bf16x8 a = lds_read_frag(reinterpret_cast<const u16*>(Xs + xrow * 128 + (((k32 * 4 + g4) ^ (l16 & 7)) << 4)));
+        for (int u = 0; u < STEPS; ++u) {
+            const unsigned char* Xs = lds + (slot + u >= NST ? slot + u - NST : slot + u) * STAGE;
+            const unsigned char* Fs = Xs + ST_XT;
 #pragma unroll
-            for (int j = 0; j < NCB; ++j) {
-                const int cb = ch * NCB + j;
-                bf16x8 b;      // (also of blocks past r_i: a condition per block makes every LDS read a wait of its own)
-                if (DENSE) {   // rows of 2 r bytes, unswizzled; a lane past r_i reads ranks 0..3 again (output not stored)
-                    const int rk = 16 * cb + (l16 & 3) * 4;
-                    const unsigned char* p = Fs + (k32 * 32 + 8 * g4 + (l16 >> 2)) * (2 * r) + (rk < r ? rk * 2 : 0);
-                    b = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 8 * r));
-                } else if (FWD) {
-                    const unsigned char* p = Fs + (k32 * 32 + 8 * g4 + (l16 >> 2)) * FROW + ((cb ^ vq) << 5) + (l16 & 3) * 8;
-                    b = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * FROW));
-                } else {
-                    const int rho = 16 * cb + l16;
-                    b = lds_read_frag(reinterpret_cast<const u16*>(Fs + rho * 128 + (((k32 * 4 + g4) ^ (l16 & 7)) << 4)));
+            for (int k32 = 0; k32 < 2; ++k32) {
+                a[u][k32] = lds_read_frag(reinterpret_cast<const u16*>(Xs + xrow * 128 + (((k32 * 4 + g4) ^ (l16 & 7)) << 4)));
+#pragma unroll
+                for (int j = 0; j < NCB; ++j) {
+                    const int cb = ch * NCB + j;
+                    // (also of blocks past r_i: a condition per block makes every LDS read a wait of its own)
+                    if (DENSE) {   // rows of 2 r bytes, unswizzled; a lane past r_i reads ranks 0..3 again (output not stored)
+                        const int rk = 16 * cb + (l16 & 3) * 4;
+                        const unsigned char* p = Fs + (k32 * 32 + 8 * g4 + (l16 >> 2)) * (2 * r) + (rk < r ? rk * 2 : 0);
+                        b[u][k32][j] = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 8 * r));
+                    } else if (FWD) {
+                        const unsigned char* p = Fs + (k32 * 32 + 8 * g4 + (l16 >> 2)) * FROW + ((cb ^ vq) << 5) + (l16 & 3) * 8;
+                        b[u][k32][j] = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * FROW));
+                    } else {
+                        const int rho = 16 * cb + l16;
+                        b[u][k32][j] = lds_read_frag(reinterpret_cast<const u16*>(Fs + rho * 128 + (((k32 * 4 + g4) ^ (l16 & 7)) << 4)));
+                    }
                 }
-                acc[j] = mfma16(a, b, acc[j]);
             }
         }
+#pragma unroll
+        for (int u = 0; u < STEPS; ++u)
+#pragma unroll
+            for (int k32 = 0; k32 < 2; ++k32)
+#pragma unroll
+                for (int j = 0; j < NCB; ++j) acc[j] = mfma16(a[u][k32], b[u][k32][j], acc[j]);
+    };
+    // Two steps per barrier: 64-row forward blocks of ranks 4, 12, 36 27.2 -> 24.5 us (8192 tokens, k = 4096), 32 adapters x 256 tokens, k = 2048
+    // 16.9 -> 16.5; what is left of a step is the load path: with every load a cache hit it still takes 0.2 of 0.28 us.
+    // Wait until the next STEPS steps have landed (only the loads of the later ones may be in flight) and every wavefront is past the steps
+    // before, whose slots the next loads overwrite; load as many steps and multiply.
+    auto advance = [&](auto count, int& slot) {
+        constexpr int STEPS = decltype(count)::value;
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NX + NF) * (AHEAD - STEPS)) : "memory");
+#pragma unroll
+        for (int u = 0; u < STEPS; ++u) issue();
+        compute(count, slot);
+        slot = slot + STEPS >= NST ? slot + STEPS - NST : slot + STEPS;
     };
 
-    for (int t = 0; t < NST - 1; ++t) issue();
+    for (int t = 0; t < AHEAD; ++t) issue();
     int slot = 0;
     // Piece by piece; sum[l] collects two sums of 2^l pieces.  All start at zero and none can become -0, so adding to zero is exact: a
     // level that this work group does not have, whose loop runs once, passes its child's sum on as it is.  (A binary counter with a
@@ -382,16 +407,12 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
             for (int a = 0; a < (pieces >= 2 ? 2 : 1); ++a) {
                 clear(acc);
                 const int end = piece_end(++piece) - step0;
-                do {
-                    // step t has landed (only the loads of the NST - 2 later steps may be in flight) and every wavefront is past
-                    // step t-1, whose slot the next load overwrites
-                    if (RB16 == 8) asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::: "memory");
-                    else           asm volatile("s_waitcnt vmcnt(14)\n\ts_barrier" ::: "memory");
-                    static_assert((NX + NF) * (NST - 2) == (RB16 == 8 ? 12 : 14), "wait count = loads of the steps that may still be in flight");
-                    issue();
-                    compute(slot);
-                    slot = slot == NST - 1 ? 0 : slot + 1;
-                } while (++t < end);
+                if (PAIRS) {
+                    for (; t + 1 < end; t += 2) advance(std::integral_constant<int, PAIRS ? 2 : 1>{}, slot);
+                    if (t < end) { advance(std::integral_constant<int, 1>{}, slot); ++t; }
+                } else {
+                    do advance(std::integral_constant<int, 1>{}, slot); while (++t < end);
+                }
                 add(sum[0], acc);
             }
             add(sum[1], sum[0]);
