@@ -584,15 +584,19 @@ __global__ __launch_bounds__(NTHR) void fused_gemm_kernel(GemmArgs g) {
     }
 }
 
-// Whether the weight gradients run beside the small tiles of a backward product (one launch less, and one begins where the other leaves CUs
-// idle): while both together are two rounds of work groups at most.  Beyond, the items get fewer work groups a CU here than in their own
-// launch, and the two ways are equal within 1 %.  us a step, apart / together, tokens x k x n (work groups of both in CUs): 600 x 1024 x 1024
-// (0.6) 36.2 / 30.3, 230 x 2048 x 512 (0.7) 33.4 / 28.9, 6000 x 512 x 768 (1.0) 55.1 / 47.4, 1000 x 512 x 4096 (1.6) 56.9 / 51.4, 1024 x 4096 x
-// 1024 (1.6) 61.1 / 60.0, 1024 x 4096 x 4096 (2.0) 103.0 / 102.5, 1024 x 4096 x 14336 (3.2) 267 / 266.
+// Whether the weight gradients run beside the small tiles of a backward product (one launch less, and they begin where the product leaves CUs
+// idle): where both together are two rounds of work groups at most and the product leaves CUs enough, the more the longer its contraction: its
+// work groups stream the weight in step, which the items disturb (the same kernel without items takes the product's own time).  us a step,
+// apart / together, tokens x k x n (work groups of the product, of the items, in CUs): 300 x 768 x 3072 (0.23, 0.06) 42.2 / 34.9, 818 x 4096 x
+// 2048 (0.88, 0.19) 70.6 / 64.5, 1200 x 1024 x 3072 (0.59, 0.38) 64.7 / 57.6, 818 x 1024 x 3072 (0.81, 0.25) 57.4 / 48.7, 1200 x 2048 x 4096
+// (0.62, 0.28) 106 / 104, 600 x 768 x 8192 (0.47, 0.14) 78.8 / 75.2; not: 2000 x 2048 x 1024 (1.0, 0.19) 64.6 / 68.2, 1200 x 768 x 4096 (0.89,
+// 0.22) 73.9 / 76.5, 500 x 4096 x 3072 (1.0, 0.11) 74.6 / 76.5, 2000 x 768 x 8192 (0.75, 0.55) 96.0 / 99.4, 1200 x 2048 x 5120 (0.62, 0.33)
+// 102.2 / 105.8, 300 x 1024 x 14336 (0.31, 1.9) 113.0 / 115.4, 200 x 5120 x 14336 (0.62, 0.30) 126 / 138.
 static bool side_by_side(int tile, const GemmArgs& g, int items, int num_cus) {
     const int64_t bm = tile == 0 ? 128 : 64, bn = tile == 2 ? 64 : 128;
     const int64_t groups = ((g.M + bm - 1) / bm) * ((g.Ncols + bn - 1) / bn);
-    return groups + items / 2 <= 2 * num_cus;
+    const int sixteenths = g.Kdim <= 2048 ? 15 : g.Kdim <= 4096 ? 13 : g.Kdim <= 8192 && (int64_t)g.Kdim * g.Ncols <= int64_t(8) << 20 ? 8 : 0;
+    return 16 * groups <= sixteenths * num_cus && groups + items / 2 <= 2 * num_cus;
 }
 
 static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, void* C, const void* E,

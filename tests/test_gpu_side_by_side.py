@@ -16,9 +16,10 @@ pytestmark = pytest.mark.gpu
 CASES = [(128, 256, [16, 8, 32], [70, 1, 200]),             # 9 items; 1, 2 and 4 steps
          (384, 128, [64, 40], [129, 640]),                  # 4 panels; a segment of two chunks (partial sums)
          (264, 136, [33, 4, 0, 12, 64], [64, 65, 10, 0, 63]),   # edges of a panel, a rank of 0, no tokens
-         (1024, 520, [16] * 3, [300, 250, 90]),             # 64 x 128 tiles
+         (1024, 520, [16] * 3, [300, 250, 90]),
+         (2048, 1024, [24, 64], [500, 200]),                # 64 x 128 tiles
          (2048, 640, [24, 64], [900, 700]),                 # 128 x 128 tiles
-         (512, 1032, [8] * 40, [30 + i for i in range(40)])]     # 13 panels x 40 adapters: more than two rounds of work groups
+         (512, 1032, [8] * 40, [30 + i for i in range(40)])]     # 13 panels x 40 adapters: past the rule
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))
