@@ -2,8 +2,8 @@
 // term alone.  No operand needs an alignment beyond its element.
 //
 // The fp32 matrix instructions of this chip run at 1/16 of the bf16 rate (154 TFLOP/s in a register-only loop), so the contraction over the
-// frozen weight goes through the bf16 units: every fp32 value is the sum of three bf16 values, exactly (eight bits of its significand each),
-// and of the nine products of parts the six that reach 2^-24 of the whole are summed in fp32, from the smallest up.  Relative error
+// frozen weight goes through the bf16 units: a fp32 value is the sum of three bf16 values, exactly (eight bits of its significand each; see
+// Range), and of the nine products of parts the six that reach 2^-24 of the whole are summed in fp32, from the smallest up.  Relative error
 // against 64 bits (standard normal operands): contraction 256 1.5e-7 -> 8.1e-8, 2048 1.8e-7 -> 1.3e-7, 4096 2.1e-7 -> 1.7e-7 (before:
 // v_mfma_f32_16x16x4_f32).  Time: 2048 x 2048 x 2048 162 -> 106 us (98 -> 162 TFLOP/s), 8000 x 512 x 512 47 -> 34; small layers, where a
 // work group's latency counts, are equal or a little faster (256 x 256 x 256 with its adapters 11.7 -> 9.8 us).
@@ -13,10 +13,14 @@
 // GHz with all CUs busy.  Measured and not adopted: the differences of the conversion by the two-element dot product (a third fewer instructions, 8 %
 // slower: its result is late), all fragments read behind the barrier (+-2 %), 8-byte stores of the parts (+3 %).
 //
-// Range: parts of a value close to the largest fp32 number round to Inf, those of a very small one vanish, and Inf itself has no parts.  So
-// the largest magnitude of every row of X and column of W (as it is contracted) is kept on the way; rows and columns where it is beyond
-// [2^-90, 2^126) (or W's column holds a NaN) are computed again with fp32 MFMAs from memory.  Which ones follows from the row and
-// the column alone.
+// Range: below 2^-110 a value's last parts fall under the smallest bf16, below 2^-134 all three do; close to the largest fp32 number the first part, or
+// a product of first parts, rounds to Inf, and Inf itself has no parts.  The first kind is off by 2^-125 at most an element (also
+// if the units dropped all that is denormal), times the other operand; the second leaves Inf or NaN.  So an output of K products is in doubt where it is
+// not finite or below K 2^-96 max(1, largest of its row of X, largest of its column of W): any other is off by less than 2^-27 of itself beside
+// the rounding of the sum.  Of those in doubt, rows (backward: and columns) of zeros and what a NaN in row or column has made NaN are right,
+// and so are small results of rows and columns that hold nothing below 2^-103 but zero and whose products are all zero or above 2^-90 (exact
+// cancellation, zero columns of W); the others are computed again with fp32 MFMAs from memory.  All of this follows from the row
+// and the column alone.
 //
 // Order of the sum, in all tiles (the tile follows from the number of tokens, and a row's bits must not): units of 32 elements that start at
 // multiples of 32, zero-filled at the end; the even and the odd ones are summed apart, in ascending order, and added; then each adapter's
@@ -154,7 +158,8 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
         split2(a, b, parts[0][h], parts[1][h], parts[2][h]);
         if (FWD && (PP == 1 || c >= PP / 2))                 // (PP == 1: the operand is the wavefront's, so both are kept)
             col_big[c % PB_][h] = __builtin_elementwise_max(col_big[c % PB_][h], __builtin_bit_cast(u16x2, parts[0][h] & 0x7fff7fffu));
-        if (!FWD || PP == 1 || c < PP / 2) row_big[c] = fmaxf(fmaxf(row_big[c], fabsf(a)), fabsf(b));
+        if (!FWD || PP == 1 || c < PP / 2)
+            row_big[c] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(row_big[c], fabsf(a)), fabsf(b));      // (NaN stays)
     };
     auto store_parts = [&](int slot, int c) __attribute__((always_inline)) {
         unsigned char* d = lds + slot * STAGE + place[c];
@@ -405,7 +410,7 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
     const bool owner = MB > 1 || kg == 0;            // (32 x 32: wavefronts 4 .. 7 have handed everything over)
     const int xb = wm * MB + (MB > 1 ? kg * OB : 0); // first row block of this wavefront inside the tile
 
-    // ---- rows and columns that three bf16 parts may not hold are computed again in fp32 ----------------------------------------------
+    // ---- what the parts may have got wrong is computed again in fp32 (see Range above) -----------------------------------------------------
     if (g.base) {
 #pragma unroll
         for (int c = 0; c < PP; ++c) {
@@ -418,45 +423,108 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
                     atomicMax(&col_max[idx % CPN * PE + 2 * q + 1], (uint32_t)m[1] << 16);
                 }
             } else {
-                atomicMax(is_b(c) ? &col_max[idx / CPK] : &row_max[idx / CPK], __float_as_uint(row_big[c]));
+                atomicMax(is_b(c) ? &col_max[idx / CPK] : &row_max[idx / CPK], __float_as_uint(row_big[c]) & 0x7fffffffu);
             }
         }
         lds_barrier();
-        auto beyond = [](uint32_t u) { return u >= 0x7e800000u || (u != 0 && u < 0x12800000u); };      // 2^126, 2^-90
         if (owner) {
-            bool bad_row[OB], bad_col[NB][4], any = false;
+            auto row_top = [&](int x) { return __uint_as_float(row_max[(xb + x) * 16 + l16]); };
+            auto col_top = [&](int y, int q) { return __uint_as_float(col_max[(wn * NB + y) * 16 + 4 * g4 + q]); };
+            const float least = (float)g.K * 0x1p-96f;
+            uint32_t redo = 0;                               // bit 4 (x NB + y) + q: column q of block y, row block x
+            bool small = false;
 #pragma unroll
-            for (int x = 0; x < OB; ++x) { bad_row[x] = beyond(row_max[(xb + x) * 16 + l16]); any = any || bad_row[x]; }
+            for (int x = 0; x < OB; ++x)
 #pragma unroll
-            for (int y = 0; y < NB; ++y)
+                for (int y = 0; y < NB; ++y)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) { bad_col[y][q] = beyond(col_max[(wn * NB + y) * 16 + 4 * g4 + q]); any = any || bad_col[y][q]; }
-            if (__ballot(any)) {
+                    for (int q = 0; q < 4; ++q) {
+                        const float rm = row_top(x), cm = col_top(y, q), v = fabsf(out[x][y][q]);
+                        const bool finite = v < __builtin_inff(), held = finite && v >= least * fmaxf(fmaxf(rm, cm), 1.f);
+                        const bool zero = v == 0.f && (rm == 0.f || (!FWD && cm == 0.f)), nan = rm != rm || cm != cm;
+                        const bool doubt = !held && !zero && !nan;
+                        redo |= (uint32_t)doubt << (4 * (x * NB + y) + q);
+                        small = small || (doubt && finite);
+                    }
+            if (__ballot(redo != 0)) {
+                constexpr int AT = BT == 128 ? 2 : 4;        // 16-wide steps of the contraction whose loads are in flight together
+                auto row_of = [&](int x) { return g.A + min(m0 + (xb + x) * 16 + l16, g.M - 1) * g.lda + 4 * g4; };
+                auto col_of = [&](int y) {
+                    const int64_t col = min(n0 + (wn * NB + y) * 16 + l16, g.N - 1);
+                    return FWD ? g.W + 4 * g4 * g.ldw + col : g.W + col * g.ldw + 4 * g4;
+                };
+                auto load_w = [&](const float* w, int64_t k, int valid) { return FWD ? gather16(w + k * g.ldw, g.ldw, valid) : load16(w + k, valid); };
+                auto valid_at = [&](int64_t k) { return (int)max((int64_t)0, min((int64_t)4, g.K - k - 4 * g4)); };
+                if (__ballot(small)) {                       // the smallest magnitudes but zero, as bits; small results of none that lose bits are right
+                    uint32_t lo[OB + NB];
+                    const float* src[OB + NB];
 #pragma unroll
-                for (int x = 0; x < OB; ++x) {
-                    const float* a = g.A + min(m0 + (xb + x) * 16 + l16, g.M - 1) * g.lda;
-                    f32x4 sum[NB], part[NB];
+                    for (int i = 0; i < OB + NB; ++i) { lo[i] = ~0u; src[i] = i < OB ? row_of(i) : col_of(i - OB); }
+                    auto take = [&](int i, uint4 v) { lo[i] = min(min(lo[i], min(2 * v.x - 1, 2 * v.y - 1)), min(2 * v.z - 1, 2 * v.w - 1)); };
+                    int64_t k = 0;
+                    for (; k + 16 * AT <= g.K; k += 16 * AT) {
+                        uint4 v[AT][OB + NB];
 #pragma unroll
-                    for (int y = 0; y < NB; ++y) sum[y] = part[y] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    for (int64_t k0 = 0; k0 < g.K; k0 += 16) {
-                        const int64_t k = k0 + 4 * g4;
-                        const int valid = (int)max((int64_t)0, min((int64_t)4, g.K - k));
-                        const uint4 av = load16(a + k, valid);
+                        for (int s = 0; s < AT; ++s)
 #pragma unroll
-                        for (int y = 0; y < NB; ++y) {
-                            const int64_t n = min(n0 + (wn * NB + y) * 16 + l16, g.N - 1);
-                            const uint4 bv = FWD ? gather16(g.W + k * g.ldw + n, g.ldw, valid) : load16(g.W + n * g.ldw + k, valid);
-                            part[y] = block_mma<float>(bv, av, part[y]);
-                        }
-                        if ((k0 & 48) == 48 || k0 + 16 >= g.K) {
+                            for (int i = 0; i < OB + NB; ++i) v[s][i] = i < OB ? load16(src[i] + k + 16 * s, 4) : load_w(src[i], k + 16 * s, 4);
 #pragma unroll
-                            for (int y = 0; y < NB; ++y) { sum[y] += part[y]; part[y] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-                        }
+                        for (int s = 0; s < AT; ++s)
+#pragma unroll
+                            for (int i = 0; i < OB + NB; ++i) take(i, v[s][i]);
+                    }
+                    for (; k < g.K; k += 16)
+#pragma unroll
+                        for (int i = 0; i < OB + NB; ++i) take(i, i < OB ? load16(src[i] + k, valid_at(k)) : load_w(src[i], k, valid_at(k)));
+                    auto value = [](uint32_t u) { return __uint_as_float(min(u >> 1, 0x7f7fffffu)); };
+#pragma unroll
+                    for (int i = 0; i < OB + NB; ++i) {
+                        lo[i] = min(lo[i], (uint32_t)__shfl_xor((int)lo[i], 16));
+                        lo[i] = min(lo[i], (uint32_t)__shfl_xor((int)lo[i], 32));
                     }
 #pragma unroll
                     for (int y = 0; y < NB; ++y)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) out[x][y][q] = bad_row[x] || bad_col[y][q] ? sum[y][q] : out[x][y][q];
+                        for (int q = 0; q < 4; ++q) {
+                            const float c = value((uint32_t)__shfl((int)lo[OB + y], 4 * g4 + q));
+#pragma unroll
+                            for (int x = 0; x < OB; ++x) {
+                                const float r = value(lo[x]);
+                                const bool right = fabsf(out[x][y][q]) < __builtin_inff() && r >= 0x1p-103f && c >= 0x1p-103f && r * c >= 0x1p-90f;
+                                redo &= ~((uint32_t)right << (4 * (x * NB + y) + q));
+                            }
+                        }
+                }
+#pragma nounroll
+                for (int b = 0; b < OB * NB; ++b) {
+                    const uint32_t mine = redo >> (4 * b) & 15;
+                    if (!__ballot(mine != 0)) continue;
+                    const float* a = row_of(b / NB);
+                    const float* w = col_of(b % NB);
+                    f32x4 sum{0.f, 0.f, 0.f, 0.f}, part;
+                    uint4 av[4], wv[4], an[4], wn_[4];       // 64 elements of the contraction, and the next
+                    auto load = [&](uint4 (&to_a)[4], uint4 (&to_w)[4], int64_t k) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) { to_a[s] = load16(a + k + 16 * s, 4); to_w[s] = load_w(w, k + 16 * s, 4); }
+                    };
+                    const int64_t whole = g.K & ~int64_t(63);
+                    if (whole > 0) load(av, wv, 0);
+                    for (int64_t k = 0; k < whole; k += 64) {
+                        load(an, wn_, min(k + 64, whole - 64));
+                        part = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) part = block_mma<float>(wv[s], av[s], part);
+                        sum += part;
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) { av[s] = an[s]; wv[s] = wn_[s]; }
+                    }
+                    part = f32x4{0.f, 0.f, 0.f, 0.f};
+                    for (int64_t k = whole; k < g.K; k += 16) part = block_mma<float>(load_w(w, k, valid_at(k)), load16(a + k, valid_at(k)), part);
+                    sum += part;
+#pragma unroll
+                    for (int c = 0; c < OB * NB; ++c)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) out[c / NB][c % NB][q] = c == b && (mine >> q & 1) ? sum[q] : out[c / NB][c % NB][q];
                 }
             }
         }

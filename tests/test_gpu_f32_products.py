@@ -73,3 +73,56 @@ def test_products_and_their_range(T, k, n):
     Y, dX = _products(X.cuda(), W.cuda(), dY.cuda())
     _check(Y, X, W)
     _check(dX, dY, W.T)
+
+
+def _check_all(got, a, b):
+    """As _check, for every element whose sum of magnitudes fp32 holds: no order of the sum overflows there."""
+    a, b = a.double().cpu(), b.double().cpu()
+    size, K = a.abs() @ b.abs(), a.shape[1]
+    held = size < torch.finfo(torch.float32).max * (1 - (K + 8) * 2.0 ** -24)
+    err = (got.double() - a @ b).abs()
+    bad = held & ~(err <= (K + 8) * 2.0 ** -24 * size + K * 2.0 ** -149)
+    assert not bool(bad.any()), [(i, j, got[i, j].item(), (a[i] @ b[:, j]).item()) for i, j in bad.nonzero()[:4].tolist()]
+
+
+def _meet(small_rows, large_rows, small, large):
+    """In place: two sets of rows (an operand's, and the other's along the contraction) that meet as 2^small against 2^large in every other element,
+    as an ordinary value against zero in the rest."""
+    every_other = torch.arange(small_rows.shape[1]) % 2 == (small_rows.shape[1] - 1) % 2
+    small_rows[:, every_other] *= 2.0 ** small
+    large_rows[:] = torch.where(every_other, large_rows * 2.0 ** large, 0.0)
+
+
+@pytest.mark.parametrize("T,k,n", SHAPES)
+def test_small_values_in_ordinary_rows(T, k, n):
+    """Values whose second and third part, or all three, are below what bf16 holds, in rows (columns) of ordinary ones and against large ones, where
+    their products are ordinary numbers; columns of nothing but such values; products that only fp32's rounding keeps finite; denormal ones."""
+    g = torch.Generator().manual_seed(T + k + n)
+    print(f"[case] fp32 small values T={T} k={k} n={n}", flush=True)
+    mags = [(-104, 90), (-112, 100), (-121, 100), (-130, 110), (-140, 120), (-147, 125)]
+    for transposed in (False, True):              # the forward contracts k, the backward n
+        K, N = (n, k) if transposed else (k, n)
+        for weights_small in (False, True):
+            A, B = torch.randn((T, K), generator=g), torch.randn((N, K), generator=g)
+            for j, (lo, hi) in enumerate(mags):
+                rows, cols = A[T * j // 6:T * j // 6 + 2], B[N * j // 6:N * j // 6 + 1]
+                _meet(*((cols, rows) if weights_small else (rows, cols)), lo, hi)
+            W = B if transposed else B.T.contiguous()
+            X, dY = (torch.randn((T, k), generator=g), A) if transposed else (A, torch.randn((T, n), generator=g))
+            Y, dX = _products(X.cuda(), W.cuda(), dY.cuda())
+            _check_all(Y, X, W)
+            _check_all(dX, dY, W.T)
+        A, B = torch.randn((T, K), generator=g), torch.randn((N, K), generator=g)
+        A[T // 2] *= 2.0 ** 100                   # against a column of tiny values
+        B[N // 3] *= 2.0 ** -140
+        A[T // 3] *= 2.0 ** -70                   # denormal products
+        B[N // 2] *= 2.0 ** -72
+        A[T // 4] = 0.0                           # 2^128 (1 - 2^-9): each factor rounds up to a power of two in bf16
+        A[T // 4, K - 1] = 2.0 ** 64 * (1 - 2.0 ** -10)
+        B[N - 1] = 0.0
+        B[N - 1, K - 1] = -2.0 ** 64 * (1 - 2.0 ** -10)
+        W = B if transposed else B.T.contiguous()
+        X, dY = (torch.randn((T, k), generator=g), A) if transposed else (A, torch.randn((T, n), generator=g))
+        Y, dX = _products(X.cuda(), W.cuda(), dY.cuda())
+        _check_all(Y, X, W)
+        _check_all(dX, dY, W.T)
