@@ -532,16 +532,22 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
 
     // ---- rank extension, adapter by adapter into an accumulator set of its own, of which the adapter's own rows are added: another
     // adapter's operands never touch a row, whatever they hold
-    constexpr int XP = 144, XN = (BT + 4) * 4;               // bytes of a contraction row (32 elements) of the staged operands, of a column row
+    // All ranks of an adapter at once: one wait for its operands instead of one per 32 ranks, which nothing hides with one work group per CU; and no
+    // products for 16-row blocks without a row of its.  us, 32 ranks at a time / all, and with v_mfma_f32_16x16x4_f32 for the frozen weight too (tiles of
+    // 64 x 64 and three work groups per CU): 100 x 300 x 300 with 32 adapters of rank 128 47.8 / 38.8 / 36.9, 500 x 500 x 3000 with these 89.6 / 67.8 / 72.4,
+    // 2000 x 2000 x 2000 with these 144 / 129 / 191, 4000 x 100 x 2500 with 6 of rank 128 113 / 107 / 76.
+    constexpr int KX = EDGE ? 32 : MLORA_MAX_RANK;           // ranks whose loads are in flight together
+    constexpr int XC = KX / 32;                              // in chunks of 32
+    constexpr int XP = KX * 4 + 16, XN = (BT + 4) * 4;       // bytes of a row of the staged operands, of a column row
     constexpr int XB = BT * XP;                              // where the second operand starts
-    static_assert(XB + (FWD ? KU * XN : BT * XP) <= SLOTS * STAGE, "the extension's operands fit the ring");
-    constexpr int XW = BT / 32, XCPN = BT / 4;             // words per thread, both operands; words of a column row
+    static_assert(XB + (FWD ? KX * XN : BT * XP) <= SLOTS * STAGE, "the extension's operands fit the ring");
+    constexpr int XW = BT / 32, XCPN = BT / 4;             // words per thread and chunk, both operands; words of a column row
     auto x_is_b = [&](int c) { return BT == 32 ? tid >= 256 : c >= XW / 2; };
     auto x_index = [&](int c) { return BT == 32 ? tid & 255 : tid + FG_THREADS * (c % (XW > 1 ? XW / 2 : 1)); };
-    auto x_place = [&](int c) {
+    auto x_place = [&](int h, int c) {
         const int idx = x_index(c);
-        if (FWD && x_is_b(c)) return XB + idx / XCPN * XN + idx % XCPN * 16;
-        return (x_is_b(c) ? XB : 0) + (idx >> 3) * XP + (idx & 7) * 16;
+        if (FWD && x_is_b(c)) return XB + (32 * h + idx / XCPN) * XN + idx % XCPN * 16;
+        return (x_is_b(c) ? XB : 0) + (idx >> 3) * XP + 128 * h + (idx & 7) * 16;
     };
     bool owned[OB] = {};
     const int lo_t = (int)m0, hi_t = (int)min(g.M, m0 + BT);
@@ -563,59 +569,74 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
             for (int x = 0; x < OB; ++x)
 #pragma unroll
                 for (int y = 0; y < NB; ++y) ext[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
-            for (int r0 = 0; r0 < r; r0 += KU) {
-                const int left = min(KU, r - r0);
-                piece_t v[XW];
+            for (int r0 = 0; r0 < r; r0 += KX) {
+                const int left = min(KX, r - r0);
+                piece_t v[XC][XW];
 #pragma unroll
-                for (int c = 0; c < XW; ++c) {
-                    const int idx = x_index(c), row = idx >> 3, k = (idx & 7) * 4;
-                    if (!x_is_b(c)) {
-                        v[c] = as_piece(load16(E + (int64_t)row * r + r0 + k, lo_t + row >= lo && lo_t + row < hi ? left - k : 0));
-                    } else if (FWD) {
-                        const int kr = idx / XCPN;
-                        const int64_t col = n0 + (idx % XCPN) * 4;
-                        v[c] = as_piece(load16(F + (int64_t)(r0 + kr) * g.N + col, kr < left ? (int)max((int64_t)0, min((int64_t)4, g.N - col)) : 0));
-                    } else {
-                        v[c] = as_piece(load16(F + (n0 + row) * r + r0 + k, n0 + row < g.N ? left - k : 0));
+                for (int h = 0; h < XC; ++h) {
+                    if (h > 0 && 32 * h >= left) break;      // (uniform)
+#pragma unroll
+                    for (int c = 0; c < XW; ++c) {
+                        const int idx = x_index(c), row = idx >> 3, k = 32 * h + (idx & 7) * 4;
+                        if (!x_is_b(c)) {
+                            v[h][c] = as_piece(load16(E + (int64_t)row * r + r0 + k, lo_t + row >= lo && lo_t + row < hi ? left - k : 0));
+                        } else if (FWD) {
+                            const int kr = 32 * h + idx / XCPN;
+                            const int64_t col = n0 + (idx % XCPN) * 4;
+                            v[h][c] = as_piece(load16(F + (int64_t)(r0 + kr) * g.N + col, kr < left ? (int)max((int64_t)0, min((int64_t)4, g.N - col)) : 0));
+                        } else {
+                            v[h][c] = as_piece(load16(F + (n0 + row) * r + r0 + k, n0 + row < g.N ? left - k : 0));
+                        }
                     }
                 }
                 lds_barrier();                       // whoever read the stage before is done
 #pragma unroll
-                for (int c = 0; c < XW; ++c) *reinterpret_cast<piece_t*>(lds + x_place(c)) = v[c];
+                for (int h = 0; h < XC; ++h) {
+                    if (h > 0 && 32 * h >= left) break;
+#pragma unroll
+                    for (int c = 0; c < XW; ++c) *reinterpret_cast<piece_t*>(lds + x_place(h, c)) = v[h][c];
+                }
                 lds_barrier();
                 if (owner) {
-                    f32x4 part[OB][NB];
 #pragma unroll
-                    for (int x = 0; x < OB; ++x)
+                    for (int k = 0; k < KX; k += 32) {       // 32 ranks are summed by themselves
+                        if (k >= left) break;
+                        f32x4 part[OB][NB];
 #pragma unroll
-                        for (int y = 0; y < NB; ++y) part[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        for (int x = 0; x < OB; ++x)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        if (h * 16 >= left) continue;
-                        uint4 ea[OB], eb[NB];
+                            for (int y = 0; y < NB; ++y) part[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int x = 0; x < OB; ++x) {
-                            ea[x] = *reinterpret_cast<const uint4*>(lds + ((xb + x) * 16 + l16) * XP + h * 64 + g4 * 16);
-                        }
+                        for (int h = k / 16; h < k / 16 + 2; ++h) {
+                            if (h * 16 >= left) continue;
+                            uint4 ea[OB], eb[NB];
 #pragma unroll
-                        for (int y = 0; y < NB; ++y) {
-                            const int col = (wn * NB + y) * 16 + l16;
-                            if (FWD) {
-                                const uint32_t* p = reinterpret_cast<const uint32_t*>(lds + XB + (h * 16 + 4 * g4) * XN) + col;
-                                eb[y] = make_uint4(p[0], p[XN / 4], p[2 * (XN / 4)], p[3 * (XN / 4)]);
-                            } else {
-                                eb[y] = *reinterpret_cast<const uint4*>(lds + XB + col * XP + h * 64 + g4 * 16);
+                            for (int x = 0; x < OB; ++x) {
+                                ea[x] = *reinterpret_cast<const uint4*>(lds + ((xb + x) * 16 + l16) * XP + h * 64 + g4 * 16);
+                            }
+#pragma unroll
+                            for (int y = 0; y < NB; ++y) {
+                                const int col = (wn * NB + y) * 16 + l16;
+                                if (FWD) {
+                                    const uint32_t* p = reinterpret_cast<const uint32_t*>(lds + XB + (h * 16 + 4 * g4) * XN) + col;
+                                    eb[y] = make_uint4(p[0], p[XN / 4], p[2 * (XN / 4)], p[3 * (XN / 4)]);
+                                } else {
+                                    eb[y] = *reinterpret_cast<const uint4*>(lds + XB + col * XP + h * 64 + g4 * 16);
+                                }
+                            }
+#pragma unroll
+                            for (int x = 0; x < OB; ++x) {
+                                const int row0 = lo_t + (xb + x) * 16;
+                                if (row0 + 16 <= lo || row0 >= hi) continue;      // (uniform: none of the adapter's rows)
+#pragma unroll
+                                for (int y = 0; y < NB; ++y) part[x][y] = block_mma<float>(eb[y], ea[x], part[x][y]);
                             }
                         }
 #pragma unroll
                         for (int x = 0; x < OB; ++x)
 #pragma unroll
-                            for (int y = 0; y < NB; ++y) part[x][y] = block_mma<float>(eb[y], ea[x], part[x][y]);
+                            for (int y = 0; y < NB; ++y) ext[x][y] += part[x][y];
                     }
-#pragma unroll
-                    for (int x = 0; x < OB; ++x)
-#pragma unroll
-                        for (int y = 0; y < NB; ++y) ext[x][y] += part[x][y];
                 }
             }
 #pragma unroll
