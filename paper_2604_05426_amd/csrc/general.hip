@@ -538,14 +538,17 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     a.src = (const T*)src; a.ld = FWD ? p->k : p->n; a.out = (T*)out; a.pv = p->view;
     ProfScope prof(p, FWD ? MLORA_K_SHRINK : MLORA_K_DSHRINK, st);
     const int64_t groups = (int64_t)p->n_row_blocks * 4;
-    // Ranks per work group: 16, 64 or all.  With all of them a few row blocks of wide ranks kept a few CUs busy with the whole adapter matrix
-    // each; with 16 the rows are read once per 16 ranks (from the caches).  us, all / 64 / 16, work groups in CUs with 16 (64) ranks each:
-    // fp32 333 tokens, contraction 4000, rank 128 (0.7) 68.6 / - / 18.5; 100, 3000, rank 100 (0.9) 42.8 / - / 12.9; 2048, 2048, ranks to 64 (2.3)
-    // - / 23.7 / 19.0; 4000, 1000, ranks to 100 (6.9) 27.8 / 27.4 / 16.1; 8000, 2000, rank 128 (15.8; 3.9) 59 / 66 / 96; bf16 1500, 2048, ranks to 33
-    // (1.2) - / 13.0 / 8.4; 2000, 4095, ranks to 100 (3.5; 1) 99 / 66 / 100; 6000, 1001, rank 64 (6) - / 25.1 / 28.4.
+    // Ranks per work group: 16, 64 or all.  With all of them a few row blocks of wide ranks keep a few CUs busy with the whole adapter matrix
+    // each; with 16 the rows are read once per 16 ranks (from the caches).  The lines are limits on the work groups in CUs that 309 drawn shapes
+    // give (each both ways, 64 .. 8000 tokens, contractions 64 .. 4095): with them a launch takes 3.6 % more than the best of the three on average
+    // (all ranks, always: 38 %), and at most 1.24 times what it takes with all ranks.  us, 16 / 64 / all: forward, bf16 2197 tokens, contraction 769, ranks
+    // to 100 - / 13.2 / 10.6, 414, 3076, 24 adapters to 64 15.1 / 12.1 / -, fp32 2814, 3415, rank 128 78 / 55 / 49, 333, 4000, rank 128 18.5 / - / 68.6; backward, bf16
+    // 1500, 2048, ranks to 33 8.4 / 13.0 / -, fp32 7383, 963, rank 64 28.0 / 26.1 / -.
     auto items = [&](int nb) { return (p->max_rank + 16 * nb - 1) / (16 * nb); };
-    const int lim = (sizeof(T) == 4 ? 8 : 2) * p->num_cus;
-    const int nb = p->max_rank <= 16 || groups * items(1) <= lim ? 1 : p->max_rank <= 64 || groups * items(4) <= 2 * p->num_cus ? 4 : 8;
+    const bool wide = p->max_rank > 64;
+    const int one = (sizeof(T) == 4 ? (FWD ? (wide ? 4 : 2) : (wide ? 6 : 4)) : (FWD ? (wide ? 2 : 1) : (wide ? 4 : 2))) * p->num_cus;
+    const int four = p->num_cus * (FWD ? 2 : 3) / 2;
+    const int nb = p->max_rank <= 16 || groups * items(1) <= one ? 1 : !wide || groups * items(4) <= four ? 4 : 8;
     a.rank_items = items(nb);
     const dim3 grid = two_dims(groups * a.rank_items);
     if (nb == 1)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1>), grid, dim3(512), 0, st, a);
@@ -562,11 +565,12 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
 // 149.7, 6000 x 300 x 777 (1000, 2.7) 77.3 / 74.0, 2000 x 100 x 333 (2000, 1.0) 35.9 / 30.6; not: 2000 x 1001 x 300 (2000, 2.1) 45.9 / 46.9,
 // 6000 x 1001 x 300 (1000, 6.9) 73.1 / 77.4, 6000 x 100 x 333 (3000, 1.0) 56.0 / 60.1, 8000 x 1001 x 300 (4000, 8.5) 98.9 / 120.5.
 bool beside_product(const mlora_plan* p, const GenWgradArgs<u16>& w, int64_t groups, int64_t K) {
+    const int64_t all = groups + (int64_t)w.panels * p->N * ((p->max_rank + 15) / 16);
+    if (all > 10 * p->num_cus) return false;
     int64_t longest = 0;
     for (int32_t i = 0; i < p->N; ++i)
         if (p->ranks[i] > 0) longest = std::max(longest, p->off[i + 1] - p->off[i]);
-    const int64_t all = groups + (int64_t)w.panels * p->N * ((p->max_rank + 15) / 16);
-    return all <= 10 * p->num_cus && longest <= 2000 && (longest * all <= 4000 * p->num_cus || 2 * longest <= K);
+    return longest <= 2000 && (longest * all <= 4000 * p->num_cus || 2 * longest <= K);
 }
 
 template <bool FWD>

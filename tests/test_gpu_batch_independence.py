@@ -73,5 +73,5 @@ def test_splits_of_the_shrink(k, n, rank):
 @pytest.mark.parametrize("rank,rows", [(8, 20), (16, 150), (33, 150), (100, 40)])
 def test_tiles_and_builds_of_the_general_kernels(dtype, k, n, rank, rows):
     """Both tiles of the general products (32 x 32 alone, 64 x 64 with the neighbours), fewer rows than a tile, contractions with
-    and without a remainder and shorter than a step, and neighbours whose ranks send the shrink to its builds for 16, 64 and 128."""
+    and without a remainder and shorter than a step, and neighbours with other ranks (the shrink's ranks per work group: test_gpu_shrink_ranks.py)."""
     _same_bits(dtype, k, n, rank, [([(4, 9)], [(16, 30)]), ([(64, 37)], [(8, 300)]), ([(8, 1301)], [(64, 1500)]), ([(128, 700)], [(16, 3000)])], rows)

@@ -6,10 +6,20 @@ from test_gpu_batch_independence import _same_bits
 
 pytestmark = pytest.mark.gpu
 
+# Neighbours that take the batch to 64 ranks a work group (in both directions with (64, 4600), forward with (128, 1500), backward with (128, 2500)
+# - bf16 - where the adapter's own rank is no wider) and to all (128, 5100); alone it is 16.
+BATCHES = {"f32": [([(16, 37)], [(64, 4600)]), ([(8, 40)], [(128, 5100)])],
+           "bf16": [([(64, 37)], [(64, 4600)]), ([(8, 40)], [(128, 1500)]), ([(8, 40)], [(128, 2500)]), ([(8, 40)], [(128, 5100)])]}
+
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("rank", [3, 16, 17, 33, 64, 65, 100, 128])
 def test_ranks_per_work_group(dtype, rank):
-    # fp32: 8700 tokens of ranks to 64 (64 at a time), 5300 with a rank of 128 (all); bf16: 2300 with 64 and 128 (64 at a time), 4600 (all)
-    batches = [([(16, 37)], [(64, 8500)]), ([(8, 40)], [(128, 5100)])] if dtype == "f32" else [([(64, 37)], [(128, 2100)]), ([(8, 40)], [(128, 4400)])]
-    _same_bits(dtype, 130, 201, rank, batches, rows=90)
+    _same_bits(dtype, 130, 201, rank, BATCHES[dtype], rows=90)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rank", [33, 100])
+def test_ranks_per_work_group_of_long_contractions(dtype, rank):
+    """Several pieces of the contraction per wavefront, and a remainder: the chains that take turns go past their first piece."""
+    _same_bits(dtype, 1030, 2051, rank, BATCHES[dtype], rows=90)
