@@ -139,6 +139,7 @@ struct mlora_plan {
     bool ptr_mirror_valid = false;
     bool ptr_upload_captured = false;
     hipStream_t ptr_mirror_stream = nullptr;
+    bool grads_over_A = false;        // a gradient of the mirror lies over an A_i of it (see upload_ptrs)
     // Shares of split shrink contractions.  Up to kSplitChunks allocations of less than 2 MB, each for as many whole row blocks as
     // fit at `split_slot` bytes a share (both rank classes alike): those come from memory the runtime keeps at hand (1 us for an
     // allocation and its release, 24 us from 2 MB on, which a plan made for every step would pay every step; more than three of them

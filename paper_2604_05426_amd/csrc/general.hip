@@ -659,8 +659,9 @@ int bwd_t(mlora_plan* p, const void* dY, const void* X, const void* W, const voi
     if (lora && (rc = shrink<T, false>(p, dY, dS, st)) != MLORA_OK) return rc;
     const GenWgrad<T> w = wgrad_of<T>(p, dY, X, S, dS, flags);
     bool joined = false;
-    if constexpr (sizeof(T) == 4) rc = f32_gemm(p, false, dY, W, dX, dS, flags, grads ? &w.args : nullptr, w.nb, w.whole, &joined, st);
-    else                          rc = gemm<false>(p, dY, W, dX, dS, flags, grads && w.whole ? &w.args : nullptr, &joined, st);
+    const bool may_join = grads && !p->grads_over_A;
+    if constexpr (sizeof(T) == 4) rc = f32_gemm(p, false, dY, W, dX, dS, flags, may_join ? &w.args : nullptr, w.nb, w.whole, &joined, st);
+    else                          rc = gemm<false>(p, dY, W, dX, dS, flags, may_join && w.whole ? &w.args : nullptr, &joined, st);
     if (rc != MLORA_OK || !grads || joined) return rc;
     return launch_wgrad<T>(p, w, st);
 }

@@ -934,7 +934,7 @@ int mfma_backward(mlora_plan* p, const void* dY, const void* X, const void* W, c
     const int32_t n_wide = geo.n_chunks_wide, n_narrow = geo.n_chunks - geo.n_chunks_wide;
     const int narrow_nb = p->max_rank_narrow <= 32 ? 1 : 2;
     // (the weight gradients of a batch without wide ranks may go with the product)
-    const bool may_join = lora && n_wide == 0 && n_narrow > 0 && n_narrow * panels < (1 << 20);
+    const bool may_join = lora && !p->grads_over_A && n_wide == 0 && n_narrow > 0 && n_narrow * panels < (1 << 20);
     bool joined = false;
     const int rc = (flags & MLORA_FLAG_LORA_ONLY) ? launch_expand(p, false, dX, dS, st)
                                                   : mfma_gemm_bwd(p, dY, W, dX, dS, flags, may_join ? &w : nullptr, (int)(n_narrow * panels),

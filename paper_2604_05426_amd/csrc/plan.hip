@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <new>
 
 #include "common.h"
 
@@ -246,6 +247,32 @@ __global__ void upload_ptrs_kernel(AdapterPtrs* dst, PtrBatch batch, int32_t bas
     if (i < count) dst[base + i] = batch.p[i];
 }
 
+// Whether any dA_i or dB_i shares memory with any A_i: the weight gradients must then not run beside the product that reads A_i.
+static bool grads_over_A(const mlora_plan* p) try {
+    struct Span { uintptr_t lo, hi; bool input; };
+    std::vector<Span> spans;
+    const size_t e = p->dtype == MLORA_F32 ? 4 : 2;
+    for (int32_t i = 0; i < p->N; ++i) {
+        const AdapterPtrs& m = p->ptr_mirror[i];
+        auto add = [&](const void* ptr, int64_t width, bool input) {
+            const uintptr_t at = reinterpret_cast<uintptr_t>(ptr);
+            if (ptr && p->ranks[i] > 0) spans.push_back({at, at + (size_t)width * p->ranks[i] * e, input});
+        };
+        add(m.A, p->k, true);
+        add(m.dA, p->k, false);
+        add(m.dB, p->n, false);
+    }
+    std::sort(spans.begin(), spans.end(), [](const Span& a, const Span& b) { return a.lo < b.lo; });
+    uintptr_t end[2] = {0, 0};                        // of what came before: gradients, inputs
+    for (const Span& s : spans) {
+        if (end[!s.input] > s.lo) return true;
+        end[s.input] = std::max(end[s.input], s.hi);
+    }
+    return false;
+} catch (const std::bad_alloc&) {
+    return true;
+}
+
 // Refreshes the device table of per-adapter pointers.  The forward passes no gradient pointers and leaves the ones in
 // the table alone.  The table is left as it is when the same stream already uploaded exactly these pointers (the usual
 // case: the same buffers every training step); a stream under graph capture always records the upload, and from then
@@ -263,19 +290,20 @@ int upload_ptrs(mlora_plan* p, const void* const* A, const void* const* B, void*
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
     const bool capturing = cap != hipStreamCaptureStatusNone;
     if (capturing) p->ptr_upload_captured = true;     // replays of that graph rewrite the table: the mirror cannot follow them
-    bool same = p->ptr_mirror_valid && p->ptr_mirror_stream == st && !capturing && !p->ptr_upload_captured;
+    bool same = p->ptr_mirror_valid && p->ptr_mirror_stream == st && !capturing && !p->ptr_upload_captured, changed = false;
     for (int32_t i = 0; i < p->N; ++i) {
         AdapterPtrs& m = p->ptr_mirror[i];
         const void* a = A ? A[i] : nullptr;
         const void* b = B ? B[i] : nullptr;
-        if (m.A != a || m.B != b) { same = false; m.A = a; m.B = b; }
+        if (m.A != a || m.B != b) { changed = true; m.A = a; m.B = b; }
         if (grads) {
             void* da = dA ? dA[i] : nullptr;
             void* db = dB ? dB[i] : nullptr;
-            if (m.dA != da || m.dB != db) { same = false; m.dA = da; m.dB = db; }
+            if (m.dA != da || m.dB != db) { changed = true; m.dA = da; m.dB = db; }
         }
     }
-    if (same) return MLORA_OK;
+    if (changed) p->grads_over_A = grads_over_A(p);
+    if (same && !changed) return MLORA_OK;
     for (int32_t base = 0; base < p->N; base += 32) {
         PtrBatch batch;
         std::memset(&batch, 0, sizeof(batch));

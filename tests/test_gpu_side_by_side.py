@@ -119,3 +119,26 @@ def test_odd_width_backward_of_small_batches(case):
     for d in (dl, db):
         d.check_guards()
         d.plan.destroy()
+
+
+@pytest.mark.parametrize("dtype,k,n,rank,lens", [("bf16", 384, 128, 40, [129, 640]), ("f32", 300, 700, 32, [500, 517]), ("bf16", 300, 77, 33, [70, 257])])
+def test_gradients_over_the_adapters(dtype, k, n, rank, lens):
+    """Gradients written over the matrices they belong to, or over each other's: dX still comes from the old ones."""
+    w = wl.make_workload("over", dtype, k, n, [rank] * 2, lens, [1.0, 0.5], seed=5, b_sigma=0.3)
+    print(f"[case] gradients over the adapters {dtype} k={k} n={n}", flush=True)
+    dl = DeviceLayer(w)
+    dl.forward(); dl.backward(); dl.sync()
+    want = [t.clone() for t in [dl.dX] + dl.dA + dl.dB]
+    A, B = [t.clone() for t in dl.A], [t.clone() for t in dl.B]
+    for order in ((0, 1), (1, 0)):
+        for _ in range(3):
+            for t, old in zip(dl.A + dl.B, A + B):
+                t.copy_(old)
+            dl.dX.fill_(float("nan"))
+            dA, dB = [dl.A[j] for j in order], [dl.B[j] for j in order]
+            ml.multi_lora_bwd(dl.plan, dl.dY, dl.X, dl.W, dl.A, dl.B, dl.S, dl.dX, dA, dB, dl.workspace, 0, dl.stream)
+            dl.sync()
+            for got, ref in zip([dl.dX] + dA + dB, want):
+                assert torch.equal(got.view(torch.uint8), ref.view(torch.uint8))
+    dl.check_guards()
+    dl.plan.destroy()
