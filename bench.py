@@ -24,7 +24,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_MFMA_TFLOPS = 2500.0   # MI355X dense bf16 matrix peak
-PEAK_F32_MFMA_TFLOPS = 157.3     # MI355X fp32 matrix peak (fp32 layers)
+PEAK_F32_PRODUCT_TFLOPS = 2500.0 / 6   # fp32 products run as six bf16 products of parts each
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 
 
@@ -488,6 +488,7 @@ def measure_layer(config: int, args, mods, extras: bool, lora_and_base: bool, ce
             "shrink": ("hbm", (T * k + sum_r * k + R1) * e),
             "dshrink": ("hbm", (T * n + sum_r * n + R1) * e),
             "wgrad": ("hbm", (T * k + T * n + 2 * R1 + sum_r * (k + n)) * e),
+            "gemm_bwd_wgrad": ("mfma", 2.0 * T * k * n + 2.0 * R1 * k + 2.0 * R1 * (k + n)),      # (one launch: small batches)
         }
         for name, (bound, work) in alg.items():
             if name in kern:
@@ -495,7 +496,7 @@ def measure_layer(config: int, args, mods, extras: bool, lora_and_base: bool, ce
                 t = kern[name]["avg_ms"] * kern[name]["launches_per_step"] * 1e-3
                 if bound == "mfma":
                     kern[name].update(bound="mfma", achieved_tflops=work / t / 1e12,
-                                      frac=work / t / 1e12 / (PEAK_F32_MFMA_TFLOPS if w.dtype == "f32" else PEAK_BF16_MFMA_TFLOPS))
+                                      frac=work / t / 1e12 / (PEAK_F32_PRODUCT_TFLOPS if w.dtype == "f32" else PEAK_BF16_MFMA_TFLOPS))
                 else:
                     kern[name].update(bound="hbm", achieved_gbs=work / t / 1e9, frac=work / t / 1e9 / PEAK_HBM_GBS)
         out["kernels"] = kern
@@ -510,7 +511,7 @@ def measure_layer(config: int, args, mods, extras: bool, lora_and_base: bool, ce
         bound, work = alg[dom] if dom else (None, 0.0)
         t = kern[dom]["avg_ms"] * kern[dom]["launches_per_step"] * 1e-3 if dom else 1.0
         if bound == "mfma":
-            peak = PEAK_F32_MFMA_TFLOPS if w.dtype == "f32" else PEAK_BF16_MFMA_TFLOPS
+            peak = PEAK_F32_PRODUCT_TFLOPS if w.dtype == "f32" else PEAK_BF16_MFMA_TFLOPS
             out["roofline"] = {"kernel": dom, "bound": "mfma", "achieved": work / t / 1e12, "peak": peak,
                                "unit": "TFLOP/s", "frac": work / t / 1e12 / peak, "traffic": traffic.get(dom),
                                "traffic_source": traffic_source, "algorithmic_flop_per_launch": work,
@@ -549,7 +550,7 @@ def measure_layer(config: int, args, mods, extras: bool, lora_and_base: bool, ce
             step(ml.FLAG_LORA_ONLY)
         per_lo = {}
         for kid, ms in dl.plan.profile_end(K * 16):
-            per_lo.setdefault({"gemm_fwd": "expand_add_fwd", "gemm_bwd": "expand_add_bwd"}.get(ml.KERNEL_NAMES[kid], ml.KERNEL_NAMES[kid]), []).append(ms)
+            per_lo.setdefault({"gemm_fwd": "expand_add_fwd", "gemm_bwd": "expand_add_bwd", "gemm_bwd_wgrad": "expand_add_bwd_wgrad"}.get(ml.KERNEL_NAMES[kid], ml.KERNEL_NAMES[kid]), []).append(ms)
         alg_lo = {"shrink": (T * k + sum_r * k + R1) * e, "dshrink": (T * n + sum_r * n + R1) * e,
                   "wgrad": (T * k + T * n + 2 * R1 + sum_r * (k + n)) * e,
                   "expand_add_fwd": (2 * T * n + R1 + sum_r * n) * e, "expand_add_bwd": (2 * T * k + R1 + sum_r * k) * e}

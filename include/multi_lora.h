@@ -244,7 +244,9 @@ enum {
     MLORA_K_WGRAD = 4,       /* dA_i, dB_i token reductions (grouped) */
     MLORA_K_WGRAD_REDUCE = 5,/* fixed-order sum of chunk partials */
     MLORA_K_OTHER = 6,       /* pointer upload, zero fills */
-    MLORA_K_ADAMW = 7        /* grouped per-adapter AdamW update */
+    MLORA_K_ADAMW = 7,       /* grouped per-adapter AdamW update */
+    MLORA_K_GEMM_BWD_WGRAD = 8 /* MLORA_K_GEMM_BWD and MLORA_K_WGRAD in one launch (small batches, which then have neither id;
+                                  split token chunks still have their MLORA_K_WGRAD_REDUCE) */
 };
 
 /*

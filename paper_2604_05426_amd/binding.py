@@ -45,7 +45,7 @@ EXPORTS = ["multi_lora_plan_create", "multi_lora_plan_create_like", "multi_lora_
 EXIT_CONTINUE, EXIT_DIVERGING, EXIT_OVERFITTING, EXIT_UNDERPERFORMING = 0, 1, 2, 3
 
 KERNEL_NAMES = {0: "shrink", 1: "gemm_fwd", 2: "dshrink", 3: "gemm_bwd", 4: "wgrad", 5: "wgrad_reduce", 6: "other",
-                7: "adamw"}
+                7: "adamw", 8: "gemm_bwd_wgrad"}
 
 
 class MonitorParams(ctypes.Structure):

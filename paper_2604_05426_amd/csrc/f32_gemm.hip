@@ -718,16 +718,18 @@ void launch(F32GemmArgs a, hipStream_t st) {
 // CUs): 4 x 64 tokens, 256 x 256 (0.4) 25.1 / 21.3, 600 x 512 x 512 (2.3) 37.4 / 33.6, 1000 x 300 x 700 (3.3) 46.5 / 42.1, 4000 x 128 x 256 (4)
 // 40.1 / 37.4, 2048 x 2048 x 2048 (3) 278 / 267, 8000 x 512 x 512 (2.5) 104.5 / 101.9; 32 x 32 tiles and ranks of 64, 500 x 1024 x 512 (2.2)
 // 54.9 / 57.7.
+template <int BT> bool side_by_side(const F32GemmArgs& g, const GenWgradArgs<float>& w, int nb, int num_cus) {
+    F32GemmArgs a = g;
+    return set_tiles<BT>(a) + (int64_t)w.panels * w.pv.N * w.rank_items <= 8 * num_cus && !(BT == 32 && nb == 4);
+}
 template <int BT>
-bool launch_with_wgrad(F32GemmArgs a, const GenWgradArgs<float>& w, int nb, bool whole, int num_cus, hipStream_t st) {
+void launch_with_wgrad(F32GemmArgs a, const GenWgradArgs<float>& w, int nb, bool whole, hipStream_t st) {
     const int64_t groups = set_tiles<BT>(a), items = (int64_t)w.panels * w.pv.N * w.rank_items;
-    if (groups + items > 8 * num_cus || (BT == 32 && nb == 4)) return false;
     const dim3 grid((unsigned)(groups + items)), block(FG_THREADS);
     if (!whole)       hipLaunchKernelGGL((f32_bwd_kernel<BT, 1, false>), grid, block, 0, st, a, w, (int)groups);
     else if (nb == 1) hipLaunchKernelGGL((f32_bwd_kernel<BT, 1, true>), grid, block, 0, st, a, w, (int)groups);
     else if (nb == 2) hipLaunchKernelGGL((f32_bwd_kernel<BT, 2, true>), grid, block, 0, st, a, w, (int)groups);
     else if constexpr (BT != 32) hipLaunchKernelGGL((f32_bwd_kernel<BT, 4, true>), grid, block, 0, st, a, w, (int)groups);
-    return true;
 }
 
 // Tile edge for M x N outputs over a contraction of K, the one that the times measured give the least for:
@@ -751,10 +753,14 @@ void forward(const F32GemmArgs& a, int edge, hipStream_t st) {
     else if (edge == 64 && a.N >= 64)   launch<true, 64>(a, st);
     else                                launch<true, 32>(a, st);
 }
-void backward(const F32GemmArgs& a, int edge, hipStream_t st) {
-    if (edge == 128)     launch<false, 128>(a, st);
-    else if (edge == 64) launch<false, 64>(a, st);
-    else                 launch<false, 32>(a, st);
+// whether the weight gradients `w` (may be null) went with it
+template <int BT>
+bool backward(mlora_plan* p, const F32GemmArgs& a, const GenWgradArgs<float>* w, int nb, bool whole, hipStream_t st) {
+    const bool beside = w && side_by_side<BT>(a, *w, nb, p->num_cus);
+    ProfScope prof(p, beside ? MLORA_K_GEMM_BWD_WGRAD : MLORA_K_GEMM_BWD, st);
+    if (beside) launch_with_wgrad<BT>(a, *w, nb, whole, st);
+    else        launch<false, BT>(a, st);
+    return beside;
 }
 
 }  // namespace
@@ -769,15 +775,15 @@ int f32_gemm(mlora_plan* p, bool fwd, const void* A, const void* W, void* C, con
     a.lora = ((flags & MLORA_FLAG_BASE_ONLY) || p->n_row_blocks == 0) ? 0 : 1;
     a.pv = p->view;
     if (a.M == 0 || (!a.base && !a.lora)) return MLORA_OK;
-    ProfScope prof(p, fwd ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
     const int edge = tile_edge(a.M, a.N, a.K, p->num_cus);
     if (fwd) {
+        ProfScope prof(p, MLORA_K_GEMM_FWD, st);
         forward(a, edge, st);
     } else {
-        if (w) *with_w = edge == 128   ? launch_with_wgrad<128>(a, *w, nb, whole, p->num_cus, st)
-                         : edge == 64  ? launch_with_wgrad<64>(a, *w, nb, whole, p->num_cus, st)
-                                       : launch_with_wgrad<32>(a, *w, nb, whole, p->num_cus, st);
-        if (!w || !*with_w) backward(a, edge, st);
+        const bool joined = edge == 128  ? backward<128>(p, a, w, nb, whole, st)
+                            : edge == 64 ? backward<64>(p, a, w, nb, whole, st)
+                                         : backward<32>(p, a, w, nb, whole, st);
+        if (w) *with_w = joined;
     }
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;

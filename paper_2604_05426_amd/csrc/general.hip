@@ -584,7 +584,6 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
     a.lora = ((flags & MLORA_FLAG_BASE_ONLY) || p->n_row_blocks == 0) ? 0 : 1;
     a.pv = p->view;
     if (a.M == 0 || (!a.base && !a.lora)) return MLORA_OK;
-    ProfScope prof(p, FWD ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
     auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
     // 32 x 32 tiles where 64 x 64 ones would leave half the chip idle.  us, 32 x 32 / 64 x 64, by the number of 64 x 64 tiles: 20 (256 x 257,
     // contraction 256) 8.4 / 9.6, 72 (500 x 513, 1000) 14.2 / 14.1, 128 (512 x 1024, 1024) 20 / 14, 136 (500 x 1025, 4096) 44 / 31, 176
@@ -592,8 +591,10 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
     const bool split = tiles(64) <= p->num_cus / 2;
     a.tiles_n = (a.N + (split ? 31 : 63)) / (split ? 32 : 64);
     const int64_t groups = tiles(split ? 32 : 64);
+    const bool beside = !FWD && w && beside_product(p, *w, groups, a.K);
+    ProfScope prof(p, FWD ? MLORA_K_GEMM_FWD : beside ? MLORA_K_GEMM_BWD_WGRAD : MLORA_K_GEMM_BWD, st);
     if constexpr (!FWD) {
-        if (w && beside_product(p, *w, groups, a.K)) {
+        if (beside) {
             GenWgradArgs<u16> b = *w;
             b.rank_items = (uint32_t)((p->max_rank + 15) / 16);
             const dim3 grid((unsigned)(groups + (int64_t)b.panels * p->N * b.rank_items));

@@ -637,8 +637,8 @@ static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, 
     g.xcd_run = g.tiles_m * g.tiles_n < 256 ? (g.tiles_m * g.tiles_n + 7) / 8 : 0;
     const int small = (flags & MLORA_FLAG_GROUP_BANDS) ? -1 : small_gemm_tile(g.M, g.Ncols, g.Kdim, p->num_cus);
     if (small >= 0) {
-        ProfScope prof(p, fwd ? MLORA_K_GEMM_FWD : MLORA_K_GEMM_BWD, st);
         const WgradArgs* beside = w && side_by_side(small, g, items, p->num_cus) ? w : nullptr;
+        ProfScope prof(p, fwd ? MLORA_K_GEMM_FWD : beside ? MLORA_K_GEMM_BWD_WGRAD : MLORA_K_GEMM_BWD, st);
         launch_small_gemm(small, g, fwd, beside, items, max_nb, st);
         if (beside) *with_w = true;
         MLORA_HIP_TRY(hipGetLastError());
