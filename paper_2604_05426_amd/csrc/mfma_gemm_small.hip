@@ -40,8 +40,44 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 template <int BM, int BN> constexpr int kStages = SG_LDS / ((BM + BN) * 128) < 8 ? SG_LDS / ((BM + BN) * 128) : 8;
 template <int BM, int BN> constexpr int kRing = kStages<BM, BN> * (BM + BN) * 128;
 
-template <bool NN, int BM, int BN>
-__device__ __forceinline__ void small_gemm_body(const GemmArgs& g, unsigned char* const lds) {
+// The weight gradients of a batch that fills the chip with neither go with the backward product: both need dS alone and run side by side, the
+// first `gemm_groups` work groups on the tiles of dX, the others on two weight-gradient items each (four wavefronts an item).
+template <int MAXNB> struct Beside { WgradArgs w; int32_t gemm_groups, items; };
+template <> struct Beside<0> {};
+template <int MAXNB> constexpr int kItem = 2 * (WX_TILE + WT * MAXNB * 32);      // elements of LDS an item takes
+template <int MAXNB>
+__device__ __forceinline__ void two_items(const Beside<MAXNB>& b, unsigned char* lds) {
+    const WgradArgs& w = b.w;
+    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int panels = w.panels_k + w.panels_n;
+    const int item = 2 * (int)(blockIdx.x - b.gemm_groups) + half, other = item ^ 1;
+    const Entry4 none{0, 0, 0, 0};
+    const Entry4 e = item < b.items ? w.pv.wgrad_chunks[w.chunk_base + item / panels] : none;
+    const Entry4 o = other < b.items ? w.pv.wgrad_chunks[w.chunk_base + other / panels] : none;
+    const int steps = max(wgrad_steps(e), wgrad_steps(o));           // both halves pass the same barriers
+    if (item >= b.items) {
+        for (int t = 0; t <= steps; ++t) __syncthreads();
+        return;
+    }
+    u16* mine = reinterpret_cast<u16*>(lds) + half * kItem<MAXNB>;
+    const int panel = item % panels, tid = threadIdx.x & 255;
+    if (panel < w.panels_k) wgrad_body<MAXNB, true, 4, true>(w, mine, tid, e, panel, steps);
+    else                    wgrad_body<MAXNB, false, 4, true>(w, mine, tid, e, panel - w.panels_k, steps);
+}
+
+// MAXNB > 0: with weight gradients, built for that many 32-wide rank blocks.  (The product stands in the kernel itself: as a function that two kernels
+// call it took 1-3 % longer, 149 x 256 x 12288 backward 73.9 -> 75.8 us.)
+template <bool NN, int BM, int BN, int MAXNB = 0>
+__global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Beside<MAXNB> beside) {
+    constexpr int LDS = MAXNB > 0 && 4 * kItem<MAXNB> > kRing<BM, BN> ? 4 * kItem<MAXNB> : kRing<BM, BN>;
+    static_assert(LDS <= SG_LDS, "two items fit");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS];
+    if constexpr (MAXNB > 0) {
+        if ((int)blockIdx.x >= beside.gemm_groups) {
+            two_items(beside, lds);
+            return;
+        }
+    }
     constexpr int AT = BM * 128, BT = BN * 128, STAGE = AT + BT;   // bytes: operand tiles of one 64-wide step
     constexpr int NST = kStages<BM, BN>;                           // ring stages
     constexpr int NA = BM / 64, NB_ = BN / 64, LPS = NA + NB_;     // direct loads per wavefront and step
@@ -369,41 +405,6 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& g, unsigned char
     }
 }
 
-template <bool NN, int BM, int BN>
-__global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[kRing<BM, BN>];
-    small_gemm_body<NN, BM, BN>(g, lds);
-}
-
-// The backward product and the weight gradients of a batch that fills the chip with neither: both need dS alone and run side by side, the first
-// `gemm_groups` work groups on the tiles of dX, the others on two weight-gradient items each (four wavefronts an item).
-template <int BM, int BN, int MAXNB>
-__global__ __launch_bounds__(SG_THREADS) void small_bwd_kernel(GemmArgs g, WgradArgs w, int gemm_groups, int items) {
-    constexpr int ITEM = 2 * (WX_TILE + WT * MAXNB * 32);            // elements of LDS an item takes
-    constexpr int BYTES = kRing<BM, BN> > 4 * ITEM ? kRing<BM, BN> : 4 * ITEM;
-    static_assert(BYTES <= SG_LDS, "two items fit");
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[BYTES];
-    if ((int)blockIdx.x < gemm_groups) {
-        small_gemm_body<false, BM, BN>(g, lds);
-        return;
-    }
-    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-    const int panels = w.panels_k + w.panels_n;
-    const int item = 2 * (int)(blockIdx.x - gemm_groups) + half, other = item ^ 1;
-    const Entry4 none{0, 0, 0, 0};
-    const Entry4 e = item < items ? w.pv.wgrad_chunks[w.chunk_base + item / panels] : none;
-    const Entry4 o = other < items ? w.pv.wgrad_chunks[w.chunk_base + other / panels] : none;
-    const int steps = max(wgrad_steps(e), wgrad_steps(o));           // both halves pass the same barriers
-    if (item >= items) {
-        for (int t = 0; t <= steps; ++t) __syncthreads();
-        return;
-    }
-    u16* mine = reinterpret_cast<u16*>(lds) + half * ITEM;
-    const int panel = item % panels, tid = threadIdx.x & 255;
-    if (panel < w.panels_k) wgrad_body<MAXNB, true>(w, mine, tid, e, panel, steps);
-    else                    wgrad_body<MAXNB, false>(w, mine, tid, e, panel - w.panels_k, steps);
-}
-
 }  // namespace
 
 // `w` (backward only, may be null): the weight-gradient items that run beside the product, `items` of them, built for max_nb 32-wide rank blocks
@@ -416,12 +417,12 @@ static void launch_small(GemmArgs g, bool fwd, const WgradArgs* w, int items, in
     const int per = 8 * g.xcd_run, grid = (total + per - 1) / per * per;
     if (w) {
         const dim3 both(grid + (items + 1) / 2);
-        if (max_nb == 1) hipLaunchKernelGGL((small_bwd_kernel<BM, BN, 1>), both, dim3(SG_THREADS), 0, st, g, *w, grid, items);
-        else             hipLaunchKernelGGL((small_bwd_kernel<BM, BN, 2>), both, dim3(SG_THREADS), 0, st, g, *w, grid, items);
+        if (max_nb == 1) hipLaunchKernelGGL((small_gemm_kernel<false, BM, BN, 1>), both, dim3(SG_THREADS), 0, st, g, (Beside<1>{*w, grid, items}));
+        else             hipLaunchKernelGGL((small_gemm_kernel<false, BM, BN, 2>), both, dim3(SG_THREADS), 0, st, g, (Beside<2>{*w, grid, items}));
     } else if (fwd) {
-        hipLaunchKernelGGL((small_gemm_kernel<true, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g);
+        hipLaunchKernelGGL((small_gemm_kernel<true, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g, Beside<0>{});
     } else {
-        hipLaunchKernelGGL((small_gemm_kernel<false, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g);
+        hipLaunchKernelGGL((small_gemm_kernel<false, BM, BN>), dim3(grid), dim3(SG_THREADS), 0, st, g, Beside<0>{});
     }
 }
 

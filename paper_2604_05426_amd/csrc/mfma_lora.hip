@@ -588,9 +588,9 @@ void wgrad_kernel(WgradArgs g) {
     __shared__ __attribute__((aligned(16))) u16 lds[2 * (WX_TILE + WT * MAXNB * 32)];
     const int panels = g.panels_k + g.panels_n;
     const Entry4 e = g.pv.wgrad_chunks[g.chunk_base + blockIdx.x / panels];
-    const int panel = blockIdx.x % panels, nt = wgrad_steps(e);
-    if (panel < g.panels_k) wgrad_body<MAXNB, true, NW>(g, lds, threadIdx.x, e, panel, nt);
-    else wgrad_body<MAXNB, false, NW>(g, lds, threadIdx.x, e, panel - g.panels_k, nt);
+    const int panel = blockIdx.x % panels;
+    if (panel < g.panels_k) wgrad_body<MAXNB, true, NW>(g, lds, threadIdx.x, e, panel);
+    else wgrad_body<MAXNB, false, NW>(g, lds, threadIdx.x, e, panel - g.panels_k);
 }
 
 // Adds the chunk partials of one adapter in chunk order and rounds once.  blockIdx.y walks the adapters that have

@@ -41,9 +41,10 @@ __device__ __forceinline__ int wgrad_steps(const Entry4& e) { return (e.d + WT -
 // NW: wavefronts per work group: 4, or 8 for the wide build (64 columns x 32 ranks per wavefront: half the accumulators and half
 // the prefetch registers per wavefront, 128 registers instead of 240, so twice the wavefronts per CU hide the latency of the
 // same two work groups' loads; weight gradients of 4 x 2048 tokens at rank 128, 8192 + 28672 wide: 190 -> 173 us)
-// tid: index within the item's 64 NW threads; sync_steps: steps that the work group runs (at least the item's own: another item may share it)
-template <int MAXNB, bool isA, int NW = 4>
-__device__ __forceinline__ void wgrad_body(const WgradArgs& g, u16* lds, const int tid, const Entry4 e, const int panel, const int sync_steps) {
+// tid: index within the item's 64 NW threads; SHARED: another item has the rest of the work group, which runs sync_steps steps (at least the
+// item's own)
+template <int MAXNB, bool isA, int NW = 4, bool SHARED = false>
+__device__ __forceinline__ void wgrad_body(const WgradArgs& g, u16* lds, const int tid, const Entry4 e, const int panel, const int sync_steps = 0) {
     constexpr int NTHW = 64 * NW;
     static_assert(NW == 4 || (NW == 8 && MAXNB == 4), "8 wavefronts: wide build only");
     constexpr int SW = MAXNB * 32;                 // S / dS tile width (elements)
@@ -169,12 +170,13 @@ __device__ __forceinline__ void wgrad_body(const WgradArgs& g, u16* lds, const i
         if (nt > 2) gload(2, 0);
     }
     __syncthreads();
-    for (int tt = 0; tt < sync_steps; tt += 2) {
+    const int all = SHARED ? sync_steps : nt;
+    for (int tt = 0; tt < all; tt += 2) {
         if (tt + 1 < nt) lstore(1, 1);
         if (tt + 3 < nt) gload(tt + 3, 1);
         if (tt < nt) compute(0);
         __syncthreads();
-        if (tt + 1 < sync_steps) {
+        if (tt + 1 < all) {
             if (tt + 2 < nt) lstore(0, 0);
             if (tt + 4 < nt) gload(tt + 4, 0);
             if (tt + 1 < nt) compute(1);
