@@ -539,14 +539,15 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     ProfScope prof(p, FWD ? MLORA_K_SHRINK : MLORA_K_DSHRINK, st);
     const int64_t groups = (int64_t)p->n_row_blocks * 4;
     // Ranks per work group: 16, 64 or all.  With all of them a few row blocks of wide ranks keep a few CUs busy with the whole adapter matrix
-    // each; with 16 the rows are read once per 16 ranks (from the caches).  The lines are limits on the work groups in CUs that 309 drawn shapes
-    // give (each both ways, 64 .. 8000 tokens, contractions 64 .. 4095): with them a launch takes 3.6 % more than the best of the three on average
-    // (all ranks, always: 38 %), and at most 1.24 times what it takes with all ranks.  us, 16 / 64 / all: forward, bf16 2197 tokens, contraction 769, ranks
-    // to 100 - / 13.2 / 10.6, 414, 3076, 24 adapters to 64 15.1 / 12.1 / -, fp32 2814, 3415, rank 128 78 / 55 / 49, 333, 4000, rank 128 18.5 / - / 68.6; backward, bf16
-    // 1500, 2048, ranks to 33 8.4 / 13.0 / -, fp32 7383, 963, rank 64 28.0 / 26.1 / -.
+    // each; with 16 the rows are read once per 16 ranks (from the caches).  The lines are limits on the work groups in CUs that 295 drawn shapes
+    // give (64 .. 8000 tokens, contractions 64 .. 4095; each type and direction): with them a launch takes 3.4 % more than the best of the three
+    // on average (by the widest rank alone: 38 %), and at most 1.24 times as long as by the widest rank alone.  us, 16 / 64 / all: forward, bf16
+    // 2197 tokens, contraction 769, ranks to 100 - / 13.2 / 10.6, 414, 3076, 24 adapters to 64 15.1 / 12.1 / -, fp32 2814, 3415, rank 128 78 / 55
+    // / 49, 333, 4000, rank 128 18.5 / - / 68.6; backward, bf16 1500, 2048, ranks to 33 8.4 / 13.0 / -, fp32 7383, 963, rank 64 28.0 / 26.1 / -.
     auto items = [&](int nb) { return (p->max_rank + 16 * nb - 1) / (16 * nb); };
     const bool wide = p->max_rank > 64;
-    const int one = (sizeof(T) == 4 ? (FWD ? (wide ? 4 : 2) : (wide ? 6 : 4)) : (FWD ? (wide ? 2 : 1) : (wide ? 4 : 2))) * p->num_cus;
+    const int eighths = sizeof(T) == 4 ? (FWD ? (wide ? 32 : 28) : 48) : (FWD ? (wide ? 16 : 11) : (wide ? 28 : 16));      // of the CUs
+    const int one = eighths * p->num_cus / 8;
     const int four = p->num_cus * (FWD ? 2 : 3) / 2;
     const int nb = p->max_rank <= 16 || groups * items(1) <= one ? 1 : !wide || groups * items(4) <= four ? 4 : 8;
     a.rank_items = items(nb);
