@@ -5,8 +5,11 @@
 // frozen weight goes through the bf16 units: a fp32 value is the sum of three bf16 values, exactly (eight bits of its significand each; see
 // Range), and of the nine products of parts the six that reach 2^-24 of the whole are summed in fp32, from the smallest up.  Relative error
 // against 64 bits (standard normal operands): contraction 256 1.5e-7 -> 8.1e-8, 2048 1.8e-7 -> 1.3e-7, 4096 2.1e-7 -> 1.7e-7 (before:
-// v_mfma_f32_16x16x4_f32).  Time: 2048 x 2048 x 2048 162 -> 106 us (98 -> 162 TFLOP/s), 8000 x 512 x 512 47 -> 34; small layers, where a
-// work group's latency counts, are equal or a little faster (256 x 256 x 256 with its adapters 11.7 -> 9.8 us).
+// v_mfma_f32_16x16x4_f32).  Time: 2048 x 2048 x 2048 162 -> 106 us (106 -> 162 TFLOP/s), 8000 x 512 x 512 47 -> 34; small layers, where a
+// work group's latency counts, are equal or a little faster (256 x 256 x 256 with its adapters 11.7 -> 9.8 us).  Slower are wide outputs of
+// a contraction below about 150, forward: a work group takes 17000 cycles for a 64 x 64 tile whose products are a sixth of that, and is alone
+// on its CU, where three of the fp32 instruction's were (1500 x 80 x 3000 28 -> 41 us, 4000 x 100 x 2500 52 -> 61, with six adapters of rank
+// 128 76 -> 107).
 //
 // What bounds it: a 128 x 128 work group spends 2650 cycles per 32 elements of contraction whatever else runs (1536 of them are MFMAs; without
 // the conversions 1950, without the MFMAs 1500: the two hardly overlap, although they alternate in the code), and the clock falls to 1.85
@@ -20,7 +23,8 @@
 // the rounding of the sum.  Of those in doubt, rows (backward: and columns) of zeros and what a NaN in row or column has made NaN are right,
 // and so are small results of rows and columns that hold nothing below 2^-103 but zero and whose products are all zero or above 2^-90 (exact
 // cancellation, zero columns of W); the others are computed again with fp32 MFMAs from memory.  All of this follows from the row
-// and the column alone.
+// and the column alone.  us, 2048 x 2048 x 2048 forward / backward (ordinary values 110 / 95): one Inf in X 203 / 149, an eighth of the rows
+// with Inf 388 / 365, W zero 179 / 82, -1, 0 and 1 throughout 185 / 249; rows of zeros and NaN anywhere 108 / 97.
 //
 // Order of the sum, in all tiles (the tile follows from the number of tokens, and a row's bits must not): units of 32 elements that start at
 // multiples of 32, zero-filled at the end; the even and the odd ones are summed apart, in ascending order, and added; then each adapter's
@@ -495,36 +499,49 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
                             }
                         }
                 }
+                constexpr int YB = FWD && NB > 2 ? 2 : NB;   // blocks of a row block that are computed together (registers)
 #pragma nounroll
-                for (int b = 0; b < OB * NB; ++b) {
-                    const uint32_t mine = redo >> (4 * b) & 15;
+                for (int b = 0; b < OB * NB; b += YB) {
+                    const uint32_t mine = redo >> (4 * b) & (uint32_t)((1ull << (4 * YB)) - 1);
                     if (!__ballot(mine != 0)) continue;
                     const float* a = row_of(b / NB);
-                    const float* w = col_of(b % NB);
-                    f32x4 sum{0.f, 0.f, 0.f, 0.f}, part;
-                    uint4 av[4], wv[4], an[4], wn_[4];       // 64 elements of the contraction, and the next
-                    auto load = [&](uint4 (&to_a)[4], uint4 (&to_w)[4], int64_t k) {
+                    const float* w[YB];
+                    f32x4 sum[YB], part[YB];
 #pragma unroll
-                        for (int s = 0; s < 4; ++s) { to_a[s] = load16(a + k + 16 * s, 4); to_w[s] = load_w(w, k + 16 * s, 4); }
+                    for (int y = 0; y < YB; ++y) { w[y] = col_of(b % NB + y); sum[y] = part[y] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+                    auto multiply = [&](uint4 av, const uint4 (&wv)[YB]) {
+#pragma unroll
+                        for (int y = 0; y < YB; ++y) part[y] = block_mma<float>(wv[y], av, part[y]);
                     };
-                    const int64_t whole = g.K & ~int64_t(63);
-                    if (whole > 0) load(av, wv, 0);
-                    for (int64_t k = 0; k < whole; k += 64) {
-                        load(an, wn_, min(k + 64, whole - 64));
-                        part = f32x4{0.f, 0.f, 0.f, 0.f};
+                    auto add = [&]() {
 #pragma unroll
-                        for (int s = 0; s < 4; ++s) part = block_mma<float>(wv[s], av[s], part);
-                        sum += part;
+                        for (int y = 0; y < YB; ++y) { sum[y] += part[y]; part[y] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+                    };
+                    int64_t k = 0;
+                    for (; k + 64 <= g.K; k += 64) {
+                        uint4 av[4], wv[4][YB];              // all in flight together
 #pragma unroll
-                        for (int s = 0; s < 4; ++s) { av[s] = an[s]; wv[s] = wn_[s]; }
+                        for (int s = 0; s < 4; ++s) {
+                            av[s] = load16(a + k + 16 * s, 4);
+#pragma unroll
+                            for (int y = 0; y < YB; ++y) wv[s][y] = load_w(w[y], k + 16 * s, 4);
+                        }
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) multiply(av[s], wv[s]);
+                        add();
                     }
-                    part = f32x4{0.f, 0.f, 0.f, 0.f};
-                    for (int64_t k = whole; k < g.K; k += 16) part = block_mma<float>(load_w(w, k, valid_at(k)), load16(a + k, valid_at(k)), part);
-                    sum += part;
+                    for (; k < g.K; k += 16) {
+                        uint4 wv[YB];
+#pragma unroll
+                        for (int y = 0; y < YB; ++y) wv[y] = load_w(w[y], k, valid_at(k));
+                        multiply(load16(a + k, valid_at(k)), wv);
+                    }
+                    add();
 #pragma unroll
                     for (int c = 0; c < OB * NB; ++c)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) out[c / NB][c % NB][q] = c == b && (mine >> q & 1) ? sum[q] : out[c / NB][c % NB][q];
+                        for (int q = 0; q < 4; ++q)
+                            out[c / NB][c % NB][q] = c / YB == b / YB && (mine >> (4 * (c % YB) + q) & 1) ? sum[c % YB][q] : out[c / NB][c % NB][q];
                 }
             }
         }
