@@ -15,7 +15,7 @@
 // of S, Y, dS and dX have the same bits whatever its neighbours' tokens and ranks are.
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
-// tokens, 256 x 256: 171 -> 21 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 258 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 67 us.
+// tokens, 256 x 256: 171 -> 21 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 261 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 67 us.
 #include "general_wgrad.h"
 
 namespace mlora {
@@ -23,11 +23,11 @@ namespace mlora {
 namespace {
 
 // ---- shrink ------------------------------------------------------------------------------------------------------------------
-// Work group = 16 rows of one adapter x 16 NB of its ranks (see `shrink`); its eight wavefronts deal the contraction among themselves two neighbouring pieces at
-// a time (whole 128-byte lines of a row), straight from memory into MFMA operands (X / dY rows are read once; the adapter matrix
-// comes from the caches), with the operands of the next load in flight.  In fp32 a wavefront's pairs of pieces take turns on two accumulator
-// sets (less rounding error than one chain) and a contraction of up to eight pieces is dealt singly; the wavefronts' sums are added in
-// LDS in wavefront order.
+// Work group = 16 rows of one adapter x 16 NB of its ranks (see `shrink`); its eight wavefronts deal the contraction among themselves
+// two neighbouring pieces at a time (whole 128-byte lines of a row), straight from memory into MFMA operands (X / dY rows are read
+// once; the adapter matrix comes from the caches), with the operands of the next load in flight.  In fp32 a wavefront's pairs of
+// pieces take turns on two accumulator sets (less rounding error than one chain) and a contraction of up to eight pieces is dealt
+// singly; the wavefronts' sums are added in LDS in wavefront order.
 template <typename T> struct GenShrinkArgs {
     const T* src; int64_t ld;     // X (ld k) or dY (ld n); the contraction has ld elements
     T* out;                       // ragged S or dS
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
     }
 }
 
-// ---- bf16 products with the frozen weight, and the rank extension (fp32: f32_gemm.hip) -------------------------------------------------------------------
+// ---- bf16 products with the frozen weight, and the rank extension (fp32: f32_gemm.hip) -------------------------------------------
 struct GenGemmArgs {
     typedef u16 T;
     const T* A; const T* W;       // X (fwd) or dY (bwd); W [k][n]
