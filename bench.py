@@ -300,7 +300,8 @@ def bench_power_clock(args, np, torch, ml, wl) -> int:
     return 0
 
 
-KERNEL_SOURCES = ("mfma_common.h", "mfma_gemm.hip", "mfma_gemm_small.hip", "mfma_lora.hip", "general.hip", "adamw.hip", "plan.hip", "common.h")
+KERNEL_SOURCES = ("mfma_common.h", "mfma_gemm.hip", "mfma_gemm_small.hip", "mfma_lora.hip", "mfma_wgrad.h", "general.hip", "general_common.h",
+                  "general_wgrad.h", "f32_gemm.hip", "adamw.hip", "plan.hip", "common.h")
 
 
 def kernel_sources_sha256() -> str:
@@ -550,7 +551,9 @@ def measure_layer(config: int, args, mods, extras: bool, lora_and_base: bool, ce
             step(ml.FLAG_LORA_ONLY)
         per_lo = {}
         for kid, ms in dl.plan.profile_end(K * 16):
-            per_lo.setdefault({"gemm_fwd": "expand_add_fwd", "gemm_bwd": "expand_add_bwd", "gemm_bwd_wgrad": "expand_add_bwd_wgrad"}.get(ml.KERNEL_NAMES[kid], ml.KERNEL_NAMES[kid]), []).append(ms)
+            name = ml.KERNEL_NAMES[kid]
+            name = {"gemm_fwd": "expand_add_fwd", "gemm_bwd": "expand_add_bwd", "gemm_bwd_wgrad": "expand_add_bwd_wgrad"}.get(name, name)
+            per_lo.setdefault(name, []).append(ms)
         alg_lo = {"shrink": (T * k + sum_r * k + R1) * e, "dshrink": (T * n + sum_r * n + R1) * e,
                   "wgrad": (T * k + T * n + 2 * R1 + sum_r * (k + n)) * e,
                   "expand_add_fwd": (2 * T * n + R1 + sum_r * n) * e, "expand_add_bwd": (2 * T * k + R1 + sum_r * k) * e}

@@ -18,13 +18,13 @@
 //
 // Range: below 2^-110 a value's last parts fall under the smallest bf16, below 2^-134 all three do; close to the largest fp32 number the first part, or
 // a product of first parts, rounds to Inf, and Inf itself has no parts.  The first kind is off by 2^-125 at most an element (also
-// if the units dropped all that is denormal), times the other operand; the second leaves Inf or NaN.  So an output of K products is in doubt where it is
-// not finite or below K 2^-96 max(1, largest of its row of X, largest of its column of W): any other is off by less than 2^-27 of itself beside
-// the rounding of the sum.  Of those in doubt, rows (backward: and columns) of zeros and what a NaN in row or column has made NaN are right,
-// and so are small results of rows and columns that hold nothing below 2^-103 but zero and whose products are all zero or above 2^-90 (exact
-// cancellation, zero columns of W); the others are computed again with fp32 MFMAs from memory.  All of this follows from the row
-// and the column alone.  us, 2048 x 2048 x 2048 forward / backward (ordinary values 110 / 95): one Inf in X 203 / 149, an eighth of the rows
-// with Inf 388 / 365, W zero 179 / 82, -1, 0 and 1 throughout 185 / 249; rows of zeros and NaN anywhere 108 / 97.
+// if the units dropped all that is denormal), times the other operand; the second leaves Inf or NaN.  So an output of K products is in doubt where it
+// is not finite or below K 2^-96 max(1, largest of its row of X, largest of its column of W): any other is off by less than 2^-27 of itself beside
+// the rounding of the sum.  Of those in doubt, rows (backward: and columns) of zeros and what a NaN in row or column has made NaN are right, and so
+// are small results of rows and columns that hold nothing below 2^-103 but zero and whose products are all zero or above 2^-90 (exact cancellation,
+// zero columns of W); the others are computed again with fp32 MFMAs from memory.  All of this follows from the row and the column alone.  us, 2048 x
+// 2048 x 2048 forward / backward (ordinary values 110 / 95): one Inf in X 203 / 149, an eighth of the rows with Inf 388 / 365, W zero 179 / 82, -1, 0
+// and 1 throughout 185 / 249; rows of zeros and NaN anywhere 108 / 97.
 //
 // Order of the sum, in all tiles (the tile follows from the number of tokens, and a row's bits must not): units of 32 elements that start at
 // multiples of 32, zero-filled at the end; the even and the odd ones are summed apart, in ascending order, and added; then each adapter's

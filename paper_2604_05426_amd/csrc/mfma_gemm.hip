@@ -591,8 +591,8 @@ __global__ __launch_bounds__(NTHR) void fused_gemm_kernel(GemmArgs g) {
 // 2048 (0.88, 0.19) 70.6 / 64.5, 1200 x 1024 x 3072 (0.59, 0.38) 64.7 / 57.6, 818 x 1024 x 3072 (0.81, 0.25) 57.4 / 48.7, 1200 x 2048 x 4096
 // (0.62, 0.28) 106 / 104, 600 x 768 x 8192 (0.47, 0.14) 78.8 / 75.2; not: 2000 x 2048 x 1024 (1.0, 0.19) 64.6 / 68.2, 1200 x 768 x 4096 (0.89,
 // 0.22) 73.9 / 76.5, 500 x 4096 x 3072 (1.0, 0.11) 74.6 / 76.5, 2000 x 768 x 8192 (0.75, 0.55) 96.0 / 99.4, 1200 x 2048 x 5120 (0.62, 0.33)
-// 102.2 / 105.8, 300 x 1024 x 14336 (0.31, 1.9) 113.0 / 115.4, 200 x 5120 x 14336 (0.62, 0.30) 126 / 138.  Over 150 drawn shapes (64 .. 3000 tokens) a backward call takes 2.2 %
-// more than the better of the two on average (always apart 10.8 %), and at most 1.4 % more than apart.
+// 102.2 / 105.8, 300 x 1024 x 14336 (0.31, 1.9) 113.0 / 115.4, 200 x 5120 x 14336 (0.62, 0.30) 126 / 138.  Over 150 drawn shapes (64 .. 3000 tokens)
+// a backward call takes 2.2 % more than the better of the two on average (always apart 10.8 %), and at most 1.4 % more than apart.
 static bool side_by_side(int tile, const GemmArgs& g, int items, int num_cus) {
     const int64_t bm = tile == 0 ? 128 : 64, bn = tile == 2 ? 64 : 128;
     const int64_t groups = ((g.M + bm - 1) / bm) * ((g.Ncols + bn - 1) / bn);

@@ -370,10 +370,11 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
 #pragma unroll
                 for (int j = 0; j < NCB; ++j) acc[j] = mfma16(a[u][k32], b[u][k32][j], acc[j]);
     };
-    // Two steps per barrier: a launch of few blocks takes 1-4 % less (1024 tokens, k = 14336 40.4 -> 39.1 us; 1131 tokens, k = 4864 14.0 -> 13.5; backward
-    // 3000 tokens, n = 1024 10.4 -> 10.0), some take 1 % more (6369 tokens, n = 3328, ranks to 128 40.8 -> 41.2); what is left of a step is the load path: with every load a cache hit it still takes 0.2 of 0.28 us.
-    // Wait until the next STEPS steps have landed (only the loads of the later ones may be in flight) and every wavefront is past the steps
-    // before, whose slots the next loads overwrite; load as many steps and multiply.
+    // Two steps per barrier: a launch of few blocks takes 1-4 % less (1024 tokens, k = 14336 40.4 -> 39.1 us; 1131 tokens, k = 4864 14.0 -> 13.5;
+    // backward 3000 tokens, n = 1024 10.4 -> 10.0), some take 1 % more (6369 tokens, n = 3328, ranks to 128 40.8 -> 41.2); what is left of a step is
+    // the load path: with every load a cache hit it still takes 0.2 of 0.28 us.  Wait until the next STEPS steps have landed (only the loads of the
+    // later ones may be in flight) and every wavefront is past the steps before, whose slots the next loads overwrite; load as many steps and
+    // multiply.
     auto advance = [&](auto count, int& slot) {
         constexpr int STEPS = decltype(count)::value;
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NX + NF) * (AHEAD - STEPS)) : "memory");
