@@ -21,10 +21,12 @@
 // if the units dropped all that is denormal), times the other operand; the second leaves Inf or NaN.  So an output of K products is in doubt where it
 // is not finite or below K 2^-96 max(1, largest of its row of X, largest of its column of W): any other is off by less than 2^-27 of itself beside
 // the rounding of the sum.  Of those in doubt, rows (backward: and columns) of zeros and what a NaN in row or column has made NaN are right, and so
-// are small results of rows and columns that hold nothing below 2^-103 but zero and whose products are all zero or above 2^-90 (exact cancellation,
-// zero columns of W); the others are computed again with fp32 MFMAs from memory.  All of this follows from the row and the column alone.  us, 2048 x
-// 2048 x 2048 forward / backward (ordinary values 110 / 95): one Inf in X 203 / 149, an eighth of the rows with Inf 388 / 365, W zero 179 / 82, -1, 0
-// and 1 throughout 185 / 249; rows of zeros and NaN anywhere 108 / 97.
+// are small sums of two halves (see Order) that are not small: one output in 10^8 of ordinary values is an exact zero by rounding alone, and to
+// search its row and column takes the launch 104 -> 130 us at 2048 x 2048 x 2048.  Right are also small results of rows and columns that hold nothing
+// below 2^-103 but zero and whose products are all zero or above 2^-90 (cancellation inside a half, zero columns of W); the others are computed again
+// with fp32 MFMAs from memory.  All of this follows from the row and the column alone.  us, 2048 x 2048 x 2048 forward / backward (ordinary values
+// 110 / 95): one Inf in X 175 / 152, an eighth of the rows with Inf 348 / 369, W zero 183 / 82, eight of its columns zero 145 / 94, -1, 0 and 1
+// throughout 183 / 252; rows of zeros and NaN anywhere 106 / 97.
 //
 // Order of the sum, in all tiles (the tile follows from the number of tokens, and a row's bits must not): units of 32 elements that start at
 // multiples of 32, zero-filled at the end; the even and the odd ones are summed apart, in ascending order, and added; then each adapter's
@@ -452,6 +454,14 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
                     }
             if (__ballot(redo != 0)) {
                 constexpr int AT = BT == 128 ? 2 : 4;        // 16-wide steps of the contraction whose loads are in flight together
+                // The blocks stand in LDS, lane by lane, so that the loops over them need not be unrolled: with the unrolled code here, the contraction
+                // is allocated worse (ordinary values, 2048 x 2048 x 2048: 106.3 / 122.1 us forward / backward with weight gradients instead of 105.2 /
+                // 120.5; without any check 104.6 / 118.6)
+                f32x4* const held = reinterpret_cast<f32x4*>(lds) + ((8 + wave) * OB * NB) * 64 + lane;
+                const f32x4* const half = reinterpret_cast<const f32x4*>(lds) + ((wave ^ 4) * OB * NB) * 64 + lane;      // (stays until the extension)
+                static_assert(16 * OB * NB * 64 * 16 <= SLOTS * STAGE, "two blocks' exchange fits the ring");
+#pragma unroll
+                for (int b = 0; b < OB * NB; ++b) held[b * 64] = out[b / NB][b % NB];
                 auto row_of = [&](int x) { return g.A + min(m0 + (xb + x) * 16 + l16, g.M - 1) * g.lda + 4 * g4; };
                 auto col_of = [&](int y) {
                     const int64_t col = min(n0 + (wn * NB + y) * 16 + l16, g.N - 1);
@@ -459,6 +469,22 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
                 };
                 auto load_w = [&](const float* w, int64_t k, int valid) { return FWD ? gather16(w + k * g.ldw, g.ldw, valid) : load16(w + k, valid); };
                 auto valid_at = [&](int64_t k) { return (int)max((int64_t)0, min((int64_t)4, g.K - k - 4 * g4)); };
+                if (__ballot(small)) {                       // halves that cancel: their sum is exact, so either one gives both
+                    small = false;
+#pragma nounroll
+                    for (int b = 0; b < OB * NB; ++b) {
+                        if (!__ballot((redo >> (4 * b) & 15) != 0)) continue;
+                        const f32x4 v = held[b * 64], h = half[b * 64];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float top = least * fmaxf(fmaxf(row_top(b / NB), col_top(b % NB, q)), 1.f);
+                            const uint32_t bit = 1u << (4 * b + q);
+                            const bool finite = fabsf(v[q]) < __builtin_inff();
+                            if (finite && fabsf(h[q]) >= 3.f * top && fmaxf(fabsf(h[q]), fabsf(v[q] - h[q])) >= 4.f * top) redo &= ~bit;
+                            small = small || (finite && (redo & bit));
+                        }
+                    }
+                }
                 if (__ballot(small)) {                       // the smallest magnitudes but zero, as bits; small results of none that lose bits are right
                     uint32_t lo[OB + NB];
                     const float* src[OB + NB];
@@ -494,7 +520,7 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
 #pragma unroll
                             for (int x = 0; x < OB; ++x) {
                                 const float r = value(lo[x]);
-                                const bool right = fabsf(out[x][y][q]) < __builtin_inff() && r >= 0x1p-103f && c >= 0x1p-103f && r * c >= 0x1p-90f;
+                                const bool right = fabsf(held[(x * NB + y) * 64][q]) < __builtin_inff() && r >= 0x1p-103f && c >= 0x1p-103f && r * c >= 0x1p-90f;
                                 redo &= ~((uint32_t)right << (4 * (x * NB + y) + q));
                             }
                         }
@@ -538,11 +564,15 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
                     }
                     add();
 #pragma unroll
-                    for (int c = 0; c < OB * NB; ++c)
+                    for (int y = 0; y < YB; ++y) {
+                        f32x4 v = held[(b + y) * 64];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            out[c / NB][c % NB][q] = c / YB == b / YB && (mine >> (4 * (c % YB) + q) & 1) ? sum[c % YB][q] : out[c / NB][c % NB][q];
+                        for (int q = 0; q < 4; ++q) v[q] = mine >> (4 * y + q) & 1 ? sum[y][q] : v[q];
+                        held[(b + y) * 64] = v;
+                    }
                 }
+#pragma unroll
+                for (int b = 0; b < OB * NB; ++b) out[b / NB][b % NB] = held[b * 64];
             }
         }
     }

@@ -126,3 +126,50 @@ def test_small_values_in_ordinary_rows(T, k, n):
         Y, dX = _products(X.cuda(), W.cuda(), dY.cuda())
         _check_all(Y, X, W)
         _check_all(dX, dY, W.T)
+
+
+def _times(calls):
+    """Least time of each call, us, taken in turn (eager launches on one stream)."""
+    best = [float("inf")] * len(calls)
+    for _ in range(12):
+        for i, call in enumerate(calls):
+            call()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) * 100)
+    return best
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("T,N", [(128, 128), (512, 1024), (2048, 2048)])
+def test_outputs_that_cancel_take_no_longer(T, N, transposed):
+    """One output in 10^8 of ordinary values is an exact zero: the halves of its sum (units 0, 2, .. and 1, 3, ..) cancel.  Its row and column are not
+    searched for small values: as fast as without (the search takes 1.2 to 3 times the product here; noise is a few per cent)."""
+    K, g = 16384 if N < 2048 else 4096, torch.Generator().manual_seed(T)
+    A, B = torch.randn((T, K), generator=g), torch.randn((N, K), generator=g)
+    A[5] = 0.0
+    A[5, 0] = A[5, 32] = 1.0
+    plain = B.clone()
+    B[N // 2, 32] = -B[N // 2, 0]
+    calls, results = [], []
+    for b in (plain, B):
+        A_, W = A.cuda(), (b if transposed else b.T.contiguous()).cuda()
+        plan = ml.Plan(ml.F32, T, *W.shape, [], [], [0])
+        out, ws = torch.full((T, N), float("nan"), device="cuda"), torch.empty(256, dtype=torch.uint8, device="cuda")
+        if transposed:
+            calls.append(lambda p=plan, a=A_, w=W, o=out, s=ws: ml.multi_lora_bwd(p, a, a, w, [], [], None, o, [], [], s))
+        else:
+            calls.append(lambda p=plan, a=A_, w=W, o=out, s=ws: ml.multi_lora_fwd(p, a, w, [], [], o, None, s))
+        results.append((out, plan))
+    ordinary, cancelling = _times(calls)
+    print(f"[case] cancelling output T={T} N={N} K={K}: {ordinary:.1f} us, {cancelling:.1f} us", flush=True)
+    got = results[1][0].cpu()
+    assert got[5, N // 2] == 0.0
+    assert torch.equal(got[5].float(), (B[:, 0].double() + B[:, 32].double()).float())
+    for _, plan in results:
+        plan.destroy()
+    assert cancelling < 1.12 * ordinary
