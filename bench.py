@@ -300,8 +300,8 @@ def bench_power_clock(args, np, torch, ml, wl) -> int:
     return 0
 
 
-KERNEL_SOURCES = ("mfma_common.h", "mfma_gemm.hip", "mfma_gemm_small.hip", "mfma_lora.hip", "mfma_wgrad.h", "general.hip", "general_common.h",
-                  "general_wgrad.h", "f32_gemm.hip", "adamw.hip", "plan.hip", "common.h")
+# what a bf16 layer of aligned widths runs
+KERNEL_SOURCES = ("mfma_common.h", "mfma_gemm.hip", "mfma_gemm_small.hip", "mfma_lora.hip", "mfma_wgrad.h", "adamw.hip", "plan.hip", "common.h")
 
 
 def kernel_sources_sha256() -> str:

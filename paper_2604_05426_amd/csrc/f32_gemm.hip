@@ -456,7 +456,7 @@ __device__ __forceinline__ void f32_gemm_body(const F32GemmArgs& g, unsigned cha
                 constexpr int AT = BT == 128 ? 2 : 4;        // 16-wide steps of the contraction whose loads are in flight together
                 // The blocks stand in LDS, lane by lane, so that the loops over them need not be unrolled: with the unrolled code here, the contraction
                 // is allocated worse (ordinary values, 2048 x 2048 x 2048: 106.3 / 122.1 us forward / backward with weight gradients instead of 105.2 /
-                // 120.5; without any check 104.6 / 118.6)
+                // 120.5)
                 f32x4* const held = reinterpret_cast<f32x4*>(lds) + ((8 + wave) * OB * NB) * 64 + lane;
                 const f32x4* const half = reinterpret_cast<const f32x4*>(lds) + ((wave ^ 4) * OB * NB) * 64 + lane;      // (stays until the extension)
                 static_assert(16 * OB * NB * 64 * 16 <= SLOTS * STAGE, "two blocks' exchange fits the ring");
