@@ -15,7 +15,7 @@
 // of S, Y, dS and dX have the same bits whatever its neighbours' tokens and ranks are.
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
-// tokens, 256 x 256: 171 -> 21 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 261 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 67 us.
+// tokens, 256 x 256: 171 -> 21 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 265 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 67 us.
 #include "general_wgrad.h"
 
 namespace mlora {
