@@ -128,6 +128,28 @@ def test_small_values_in_ordinary_rows(T, k, n):
         _check_all(dX, dY, W.T)
 
 
+@pytest.mark.parametrize("T,k,n", [(40, 64, 96), (700, 500, 515), (2051, 1111, 514)])
+@pytest.mark.parametrize("scale", [0, -80, -90, -100, -125, -140])
+def test_halves_that_cancel(T, k, n, scale):
+    """Sums of one value in an even and one in an odd unit, nearly or wholly opposite, from ordinary size to below what the parts hold: the halves
+    above the limit stand, those below are computed again.  Both are exact in fp32, and so is their sum."""
+    g = torch.Generator().manual_seed(T - scale)
+    print(f"[case] fp32 halves that cancel T={T} k={k} n={n} scale={scale}", flush=True)
+    for transposed in (False, True):
+        K, N = (n, k) if transposed else (k, n)
+        A, B = torch.zeros((T, K)), torch.randn((N, K), generator=g)
+        A[:, 0] = A[:, 32] = 1.0
+        B[:, 0] *= 2.0 ** scale
+        B[:, 32] = -B[:, 0]
+        B[::3, 32] *= 1 + 2.0 ** -20
+        A, B = A.cuda(), B.cuda()
+        W = B if transposed else B.T.contiguous()
+        X, dY = (torch.ones((T, k), device="cuda"), A) if transposed else (A, torch.ones((T, n), device="cuda"))
+        got = _products(X, W, dY)[1 if transposed else 0]
+        want = (B[:, 0].double() + B[:, 32].double()).float().cpu()
+        assert torch.equal(got, want.expand(T, N))
+
+
 def _times(calls):
     """Least time of each call, us, taken in turn (eager launches on one stream)."""
     best = [float("inf")] * len(calls)
