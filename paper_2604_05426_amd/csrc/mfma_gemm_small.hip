@@ -3,25 +3,26 @@
 // one store of the output, like the large-tile kernel.
 //
 // With one 256 x 256 tile per CU a layer of 1024 x 4096 outputs keeps 64 of 256 CUs busy for the whole contraction; 128 x 128
-// tiles keep all of them busy.  What bounds a CU then is the operand stream (32 KB per 64-wide step against 512 cycles of MFMA)
-// and, before that, latency, so the tiles come by direct global -> LDS loads into a ring that fills the LDS (all but the
-// current step in flight, one barrier per step) and the fragments of each 32-wide half step are read while the one before it is
-// multiplied.
+// tiles keep all of them busy.  What bounds a CU then is the operand stream: 32 KB per 64-wide step at the 47-51 B/clk its load path takes are
+// 640-690 cycles, against 512 of MFMA.  Four wavefronts load (direct global -> LDS loads into rings that fill the LDS, one barrier per step)
+// and four multiply, one of each per SIMD: sub-tiles of a quarter of the tile need a third fewer LDS reads than eighths, no MFMA waits behind
+// the issue of a load, and the fragments of the next step (128 x 128: half step) are read while one is multiplied.  Cycles per step, eight
+// wavefronts that do both / now: 128 x 128 forward 847 / 697, backward 805 / 660; 64 x 128 632 / 500 and 519 / 515; 64 x 64 460 / 343 and 430 / 355
+// (without direct loads 128 x 128 takes 690-750: both halves of the work group are near their own limit).
 //
 // Order of the sum: every output element is one chain of MFMAs - rank extension, contraction in ascending order, tail - exactly as in
 // the 256 x 256 kernel, so that a row has the same bits whichever tile its batch is given: the tile follows from the number of tokens
-// of the whole batch, and a job's results must not change when a neighbour joins or leaves it.  That is why the 8 wavefronts
-// (2 x 4 sub-tiles of the output, two per SIMD) do not share a step's contraction among themselves; with 2 x 2 sub-tiles and the
-// two halves of a step summed apart the LDS reads per MFMA were a third fewer; over 190 products the mean time moved by -2.5 %
-// (128 x 128), 0 (64 x 128) and +5 % (64 x 64).
+// of the whole batch, and a job's results must not change when a neighbour joins or leaves it.  That is why the wavefronts (2 x 2 sub-tiles of
+// the output) do not share a step's contraction among themselves.
 //
-// Rank extension: adapter by adapter into a second accumulator set, of which the adapter's own rows are then taken over (scaled
+// Rank extension: adapter by adapter into the accumulators, of which only the adapter's own rows take the result over (scaled
 // in fp32).  Rows of other adapters never reach the result, so no operand has to be masked and a diverged neighbour's Inf / NaN
 // stays out of it.
 //
-// 1000 x 4096 outputs, k = 4096: 85 us with 256 x 256 tiles, 40 with 128 x 128; 200 x 512, k = 2048: 67 and, with 64 x 64, 14.  A
-// 128 x 128 work group spends about 0.5 us per step with all CUs busy (32 KB of operands at the 45-50 B/clk a CU's load path takes
-// are 0.3), where the MFMAs alone would take 0.21.
+// us, 256 x 256 tiles / eight wavefronts that load and multiply / now: 1024 x 14336 x 4096 forward - / 112 / 102, its weight from HBM 133 / 121; 1024 x
+// 4096 x 4096 forward with eight adapters, with its shrink, - / 46.0 / 43.5; 200 x 512, k = 2048: 67 / 9.2 / 8.1.
+#include <type_traits>
+
 #include "mfma_wgrad.h"
 
 namespace mlora {
@@ -36,9 +37,10 @@ template <int N> __device__ __forceinline__ void wait_loads_and_barrier() {
 }
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// bytes of LDS: ring stages of the operand tiles of one 64-wide step
-template <int BM, int BN> constexpr int kStages = SG_LDS / ((BM + BN) * 128) < 8 ? SG_LDS / ((BM + BN) * 128) : 8;
-template <int BM, int BN> constexpr int kRing = kStages<BM, BN> * (BM + BN) * 128;
+// Stages of the two rings, operand tiles of 64-wide steps: the rows (X / dY, which the shrink has just read) and the weight, which comes from further away
+template <int BM, int BN> constexpr int kStagesA = BN == 64 ? 5 : BM == 64 ? 4 : 3;
+template <int BM, int BN> constexpr int kStagesB = (SG_LDS - kStagesA<BM, BN> * BM * 128) / (BN * 128);
+template <int BM, int BN> constexpr int kRing = kStagesA<BM, BN> * BM * 128 + kStagesB<BM, BN> * BN * 128;      // bytes of LDS
 
 // The weight gradients of a batch that fills the chip with neither go with the backward product: both need dS alone and run side by side, the
 // first `gemm_groups` work groups on the tiles of dX, the others on two weight-gradient items each (four wavefronts an item).
@@ -78,16 +80,17 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
             return;
         }
     }
-    constexpr int AT = BM * 128, BT = BN * 128, STAGE = AT + BT;   // bytes: operand tiles of one 64-wide step
-    constexpr int NST = kStages<BM, BN>;                           // ring stages
-    constexpr int NA = BM / 64, NB_ = BN / 64, LPS = NA + NB_;     // direct loads per wavefront and step
-    constexpr int WTM = BM / 2, WTN = BN / 4;                      // sub-tile of a wavefront
+    constexpr int AT = BM * 128, BT = BN * 128;                    // bytes: operand tiles of one 64-wide step
+    constexpr int NSA = kStagesA<BM, BN>, NSB = kStagesB<BM, BN>;  // ring stages
+    constexpr int B0 = NSA * AT;                                   // where the weight's ring starts
+    constexpr int NA = BM / 32, NB_ = BN / 32;                     // direct loads per multiplying wavefront and pass (rank extension, tail)
+    constexpr int WTM = BM / 2, WTN = BN / 2;                      // sub-tile of a multiplying wavefront
     constexpr int MB = WTM / 16, NB = WTN / 16;
     constexpr int BROW = BN * 2;                                   // NN: bytes per contraction row of the weight tile
-    static_assert(LPS * (NST - 2) < 64, "vmcnt holds 6 bits");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 2, wn = wave & 3;
+    const bool loader = wave >= 4;       // wavefronts 4 .. 7 load (4, 5 the rows, 6, 7 the weight), 0 .. 3 multiply
+    const int wm = (wave >> 1) & 1, wn = wave & 1;
     const int l16 = lane & 15, g4 = lane >> 4;
 
     // Tile order: bands of 8 row tiles x all column tiles, numbered down the rows first; every XCD (blockIdx % 8) takes runs of
@@ -108,46 +111,9 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
 
     // ---- direct loads ---------------------------------------------------------------------------
     const int nk = g.Kdim / 64;
-    unsigned oa[NA], ob[NB_];
-#pragma unroll
-    for (int c = 0; c < NA; ++c) {
-        const int row = (wave * NA + c) * 8 + (lane >> 3), ch = (lane & 7) ^ (lane >> 3);
-        oa[c] = (unsigned)((int64_t)(min(m0 + row, g.M - 1) - m0) * g.lda + ch * 8) * 2u;
-    }
-#pragma unroll
-    for (int c = 0; c < NB_; ++c) {
-        const int kb = wave * NB_ + c;
-        if (NN) {
-            constexpr int LPR = BROW / 16;
-            const int k = kb * (64 / LPR) + lane / LPR, pos = lane % LPR;
-            const int chunk = (((pos >> 1) ^ fkey(k)) << 1) | (pos & 1);
-            ob[c] = (unsigned)((int64_t)k * g.ldb + min(n0 + chunk * 8, g.Ncols - 8)) * 2u;
-        } else {
-            const int row = kb * 8 + (lane >> 3), ch = (lane & 7) ^ (lane >> 3);
-            ob[c] = (unsigned)((int64_t)(min(n0 + row, g.Ncols - 1) - n0) * g.ldb + ch * 8) * 2u;
-        }
-    }
-    const char* baseA = uniform_ptr(g.Aop + (int64_t)m0 * g.lda);
-    const char* baseB = NN ? uniform_ptr(g.Bop) : uniform_ptr(g.Bop + (int64_t)n0 * g.ldb);
-    const int64_t bstep = NN ? (int64_t)64 * g.ldb * 2 : 128;
     const unsigned lds0 = (unsigned)(uintptr_t)lds;
-    int slot_in = 0;
-    auto issue1 = [&](int c) {           // load c (of LPS) of the next step's tiles into the next ring slot
-        const unsigned dst = lds0 + slot_in * STAGE;
-        if (c < NA) dma16(oa[c < NA ? c : 0], baseA, dst + (wave * NA + c) * 1024);
-        else        dma16(ob[c < NA ? 0 : c - NA], baseB, dst + AT + (wave * NB_ + c - NA) * 1024);
-        if (c == LPS - 1) {
-            baseA += 128; baseB += bstep;
-            slot_in = slot_in == NST - 1 ? 0 : slot_in + 1;
-        }
-    };
-    auto issue = [&]() {
-#pragma unroll
-        for (int c = 0; c < LPS; ++c) issue1(c);
-    };
-    // all slots but the last, which the rank extension uses first
-    const int early = min(nk, NST - 1);
-    for (int t = 0; t < early; ++t) issue();
+    constexpr int LPR = BROW / 16;       // NN: lanes of a contraction row
+    constexpr int CA = BM / 8, CB = BN / 8;          // pieces of 1 KB, a load each, of a step's tiles
 
     // ---- fragments and MFMAs ----------------------------------------------------------------------
     f32x4 acc[MB][NB];
@@ -155,245 +121,382 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
     for (int a = 0; a < MB; ++a)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 fa[2][MB], fb[2][NB];
-    // a step is two 32-wide halves h; the fragments of one are read while the other is multiplied
+    // Register sets: what is multiplied and what is read meanwhile, U 32-wide halves of a step each (128 x 128: one, or they would spill)
+    constexpr int U = MB * NB < 16 ? 2 : 1;
+    static_assert(U == 2 || MB == NB, "a row block and a column block with each group of products");
+    bf16x8 fa[2][U][MB], fb[2][U][NB];
     const int a_off = (wm * WTM + l16) * 128, bnt_off = (wn * WTN + l16) * 128;
     const int vq = fkey(8 * g4 + (l16 >> 2));
     const int bnn_off = (8 * g4 + (l16 >> 2)) * BROW + (l16 & 3) * 8;
-    auto read_frag_a = [&](int slot, int h, int a) {
-        fa[h][a] = lds_read_frag(reinterpret_cast<const u16*>(lds + slot * STAGE + a_off + (((h * 4 + g4) ^ (l16 & 7)) << 4) + a * 2048));
+    auto frag_a = [&](int slot, int h, int a) {
+        return lds_read_frag(reinterpret_cast<const u16*>(lds + slot * AT + a_off + (((h * 4 + g4) ^ (l16 & 7)) << 4) + a * 2048));
     };
-    auto read_frag_b = [&](int slot, int h, int b) {
-        const unsigned char* Bs = lds + slot * STAGE + AT;
+    auto frag_b = [&](int slot, int h, int b) {
+        const unsigned char* Bs = lds + B0 + slot * BT;
         if (NN) {
             const unsigned char* p = Bs + bnn_off + h * 32 * BROW + (((wn * NB + b) ^ vq) << 5);
-            fb[h][b] = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * BROW));
-        } else {
-            fb[h][b] = lds_read_frag(reinterpret_cast<const u16*>(Bs + bnt_off + (((h * 4 + g4) ^ (l16 & 7)) << 4) + b * 2048));
+            return lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * BROW));
         }
+        return lds_read_frag(reinterpret_cast<const u16*>(Bs + bnt_off + (((h * 4 + g4) ^ (l16 & 7)) << 4) + b * 2048));
     };
-    auto read_frags = [&](int slot, int h) {
-#pragma unroll
-        for (int a = 0; a < MB; ++a) read_frag_a(slot, h, a);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) read_frag_b(slot, h, b);
+    // fragment i of a set that starts with half h0 of the step in slots slot_a, slot_b, in the order the products want them
+    constexpr int NF = U * (MB + NB);
+    auto read_frag = [&](int slot_a, int slot_b, int h0, int set, int i) {
+        const int u = i / (MB + NB), j = i % (MB + NB);
+        if (j < NB) fb[set][u][j] = frag_b(slot_b, h0 + u, j);
+        else        fa[set][u][j - NB] = frag_a(slot_a, h0 + u, j - NB);
     };
-    // ask the scheduler to alternate a group's LDS reads with its MFMAs
-    auto interleave = [&]() {
-        for (int i = 0; i < NB; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, NB == 1 ? 3 : 1, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    int sa = 0, sb = 0;                  // slots of the step that is read
+    auto read_set = [&](int h0, int set) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) read_frag(sa, sb, h0, set, f);
     };
-    // operands swapped: a lane ends with one output row and 4 consecutive columns of each 16 x 16 block
-    auto mma = [&](f32x4 (&c)[MB][NB], int h) {
+    // The products of register set `set`; with `read` the next set's fragments are read meanwhile, most of them early.  Operands swapped: a
+    // lane ends with one output row and 4 consecutive columns of each 16 x 16 block.
+    auto multiply = [&](auto set_, bool read, int h0) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_)::value;
 #pragma unroll
-        for (int a = 0; a < MB; ++a)
+        for (int i = 0; i < U * MB; ++i) {
+            const int u = i / MB, a = i % MB;
+            constexpr int G = U * MB > 4 ? U * MB - 2 : U * MB - 1;            // U = 2: groups of products that the reads go with
+            __builtin_amdgcn_sched_barrier(0);
+            if (read && U == 1) {                        // a row block and a column block with each group
+                read_frag(sa, sb, h0, set ^ 1, NB + a);
+                read_frag(sa, sb, h0, set ^ 1, a);
+            } else if (read) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) c[a][b] = mfma16(fb[h][b], fa[h][a], c[a][b]);
-    };
-
-    // Operands that are not whole aligned 64-wide steps (rank extension, tail of the contraction) go through registers into the
-    // last slot, zero-filled up to a multiple of 32 in the contraction.
-    unsigned char* const Ps = lds + (NST - 1) * STAGE;
-    uint4 pa[NA], pb[NB_];
-    auto pass_load = [&](const u16* a_src, int64_t a_ld, int a_lo, int a_hi, bool a_vec, const u16* b_src, int64_t b_ld, bool b_vec,
-                         int kc) {                  // a_src: row a_lo
+                for (int f = i * NF / G; f < (i + 1) * NF / G && f < NF; ++f) read_frag(sa, sb, h0, set ^ 1, f);
+            }
 #pragma unroll
-        for (int c = 0; c < NA; ++c) {
-            const int idx = tid + SG_THREADS * c, t = m0 + (idx & (BM - 1)), cc = idx / BM;
-            pa[c] = zero4();
-            if (t >= a_lo && t < a_hi && cc * 8 < kc) pa[c] = load_chunk(a_src + (int64_t)(t - a_lo) * a_ld + cc * 8, min(8, kc - cc * 8), a_vec);
-        }
-#pragma unroll
-        for (int c = 0; c < NB_; ++c) {
-            const int idx = tid + SG_THREADS * c;
-            pb[c] = zero4();
-            if (NN) {
-                const int k = idx / (BN / 8), gcol = n0 + (idx % (BN / 8)) * 8;
-                if (k < kc && gcol < g.Ncols) pb[c] = *reinterpret_cast<const uint4*>(b_src + (int64_t)k * b_ld + gcol);
-            } else {
-                const int gcol = n0 + (idx & (BN - 1)), cc = idx / BN;
-                if (gcol < g.Ncols && cc * 8 < kc) pb[c] = load_chunk(b_src + (int64_t)gcol * b_ld + cc * 8, min(8, kc - cc * 8), b_vec);
+            for (int b = 0; b < NB; ++b) acc[a][b] = mfma16(fb[set][u][b], fa[set][u][a], acc[a][b]);
+            if (read) {
+                for (int x = 0; x < NB; ++x) {
+                    if (U == 1) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, (NN ? 2 : 1) * (MB == 2 && NB == 2 ? 2 : 1), 0);
+                    if (U == 2) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
-    auto pass_store = [&](int kc) {
-        const int kpad = (kc + 31) & ~31;
+    const std::integral_constant<int, 0> zero{};
+    const std::integral_constant<int, 1> one{};
+    // ---- passes: at most 64 contraction elements that are not a whole step (rank extension, tail), through the last two slots of each ring ----
+    // Rows outside [lo, hi) repeat the first or last one inside and columns past the edge the last ones; their results are dropped.  Chunks
+    // past kc repeat the first and are taken as zero (take_pass).  Element (row t, c) of the row operand at a[(t - lo) a_ld + c], of the weight's
+    // at b[c b_ld + col] (NN) or b[(col - n0) b_ld + c].
+    auto dma_pass = [&](int slot /* 0: the rings' last, 1: the ones before */, const void* a, int64_t a_ld, int lo, int hi, const void* b, int64_t b_ld, int kc) {
+        const char* ab = uniform_ptr(a);
+        const char* bb = uniform_ptr(b);
+        const unsigned dst_a = lds0 + (NSA - 1 - slot) * AT, dst_b = lds0 + B0 + (NSB - 1 - slot) * BT;
 #pragma unroll
         for (int c = 0; c < NA; ++c) {
-            const int idx = tid + SG_THREADS * c, row = idx & (BM - 1), cc = idx / BM;
-            if (cc * 8 < kpad) *reinterpret_cast<uint4*>(Ps + row * 128 + ((cc ^ (row & 7)) << 4)) = pa[c];
+            const int row = (wave * NA + c) * 8 + (lane >> 3), ch = (lane & 7) ^ (lane >> 3);
+            const unsigned v = (unsigned)((int64_t)(min(max(m0 + row, lo), hi - 1) - lo) * a_ld + (ch * 8 < kc ? ch : 0) * 8) * 2u;
+            dma16(v, ab, dst_a + (wave * NA + c) * 1024);
         }
 #pragma unroll
         for (int c = 0; c < NB_; ++c) {
-            const int idx = tid + SG_THREADS * c;
+            const int kb = wave * NB_ + c;
+            unsigned v;
+            if (NN) {
+                const int k = kb * (64 / LPR) + lane / LPR, pos = lane % LPR;
+                const int chunk = (((pos >> 1) ^ fkey(k)) << 1) | (pos & 1);
+                v = (unsigned)((int64_t)(k < kc ? k : 0) * b_ld + min(n0 + chunk * 8, g.Ncols - 8)) * 2u;
+            } else {
+                const int row = kb * 8 + (lane >> 3), ch = (lane & 7) ^ (lane >> 3);
+                v = (unsigned)((int64_t)(min(n0 + row, g.Ncols - 1) - n0) * b_ld + (ch * 8 < kc ? ch : 0) * 8) * 2u;
+            }
+            dma16(v, bb, dst_b + kb * 1024);
+        }
+    };
+    // The same for rows of r elements that start anywhere (ranks that are no multiples of 8): elements r0 .. r0 + kc - 1 of each, through
+    // registers.  A piece that would reach past its row is loaded from where it still fits and shifted.
+    auto row_piece = [&](const u16* row, int r, int at) {
+        if (r < 8) return load_chunk(row + min(at, r), max(0, r - at), false);
+        const int from = min(at, r - 8), sh = min((at - from) * 16, 128);
+        uint4 v;
+        __builtin_memcpy(&v, row + from, 16);
+        const uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+        const uint64_t l = sh == 0 ? lo : sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : sh < 128 ? hi >> (sh - 64) : 0, h = sh < 64 ? hi >> sh : 0;
+        return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+    };
+    auto stage_pass = [&](int slot, const u16* e, int lo, int hi, const u16* F, int r, int r0, int kc) {
+        unsigned char* const Pa = lds + (NSA - 1 - slot) * AT;
+        unsigned char* const Pb = lds + B0 + (NSB - 1 - slot) * BT;
+        constexpr int PT = SG_THREADS / 2;               // the multiplying wavefronts' threads
+        uint4 pa[NA], pb[NB_];
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+            const int idx = tid + PT * c, t = min(max(m0 + (idx & (BM - 1)), lo), hi - 1), cc = idx / BM;
+            pa[c] = row_piece(e + (int64_t)(t - lo) * r, r, r0 + cc * 8);
+        }
+#pragma unroll
+        for (int c = 0; c < NB_; ++c) {
+            const int idx = tid + PT * c;
+            if (NN) {
+                const int k = idx / (BN / 8), gcol = min(n0 + (idx % (BN / 8)) * 8, g.Ncols - 8);
+                const uint4 v = *reinterpret_cast<const uint4*>(F + (int64_t)(r0 + min(k, kc - 1)) * g.Ncols + gcol);
+                pb[c] = k < kc ? v : zero4();
+            } else {
+                pb[c] = row_piece(F + (int64_t)min(n0 + (idx & (BN - 1)), g.Ncols - 1) * r, r, r0 + idx / BN * 8);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+            const int idx = tid + PT * c, row = idx & (BM - 1), cc = idx / BM;
+            *reinterpret_cast<uint4*>(Pa + row * 128 + ((cc ^ (row & 7)) << 4)) = pa[c];
+        }
+#pragma unroll
+        for (int c = 0; c < NB_; ++c) {
+            const int idx = tid + PT * c;
             if (NN) {
                 const int k = idx / (BN / 8), nc = idx % (BN / 8);
-                if (k < kpad) *reinterpret_cast<uint4*>(Ps + AT + k * BROW + ((((nc >> 1) ^ fkey(k)) << 5) | ((nc & 1) << 4))) = pb[c];
+                *reinterpret_cast<uint4*>(Pb + k * BROW + ((((nc >> 1) ^ fkey(k)) << 5) | ((nc & 1) << 4))) = pb[c];
             } else {
                 const int row = idx & (BN - 1), cc = idx / BN;
-                if (cc * 8 < kpad) *reinterpret_cast<uint4*>(Ps + AT + row * 128 + ((cc ^ (row & 7)) << 4)) = pb[c];
+                *reinterpret_cast<uint4*>(Pb + row * 128 + ((cc ^ (row & 7)) << 4)) = pb[c];
+            }
+        }
+    };
+    // rows [lo, hi) of the accumulators take the products of the pass in `slot`, then times f
+    auto take_pass = [&](int slot, int kc, int lo, int hi, float f) {
+        for (int h = 0; h * 32 < kc; ++h) {
+            const bool in = h * 32 + 8 * g4 < kc;
+            const bf16x8 z = __builtin_bit_cast(bf16x8, zero4());
+            const float fh = h * 32 + 32 >= kc ? f : 1.0f;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) { fb[0][0][b] = frag_b(NSB - 1 - slot, h, b); fb[0][0][b] = in ? fb[0][0][b] : z; }
+#pragma unroll
+            for (int a = 0; a < MB; ++a) {
+                const int row0 = m0 + wm * WTM + a * 16, row = row0 + l16;
+                if (row0 >= hi || row0 + 16 <= lo) continue;     // (uniform)
+                fa[0][0][a] = frag_a(NSA - 1 - slot, h, a);
+                fa[0][0][a] = in ? fa[0][0][a] : z;
+                const bool own = row >= lo && row < hi;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const f32x4 t = mfma16(fb[0][0][b], fa[0][0][a], acc[a][b]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[a][b][q] = own ? fh * t[q] : acc[a][b][q];
+                }
             }
         }
     };
 
-    // ---- rank extension -----------------------------------------------------------------------------
-    // Lane l holds the metadata of candidate adapter base + l, so that walking the adapters of a tile costs no memory round
-    // trips; the operands of the next pass are in flight while one is multiplied.
-    if (!g.skip_lora) {
+    int first = 0, cand_end = g.pv.N;    // candidate adapters of the tile
+    // (up to 64 adapters are all candidates: one round trip less than by way of the row-tile table)
+    if (!g.skip_lora && cand_end > 64) {
         const Entry4 tile = g.pv.gemm_tiles[m0 / kGemmTileRows];
+        first = tile.c; cand_end = tile.d;
+    }
+    uint32_t* const count = reinterpret_cast<uint32_t*>(lds + (NSA - 2) * AT);     // free until the second pass is asked for
+
+    // ---- the loading wavefronts ---------------------------------------------------------------------
+    // Wavefronts 4 and 5 load the rows.  The weight's lines are the same for the row tiles of a band, on one XCD: asked for by all of them at once, a
+    // line that is not in its L2 yet is fetched for each.  So each of 8, 4 or 2 row tiles asks for its share of the lines early (wavefront 6)
+    // and for the others' when they are there (wavefront 7).  One copy of the loads for filling the rings and for the steady state: what a
+    // launch of few steps executes is short.
+    if (loader) {
+        constexpr int D_REST = (NSB + 1) / 2;        // steps ahead
+        const bool rows = wave < 6;
+        // piece kb at byte min(kb stride + at, last) of the step's tile (at0 or at1 by its swizzle); rows past the edge repeat the last one
+        const int64_t ld = rows ? g.lda : g.ldb;
+        unsigned at0, at1, last, stride;
+        if (rows || !NN) {
+            const unsigned ch = ((lane & 7) ^ (lane >> 3)) * 16;
+            stride = (unsigned)ld * 16u;
+            at0 = at1 = (unsigned)(lane >> 3) * (unsigned)ld * 2u + ch;
+            last = (unsigned)((rows ? min(g.M - m0, BM) - 1 : min(g.Ncols - n0, BN) - 1) * ld * 2) + ch;
+        } else {
+            const int k = lane / LPR, pos = lane % LPR;
+            stride = (unsigned)(64 / LPR * ld * 2);
+            auto column = [&](int key) { return min(n0 + ((((pos >> 1) ^ key) << 1) | (pos & 1)) * 8, g.Ncols - 8); };
+            at0 = (unsigned)(k * ld + column(fkey(k))) * 2u;
+            at1 = (unsigned)(k * ld + column(fkey(k + 8))) * 2u;
+            last = ~0u;
+        }
+        const char* base = uniform_ptr(rows ? g.Aop + (int64_t)m0 * g.lda : NN ? g.Bop : g.Bop + (int64_t)n0 * g.ldb);
+        const int64_t lstep = !rows && NN ? (int64_t)64 * g.ldb * 2 : 128;
+        // NUM loads a step, piece(c) the c-th; D steps ahead in a ring of NS
+        auto run = [&](auto num, auto ahead, auto stages, auto piece) __attribute__((always_inline)) {
+            constexpr int NUM = decltype(num)::value, D = decltype(ahead)::value, NS = decltype(stages)::value;
+            static_assert(NUM * D < 64 && D <= NS && D <= 16 && D > 1, "vmcnt holds 6 bits; drain steps");
+            int slot = 0;
+            bool extended = g.skip_lora != 0;
+            auto extension = [&]() __attribute__((always_inline)) {      // passes the barriers of the multiplying wavefronts' passes
+                extended = true;
+                for (int f = first; f < cand_end; f += 64) {
+                    lds_barrier();
+                    const int passes = __builtin_amdgcn_readfirstlane((int)*count);
+                    for (int q = 0; q <= passes; ++q) lds_barrier();
+                }
+            };
+            for (int t = 0; t < nk; ++t) {
+                if (t == NS - 2 && !extended) extension();               // (it uses the last two slots)
+                if (t >= D) {
+                    if (!extended) extension();
+                    wait_loads_and_barrier<NUM * (D - 2)>();             // step t - D + 1 has landed, step t - D has been read
+                    if (t == D) lds_barrier();
+                }
+                const unsigned dst = lds0 + (rows ? slot * AT : B0 + slot * BT);
+#pragma unroll
+                for (int c = 0; c < NUM; ++c) {
+                    const int kb = piece(c);
+                    const bool odd = NN && !rows && (BN == 128 ? (kb >> 1) & 1 : kb & 1);
+                    dma16(min((unsigned)kb * stride + (odd ? at1 : at0), last), base, dst + kb * 1024);
+                }
+                base += lstep;
+                slot = slot == NS - 1 ? 0 : slot + 1;
+            }
+            if (!extended) extension();
+            // the last steps, or all of a short contraction: nothing left to load
+            if (nk == D) wait_loads_and_barrier<NUM * (D - 1)>();
+#define SG_DRAIN(J) if (J + 1 < D && J + 1 + nk >= D) wait_loads_and_barrier<(D - 2 - J > 0 ? D - 2 - J : 0) * NUM>();
+            SG_DRAIN(0) SG_DRAIN(1) SG_DRAIN(2) SG_DRAIN(3) SG_DRAIN(4) SG_DRAIN(5) SG_DRAIN(6) SG_DRAIN(7)
+            SG_DRAIN(8) SG_DRAIN(9) SG_DRAIN(10) SG_DRAIN(11) SG_DRAIN(12) SG_DRAIN(13) SG_DRAIN(14)
+#undef SG_DRAIN
+        };
+        const int tm_in = in_band % band_rows;
+        auto share = [&](auto p) __attribute__((always_inline)) {
+            constexpr int P = decltype(p)::value, OWN = CB / P, REST = CB - OWN;
+            const int own = tm_in & (P - 1);
+            const std::integral_constant<int, NSB> ring{};
+            if (wave == 6) run(std::integral_constant<int, OWN>{}, std::integral_constant<int, (NSB * OWN < 64 ? NSB : 63 / OWN)>{}, ring, [=](int c) { return c * P + own; });
+            else           run(std::integral_constant<int, REST>{}, std::integral_constant<int, D_REST>{}, ring, [=](int c) { return c / (P - 1) * P + ((own + 1 + c % (P - 1)) & (P - 1)); });
+        };
+        if (nk == 0) {
+            for (int f = first; f < cand_end && !g.skip_lora; f += 64) {
+                lds_barrier();
+                const int passes = __builtin_amdgcn_readfirstlane((int)*count);
+                for (int q = 0; q <= passes; ++q) lds_barrier();
+            }
+        } else if (rows) {
+            run(std::integral_constant<int, CA / 2>{}, std::integral_constant<int, NSA>{}, std::integral_constant<int, NSA>{}, [=](int c) { return (wave & 1) * (CA / 2) + c; });
+        } else if (band_rows >= 8) {
+            share(std::integral_constant<int, 8>{});
+        } else if (band_rows >= 4) {
+            share(std::integral_constant<int, 4>{});
+        } else {
+            share(std::integral_constant<int, 2>{});
+        }
+    }
+
+    // ---- rank extension -----------------------------------------------------------------------------
+    // Lane l holds the metadata of candidate adapter first + l, so that walking the adapters of a tile costs no memory round trips; the operands of
+    // the next pass are on their way while one is multiplied.  An adapter's own rows hold zero before its passes and nothing but its
+    // term after them; what its operands give in other rows is dropped, whatever they hold.
+    if (!g.skip_lora && !loader) {
         const int m_end = min(g.M, m0 + BM);
-        for (int base = tile.c; base < tile.d; base += 64) {
-            const int cand = min(base + lane, tile.d - 1);
+        for (; first < cand_end; first += 64) {
+            const int cand = min(first + lane, cand_end - 1);
             const int v_rank = g.pv.rank[cand], v_off = g.pv.off[cand], v_end = g.pv.off[cand + 1];
             const int64_t v_so = g.pv.soff[cand];
             const uint64_t v_f = reinterpret_cast<uint64_t>(NN ? g.pv.ptrs[cand].B : g.pv.ptrs[cand].A);
             const float v_sc = NN ? g.pv.scale[cand] : 1.0f;
-            uint64_t todo = __ballot(base + lane < tile.d && v_rank > 0 && max(v_off, m0) < min(v_end, m_end));
-            if (todo == 0) continue;
+            const bool mine = first + lane < cand_end && v_rank > 0 && max(v_off, m0) < min(v_end, m_end);
+            uint64_t todo = __ballot(mine);
+            const int passes = __popcll(todo) + __popcll(__ballot(mine && v_rank > 64));
             auto lane64 = [](uint64_t v, int l) {
                 return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)v, l);
             };
-            int l = 0, r = 0, lo = 0, hi = 0, r0 = 0;
-            auto load_next = [&]() {               // operands of pass (adapter lane l, ranks from r0)
-                const int seg0 = __builtin_amdgcn_readlane(v_off, l);
-                r = __builtin_amdgcn_readlane(v_rank, l);
+            int r0 = 0;                            // ranks of the lowest adapter in todo that have been asked for
+            int lo = 0, hi = 0, kc = 0;            // of the pass asked for last
+            float f = 1.0f;
+            auto request = [&](int slot) {
+                const int l = (int)__builtin_ctzll(todo);
+                const int r = __builtin_amdgcn_readlane(v_rank, l), seg0 = __builtin_amdgcn_readlane(v_off, l);
                 lo = max(seg0, m0);
                 hi = min(__builtin_amdgcn_readlane(v_end, l), m_end);
+                kc = min(64, r - r0);
                 const int64_t so = (int64_t)lane64((uint64_t)v_so, l);
                 const u16* F = global_ptr<const u16>(reinterpret_cast<const void*>(lane64(v_f, l)));
-                const u16* e = g.E + so + (int64_t)(lo - seg0) * r + r0;
-                const bool vec = (r & 7) == 0, e_vec = vec && (so & 7) == 0;
-                if (NN) pass_load(e, r, lo, hi, e_vec, F + (int64_t)r0 * g.Ncols, g.Ncols, true, min(64, r - r0));
-                else    pass_load(e, r, lo, hi, e_vec, F + r0, r, vec, min(64, r - r0));
-            };
-            l = (int)__builtin_ctzll(todo);
-            load_next();
-            bool first = true;
-            f32x4 ext[MB][NB];
-            for (;;) {
-                const int kc = min(64, r - r0), c_lo = lo, c_hi = hi;
-                const float sc = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v_sc), l));
-                if (r0 == 0) {
-#pragma unroll
-                    for (int a = 0; a < MB; ++a)
-#pragma unroll
-                        for (int b = 0; b < NB; ++b) ext[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-                if (!first || base != tile.c) lds_barrier();      // the previous pass has been read
-                first = false;
-                pass_store(kc);
-                const bool last_of_adapter = r0 + 64 >= r;
-                if (last_of_adapter) { todo &= todo - 1; r0 = 0; if (todo) l = (int)__builtin_ctzll(todo); }
+                const u16* e = g.E + so + (int64_t)(lo - seg0) * r;
+                if ((r & 7) == 0 && (so & 7) == 0) dma_pass(slot, e + r0, r, lo, hi, NN ? F + (int64_t)r0 * g.Ncols : F + (int64_t)n0 * r + r0, NN ? g.Ncols : r, kc);
+                else                               stage_pass(slot, e, lo, hi, F, r, r0, kc);
+                const bool last = r0 + 64 >= r;
+                f = last ? __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v_sc), l)) : 1.0f;
+                if (last) { todo &= todo - 1; r0 = 0; }
                 else r0 += 64;
-                if (todo) load_next();
-                lds_barrier();
-                read_frags(NST - 1, 0);
-                mma(ext, 0);
-                if (kc > 32) { read_frags(NST - 1, 1); mma(ext, 1); }
-                if (last_of_adapter) {
-#pragma unroll
-                    for (int a = 0; a < MB; ++a) {
-                        const int row = m0 + wm * WTM + a * 16 + l16;
-                        const bool own = row >= c_lo && row < c_hi;
-#pragma unroll
-                        for (int b = 0; b < NB; ++b)
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) acc[a][b][q] = own ? sc * ext[a][b][q] : acc[a][b][q];
-                    }
-                }
-                if (!todo) break;
+            };
+            if (todo) request(0);
+            if (tid == 0) *count = (uint32_t)passes;
+            lds_barrier();                         // the loading wavefronts read it
+            for (int q = 0; q < passes; ++q) {
+                const int slot = q & 1, p_lo = lo, p_hi = hi, p_kc = kc;
+                const float p_f = f;
+                wait_loads_and_barrier<0>();       // pass q is here, everybody is done with pass q - 1
+                if (todo) request(slot ^ 1);
+                take_pass(slot, p_kc, p_lo, p_hi, p_f);
             }
+            lds_barrier();                         // the passes have been read
         }
     }
 
     // ---- contraction over the frozen weight -----------------------------------------------------------
     // Step t starts with the fragments of its first half in registers: the second half's are read while the first is multiplied.  Then
-    // stage t + 1 has landed and everybody has read stage t (its slot is free for stage t + NST); the first half of t + 1 is
+    // stage t + 1 has landed and everybody has read stage t (its slots are free); the first half of t + 1 is
     // read while the second of t is multiplied.
-    if (nk >= NST) {
-        lds_barrier();                   // the pass slot has been read
-        issue();                         // stage NST - 1
-        wait_loads_and_barrier<LPS * (NST - 1)>();
-        read_frags(0, 0);
-        int cur = 0, nxt = 1;            // slots of stages t and t + 1
-        auto half = [&](int h, int slot, bool load) {    // multiply half h, read the other half from `slot`
-#pragma unroll
-            for (int a = 0; a < MB; ++a) {
-                __builtin_amdgcn_sched_barrier(0);
-                if (load) {
-#pragma unroll
-                    for (int c = 0; c < LPS; ++c)
-                        if (c * MB / LPS == a) issue1(c);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                read_frag_a(slot, h ^ 1, a);
-#pragma unroll
-                for (int b = a * NB / MB; b < (a + 1) * NB / MB; ++b) read_frag_b(slot, h ^ 1, b);
-#pragma unroll
-                for (int b = 0; b < NB; ++b) acc[a][b] = mfma16(fb[h][b], fa[h][a], acc[a][b]);
-                interleave();
+    if (nk > 0 && !loader) {
+        lds_barrier();
+        read_set(0, 0);
+        auto next = [&]() __attribute__((always_inline)) {      // stage t + 1 has landed, everybody has read stage t
+            lds_barrier();
+            sa = sa == NSA - 1 ? 0 : sa + 1;
+            sb = sb == NSB - 1 ? 0 : sb + 1;
+        };
+        if constexpr (U == 2) {
+            int t = 0;
+            for (; t + 2 < nk; t += 2) {
+                next();
+                multiply(zero, true, 0);
+                next();
+                multiply(one, true, 0);
             }
-        };
-        auto advance = [&]() {
-            cur = nxt;
-            nxt = nxt == NST - 1 ? 0 : nxt + 1;
-        };
-        for (int t = 0; t < nk - NST; ++t) {
-            half(0, cur, false);
-            wait_loads_and_barrier<LPS * (NST - 2)>();
-            half(1, nxt, true);
-            advance();
+            if (t + 1 < nk) {
+                next();
+                multiply(zero, true, 0);
+                multiply(one, false, 0);
+            } else {
+                multiply(zero, false, 0);
+            }
+        } else {
+            for (int t = 0; t < nk - 1; ++t) {
+                multiply(zero, true, 1);
+                next();
+                multiply(one, true, 0);
+            }
+            multiply(zero, true, 1);
+            multiply(one, false, 0);
         }
-        // the last NST stages: nothing left to load
-#define SG_DRAIN(J)                                                                             \
-        if (J < NST) {                                                                          \
-            half(0, cur, false);                                                                \
-            if (J + 1 < NST) {                                                                  \
-                wait_loads_and_barrier<(NST - 2 - J > 0 ? NST - 2 - J : 0) * LPS>();            \
-                half(1, nxt, false);                                                            \
-            } else {                                                                            \
-                mma(acc, 1);                                                                    \
-            }                                                                                   \
-            advance();                                                                          \
-        }
-        SG_DRAIN(0) SG_DRAIN(1) SG_DRAIN(2) SG_DRAIN(3) SG_DRAIN(4) SG_DRAIN(5) SG_DRAIN(6) SG_DRAIN(7)
-        static_assert(NST <= 8, "drain steps");
-#undef SG_DRAIN
-    } else if (nk > 0) {
-        wait_loads_and_barrier<0>();
-        for (int t = 0; t < nk; ++t) { read_frags(t, 0); read_frags(t, 1); mma(acc, 0); mma(acc, 1); }
     }
 
-    // ---- tail of a contraction that is not a multiple of 64 -----------------------------------------
+    // ---- tail of a contraction that is not a multiple of 64 (it is one of 8) -----------------------------
     if ((g.Kdim & 63) != 0) {
         const int k0 = nk * 64;
         lds_barrier();
-        pass_load(g.Aop + (int64_t)m0 * g.lda + k0, g.lda, m0, min(g.M, m0 + BM), true, NN ? g.Bop + (int64_t)k0 * g.ldb : g.Bop + k0,
-                  g.ldb, true, g.Kdim - k0);
-        pass_store(g.Kdim - k0);
-        lds_barrier();
-        read_frags(NST - 1, 0);
-        mma(acc, 0);
-        if (g.Kdim - k0 > 32) { read_frags(NST - 1, 1); mma(acc, 1); }
+        if (!loader) dma_pass(0, g.Aop + (int64_t)m0 * g.lda + k0, g.lda, m0, min(g.M, m0 + BM), NN ? g.Bop + (int64_t)k0 * g.ldb : g.Bop + (int64_t)n0 * g.ldb + k0,
+                              g.ldb, g.Kdim - k0);
+        wait_loads_and_barrier<0>();
+        if (!loader) take_pass(0, g.Kdim - k0, m0, g.M, 1.0f);
     }
 
     // ---- the tile goes through LDS, whole rows of it to memory ----------------------------------------
     lds_barrier();
     constexpr int E_LD = BN + 8;
-    static_assert(BM * E_LD * 2 <= NST * STAGE, "epilogue staging fits the ring");
+    static_assert(BM * E_LD * 2 <= kRing<BM, BN>, "epilogue staging fits the ring");
     u16* Es = reinterpret_cast<u16*>(lds);
+    if (!loader) {
 #pragma unroll
-    for (int a = 0; a < MB; ++a)
+        for (int a = 0; a < MB; ++a)
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            uint2 v;
-            v.x = pack2hw(acc[a][b][0], acc[a][b][1]);
-            v.y = pack2hw(acc[a][b][2], acc[a][b][3]);
-            *reinterpret_cast<uint2*>(Es + (wm * WTM + a * 16 + l16) * E_LD + wn * WTN + b * 16 + g4 * 4) = v;
-        }
+            for (int b = 0; b < NB; ++b) {
+                uint2 v;
+                v.x = pack2hw(acc[a][b][0], acc[a][b][1]);
+                v.y = pack2hw(acc[a][b][2], acc[a][b][3]);
+                *reinterpret_cast<uint2*>(Es + (wm * WTM + a * 16 + l16) * E_LD + wn * WTN + b * 16 + g4 * 4) = v;
+            }
+    }
     lds_barrier();
     constexpr int CPR = BN / 8;
 #pragma unroll
@@ -429,7 +532,9 @@ static void launch_small(GemmArgs g, bool fwd, const WgradArgs* w, int items, in
 // Which kernel a product of M x N outputs over a contraction of K takes: -1 the 256 x 256 one, else an index of the table.
 // Every kernel runs one work group per CU, so a launch takes  launch + rounds x (fill and epilogue + steps x step)  with
 // rounds = tiles over CUs, rounded up.  The step times are what the kernels sustain with all CUs busy (64-wide step; the
-// 256 x 256 kernel moves the fewest bytes per product and wins wherever its last round is not too empty).  Over 192 products
+// 256 x 256 kernel moves the fewest bytes per product and wins wherever its last round is not too empty).  They are those of the kernel before
+// its wavefronts were divided: with what it sustains now (0.44, 0.275, 0.175) more products went to small tiles, which does not fit launches that
+// leave CUs to the 256 x 256 kernel's clock (2249 x 3840 x 8448 206 -> 232 us, 2927 tokens through an 8B block 2.51 -> 2.83 ms).  Over 192 products
 // (64 .. 16384 tokens, widths 512 .. 14336, both directions) the choice takes 0.1 % longer in all than the best of the four, 11 % at worst.
 // Measured (us, 256 x 256 / 128 x 128 / 64 x 128 / 64 x 64, tokens x outputs x contraction): 1000 x 4096 x 4096  86 / 41 / 56 / 81;
 // 1000 x 1024 x 4096  81 / 34 / 28 / 23;  200 x 512 x 2048  67 / 25 / 18 / 14;  4000 x 4096 x 4096  110 / 157 / 220 / 300.
