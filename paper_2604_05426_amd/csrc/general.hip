@@ -42,13 +42,19 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
     __shared__ float red[NW * 16 * RLD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g4 = lane >> 4;
-    const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, wg = item / g.rank_items;
-    if (wg >= (int64_t)g.pv.n_row_blocks * 4) return;
+    // The rank items of 16 rows stand side by side, so that the rows come from the caches; but not where there are 2, 4 or 8 of them: work group
+    // number modulo 8 is the XCD, and the higher items, empty for most adapters, would all be on the same ones.  us, fp32, 2048 tokens, contraction
+    // 2048, ranks 8 to 64 (4 items): side by side 19.0 forward, 23.5 backward, one item after the other 14.0, 18.4; in turned order 19.8, 24.7.  bf16, 1500
+    // tokens, contraction 2048, ranks to 33 (3 items): 6.0 and 7.7, 8.1 and 8.2.
+    const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, groups = (int64_t)g.pv.n_row_blocks * 4;
+    if (item >= groups * g.rank_items) return;
+    const bool apart = (g.rank_items & 1) == 0;
+    const int64_t wg = apart ? item % groups : item / g.rank_items;
     const Entry4 e = g.pv.row_blocks[wg >> 2];
     const int sub = (wg & 3) * 16, rows = min(16, e.d - sub);
     if (rows <= 0) return;
     const int i = e.a, row0 = e.c + sub;
-    const int r = g.pv.rank[i], rho0 = (int)(item % g.rank_items) * (16 * NB), rl = min(r - rho0, 16 * NB);      // this work group's ranks
+    const int r = g.pv.rank[i], rho0 = (int)(apart ? item / groups : item % g.rank_items) * (16 * NB), rl = min(r - rho0, 16 * NB);      // this work group's ranks
     if (rl <= 0) return;
     const float s = FWD ? 1.0f : g.pv.scale[i];
     const T* F = global_ptr<const T>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B) + (FWD ? (int64_t)rho0 : rho0 * g.ld);
