@@ -16,6 +16,8 @@
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
 // tokens, 256 x 256: 171 -> 21 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 265 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 67 us.
+#include <type_traits>
+
 #include "general_wgrad.h"
 
 namespace mlora {
@@ -217,8 +219,348 @@ struct GenGemmArgs {
     int64_t M, N, K;
     int64_t tiles_n;
     int32_t base, lora;           // which terms; without the base term C += LoRA term
+    int32_t xcd_run;              // whole tiles: consecutive tiles per XCD
     PlanView pv;
 };
+
+// ---- whole 64 x 64 tiles ---------------------------------------------------------------------------------------------------------
+// For products of at least 64 in every direction that fill half of the chip with such tiles: four wavefronts load and four multiply.  The loads of four
+// steps are on their way in the loading wavefronts' registers (rows start at any element, so they cannot go to LDS directly), which hand a
+// step over in one of two LDS stages per barrier; the multiplying ones (2 x 2 sub-tiles) read a step's fragments while the one before it is
+// multiplied.  With wavefronts that did both (KC = 1 below) a step took 1500 cycles, the time of its loads, LDS stores, fragment reads and products
+// after one another.  us, before / now: 1500 x 1001 outputs, contraction 2048, 22.2 / 17.5; 1000 x 1001 15.1 / 11.0; 1500 x 2048, contraction 1001, backward 22.4 / 20.2.
+// Sums in the order of the other tiles (see below).  The operands of the first rank-extension pass are staged while the contraction ends.
+// BM x 64, BM 64 or 128.
+template <int BM> constexpr int kWholeStage = (BM + 64) * 128;       // bytes of a step's operand tiles [BM][64] and [64][64]
+template <bool FWD, int BM>
+__device__ __forceinline__ void whole_tile_body(const GenGemmArgs& g, unsigned char* const lds, const uint32_t wg) {
+    constexpr int STAGE = kWholeStage<BM>, AT = BM * 128, NA = BM / 32, MB = BM / 32;      // pieces of A per lane and step; row blocks of a wavefront
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool loader = wave >= 4;
+    const int wm = (wave >> 1) & 1, wn = wave & 1, l16 = lane & 15, g4 = lane >> 4;
+    const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)g.tiles_n;
+    const uint32_t slot_x = wg / 8, L = ((slot_x / g.xcd_run) * 8 + wg % 8) * g.xcd_run + slot_x % g.xcd_run;
+    if (L >= (uint32_t)tiles_m * (uint32_t)tiles_n) return;
+    const int band = (int)(L / (8u * tiles_n)), in_band = (int)(L - (uint32_t)band * 8u * tiles_n), band_rows = min(8, tiles_m - band * 8);
+    // The last tile of rows / columns starts early enough to be whole; what it shares with the tile before is not stored.
+    const int64_t m_own = (int64_t)(band * 8 + in_band % band_rows) * BM, n_own = (int64_t)(in_band / band_rows) * 64;
+    const int64_t m0 = min(m_own, g.M - BM), n0 = min(n_own, g.N - 64);
+    const int lo_t = (int)m0, hi_t = lo_t + BM;
+
+    // lane l holds the metadata of candidate adapter first + l
+    int first = 0, cand_end = g.lora ? g.pv.N : 0;
+    if (cand_end > 64) {
+        first = g.pv.gemm_tiles[m0 / kGemmTileRows].c;
+        cand_end = g.pv.gemm_tiles[(m0 + BM - 1) / kGemmTileRows].d;
+    }
+    int c_rank = 0, c_off = 0, c_end = 0;
+    int64_t c_so = 0;
+    uint64_t c_f = 0;
+    float c_sc = 1.0f;
+    auto candidates = [&]() {
+        const int cand = min(first + lane, cand_end - 1);
+        c_rank = g.pv.rank[cand]; c_off = g.pv.off[cand]; c_end = g.pv.off[cand + 1];
+        c_so = g.pv.soff[cand];
+        c_f = reinterpret_cast<uint64_t>(FWD ? g.pv.ptrs[cand].B : g.pv.ptrs[cand].A);
+        if (FWD) c_sc = g.pv.scale[cand];
+    };
+    auto mine = [&]() { return __ballot(first + lane < cand_end && c_rank > 0 && max(c_off, lo_t) < min(c_end, hi_t)); };
+    auto barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // where 16-byte piece (row, c) of a tile whose contraction is contiguous goes, and (contraction row k, 8 columns c) of a W / B_i tile
+    auto place = [](int row, int c) { return row * 128 + ((c ^ (row & 7)) << 4); };
+    auto key = [](int k) { return ((k >> 1) & 1) | (((k >> 3) & 1) << 1); };
+    auto place_w = [&](int k, int c) { return k * 128 + (((c >> 1) ^ key(k)) << 5) + ((c & 1) << 4); };
+    const int whole = (int)(g.K / 64), left = (int)(g.K - (int64_t)whole * 64), steps = whole + (left > 0);
+    unsigned char* const pass = lds + 2 * STAGE;
+
+    if (loader) {
+        // each wavefront takes a quarter of the rows of both tiles, eight at a time, lane l piece (l / 8, l % 8) of these
+        const int arow = (wave - 4) * (BM / 4) + (lane >> 3), row = (wave - 4) * 16 + (lane >> 3), ch = lane & 7;
+        const u16* const pa = g.A + (m0 + arow) * g.lda + ch * 8;
+        const u16* const pb = FWD ? g.W + (int64_t)row * g.ldw + n0 + ch * 8 : g.W + (n0 + row) * g.ldw + ch * 8;
+        const int64_t a8 = 8 * g.lda, b8 = 8 * g.ldw, bstep = FWD ? 64 * g.ldw : 64;
+        constexpr int D = 4;                             // steps on their way
+        auto as_vec = [](uint4 v) { return u32x4v{v.x, v.y, v.z, v.w}; };
+        auto as_uint4 = [](u32x4v v) { return make_uint4(v[0], v[1], v[2], v[3]); };
+        u32x4v ra[D + 2][NA], rb[D + 2][2];              // the last two: what is left of the contraction, a pass of the rank extension
+        auto load = [&](int d, int t) __attribute__((always_inline)) {
+            const u16* const a = pa + (int64_t)t * 64;
+            const u16* const b = pb + t * bstep;
+#pragma unroll
+            for (int j = 0; j < NA; ++j) __builtin_memcpy(&ra[d][j], a + j * a8, 16);
+            __builtin_memcpy(&rb[d][0], b, 16);
+            __builtin_memcpy(&rb[d][1], b + b8, 16);
+        };
+        auto store = [&](unsigned char* to, int d) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < NA; ++j) *reinterpret_cast<u32x4v*>(to + place(arow + 8 * j, ch)) = ra[d][j];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                *reinterpret_cast<u32x4v*>(to + AT + (FWD ? place_w(row + 8 * j, ch) : place(row + 8 * j, ch))) = rb[d][j];
+            }
+        };
+        // What is left of a contraction that is no multiple of 64: pieces that would reach past their row are loaded from where they still fit and
+        // shifted, contraction rows past the end (forward: of W) repeat the last one and are taken as zero.
+        auto load_rest = [&]() __attribute__((always_inline)) {
+            const int64_t k0 = (int64_t)whole * 64;
+            const int64_t at = min(k0 + ch * 8, g.K - 8) - ch * 8;
+#pragma unroll
+            for (int j = 0; j < NA; ++j) __builtin_memcpy(&ra[D][j], pa + at + j * a8, 16);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const u16* const b = FWD ? g.W + min(k0 + row + 8 * j, g.K - 1) * g.ldw + n0 + ch * 8 : pb + j * b8 + at;
+                __builtin_memcpy(&rb[D][j], b, 16);
+            }
+        };
+        // Passes of the rank extension: 64 ranks of an adapter each; the first one's operands are asked for before the contraction's.  Elements
+        // r0 + 8 ch .. of rows of rk that start anywhere: a piece that would reach past its row is loaded from where it still fits and shifted.
+        uint64_t todo = 0;
+        int r0 = 0, by = 0, ranks = 0;                   // ranks of the lowest adapter in todo asked for; shift and ranks of the pass asked for last
+        bool fetched = false;
+        auto fetch = [&]() __attribute__((always_inline)) {
+            fetched = todo != 0;
+            if (!fetched) return;
+            const int l = (int)__builtin_ctzll(todo);
+            auto lane64 = [&](uint64_t x) __attribute__((always_inline)) {
+                return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), l) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+            };
+            const int rk = __builtin_amdgcn_readlane(c_rank, l), seg0 = __builtin_amdgcn_readlane(c_off, l), seg1 = __builtin_amdgcn_readlane(c_end, l);
+            const u16* const F = global_ptr<const u16>(reinterpret_cast<const void*>(lane64(c_f)));
+            const u16* const E = g.E + (int64_t)lane64((uint64_t)c_so);
+            auto e_row = [&](int j) { return E + (int64_t)(min(max(lo_t + arow + 8 * j, seg0), seg1 - 1) - seg0) * rk; };      // (rows of others: dropped)
+            auto f_row = [&](int j) { return F + (n0 + row + 8 * j) * rk; };
+            const int at = r0 + ch * 8;
+            ranks = min(64, rk - r0);
+            if (rk >= 8) {
+                const int from = min(at, rk - 8);
+                by = at - from;
+#pragma unroll
+                for (int j = 0; j < NA; ++j) __builtin_memcpy(&ra[D + 1][j], e_row(j) + from, 16);
+                if (!FWD) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) __builtin_memcpy(&rb[D + 1][j], f_row(j) + from, 16);
+                }
+            } else {                                     // less than a piece: element by element, from the row's last ones where it ends
+                by = 0;
+                auto few = [&](const u16* p) __attribute__((always_inline)) {
+                    u16 e[8];
+#pragma unroll
+                    for (int i = 0; i < 7; ++i) e[i] = p[min(i, rk - 1)];
+                    uint32_t w[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) w[i] = (2 * i < rk && ch == 0 ? e[2 * i] : 0u) | (i < 3 && 2 * i + 1 < rk && ch == 0 ? (uint32_t)e[2 * i + 1] << 16 : 0u);
+                    return u32x4v{w[0], w[1], w[2], w[3]};
+                };
+#pragma unroll
+                for (int j = 0; j < NA; ++j) ra[D + 1][j] = few(e_row(j));
+                if (!FWD) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) rb[D + 1][j] = few(f_row(j));
+                }
+            }
+            if (FWD) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) __builtin_memcpy(&rb[D + 1][j], F + (int64_t)min(r0 + row + 8 * j, rk - 1) * g.N + n0 + ch * 8, 16);
+            }
+            if (r0 + 64 < rk) r0 += 64;
+            else { todo &= todo - 1; r0 = 0; }
+        };
+        auto shift = [&]() __attribute__((always_inline)) {      // zeros past the ranks
+#pragma unroll
+            for (int j = 0; j < NA; ++j) ra[D + 1][j] = as_vec(drop_front(as_uint4(ra[D + 1][j]), by));
+#pragma unroll
+            for (int j = 0; j < 2; ++j) rb[D + 1][j] = as_vec(FWD ? (row + 8 * j < ranks ? as_uint4(rb[D + 1][j]) : zero4()) : drop_front(as_uint4(rb[D + 1][j]), by));
+        };
+        // (Oldest first and in the loop's own order: the waits in the loop are for the worse of what comes in from here and from its end.)
+        if (first < cand_end) { candidates(); todo = mine(); fetch(); }
+        if (left > 0) load_rest();
+        __builtin_amdgcn_sched_barrier(0);
+        load(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load(1, min(1, whole - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        load(2, min(2, whole - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        load(3, min(3, whole - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        int t = 0;
+        auto one_step = [&](auto d_) __attribute__((always_inline)) {        // (D is even: step t + d is of the parity of d)
+            constexpr int d = decltype(d_)::value;
+            store(lds + (d & 1) * STAGE, d);
+            load(d, min(t + d + D, whole - 1));
+            __builtin_amdgcn_sched_barrier(0);
+            barrier();
+        };
+        for (; t + D <= whole; t += D) {
+            one_step(std::integral_constant<int, 0>{});
+            one_step(std::integral_constant<int, 1>{});
+            one_step(std::integral_constant<int, 2>{});
+            one_step(std::integral_constant<int, 3>{});
+        }
+        static_assert(D == 4, "what is left of the steps");
+        if (t < whole) { store(lds, 0); barrier(); }
+        if (t + 1 < whole) { store(lds + STAGE, 1); barrier(); }
+        if (t + 2 < whole) { store(lds, 2); barrier(); }
+        if (left > 0) {
+            const int sh = max(0, ch * 8 + 8 - left);
+#pragma unroll
+            for (int j = 0; j < NA; ++j) ra[D][j] = as_vec(drop_front(as_uint4(ra[D][j]), sh));
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                rb[D][j] = as_vec(FWD ? (row + 8 * j < left ? as_uint4(rb[D][j]) : zero4()) : drop_front(as_uint4(rb[D][j]), sh));
+            }
+            store(lds + (whole & 1) * STAGE, D);
+            barrier();
+        }
+        // ---- passes of the rank extension ----
+        while (first < cand_end) {
+            while (fetched) {
+                shift();
+                store(pass, D + 1);
+                barrier();                               // staged
+                fetch();
+                barrier();                               // used
+            }
+            first += 64;
+            if (first < cand_end) { candidates(); todo = mine(); fetch(); }
+        }
+    }
+
+    f32x4 acc[MB][2];
+    if (!loader) {
+        if (first < cand_end) candidates();
+#pragma unroll
+        for (int x = 0; x < MB; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+        bf16x8 fa[2][2][MB], fb[2][2][2];                // [set][32-wide half][block]
+        auto read = [&](auto set, const unsigned char* from) __attribute__((always_inline)) {
+            constexpr int S = decltype(set)::value;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int x = 0; x < MB; ++x) fa[S][h][x] = lds_read_frag(reinterpret_cast<const u16*>(from + place(wm * (BM / 2) + x * 16 + l16, h * 4 + g4)));
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    if (FWD) {
+                        const int k = h * 32 + 8 * g4 + (l16 >> 2);
+                        const unsigned char* p = from + AT + k * 128 + (((wn * 2 + x) ^ key(k)) << 5) + (l16 & 3) * 8;      // (rows k and k + 4 share their key)
+                        fb[S][h][x] = lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * 128));
+                    } else {
+                        fb[S][h][x] = lds_read_frag(reinterpret_cast<const u16*>(from + AT + place(wn * 32 + x * 16 + l16, h * 4 + g4)));
+                    }
+                }
+            }
+        };
+        // operands swapped: a lane holds one output row and 4 consecutive columns of each block
+        auto multiply = [&](f32x4 (&c)[MB][2], auto set) __attribute__((always_inline)) {
+            constexpr int S = decltype(set)::value;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int x = 0; x < MB; ++x)
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) c[x][y] = mfma16(fb[S][h][y], fa[S][h][x], c[x][y]);
+        };
+        const std::integral_constant<int, 0> f0{};
+        const std::integral_constant<int, 1> f1{};
+        barrier();
+        read(f0, lds);
+        int t = 0;
+        for (; t + 2 < steps; t += 2) {
+            barrier();
+            read(f1, lds + STAGE);
+            multiply(acc, f0);
+            barrier();
+            read(f0, lds);
+            multiply(acc, f1);
+        }
+        if (t + 1 < steps) {
+            barrier();
+            read(f1, lds + STAGE);
+            multiply(acc, f0);
+            multiply(acc, f1);
+        } else {
+            multiply(acc, f0);
+        }
+        // rank extension, adapter by adapter into a second accumulator set, of which the adapter's own rows are added: another adapter's
+        // operands never touch a row, whatever they hold
+        while (first < cand_end) {
+            uint64_t todo = mine();
+            while (todo) {
+                const int l = (int)__builtin_ctzll(todo);
+                todo &= todo - 1;
+                const int rk = __builtin_amdgcn_readlane(c_rank, l);
+                const int lo = max(__builtin_amdgcn_readlane(c_off, l), lo_t), hi = min(__builtin_amdgcn_readlane(c_end, l), hi_t);
+                const float s = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c_sc), l));
+                f32x4 ext[MB][2];
+#pragma unroll
+                for (int x = 0; x < MB; ++x)
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) ext[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int r0 = 0; r0 < rk; r0 += 64) {
+                    barrier();                           // staged
+                    read(f0, pass);
+                    multiply(ext, f0);
+                    barrier();                           // used
+                }
+#pragma unroll
+                for (int x = 0; x < MB; ++x) {
+                    const int row = lo_t + wm * (BM / 2) + x * 16 + l16;
+                    const bool own = row >= lo && row < hi;
+#pragma unroll
+                    for (int y = 0; y < 2; ++y)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[x][y][q] = own ? acc[x][y][q] + s * ext[x][y][q] : acc[x][y][q];
+                }
+            }
+            first += 64;
+            if (first < cand_end) candidates();
+        }
+    }
+
+    // the tile goes through LDS, whole rows of it to memory
+    barrier();
+    constexpr int E_LD = 64 + 8;
+    u16* const Es = reinterpret_cast<u16*>(lds);
+    if (!loader) {
+#pragma unroll
+        for (int x = 0; x < MB; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                uint2 v;
+                v.x = pack2(acc[x][y][0], acc[x][y][1]);
+                v.y = pack2(acc[x][y][2], acc[x][y][3]);
+                *reinterpret_cast<uint2*>(Es + (wm * (BM / 2) + x * 16 + l16) * E_LD + wn * 32 + y * 16 + g4 * 4) = v;
+            }
+    }
+    barrier();
+    const int c = (tid & 7) * 8;
+    const int64_t col = n0 + c;
+#pragma unroll
+    for (int it = 0; it < BM / 64; ++it) {
+        const int rr = (tid >> 3) + 64 * it;
+        const int64_t row = m0 + rr;
+        if (row < m_own) continue;
+        const uint4 v = *reinterpret_cast<const uint4*>(Es + rr * E_LD + c);
+        u16* const out = g.C + row * g.ldc + col;
+        if (col >= n_own) {
+            __builtin_memcpy(out, &v, 16);
+        } else {
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (col + e >= n_own) out[e] = (u16)(w[e >> 1] >> (16 * (e & 1)));
+        }
+    }
+}
+
+template <bool FWD, int BM>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(BM == 64 ? 4 : 2))) void whole_tile_kernel(GenGemmArgs g) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[3 * kWholeStage<BM>];      // two steps and a pass
+    whole_tile_body<FWD, BM>(g, lds, blockIdx.x);
+}
 
 // Tile: KC = 1: 64 x 64, KC = 4: 32 x 32; four wavefronts 2 x 2, each 2 x 2 blocks or one.
 // A step is KC chunks of 128 bytes per row (64 elements).  LDS rows of operands whose contraction is contiguous are padded to 144 bytes
@@ -613,8 +955,20 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
             return MLORA_OK;
         }
     }
-    if (split) hipLaunchKernelGGL((general_gemm_kernel<FWD, 4>), dim3((unsigned)groups), dim3(256), 0, st, a);
-    else       hipLaunchKernelGGL((general_gemm_kernel<FWD, 1>), dim3((unsigned)groups), dim3(256), 0, st, a);
+    if (!split && a.base && a.M >= 128 && a.N >= 64 && a.K >= 64 && groups < (1 << 24)) {
+        // 128 x 64 tiles (forward) where they make few enough rounds: a work group takes 0.45 us per 64-wide step, alone on its CU; 64 x 64 ones, two on a CU,
+        // 0.28 each.  us, 64 x 64 / 128 x 64, tokens x outputs x contraction: 1500 x 1001 x 2048 21.0 / 17.5, 4000 x 1001 x 2048 37.9 / 32.0; not 1000 x
+        // 1001 x 2048 11.0 / 16.2.  Backward (both operands from rows that start anywhere) 1500 x 2048 x 1001 20.6 / 25.1, 4000 x 2048 x 1001 46.9 / 48.4.
+        const int64_t tall = (a.M + 127) / 128 * a.tiles_n;
+        auto rounds = [&](int64_t n) { return (n + p->num_cus - 1) / p->num_cus; };
+        const bool wide = FWD && 45 * rounds(tall) < 28 * rounds(groups);
+        const int64_t n = wide ? tall : groups;
+        a.xcd_run = n >= 256 ? 32 : (int32_t)((n + 7) / 8);
+        const dim3 grid((unsigned)((n + 8 * a.xcd_run - 1) / (8 * a.xcd_run) * (8 * a.xcd_run)));
+        if (wide) hipLaunchKernelGGL((whole_tile_kernel<FWD, FWD ? 128 : 64>), grid, dim3(512), 0, st, a);
+        else      hipLaunchKernelGGL((whole_tile_kernel<FWD, 64>), grid, dim3(512), 0, st, a);
+    } else if (split) hipLaunchKernelGGL((general_gemm_kernel<FWD, 4>), dim3((unsigned)groups), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((general_gemm_kernel<FWD, 1>), dim3((unsigned)groups), dim3(256), 0, st, a);
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;
 }

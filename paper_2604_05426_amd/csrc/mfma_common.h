@@ -122,7 +122,25 @@ __device__ __forceinline__ uint4 load_chunk(const u16* p, int valid, bool vec_ok
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Same, with 64-bit pieces when p is 8-byte aligned (ranks that are multiples of 4 but not of 8).  For kernels that load a
+// a piece of eight elements without its first d, zeros behind the rest
+__device__ __forceinline__ uint4 drop_front(uint4 v, int d) {
+    const uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+    const int sh = min(d * 16, 128);
+    const uint64_t l = sh == 0 ? lo : sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : sh < 128 ? hi >> (sh - 64) : 0, h = sh < 64 ? hi >> sh : 0;
+    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+}
+
+// Elements at .. at + 7 of a row of r that starts at any element, zeros past its end: a piece that would reach past it is loaded from where it
+// still fits and shifted.
+__device__ __forceinline__ uint4 row_piece(const u16* row, int r, int at) {
+    if (r < 8) return load_chunk(row + min(at, r), max(0, r - at), false);
+    const int from = min(at, r - 8);
+    uint4 v;
+    __builtin_memcpy(&v, row + from, 16);
+    return drop_front(v, at - from);
+}
+
+// load_chunk with 64-bit pieces when p is 8-byte aligned (ranks that are multiples of 4 but not of 8).  For kernels that load a
 // chunk once per work item; the extra paths cost registers in a kernel that loads chunks in its inner loop.
 __device__ __forceinline__ uint4 load_chunk_a8(const u16* p, int valid, bool vec_ok) {
     if (valid >= 8 && vec_ok) return *reinterpret_cast<const uint4*>(p);

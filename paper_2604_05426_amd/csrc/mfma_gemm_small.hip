@@ -210,17 +210,7 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
             dma16(v, bb, dst_b + kb * 1024);
         }
     };
-    // The same for rows of r elements that start anywhere (ranks that are no multiples of 8): elements r0 .. r0 + kc - 1 of each, through
-    // registers.  A piece that would reach past its row is loaded from where it still fits and shifted.
-    auto row_piece = [&](const u16* row, int r, int at) {
-        if (r < 8) return load_chunk(row + min(at, r), max(0, r - at), false);
-        const int from = min(at, r - 8), sh = min((at - from) * 16, 128);
-        uint4 v;
-        __builtin_memcpy(&v, row + from, 16);
-        const uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
-        const uint64_t l = sh == 0 ? lo : sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : sh < 128 ? hi >> (sh - 64) : 0, h = sh < 64 ? hi >> sh : 0;
-        return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
-    };
+    // The same for rows of r elements that start anywhere (ranks that are no multiples of 8): elements r0 .. r0 + kc - 1 of each, through registers.
     auto stage_pass = [&](int slot, const u16* e, int lo, int hi, const u16* F, int r, int r0, int kc) {
         unsigned char* const Pa = lds + (NSA - 1 - slot) * AT;
         unsigned char* const Pb = lds + B0 + (NSB - 1 - slot) * BT;
