@@ -42,12 +42,16 @@ constexpr int kSplitChunks = 3, kSplitChunkBytes = (2 << 20) - (128 << 10);
 //     64 x 2048  33.9 / 31.0, x 3072  37.1 / 41.7
 //   2 ways rather than 1: 66 x 2560  14.7 / 15.9, x 3072  15.6 / 18.0; 128 x 2560  17.9 / 17.0, x 3072  19.0 / 19.2; wide: 128 x 4096
 //     52.3 / 54.5 forward, 58.5 / 53.0 backward, x 5120  58.4 / 66.4 and 60.2 / 65.4
-inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus, bool wide) {
+// `halves`: undivided, such a launch is divided by rows (shrink_halves_kernel), which hands nothing over, and the shares that it saves are
+// large (a rank above 32; the lines above hold for smaller ones: 64 x 3072, ranks to 16, divided by contraction / by rows 23.5 / 26.1):
+//   64 x 2048  23.5 / 21.6, x 3072  28.6 / 27.1, x 4096  33.0 / 33.2; 80 x 4096  42.5 / 41.4, x 4608  45.9 / 45.6; 128 x 3072  37.3 / 33.4,
+//   x 5120  53.2 / 48.9 (forward calls with products of 256 columns, rank 64)
+inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus, bool wide, bool halves = false) {
     const int64_t steps = contraction / 64;
     if (blocks <= 0 || shrink_log_pieces((int)steps) == 0) return 1;
     if (8 * blocks <= num_cus && (steps >= 64 || blocks <= 8)) return 8;
-    if (4 * blocks <= num_cus) return steps >= (wide && blocks > 32 ? 48 : 32) ? 4 : 1;
-    if (2 * blocks <= num_cus) return steps >= (wide ? 80 : 48) ? 2 : 1;
+    if (4 * blocks <= num_cus) return steps >= (blocks <= 32 ? 32 : halves ? 64 : wide ? 48 : 32) ? 4 : 1;
+    if (2 * blocks <= num_cus) return steps >= (wide || halves ? 80 : 48) ? 2 : 1;
     return 1;
 }
 

@@ -246,6 +246,8 @@ __global__ __launch_bounds__(64 * SNW) void shrink_kernel(ShrinkArgs g) {
 // at c ^ (t & 7); the A_i tile [k][ranks], read with the transposing load, keeps 32-byte unit u of row k at u ^ nn_swz(k)
 // (256-byte rows) or u ^ (((k >> 1) & 1) | (((k >> 3) & 1) << 1)) (128-byte rows).  Rows past the block and ranks past r_i
 // are clamped to valid addresses; they only feed outputs that are not stored.
+//   4 with ROWS = 32 (shrink_halves_kernel): X / dY tile 4 KB, loaded by wavefronts 0 .. 3, twelve 12 KB stages; wavefront w owns row block w & 1 and
+//     rank block w >> 1.
 //   8 with ROWS = 128 (ranks 65..128, the wide rank class, whose row blocks are 128 rows): X / dY tile 16 KB, adapter tile 16 KB,
 //     five 32 KB stages; wavefront w owns row block w (of eight) and all eight rank blocks.  With 64-row blocks the adapter tile was
 //     twice the X tile and both go through the same load path of the CU; 128 rows halve that traffic per X byte.
@@ -264,16 +266,16 @@ template <bool FWD, int RB16, bool SPLIT, bool DENSE = false, int ROWS = 64>
 __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Entry4 e, unsigned char* lds, const int block, const int split,
                                                   const int half = 0) {
     static_assert(FWD || !DENSE, "the dense adapter tile is a layout of A_i");
-    static_assert(ROWS == 64 || (ROWS == 128 && RB16 == 8 && !DENSE), "128-row blocks: wide rank class, swizzled adapter tile");
+    static_assert(ROWS == 64 || (ROWS == 32 && RB16 == 4 && !DENSE && !SPLIT) || (ROWS == 128 && RB16 == 8 && !DENSE), "128-row blocks: wide rank class, swizzled adapter tile");
     constexpr int ST_XT = ROWS * 128;               // X / dY tile bytes
     constexpr int FT = RB16 * 2048;                 // adapter tile bytes
     constexpr int STAGE = ST_XT + FT;
-    constexpr int NST = ROWS == 128 ? 5 : RB16 == 8 ? 6 : 9;   // ring stages (144 KB; 160 KB with 128-row blocks)
-    constexpr bool PAIRS = ROWS == 64;              // two steps per barrier (128-row blocks: too few stages)
+    constexpr int NST = ROWS == 128 ? 5 : ROWS == 32 ? 12 : RB16 == 8 ? 6 : 9;   // ring stages (144 KB; 160 KB with 128-row blocks)
+    constexpr bool PAIRS = ROWS <= 64;              // two steps per barrier (128-row blocks: too few stages)
     constexpr int AHEAD = PAIRS ? NST - 2 : NST - 1;            // steps loaded ahead of the one that is waited for
-    constexpr int NX = ROWS / 64;                   // X-tile loads per wavefront per step
+    constexpr int NX = ROWS == 128 ? 2 : 1;         // X-tile loads per wavefront per step (32 rows: of the first four)
     constexpr int NF = RB16 / 4;                    // adapter-tile loads per wavefront per step
-    constexpr int NCB = ROWS == 128 ? RB16 : RB16 / 2;   // rank blocks per wavefront
+    constexpr int NCB = ROWS == 128 ? RB16 : ROWS == 32 ? RB16 / 4 : RB16 / 2;   // rank blocks per wavefront
     constexpr int FROW = RB16 * 32;                 // FWD: bytes per contraction row of the A_i tile
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -323,14 +325,15 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
         const int t = min(issued, steps - 1);
         const unsigned dst = lds0 + slot_in * STAGE;
 #pragma unroll
-        for (int j = 0; j < NX; ++j) dma16(voffX[j], baseX + (int64_t)t * 128, dst + (NX * wave + j) * 1024);
+        for (int j = 0; j < NX; ++j)
+            if (ROWS != 32 || wave < 4) dma16(voffX[j], baseX + (int64_t)t * 128, dst + (NX * wave + j) * 1024);
 #pragma unroll
         for (int j = 0; j < NF; ++j) dma16(voffF[j], baseF + t * stepF, dst + ST_XT + (NF * wave + j) * 1024);
         ++issued;
         slot_in = slot_in == NST - 1 ? 0 : slot_in + 1;
     };
 
-    const int rb = ROWS == 128 ? wave : (wave & 3), ch = ROWS == 128 ? 0 : (wave >> 2);
+    const int rb = ROWS == 128 ? wave : ROWS == 32 ? (wave & 1) : (wave & 3), ch = ROWS == 128 ? 0 : ROWS == 32 ? (wave >> 1) : (wave >> 2);
     f32x4 acc[NCB];
     const int xrow = 16 * rb + l16;
     const int vq = fkey(8 * g4 + (l16 >> 2));      // key of the A_i tile rows this lane reads (rows +4, +32 share it)
@@ -377,7 +380,9 @@ __device__ __forceinline__ void shrink_tiled_body(const ShrinkArgs& g, const Ent
     // multiply.
     auto advance = [&](auto count, int& slot) {
         constexpr int STEPS = decltype(count)::value;
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NX + NF) * (AHEAD - STEPS)) : "memory");
+        if (ROWS == 32 && wave >= 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NF * (AHEAD - STEPS)) : "memory");
+        else                         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NX + NF) * (AHEAD - STEPS)) : "memory");
+        asm volatile("s_barrier" ::: "memory");
 #pragma unroll
         for (int u = 0; u < STEPS; ++u) issue();
         compute(count, slot);
@@ -539,6 +544,21 @@ __global__ __launch_bounds__(64 * SNW) void shrink_tiled_kernel(ShrinkArgs g) {
     }
 }
 
+// Launches of no more than half as many blocks as there are CUs whose contraction is not divided (ranks up to 64, multiples of 8): a work group
+// takes 32 rows of a block, 12 KB through the CU's load path per step instead of 16, and twice as many CUs load.  A row's sum is the
+// same chain.  us, forward calls with products of 256 columns, 64 rows / 32: 8192 tokens, k = 2560, ranks 8 and 64 33.8 / 31.5; 8192 x 2048 27.2 /
+// 26.3; 4001 x 1792 20.4 / 19.9; 1024 x 1024 14.2 / 13.6.  With sixteen or fewer ranks 0.1-0.3 less.
+template <bool FWD>
+__global__ __launch_bounds__(64 * SNW) void shrink_halves_kernel(ShrinkArgs g) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[147456];
+    // the halves of a block on one XCD (blockIdx % 8): they share its adapter's lines
+    const int block = (blockIdx.x / 16) * 8 + blockIdx.x % 8, first = (blockIdx.x / 8 % 2) * 32;
+    if (block >= g.blocks) return;
+    const Entry4 e = g.pv.class_blocks[block];
+    if (first >= e.d) return;
+    shrink_tiled_body<FWD, 4, false, false, 32>(g, Entry4{e.a, e.b, e.c + first, min(32, e.d - first)}, lds, block, 0);
+}
+
 template <bool FWD>
 static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
     const dim3 block(64 * SNW);
@@ -551,7 +571,8 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
     // the tiled kernels walk the class table (wide class first, 128-row blocks); the register-staged ones the canonical 64-row blocks
     a.blocks = p->n_blocks_wide + p->n_blocks_narrow;
     a.blocks_wide = p->n_blocks_wide;
-    a.splits = tiled ? shrink_splits(a.blocks, a.Kdim, p->num_cus, wide) : 1;
+    const bool halves = !wide && !mixed && 2 * a.blocks <= p->num_cus;      // where the contraction is not divided, the blocks are
+    a.splits = tiled ? shrink_splits(a.blocks, a.Kdim, p->num_cus, wide, halves && p->max_rank_narrow > 32) : 1;
     a.log_splits = a.splits == 8 ? 3 : a.splits == 4 ? 2 : a.splits == 2 ? 1 : 0;
     a.share_wide = shrink_share_bytes(p->max_rank_wide);
     a.share_narrow = shrink_share_bytes(p->max_rank_narrow);
@@ -572,7 +593,9 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
         if (!mixed) { if (!wide) go(shrink_tiled_kernel<FWD, false, false, SP>); else go(shrink_tiled_kernel<FWD, true, false, SP>); }
         else        { if (!wide) go(shrink_tiled_kernel<FWD, false, true, SP>);  else go(shrink_tiled_kernel<FWD, true, true, SP>); }
     };
-    if (tiled && a.splits > 1) {
+    if (tiled && a.splits == 1 && halves) {
+        hipLaunchKernelGGL(shrink_halves_kernel<FWD>, dim3((a.blocks + 7) / 8 * 16), block, 0, st, a);
+    } else if (tiled && a.splits > 1) {
         tiled_build(std::true_type{});
     } else if (tiled) {
         tiled_build(std::false_type{});
