@@ -1,7 +1,7 @@
 // The general kernels: fp32 plans, and bf16 plans whose k or n is not a multiple of 8 (rows that start at any element).
 // Every step of the layer (paper Sec. 5.1) is one grouped launch on the matrix units, with fp32 accumulation:
 //   S_i = X_i A_i, dS_i = s_i dY_i B_i^T               general_shrink_kernel
-//   Y = X W + s_i S_i B_i, dX = dY W^T + dS_i A_i^T    general_gemm_kernel in bf16 (also either term alone); fp32: f32_gemm.hip
+//   Y = X W + s_i S_i B_i, dX = dY W^T + dS_i A_i^T    general_gemm_kernel, whole_tile_kernel in bf16 (also either term alone); fp32: f32_gemm.hip
 //   dA_i = X_i^T dS_i, dB_i = s_i S_i^T dY_i           general_wgrad_kernel
 // No operand needs an alignment beyond its element: 16-byte pieces are loaded from wherever they start (global memory takes any
 // alignment), pieces that cross an edge element by element.
@@ -15,7 +15,7 @@
 // of S, Y, dS and dX have the same bits whatever its neighbours' tokens and ranks are.
 //
 // One step forward and backward, before (a scalar-FMA grouped product whose descriptors took a launch each) and now: fp32, 4 x 64
-// tokens, 256 x 256: 171 -> 21 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 265 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 67 us.
+// tokens, 256 x 256: 171 -> 21 us; fp32, 2048 tokens, 2048 x 2048: 1590 -> 255 us; bf16, 1500 tokens, 2048 x 1001: 1105 -> 62 us.
 #include <type_traits>
 
 #include "general_wgrad.h"
@@ -227,8 +227,9 @@ struct GenGemmArgs {
 // For products of at least 64 in every direction that fill half of the chip with such tiles: four wavefronts load and four multiply.  The loads of four
 // steps are on their way in the loading wavefronts' registers (rows start at any element, so they cannot go to LDS directly), which hand a
 // step over in one of two LDS stages per barrier; the multiplying ones (2 x 2 sub-tiles) read a step's fragments while the one before it is
-// multiplied.  With wavefronts that did both (KC = 1 below) a step took 1500 cycles, the time of its loads, LDS stores, fragment reads and products
-// after one another.  us, before / now: 1500 x 1001 outputs, contraction 2048, 22.2 / 17.5; 1000 x 1001 15.1 / 11.0; 1500 x 2048, contraction 1001, backward 22.4 / 20.2.
+// multiplied.  With wavefronts that did both (KC = 1 below, which fewer rows or columns, a shorter contraction and the LoRA term alone still take) a step took
+// 1500 cycles, the time of its loads, LDS stores, fragment reads and products after one another.  us, before / now: 1500 x 1001 outputs, contraction 2048, 22.2 /
+// 17.5; 1000 x 1001 15.1 / 11.0; 1500 x 2048, contraction 1001, backward 22.4 / 20.2.
 // Sums in the order of the other tiles (see below).  The operands of the first rank-extension pass are staged while the contraction ends.
 // BM x 64, BM 64 or 128.
 template <int BM> constexpr int kWholeStage = (BM + 64) * 128;       // bytes of a step's operand tiles [BM][64] and [64][64]
