@@ -242,7 +242,7 @@ __device__ __forceinline__ void whole_tile_body(const GenGemmArgs& g, unsigned c
     const int wm = (wave >> 1) & 1, wn = wave & 1, l16 = lane & 15, g4 = lane >> 4;
     const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)g.tiles_n;
     const uint32_t slot_x = wg / 8, L = ((slot_x / g.xcd_run) * 8 + wg % 8) * g.xcd_run + slot_x % g.xcd_run;
-    if (L >= (uint32_t)tiles_m * (uint32_t)tiles_n) return;
+    if (L >= (uint32_t)tiles_m * (uint32_t)tiles_n) return;         // (a launch of two dimensions holds more)
     const int band = (int)(L / (8u * tiles_n)), in_band = (int)(L - (uint32_t)band * 8u * tiles_n), band_rows = min(8, tiles_m - band * 8);
     // The last tile of rows / columns starts early enough to be whole; what it shares with the tile before is not stored.
     const int64_t m_own = (int64_t)(band * 8 + in_band % band_rows) * BM, n_own = (int64_t)(in_band / band_rows) * 64;
@@ -560,7 +560,7 @@ __device__ __forceinline__ void whole_tile_body(const GenGemmArgs& g, unsigned c
 template <bool FWD, int BM>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(BM == 64 ? 4 : 2))) void whole_tile_kernel(GenGemmArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[3 * kWholeStage<BM>];      // two steps and a pass
-    whole_tile_body<FWD, BM>(g, lds, blockIdx.x);
+    whole_tile_body<FWD, BM>(g, lds, blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // Tile: KC = 1: 64 x 64, KC = 4: 32 x 32; four wavefronts 2 x 2, each 2 x 2 blocks or one.
@@ -575,6 +575,7 @@ template <bool FWD, int KC>
 __device__ __forceinline__ void general_gemm_body(const GenGemmArgs& g, unsigned char* const lds, const uint32_t wg) {
     typedef u16 T;
     constexpr int BT = KC == 1 ? 64 : 32;                    // tile edge
+    if (wg >= (uint32_t)((g.M + BT - 1) / BT * g.tiles_n)) return;      // (a launch of two dimensions holds more)
     constexpr int NB = BT / 32;                              // blocks of a wavefront, each way
     constexpr int KW = 128 / (int)sizeof(T), KT = KW * KC;   // contraction per chunk and per step
     constexpr int EPC = kEpc<T>;
@@ -848,7 +849,7 @@ __device__ __forceinline__ void general_gemm_body(const GenGemmArgs& g, unsigned
 template <bool FWD, int KC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KC == 1 ? 3 : 2))) void general_gemm_kernel(GenGemmArgs g) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kGenGemmLds<FWD, KC>];
-    general_gemm_body<FWD, KC>(g, lds, blockIdx.x);
+    general_gemm_body<FWD, KC>(g, lds, blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // The backward product and the weight gradients of a small batch: both need dS alone.  The first `gemm_groups` work groups take the
@@ -876,7 +877,8 @@ __global__ __launch_bounds__(512) void general_wgrad_kernel(GenWgradArgs<T> g) {
 
 // ---- launches --------------------------------------------------------------------------------------------------------------------
 
-// Work groups along x; a dimension of a launch holds fewer than 2^32 work items (2^23 work groups of 512), the rest goes along y.
+// Work groups along x (a multiple of the 8 XCDs where there are more); a dimension of a launch holds fewer than 2^32 work items (2^23 work groups of
+// 512), the rest goes along y.  Kernels drop the groups by which the last row of the grid is too long.
 constexpr int64_t kGridX = 1 << 20;
 dim3 two_dims(int64_t groups) { return dim3((unsigned)(groups < kGridX ? groups : kGridX), (unsigned)((groups + kGridX - 1) / kGridX)); }
 
@@ -956,7 +958,7 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
             return MLORA_OK;
         }
     }
-    if (!split && a.base && a.M >= 128 && a.N >= 64 && a.K >= 64 && groups < (1 << 24)) {
+    if (!split && a.base && a.M >= 128 && a.N >= 64 && a.K >= 64) {
         // 128 x 64 tiles (forward) where they make few enough rounds: a work group takes 0.45 us per 64-wide step, alone on its CU; 64 x 64 ones, two on a CU,
         // 0.28 each.  us, 64 x 64 / 128 x 64, tokens x outputs x contraction: 1500 x 1001 x 2048 21.0 / 17.5, 4000 x 1001 x 2048 37.9 / 32.0; not 1000 x
         // 1001 x 2048 11.0 / 16.2.  Backward (both operands from rows that start anywhere) 1500 x 2048 x 1001 20.6 / 25.1, 4000 x 2048 x 1001 46.9 / 48.4.
@@ -965,11 +967,11 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
         const bool wide = FWD && 45 * rounds(tall) < 28 * rounds(groups);
         const int64_t n = wide ? tall : groups;
         a.xcd_run = n >= 256 ? 32 : (int32_t)((n + 7) / 8);
-        const dim3 grid((unsigned)((n + 8 * a.xcd_run - 1) / (8 * a.xcd_run) * (8 * a.xcd_run)));
+        const dim3 grid = two_dims((n + 8 * a.xcd_run - 1) / (8 * a.xcd_run) * (8 * a.xcd_run));
         if (wide) hipLaunchKernelGGL((whole_tile_kernel<FWD, FWD ? 128 : 64>), grid, dim3(512), 0, st, a);
         else      hipLaunchKernelGGL((whole_tile_kernel<FWD, 64>), grid, dim3(512), 0, st, a);
-    } else if (split) hipLaunchKernelGGL((general_gemm_kernel<FWD, 4>), dim3((unsigned)groups), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((general_gemm_kernel<FWD, 1>), dim3((unsigned)groups), dim3(256), 0, st, a);
+    } else if (split) hipLaunchKernelGGL((general_gemm_kernel<FWD, 4>), two_dims(groups), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((general_gemm_kernel<FWD, 1>), two_dims(groups), dim3(256), 0, st, a);
     MLORA_HIP_TRY(hipGetLastError());
     return MLORA_OK;
 }

@@ -1,4 +1,5 @@
-"""Launches of the general kernels whose work groups do not fit one dimension of a grid (2^32 work items): very many rows, very wide rows."""
+"""Launches of the general kernels whose work groups do not fit one dimension of a grid (2^32 work items): very many rows, very wide rows,
+very many output tiles."""
 import pytest
 import torch
 
@@ -41,4 +42,27 @@ def test_columns_beyond_one_grid_dimension():
     torch.cuda.synchronize()
     assert torch.equal(dA[:, 0], 3.0 * X[0]) and torch.equal(dX[0], 3.0 * A[:, 0])      # dS = 2 dY B = 3
     assert float(dB) == 0.25                                                            # 2 S dY
+    plan.destroy()
+
+
+def test_products_beyond_one_grid_dimension():
+    """dX of 2^20 rows and 32769 columns: 2^23 + tiles of 64 x 64, work groups of 512.  Entries -1, 0 and 1: every sum of 65 is exact."""
+    T, k, n = 1 << 20, 32769, 65
+    gen = torch.Generator(device="cuda").manual_seed(1)
+
+    def units(*shape):
+        return torch.randint(-1, 2, shape, device="cuda", dtype=torch.int8, generator=gen).to(torch.bfloat16)
+
+    W, dY = units(k, n), units(T, n)
+    dX = torch.full((T, k), float("nan"), device="cuda", dtype=torch.bfloat16)
+    plan = ml.Plan(ml.BF16, T, k, n, [], [], [0])
+    print(f"[case] general product T={T} k={k} n={n}", flush=True)
+    ml.multi_lora_bwd(plan, dY, None, W, None, None, None, dX, None, None, None, ml.FLAG_BASE_ONLY)
+    torch.cuda.synchronize()
+    rows = 1 << 15
+    for lo in range(0, T, rows):
+        assert not bool(torch.isnan(dX[lo:lo + rows]).any()), lo
+    Wt = W.float().T.contiguous()
+    for lo in (0, T // 2 - 100, T - 200):
+        assert torch.equal(dX[lo:lo + 200].float(), dY[lo:lo + 200].float() @ Wt)
     plan.destroy()
