@@ -43,14 +43,19 @@ constexpr int kSplitChunks = 3, kSplitChunkBytes = (2 << 20) - (128 << 10);
 //   2 ways rather than 1: 66 x 2560  14.7 / 15.9, x 3072  15.6 / 18.0; 128 x 2560  17.9 / 17.0, x 3072  19.0 / 19.2; wide: 128 x 4096
 //     52.3 / 54.5 forward, 58.5 / 53.0 backward, x 5120  58.4 / 66.4 and 60.2 / 65.4
 // `halves`: undivided, such a launch is divided by rows (shrink_halves_kernel), which hands nothing over, and the shares that it saves are
-// large (a rank above 32; the lines above hold for smaller ones: 64 x 3072, ranks to 16, divided by contraction / by rows 23.5 / 26.1):
-//   64 x 2048  23.5 / 21.6, x 3072  28.6 / 27.1, x 4096  33.0 / 33.2; 80 x 4096  42.5 / 41.4, x 4608  45.9 / 45.6; 128 x 3072  37.3 / 33.4,
-//   x 5120  53.2 / 48.9 (forward calls with products of 256 columns, rank 64)
+// large (a rank above 32; the lines above hold for smaller ones).  us, split / halves, the decoupled forward of 256 columns (shrink and expand-add), warm:
+//   4 ways, 57 to 64 blocks, from 44 steps: 64 blocks, rank 64 at 32, 44, 52 steps split 1.11, 1.07, 1.04 times the halves' time, ranks 8 .. 64
+//     1.04, 1.00, 0.98, one adapter of rank 64 among seven of 8 and 16 1.04, 0.97, 0.93; 33 to 56 blocks, from 36: 56 blocks, rank 64 at 32, 36, 44
+//     1.02, 0.99, 0.97, ranks 8 .. 64 1.01, 1.00, 0.94, rank 48 0.98, 0.97, 0.92; 40 blocks, rank 64 at 48, 63 0.90, 0.86
+//   2 ways, 65 to 128 blocks, from 80: 128 blocks, rank 64 at 48, 79 steps 1.15, 1.10, one of 64 among seven 1.09, 1.10; 96 blocks 1.09, 1.05 and
+//     1.07, 1.03
+// Blocks of 32 rows or fewer have no second half: neither form is faster for them within these lines (48 segments of 20 tokens at 32 .. 48 steps
+// 0.97 .. 1.02, 64 of 31 0.98 .. 1.01, 100 of 30 at 48 .. 79 0.98 .. 1.01).
 inline int shrink_splits(int64_t blocks, int64_t contraction, int num_cus, bool wide, bool halves = false) {
     const int64_t steps = contraction / 64;
     if (blocks <= 0 || shrink_log_pieces((int)steps) == 0) return 1;
     if (8 * blocks <= num_cus && (steps >= 64 || blocks <= 8)) return 8;
-    if (4 * blocks <= num_cus) return steps >= (blocks <= 32 ? 32 : halves ? 64 : wide ? 48 : 32) ? 4 : 1;
+    if (4 * blocks <= num_cus) return steps >= (blocks <= 32 ? 32 : halves ? (blocks > 56 ? 44 : 36) : wide ? 48 : 32) ? 4 : 1;
     if (2 * blocks <= num_cus) return steps >= (wide || halves ? 80 : 48) ? 2 : 1;
     return 1;
 }
@@ -165,6 +170,16 @@ struct mlora_plan {
 };
 
 namespace mlora {
+
+// Whether the plan's tiled shrink (fwd) or gradient shrink deals undivided row blocks out by halves, and into how many shares it divides their
+// contraction: what the launches do and what plan creation holds memory for.
+inline bool shrink_by_halves(const mlora_plan* p, bool fwd) {
+    return p->n_blocks_wide == 0 && 2 * p->n_blocks_narrow <= p->num_cus && !(fwd && !p->ranks_mult8);
+}
+inline int shrink_splits(const mlora_plan* p, bool fwd) {
+    return shrink_splits((int64_t)p->n_blocks_wide + p->n_blocks_narrow, fwd ? p->k : p->n, p->num_cus, p->n_blocks_wide != 0,
+                         shrink_by_halves(p, fwd) && p->max_rank_narrow > 32);
+}
 
 void set_error(const std::string& msg);
 int hip_fail(hipError_t e, const char* what);

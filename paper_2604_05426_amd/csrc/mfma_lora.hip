@@ -571,8 +571,7 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
     // the tiled kernels walk the class table (wide class first, 128-row blocks); the register-staged ones the canonical 64-row blocks
     a.blocks = p->n_blocks_wide + p->n_blocks_narrow;
     a.blocks_wide = p->n_blocks_wide;
-    const bool halves = !wide && !mixed && 2 * a.blocks <= p->num_cus;      // where the contraction is not divided, the blocks are
-    a.splits = tiled ? shrink_splits(a.blocks, a.Kdim, p->num_cus, wide, halves && p->max_rank_narrow > 32) : 1;
+    a.splits = tiled ? shrink_splits(p, FWD) : 1;
     a.log_splits = a.splits == 8 ? 3 : a.splits == 4 ? 2 : a.splits == 2 ? 1 : 0;
     a.share_wide = shrink_share_bytes(p->max_rank_wide);
     a.share_narrow = shrink_share_bytes(p->max_rank_narrow);
@@ -593,7 +592,7 @@ static void launch_shrink(mlora_plan* p, ShrinkArgs a, hipStream_t st) {
         if (!mixed) { if (!wide) go(shrink_tiled_kernel<FWD, false, false, SP>); else go(shrink_tiled_kernel<FWD, true, false, SP>); }
         else        { if (!wide) go(shrink_tiled_kernel<FWD, false, true, SP>);  else go(shrink_tiled_kernel<FWD, true, true, SP>); }
     };
-    if (tiled && a.splits == 1 && halves) {
+    if (tiled && a.splits == 1 && shrink_by_halves(p, FWD)) {      // where the contraction is not divided, the blocks are
         hipLaunchKernelGGL(shrink_halves_kernel<FWD>, dim3((a.blocks + 7) / 8 * 16), block, 0, st, a);
     } else if (tiled && a.splits > 1) {
         tiled_build(std::true_type{});

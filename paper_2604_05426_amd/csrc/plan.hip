@@ -481,7 +481,7 @@ static int plan_create_impl(mlora_plan** out, int dtype, int64_t T, int64_t k, i
     const size_t o_bo_tmp = take(own_seg ? sizeof(Entry4) * (size_t)(p->n_bands + 1) : 0);
     // shrink kernels over fewer row blocks than CUs: at most num_cus shares in all (forward and backward take turns)
     const int64_t class_blocks = rb_wide + rb_narrow;
-    const int max_splits = p->use_mfma ? std::max(shrink_splits(class_blocks, k, p->num_cus, rb_wide > 0), shrink_splits(class_blocks, n, p->num_cus, rb_wide > 0)) : 1;
+    const int max_splits = p->use_mfma ? std::max(shrink_splits(p, true), shrink_splits(p, false)) : 1;
     const int32_t n_arrived = max_splits > 1 ? (int32_t)(2 * class_blocks) : 0;
     const size_t o_arrived = take(sizeof(uint32_t) * (size_t)n_arrived);
     auto block1 = std::make_shared<DeviceBlock>();
