@@ -218,16 +218,17 @@ struct GenGemmArgs {
     int64_t lda, ldw, ldc;
     int64_t M, N, K;
     int64_t tiles_n;
+    int64_t R1;                   // elements of E
     int32_t base, lora;           // which terms; without the base term C += LoRA term
     int32_t xcd_run;              // whole tiles: consecutive tiles per XCD
     PlanView pv;
 };
 
 // ---- whole 64 x 64 tiles ---------------------------------------------------------------------------------------------------------
-// For products of at least 64 in every direction that fill half of the chip with such tiles: four wavefronts load and four multiply.  The loads of four
-// steps are on their way in the loading wavefronts' registers (rows start at any element, so they cannot go to LDS directly), which hand a
-// step over in one of two LDS stages per barrier; the multiplying ones (2 x 2 sub-tiles) read a step's fragments while the one before it is
-// multiplied.  With wavefronts that did both (KC = 1 below, which fewer rows or columns, a shorter contraction and the LoRA term alone still take) a step took
+// For products of at least 128 rows, 64 columns and a contraction of 64 that fill half of the chip with such tiles (see the launch): four wavefronts
+// load and four multiply.  The loads of four steps are on their way in the loading wavefronts' registers (rows start at any element, so they cannot go to
+// LDS directly), which hand a step over in one of two LDS stages per barrier; the multiplying ones (2 x 2 sub-tiles) read a step's fragments while the
+// one before it is multiplied.  With wavefronts that did both (KC = 1 below, which other sizes and the LoRA term alone still take) a step took
 // 1500 cycles, the time of its loads, LDS stores, fragment reads and products after one another.  us, before / now: 1500 x 1001 outputs, contraction 2048, 22.2 /
 // 17.5; 1000 x 1001 15.1 / 11.0; 1500 x 2048, contraction 1001, backward 22.4 / 20.2.
 // Sums in the order of the other tiles (see below).  The operands of the first rank-extension pass are staged while the contraction ends.
@@ -317,7 +318,7 @@ __device__ __forceinline__ void whole_tile_body(const GenGemmArgs& g, unsigned c
         // Passes of the rank extension: 64 ranks of an adapter each; the first one's operands are asked for before the contraction's.  Elements
         // r0 + 8 ch .. of rows of rk that start anywhere: a piece that would reach past its row is loaded from where it still fits and shifted.
         uint64_t todo = 0;
-        int r0 = 0, by = 0, ranks = 0;                   // ranks of the lowest adapter in todo asked for; shift and ranks of the pass asked for last
+        int r0 = 0, by = 0, ranks = 0, rank = 0;         // ranks of the lowest adapter in todo asked for; of the pass asked for last: shift, ranks, its adapter's
         bool fetched = false;
         auto fetch = [&]() __attribute__((always_inline)) {
             fetched = todo != 0;
@@ -333,6 +334,7 @@ __device__ __forceinline__ void whole_tile_body(const GenGemmArgs& g, unsigned c
             auto f_row = [&](int j) { return F + (n0 + row + 8 * j) * rk; };
             const int at = r0 + ch * 8;
             ranks = min(64, rk - r0);
+            rank = rk;
             if (rk >= 8) {
                 const int from = min(at, rk - 8);
                 by = at - from;
@@ -342,22 +344,18 @@ __device__ __forceinline__ void whole_tile_body(const GenGemmArgs& g, unsigned c
 #pragma unroll
                     for (int j = 0; j < 2; ++j) __builtin_memcpy(&rb[D + 1][j], f_row(j) + from, 16);
                 }
-            } else {                                     // less than a piece: element by element, from the row's last ones where it ends
+            } else {         // less than a piece: one that starts with the row, or early enough to end with the buffer
                 by = 0;
-                auto few = [&](const u16* p) __attribute__((always_inline)) {
-                    u16 e[8];
-#pragma unroll
-                    for (int i = 0; i < 7; ++i) e[i] = p[min(i, rk - 1)];
-                    uint32_t w[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) w[i] = (2 * i < rk && ch == 0 ? e[2 * i] : 0u) | (i < 3 && 2 * i + 1 < rk && ch == 0 ? (uint32_t)e[2 * i + 1] << 16 : 0u);
-                    return u32x4v{w[0], w[1], w[2], w[3]};
+                auto few = [&](u32x4v& v, const u16* row_, const u16* end, int j) __attribute__((always_inline)) {
+                    const u16* const from = min(row_, end - 8);
+                    by |= (int)(row_ - from) << 4 * j;
+                    __builtin_memcpy(&v, from, 16);
                 };
 #pragma unroll
-                for (int j = 0; j < NA; ++j) ra[D + 1][j] = few(e_row(j));
+                for (int j = 0; j < NA; ++j) few(ra[D + 1][j], e_row(j), g.E + g.R1, j);
                 if (!FWD) {
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) rb[D + 1][j] = few(f_row(j));
+                    for (int j = 0; j < 2; ++j) few(rb[D + 1][j], f_row(j), F + g.N * rk, NA + j);
                 }
             }
             if (FWD) {
@@ -368,10 +366,21 @@ __device__ __forceinline__ void whole_tile_body(const GenGemmArgs& g, unsigned c
             else { todo &= todo - 1; r0 = 0; }
         };
         auto shift = [&]() __attribute__((always_inline)) {      // zeros past the ranks
+            auto each = [&](auto piece) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < NA; ++j) ra[D + 1][j] = as_vec(drop_front(as_uint4(ra[D + 1][j]), by));
+                for (int j = 0; j < NA; ++j) ra[D + 1][j] = as_vec(piece(as_uint4(ra[D + 1][j]), j));
+                if (!FWD) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) rb[D + 1][j] = as_vec(FWD ? (row + 8 * j < ranks ? as_uint4(rb[D + 1][j]) : zero4()) : drop_front(as_uint4(rb[D + 1][j]), by));
+                    for (int j = 0; j < 2; ++j) rb[D + 1][j] = as_vec(piece(as_uint4(rb[D + 1][j]), NA + j));
+                }
+            };
+            if ((rank & 7) == 0) each([&](uint4 v, int) { return by == 0 ? v : zero4(); });      // (a pass takes longer by what stands here)
+            else if (rank > 8)   each([&](uint4 v, int) { return drop_front(v, by); });
+            else                 each([&](uint4 v, int j) { return keep_front(drop_front(v, by >> 4 * j & 15), ch == 0 ? rank : 0); });
+            if (FWD) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) rb[D + 1][j] = as_vec(row + 8 * j < ranks ? as_uint4(rb[D + 1][j]) : zero4());
+            }
         };
         // (Oldest first and in the loop's own order: the waits in the loop are for the worse of what comes in from here and from its end.)
         if (first < cand_end) { candidates(); todo = mine(); fetch(); }
@@ -932,7 +941,7 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
     GenGemmArgs a{};
     a.A = (const u16*)A; a.W = (const u16*)W; a.C = (u16*)C; a.E = (const u16*)E;
     a.M = p->T; a.K = FWD ? p->k : p->n; a.N = FWD ? p->n : p->k;
-    a.lda = a.K; a.ldw = p->n; a.ldc = a.N;
+    a.lda = a.K; a.ldw = p->n; a.ldc = a.N; a.R1 = p->R1;
     a.base = (flags & MLORA_FLAG_LORA_ONLY) ? 0 : 1;
     a.lora = ((flags & MLORA_FLAG_BASE_ONLY) || p->n_row_blocks == 0) ? 0 : 1;
     a.pv = p->view;
@@ -958,13 +967,28 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
             return MLORA_OK;
         }
     }
-    if (!split && a.base && a.M >= 128 && a.N >= 64 && a.K >= 64) {
-        // 128 x 64 tiles (forward) where they make few enough rounds: a work group takes 0.45 us per 64-wide step, alone on its CU; 64 x 64 ones, two on a CU,
-        // 0.28 each.  us, 64 x 64 / 128 x 64, tokens x outputs x contraction: 1500 x 1001 x 2048 21.0 / 17.5, 4000 x 1001 x 2048 37.9 / 32.0; not 1000 x
-        // 1001 x 2048 11.0 / 16.2.  Backward (both operands from rows that start anywhere) 1500 x 2048 x 1001 20.6 / 25.1, 4000 x 2048 x 1001 46.9 / 48.4.
+    // Whole tiles of 128 rows, 64 columns and a contraction of 64 or more where that makes one round, two work groups a CU, or the contraction has two steps
+    // and as many as its tiles have passes of the rank extension: of the others' work groups three or four share a CU and hide each other's beginnings and passes.
+    // us, others / whole, tokens x outputs x contraction (rounds; passes a tile): forward 1500 x 1001 x 300 (0.8; 1.2) 17.4 / 15.8, 600 x 2001 x 130 (0.6; 4.8)
+    // 22.9 / 18.6, 8000 x 2048 x 65 (7.8; 1.1) 0.93 of whole's time, 2000 x 2048 x 129 (2; 1.2) 1.10, 2000 x 2048 x 129 and 193 (2; 3.1) 0.98, 333 1.10.
+    const double steps = (double)a.K / 64;
+    auto passes = [&](int log_rows) {                    // of the rank extension, a tile of that many rows on average
+        int64_t sum = 0;
+        for (int32_t i = 0; a.lora && i < p->N; ++i)
+            if (p->off[i + 1] > p->off[i]) sum += (((p->off[i + 1] - 1) >> log_rows) - (p->off[i] >> log_rows) + 1) * ((p->ranks[i] + 63) >> 6);
+        return (double)sum / (double)(((a.M - 1) >> log_rows) + 1);
+    };
+    const bool pieces = !a.lora || a.R1 >= 8;            // (what a tile reads of E at least)
+    if (!split && a.base && a.M >= 128 && a.N >= 64 && a.K >= 64 && pieces && (groups <= 2 * p->num_cus || (steps >= 2 && steps >= passes(6)))) {
+        // 128 x 64 tiles (forward) by what both take in us: a work group of 128 x 64, alone on its CU, waits for every pass with nothing else to run.  us, 64 x 64 /
+        // 128 x 64, tokens x outputs x contraction (passes a tile of 64, 128 rows): 1500 x 1001 x 2048 (1.2, 1.4) 28.9 / 25.4, 4000 x 1001 x 2048 (1.5,
+        // 2.0) 52.5 / 49.8, 2000 x 1001 x 700 (3.8, 6.3) 38.0 / 41.2, 2000 x 2001 x 130 (3.1, 5.3) 32.6 / 45.8, 4000 x 1001 x 700 (3.7, 6.4) 55.4 / 65.3;
+        // without extension 1500 x 1001 x 300 8.6 / 7.5, 4611 x 4018 x 729 77 / 99, 8000 x 1001 x 700 35.4 / 38.7.  Over 500 forward calls the choice takes
+        // 0.4 % longer than the best of these and the others, 12 % at worst (by rounds and steps alone 4.8 and 59 %).  Backward (both operands
+        // from rows that start anywhere) 1500 x 2048 x 1001 20.6 / 25.1, 4000 x 2048 x 1001 46.9 / 48.4.
         const int64_t tall = (a.M + 127) / 128 * a.tiles_n;
-        auto rounds = [&](int64_t n) { return (n + p->num_cus - 1) / p->num_cus; };
-        const bool wide = FWD && 45 * rounds(tall) < 28 * rounds(groups);
+        auto rounds = [&](int64_t n) { return (double)((n + p->num_cus - 1) / p->num_cus); };
+        const bool wide = FWD && rounds(tall) * (3.5 + 0.45 * steps + 0.8 * passes(7)) < 2.5 + rounds(groups) * (0.5 + 0.28 * steps + 0.3 * passes(6));
         const int64_t n = wide ? tall : groups;
         a.xcd_run = n >= 256 ? 32 : (int32_t)((n + 7) / 8);
         const dim3 grid = two_dims((n + 8 * a.xcd_run - 1) / (8 * a.xcd_run) * (8 * a.xcd_run));

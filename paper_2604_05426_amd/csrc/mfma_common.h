@@ -130,6 +130,12 @@ __device__ __forceinline__ uint4 drop_front(uint4 v, int d) {
     return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
 }
 
+// a piece with zeros behind its first n elements
+__device__ __forceinline__ uint4 keep_front(uint4 v, int n) {
+    auto word = [&](uint32_t w, int at) { return n > at + 1 ? w : n > at ? w & 0xffffu : 0u; };
+    return make_uint4(word(v.x, 0), word(v.y, 2), word(v.z, 4), word(v.w, 6));
+}
+
 // Elements at .. at + 7 of a row of r that starts at any element, zeros past its end: a piece that would reach past it is loaded from where it
 // still fits and shifted.
 __device__ __forceinline__ uint4 row_piece(const u16* row, int r, int at) {

@@ -1,6 +1,7 @@
 """The bf16 products and shrinks at the edges of their tiles, rings and dispatch rules: against the oracle, and bit for bit against the
 form that the same rows take in another tile or batch."""
 import pytest
+import torch
 
 from oracle import multilora_oracle as orc
 from paper_2604_05426_amd import binding as ml
@@ -51,7 +52,8 @@ def test_small_tiles(T, cols, steps):
             dl.plan.destroy()
 
 
-# odd widths: products of 128 rows, 64 columns and a contraction of 64 or more take whole tiles, 64 x 64 or (2000 x 700) 128 x 64; just below, the others
+# odd widths: 2000 and 2001 rows take whole tiles forward, 64 x 64 or 128 x 64; the others, whose tiles fill less than half of the chip, 32 x 32 tiles, and the
+# backward of all goes with the weight gradients (test_whole_tiles_alone has the whole tiles' own edges)
 @pytest.mark.parametrize("T,k,n", [(128, 64, 65), (127, 64, 65), (129, 63, 66), (191, 65, 127), (192, 319, 129), (193, 320, 321), (255, 323, 64),
                                    (257, 449, 131), (2000, 700, 333), (2001, 333, 701)])
 def test_whole_tiles_of_odd_widths(T, k, n):
@@ -64,6 +66,61 @@ def test_whole_tiles_of_odd_widths(T, k, n):
         for got, want in ((dl.Y, w.X.astype("f8") @ w.W.astype("f8")), (dl.dX, w.dY.astype("f8") @ w.W.T.astype("f8"))):
             assert rel_fro(to_host(got), want) <= 1e-2 and row_rel_max(to_host(got), want) <= 4e-2
         dl.plan.destroy()
+
+
+def _whole(dl, rows, cols, contraction, w):
+    """Whether a product of that size takes whole tiles (at least half of the chip, one round of two a CU or two steps and as many as passes)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = -(-rows // 64) * -(-cols // 64)
+    passes = sum(((b - 1) // 64 - a // 64 + 1) * -(-r // 64) for r, a, b in zip(w.ranks, w.offsets, w.offsets[1:]) if b > a) / -(-rows // 64)
+    return 2 * tiles > cus and rows >= 128 and min(cols, contraction) >= 64 and (tiles <= 2 * cus or contraction / 64 >= max(2, passes))
+
+
+# Products of 129 x 2, 2 x 68, 3 x 68, 129 x 6 tiles (the last: several rounds); the last tile of rows and columns whole or not; contractions of one step and
+# less than two, and on both sides of the four steps that are on their way.  Backward apart: a long segment, or tables too large to join.
+@pytest.mark.parametrize("T,cols,contractions", [(8200, 65, (64, 65, 127, 128)), (8256, 127, (191, 192, 193, 255)), (8193, 128, (257, 319, 321, 449)),
+                                                 (128, 4289, (64, 129)), (129, 4352, (65, 323)), (192, 4290, (191, 257)), (8200, 321, (193, 387))])
+@pytest.mark.parametrize("adapters", [9, 70])
+def test_whole_tiles_alone(T, cols, contractions, adapters):
+    # ranks below, at and above a 16-byte piece and a pass; a short, an empty and a long segment; rows of 3 that end with the buffer
+    ranks = ((33, 1, 7, 100, 0, 64, 8, 2, 3) if adapters == 9 else tuple((33, 1, 3, 7, 16, 5, 100)[i % 7] for i in range(69)) + (3,))
+    first = min(2100, T // 2)
+    rest = T - first - 1
+    lens = [first, 1, 0] + [rest // (adapters - 3)] * (adapters - 4)
+    lens.append(T - sum(lens))
+    for c in contractions:
+        for k, n in ((c, cols), (cols, c)):
+            if k % 8 == 0 and n % 8 == 0:
+                continue
+            print(f"[case] whole tiles alone T={T} k={k} n={n} adapters={adapters}", flush=True)
+            w = wl.make_workload("whole_tiles", "bf16", k, n, ranks, lens, [(2.0, 0.5, 1.0, 0.25)[i % 4] for i in range(adapters)], seed=T + k + n, b_sigma=0.3)
+            dl = DeviceLayer(w)
+            assert _whole(dl, T, cols, c, w)
+            dl.forward()
+            dl.plan.profile_begin(64)
+            dl.backward()
+            kernels = {ml.KERNEL_NAMES[i] for i, _ in dl.plan.profile_end(64)}
+            assert k != cols or "gemm_bwd" in kernels
+            dl.sync()
+            _check(dl, w)
+            dl.plan.destroy()
+
+
+@pytest.mark.parametrize("rank", [1, 7, 33, 100])
+@pytest.mark.parametrize("k,n,rows", [(129, 65, 150), (65, 321, 70), (300, 1001, 130)])
+def test_whole_tiles_leave_every_bit_alone(k, n, rows, rank):
+    """An adapter by itself (32 x 32 tiles) and with neighbours whose rows make whole tiles, before and behind it and with most of the passes."""
+    _same_bits("bf16", k, n, rank, [([(5, 3000)], [(3, 5300)]), ([(33, 1), (2, 8000)], []), ([], [(100, 2100)] + [(4, 100)] * 62)], rows)
+
+
+def test_whole_tiles_need_a_piece_of_the_rank_rows():
+    """Two rank rows of three elements: less than a piece, the launch takes the tiles that load them singly."""
+    w = wl.make_workload("six_elements", "bf16", 129, 65, (0, 3), (8198, 2), (1.0, 2.0), seed=6, b_sigma=0.3)
+    dl = DeviceLayer(w)
+    print("[case] six rank elements", flush=True)
+    dl.forward(); dl.backward(); dl.sync()
+    _check(dl, w)
+    dl.plan.destroy()
 
 
 @pytest.mark.parametrize("T,k,n", [(70, 520, 256), (200, 1096, 520)])
