@@ -744,13 +744,6 @@ __device__ __forceinline__ void general_gemm_body(const GenGemmArgs& g, unsigned
         }
         const int left = (int)(K - nt * KT);
         if (left > 0) {
-            auto drop = [&](uint4 v, int d) {            // the piece without its first d elements, zeros behind it
-                uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
-                const int sh = min(d * (int)sizeof(T) * 8, 128);
-                const uint64_t up = sh == 0 ? lo : sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : sh < 128 ? hi >> (sh - 64) : 0;
-                hi = sh < 64 ? hi >> sh : 0;
-                return make_uint4((uint32_t)up, (uint32_t)(up >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
-            };
             int miss[NCH];                               // elements by which a piece of this step reaches past the end
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
@@ -762,8 +755,8 @@ __device__ __forceinline__ void general_gemm_body(const GenGemmArgs& g, unsigned
             }
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
-                ra[0][c] = drop(ra[0][c], miss[c]);
-                rb[0][c] = FWD ? ((tid + 256 * c) / CPN < left ? rb[0][c] : zero4()) : drop(rb[0][c], miss[c]);
+                ra[0][c] = drop_front(ra[0][c], miss[c]);
+                rb[0][c] = FWD ? ((tid + 256 * c) / CPN < left ? rb[0][c] : zero4()) : drop_front(rb[0][c], miss[c]);
             }
             __syncthreads();                             // the fragments of stage 0 have been read
             store(0, ra[0], rb[0]);
