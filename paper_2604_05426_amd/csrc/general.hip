@@ -34,6 +34,7 @@ template <typename T> struct GenShrinkArgs {
     const T* src; int64_t ld;     // X (ld k) or dY (ld n); the contraction has ld elements
     T* out;                       // ragged S or dS
     int32_t rank_items;           // work groups along the ranks, 16 NB each
+    int32_t apart;                // these one after the other instead of side by side
     PlanView pv;
 };
 
@@ -44,19 +45,14 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
     __shared__ float red[NW * 16 * RLD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g4 = lane >> 4;
-    // The rank items of 16 rows stand side by side, so that the rows come from the caches; but not where there are 2, 4 or 8 of them: work group
-    // number modulo 8 is the XCD, and the higher items, empty for most adapters, would all be on the same ones.  us, fp32, 2048 tokens, contraction
-    // 2048, ranks 8 to 64 (4 items): side by side 19.0 forward, 23.5 backward, one item after the other 14.0, 18.4; in turned order 19.8, 24.7.  bf16, 1500
-    // tokens, contraction 2048, ranks to 33 (3 items): 6.0 and 7.7, 8.1 and 8.2.
     const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, groups = (int64_t)g.pv.n_row_blocks * 4;
     if (item >= groups * g.rank_items) return;
-    const bool apart = (g.rank_items & 1) == 0;
-    const int64_t wg = apart ? item % groups : item / g.rank_items;
+    const int64_t wg = g.apart ? item % groups : item / g.rank_items;
     const Entry4 e = g.pv.row_blocks[wg >> 2];
     const int sub = (wg & 3) * 16, rows = min(16, e.d - sub);
     if (rows <= 0) return;
     const int i = e.a, row0 = e.c + sub;
-    const int r = g.pv.rank[i], rho0 = (int)(apart ? item / groups : item % g.rank_items) * (16 * NB), rl = min(r - rho0, 16 * NB);      // this work group's ranks
+    const int r = g.pv.rank[i], rho0 = (int)(g.apart ? item / groups : item % g.rank_items) * (16 * NB), rl = min(r - rho0, 16 * NB);      // this work group's ranks
     if (rl <= 0) return;
     const float s = FWD ? 1.0f : g.pv.scale[i];
     const T* F = global_ptr<const T>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B) + (FWD ? (int64_t)rho0 : rho0 * g.ld);
@@ -904,6 +900,23 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     const int four = p->num_cus * (FWD ? 2 : 3) / 2;
     const int nb = p->max_rank <= 16 || groups * items(1) <= one ? 1 : !wide || groups * items(4) <= four ? 4 : 8;
     a.rank_items = items(nb);
+    // The rank items of 16 rows stand side by side, so that the rows come from the caches, or one after the other.  Work group number modulo 8 is the XCD: with
+    // an even number of items the higher ones, empty for most adapters, would all be on the same ones; with ranks that fill them a number of neighbours on an
+    // XCD want the same slice of the adapter's matrix, which is worth more as long as the rows' second reading comes from the L2s (32 MB in all).  Side by side's
+    // time over apart's in 396 shapes (256 .. 8000 tokens, contractions 520 .. 4095, both directions), fp32 and bf16: even, more than half of the items empty
+    // 1.11, 1.07 (8 items to 1.65); even and full 1.02, 1.01 (64 MB, ranks 64 0.91); odd and full 1.03, 1.02 (ranks 100, 8 MB 1.14; ranks 33, 33 and 65 MB
+    // 0.95, 0.93 of a call); odd, more than half empty 0.98, 0.96 (three items from 0.66).  The rule takes 0.5 % longer than the better of the two, 14 % at worst.
+    auto mostly_full = [&]() {
+        int64_t all = 0, full = 0;
+        for (int32_t i = 0; i < p->N; ++i) {
+            const int64_t rows = p->ranks[i] > 0 ? p->off[i + 1] - p->off[i] : 0;
+            all += rows * a.rank_items;
+            full += rows * ((p->ranks[i] + 16 * nb - 1) / (16 * nb));
+        }
+        return 5 * full >= 3 * all;
+    };
+    const int64_t bytes = p->T * a.ld * (int64_t)sizeof(T);
+    a.apart = (a.rank_items & 1) == 0 ? bytes < 50000000 || !mostly_full() : bytes < 30000000 && mostly_full();
     const dim3 grid = two_dims(groups * a.rank_items);
     if (nb == 1)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1>), grid, dim3(512), 0, st, a);
     else if (nb == 4) hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 4>), grid, dim3(512), 0, st, a);

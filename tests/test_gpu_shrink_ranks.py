@@ -23,3 +23,11 @@ def test_ranks_per_work_group(dtype, rank):
 def test_ranks_per_work_group_of_long_contractions(dtype, rank):
     """Several pieces of the contraction per wavefront, and a remainder: the chains that take turns go past their first piece."""
     _same_bits(dtype, 1030, 2051, rank, BATCHES[dtype], rows=90)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rank", [33, 48, 100])
+def test_order_of_the_rank_items(dtype, rank):
+    """Three or seven items of 16 ranks: one after the other where the adapter is alone, side by side with neighbours that leave most of them empty; a
+    neighbour whose rank makes their number even."""
+    _same_bits(dtype, 391, 520, rank, [([(4, 500)], [(8, 300)]), ([(64 if rank < 64 else 128, 70)], [(3, 150)])], rows=90)
