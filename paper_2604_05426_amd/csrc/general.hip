@@ -927,18 +927,19 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
 
 // Whether the weight gradients go with the backward product (one launch less).  A work group of four wavefronts takes twice as long for an item as
 // the eight of a launch of its own, so the longest adapter decides: its tokens times the work groups of both in CUs, or a contraction of
-// the product twice its tokens.  us a step, apart / together, tokens x k x n (longest adapter, work groups of both in CUs): 1500 x 2048 x 1001
-// (about 400, 6.4) 74.2 / 67.3, 256 x 257 x 256 (100, 0.4) 27.8 / 24.1, 1024 x 1001 x 3000 (60, 8.9) 79 / 70.6, 6000 x 1001 x 2048 (1000, 7.4) 154.5 /
-// 149.7, 6000 x 300 x 777 (1000, 2.7) 77.3 / 74.0, 2000 x 100 x 333 (2000, 1.0) 35.9 / 30.6; not: 2000 x 1001 x 300 (2000, 2.1) 45.9 / 46.9,
-// 6000 x 1001 x 300 (1000, 6.9) 73.1 / 77.4, 6000 x 100 x 333 (3000, 1.0) 56.0 / 60.1, 8000 x 1001 x 300 (4000, 8.5) 98.9 / 120.5.  Over 150 drawn
-// shapes a backward call takes 2.8 % more than the better of the two on average (always apart 18.3 %), and at most 2.8 % more than apart.
+// the product twice its tokens.  us a backward call, apart / together, tokens x k x n (longest adapter, work groups of both in CUs): 1500 x 2048 x 1001
+// (534, 6.4) 40.0 / 35.3, 256 x 257 x 256 (105, 0.4) 15.2 / 12.0, 1600 x 2048 x 1001 (1600, 3.5) 47.0 / 41.9, 2000 x 100 x 333 (2000, 1.0) 23.0 / 19.2;
+// not: 2000 x 1001 x 300 (2000, 2.1) 25.9 / 27.9, 3200 x 300 x 777 (1600, 1.1) 27.4 / 29.5, 6000 x 1001 x 2048 (1617, 10.4) 79.6 / 83.2, 6000 x 1001 x 300
+// (1617, 6.4) 39.0 / 42.2, 6000 x 100 x 333 (4241, 0.9) 36.5 / 42.9, 8000 x 1001 x 300 (6444, 8.9) 66.5 / 82.8.  Over 398 shapes a
+// call takes 4.5 % more than the better of the two on average (always apart 14.4 %), and at most 4.5 % more than apart; what the limit of ten work groups a CU
+// leaves apart would take up to a third less together (127 x 1232 x 553, 24 adapters 45.0 / 29.6).
 bool beside_product(const mlora_plan* p, const GenWgradArgs<u16>& w, int64_t groups, int64_t K) {
     const int64_t all = groups + (int64_t)w.panels * p->N * ((p->max_rank + 15) / 16);
     if (all > 10 * p->num_cus) return false;
     int64_t longest = 0;
     for (int32_t i = 0; i < p->N; ++i)
         if (p->ranks[i] > 0) longest = std::max(longest, p->off[i + 1] - p->off[i]);
-    return longest <= 2000 && (longest * all <= 4000 * p->num_cus || 2 * longest <= K);
+    return longest <= (p->T <= 2048 ? 2000 : 1500) && (longest * all <= 4000 * p->num_cus || 2 * longest <= K);
 }
 
 template <bool FWD>
