@@ -136,16 +136,6 @@ __device__ __forceinline__ uint4 keep_front(uint4 v, int n) {
     return make_uint4(word(v.x, 0), word(v.y, 2), word(v.z, 4), word(v.w, 6));
 }
 
-// Elements at .. at + 7 of a row of r that starts at any element, zeros past its end: a piece that would reach past it is loaded from where it
-// still fits and shifted.
-__device__ __forceinline__ uint4 row_piece(const u16* row, int r, int at) {
-    if (r < 8) return load_chunk(row + min(at, r), max(0, r - at), false);
-    const int from = min(at, r - 8);
-    uint4 v;
-    __builtin_memcpy(&v, row + from, 16);
-    return drop_front(v, at - from);
-}
-
 // load_chunk with 64-bit pieces when p is 8-byte aligned (ranks that are multiples of 4 but not of 8).  For kernels that load a
 // chunk once per work item; the extra paths cost registers in a kernel that loads chunks in its inner loop.
 __device__ __forceinline__ uint4 load_chunk_a8(const u16* p, int valid, bool vec_ok) {
@@ -183,6 +173,7 @@ struct GemmArgs {
     const u16* Bop; int64_t ldb;   // W [k,n]
     u16* C; int64_t ldc;           // Y [T,n] or dX [T,k]
     const u16* E;                  // ragged S (fwd) or dS (bwd)
+    int64_t R1;                    // its elements
     int32_t M, Ncols, Kdim;
     int32_t tiles_m, tiles_n;
     int32_t skip_lora;             // MLORA_FLAG_BASE_ONLY, or a plan without adapters (the LoRA-only mode has a kernel of its own)

@@ -613,7 +613,7 @@ static int launch_gemm(mlora_plan* p, bool fwd, const void* Aop, const void* W, 
     g.Bop = (const u16*)W;
     g.ldb = p->n;
     g.C = (u16*)C;
-    g.E = (const u16*)E;
+    g.E = (const u16*)E; g.R1 = p->R1;
     g.M = (int32_t)p->T;
     if (fwd) { g.lda = p->k; g.ldc = p->n; g.Ncols = (int32_t)p->n; g.Kdim = (int32_t)p->k; }
     else     { g.lda = p->n; g.ldc = p->k; g.Ncols = (int32_t)p->k; g.Kdim = (int32_t)p->n; }

@@ -8,7 +8,8 @@
 // and four multiply, one of each per SIMD: sub-tiles of a quarter of the tile need a third fewer LDS reads than eighths, no MFMA waits behind
 // the issue of a load, and the fragments of the next step (128 x 128: half step) are read while one is multiplied.  Cycles per step, eight
 // wavefronts that do both / now: 128 x 128 forward 847 / 697, backward 805 / 660; 64 x 128 632 / 500 and 519 / 515; 64 x 64 460 / 343 and 430 / 355
-// (without direct loads 128 x 128 takes 690-750: both halves of the work group are near their own limit).
+// (without direct loads 128 x 128 takes 690-750: both halves of the work group are near their own limit).  Half as many wavefronts issue a step's loads:
+// a contraction of up to eight steps takes 0.2-0.35 us longer (64 x 256, contraction 64 2.7 / 3.0 us, 256 3.1 / 3.45; 300 x 3072, 768 the same).
 //
 // Order of the sum: every output element is one chain of MFMAs - rank extension, contraction in ascending order, tail - exactly as in
 // the 256 x 256 kernel, so that a row has the same bits whichever tile its batch is given: the tile follows from the number of tokens
@@ -17,7 +18,11 @@
 //
 // Rank extension: adapter by adapter into the accumulators, of which only the adapter's own rows take the result over (scaled
 // in fp32).  Rows of other adapters never reach the result, so no operand has to be masked and a diverged neighbour's Inf / NaN
-// stays out of it.
+// stays out of it.  What bounds it is a pass's own chain - operands, fragments, products, selects - since nothing else runs on the CU (three passes
+// in flight instead of two were 10 % slower).  us, eight wavefronts / four that waited for fragments per row block / now: 64 x 256, contraction 256, 16
+// adapters of rank 64 forward 15.7 / 19.3 / 15.7, backward 16.6 / 14.8 / 13.8, of rank 8 13.7 / 15.2 / 13.8, 14.0 / 12.5 / 12.2; 48 adapters of rank 33 in 300
+// x 256 forward 18.8 / 19.4 / 19.1, backward with the weight gradients 26.7 / 25.4 / 18.4; 128 x 128 tiles of 2000 x 2048, contraction 512, 64 adapters of
+// rank 33 22.0 / 22.0 / 23.0, 16 of rank 128 15.2 / 16.5 / 15.9.
 //
 // us, 256 x 256 tiles / eight wavefronts that load and multiply / now: 1024 x 14336 x 4096 forward - / 112 / 102, its weight from HBM 133 / 121; 1024 x
 // 4096 x 4096 forward with eight adapters, with its shrink, - / 46.0 / 43.5; 200 x 512, k = 2048: 67 / 9.2 / 8.1.
@@ -83,6 +88,9 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
     constexpr int AT = BM * 128, BT = BN * 128;                    // bytes: operand tiles of one 64-wide step
     constexpr int NSA = kStagesA<BM, BN>, NSB = kStagesB<BM, BN>;  // ring stages
     constexpr int B0 = NSA * AT;                                   // where the weight's ring starts
+    constexpr int HELD = 2 + (2 * AT + BT - 1) / BT;               // weight stages that the passes of the rank extension use first: two of each operand
+    auto pass_a = [](int slot) { return B0 + (NSB - 2) * BT - (slot + 1) * AT; };
+    auto pass_b = [](int slot) { return B0 + (NSB - 1 - slot) * BT; };
     constexpr int NA = BM / 32, NB_ = BN / 32;                     // direct loads per multiplying wavefront and pass (rank extension, tail)
     constexpr int WTM = BM / 2, WTN = BN / 2;                      // sub-tile of a multiplying wavefront
     constexpr int MB = WTM / 16, NB = WTN / 16;
@@ -128,11 +136,11 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
     const int a_off = (wm * WTM + l16) * 128, bnt_off = (wn * WTN + l16) * 128;
     const int vq = fkey(8 * g4 + (l16 >> 2));
     const int bnn_off = (8 * g4 + (l16 >> 2)) * BROW + (l16 & 3) * 8;
-    auto frag_a = [&](int slot, int h, int a) {
-        return lds_read_frag(reinterpret_cast<const u16*>(lds + slot * AT + a_off + (((h * 4 + g4) ^ (l16 & 7)) << 4) + a * 2048));
+    auto frag_a = [&](int at, int h, int a) {
+        return lds_read_frag(reinterpret_cast<const u16*>(lds + at + a_off + (((h * 4 + g4) ^ (l16 & 7)) << 4) + a * 2048));
     };
-    auto frag_b = [&](int slot, int h, int b) {
-        const unsigned char* Bs = lds + B0 + slot * BT;
+    auto frag_b = [&](int at, int h, int b) {
+        const unsigned char* Bs = lds + at;
         if (NN) {
             const unsigned char* p = Bs + bnn_off + h * 32 * BROW + (((wn * NB + b) ^ vq) << 5);
             return lds_read_frag_tr(reinterpret_cast<const u16*>(p), reinterpret_cast<const u16*>(p + 4 * BROW));
@@ -143,8 +151,8 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
     constexpr int NF = U * (MB + NB);
     auto read_frag = [&](int slot_a, int slot_b, int h0, int set, int i) {
         const int u = i / (MB + NB), j = i % (MB + NB);
-        if (j < NB) fb[set][u][j] = frag_b(slot_b, h0 + u, j);
-        else        fa[set][u][j - NB] = frag_a(slot_a, h0 + u, j - NB);
+        if (j < NB) fb[set][u][j] = frag_b(B0 + slot_b * BT, h0 + u, j);
+        else        fa[set][u][j - NB] = frag_a(slot_a * AT, h0 + u, j - NB);
     };
     int sa = 0, sb = 0;                  // slots of the step that is read
     auto read_set = [&](int h0, int set) {
@@ -181,96 +189,145 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
     };
     const std::integral_constant<int, 0> zero{};
     const std::integral_constant<int, 1> one{};
-    // ---- passes: at most 64 contraction elements that are not a whole step (rank extension, tail), through the last two slots of each ring ----
-    // Rows outside [lo, hi) repeat the first or last one inside and columns past the edge the last ones; their results are dropped.  Chunks
-    // past kc repeat the first and are taken as zero (take_pass).  Element (row t, c) of the row operand at a[(t - lo) a_ld + c], of the weight's
-    // at b[c b_ld + col] (NN) or b[(col - n0) b_ld + c].
-    auto dma_pass = [&](int slot /* 0: the rings' last, 1: the ones before */, const void* a, int64_t a_ld, int lo, int hi, const void* b, int64_t b_ld, int kc) {
+    // ---- passes: at most 64 contraction elements that are not a whole step (rank extension, tail) ----
+    // Pieces of rows outside [lo, hi) alone and chunks past kc are not loaded: what stands there is dropped or taken as zero (take_pass); the other
+    // rows outside repeat the first or last one inside and columns past the edge the last ones.  Element (row t, c) of the row operand at a[(t - lo) a_ld + c],
+    // of the weight's at b[c b_ld + col] (NN) or b[(col - n0) b_ld + c].
+    auto dma_pass = [&](int slot, const void* a, int64_t a_ld, int lo, int hi, const void* b, int64_t b_ld, int kc) {
         const char* ab = uniform_ptr(a);
         const char* bb = uniform_ptr(b);
-        const unsigned dst_a = lds0 + (NSA - 1 - slot) * AT, dst_b = lds0 + B0 + (NSB - 1 - slot) * BT;
+        const unsigned dst_a = lds0 + pass_a(slot), dst_b = lds0 + pass_b(slot);
 #pragma unroll
-        for (int c = 0; c < NA; ++c) {
-            const int row = (wave * NA + c) * 8 + (lane >> 3), ch = (lane & 7) ^ (lane >> 3);
-            const unsigned v = (unsigned)((int64_t)(min(max(m0 + row, lo), hi - 1) - lo) * a_ld + (ch * 8 < kc ? ch : 0) * 8) * 2u;
-            dma16(v, ab, dst_a + (wave * NA + c) * 1024);
-        }
-#pragma unroll
-        for (int c = 0; c < NB_; ++c) {
+        for (int c = 0; c < NB_; ++c) {                  // (first: of many lines)
             const int kb = wave * NB_ + c;
             unsigned v;
             if (NN) {
+                if (kb * (64 / LPR) >= kc) continue;             // (uniform; kc is a multiple of 8: a piece is there or not)
                 const int k = kb * (64 / LPR) + lane / LPR, pos = lane % LPR;
                 const int chunk = (((pos >> 1) ^ fkey(k)) << 1) | (pos & 1);
-                v = (unsigned)((int64_t)(k < kc ? k : 0) * b_ld + min(n0 + chunk * 8, g.Ncols - 8)) * 2u;
+                v = (unsigned)((int64_t)k * b_ld + min(n0 + chunk * 8, g.Ncols - 8)) * 2u;
+                dma16(v, bb, dst_b + kb * 1024);
             } else {
                 const int row = kb * 8 + (lane >> 3), ch = (lane & 7) ^ (lane >> 3);
-                v = (unsigned)((int64_t)(min(n0 + row, g.Ncols - 1) - n0) * b_ld + (ch * 8 < kc ? ch : 0) * 8) * 2u;
+                v = (unsigned)((int64_t)(min(n0 + row, g.Ncols - 1) - n0) * b_ld + ch * 8) * 2u;
+                if (ch * 8 < kc) dma16(v, bb, dst_b + kb * 1024);
             }
-            dma16(v, bb, dst_b + kb * 1024);
+        }
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+            const int row0 = m0 + (wave * NA + c) * 8, ch = (lane & 7) ^ (lane >> 3);
+            if (row0 >= hi || row0 + 8 <= lo) continue;          // (uniform)
+            const unsigned v = (unsigned)((int64_t)(min(max(row0 + (lane >> 3), lo), hi - 1) - lo) * a_ld + ch * 8) * 2u;
+            if (ch * 8 < kc) dma16(v, ab, dst_a + (wave * NA + c) * 1024);
         }
     };
-    // The same for rows of r elements that start anywhere (ranks that are no multiples of 8): elements r0 .. r0 + kc - 1 of each, through registers.
-    auto stage_pass = [&](int slot, const u16* e, int lo, int hi, const u16* F, int r, int r0, int kc) {
-        unsigned char* const Pa = lds + (NSA - 1 - slot) * AT;
-        unsigned char* const Pb = lds + B0 + (NSB - 1 - slot) * BT;
-        constexpr int PT = SG_THREADS / 2;               // the multiplying wavefronts' threads
-        uint4 pa[NA], pb[NB_];
+    // The same for rows of r elements that start anywhere (ranks that are no multiples of 8): elements r0 .. r0 + kc - 1 of each, through registers, loaded while
+    // the pass before is multiplied.  A piece that would reach past its row is loaded from where it still fits (ranks below 8: past its buffer, which then
+    // has a piece; else element by element) and shifted.
+    constexpr int PT = SG_THREADS / 2;                   // the multiplying wavefronts' threads
+    uint4 pa[NA], pb[NB_];
+    int ea[NA], eb[NB_];                                 // elements to drop in front
+    auto any_piece = [&](const u16* row, int r, int at, const u16* end, bool whole, int& drop) {
+        uint4 v;
+        if (whole) {
+            const u16* const from = r >= 8 ? row + min(at, r - 8) : min(row, end - 8);
+            drop = (int)(r >= 8 ? row + at - from : row - from);
+            __builtin_memcpy(&v, from, 16);
+        } else {
+            drop = 0;
+            v = load_chunk(row, r, false);
+        }
+        return v;
+    };
+    auto load_pass = [&](const u16* e, int lo, int hi, const u16* F, int r, int r0, int kc) {
+        const bool whole = r >= 8 || g.R1 >= 8;
 #pragma unroll
         for (int c = 0; c < NA; ++c) {
             const int idx = tid + PT * c, t = min(max(m0 + (idx & (BM - 1)), lo), hi - 1), cc = idx / BM;
-            pa[c] = row_piece(e + (int64_t)(t - lo) * r, r, r0 + cc * 8);
+            if (c >= NA / 2 && kc <= 32) continue;
+            pa[c] = any_piece(e + (int64_t)(t - lo) * r, r, r0 + cc * 8, g.E + g.R1, whole, ea[c]);
         }
 #pragma unroll
         for (int c = 0; c < NB_; ++c) {
             const int idx = tid + PT * c;
+            if (c >= NB_ / 2 && kc <= 32) continue;
             if (NN) {
                 const int k = idx / (BN / 8), gcol = min(n0 + (idx % (BN / 8)) * 8, g.Ncols - 8);
-                const uint4 v = *reinterpret_cast<const uint4*>(F + (int64_t)(r0 + min(k, kc - 1)) * g.Ncols + gcol);
-                pb[c] = k < kc ? v : zero4();
+                pb[c] = *reinterpret_cast<const uint4*>(F + (int64_t)(r0 + min(k, kc - 1)) * g.Ncols + gcol);
             } else {
-                pb[c] = row_piece(F + (int64_t)min(n0 + (idx & (BN - 1)), g.Ncols - 1) * r, r, r0 + idx / BN * 8);
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < NA; ++c) {
-            const int idx = tid + PT * c, row = idx & (BM - 1), cc = idx / BM;
-            *reinterpret_cast<uint4*>(Pa + row * 128 + ((cc ^ (row & 7)) << 4)) = pa[c];
-        }
-#pragma unroll
-        for (int c = 0; c < NB_; ++c) {
-            const int idx = tid + PT * c;
-            if (NN) {
-                const int k = idx / (BN / 8), nc = idx % (BN / 8);
-                *reinterpret_cast<uint4*>(Pb + k * BROW + ((((nc >> 1) ^ fkey(k)) << 5) | ((nc & 1) << 4))) = pb[c];
-            } else {
-                const int row = idx & (BN - 1), cc = idx / BN;
-                *reinterpret_cast<uint4*>(Pb + row * 128 + ((cc ^ (row & 7)) << 4)) = pb[c];
+                pb[c] = any_piece(F + (int64_t)min(n0 + (idx & (BN - 1)), g.Ncols - 1) * r, r, r0 + idx / BN * 8, F + (int64_t)g.Ncols * r, true, eb[c]);
             }
         }
     };
-    // rows [lo, hi) of the accumulators take the products of the pass in `slot`, then times f
-    auto take_pass = [&](int slot, int kc, int lo, int hi, float f) {
-        for (int h = 0; h * 32 < kc; ++h) {
-            const bool in = h * 32 + 8 * g4 < kc;
-            const bf16x8 z = __builtin_bit_cast(bf16x8, zero4());
-            const float fh = h * 32 + 32 >= kc ? f : 1.0f;
+    auto store_pass = [&](int slot, int r, int r0, int kc) {
+        unsigned char* const Pa = lds + pass_a(slot);
+        unsigned char* const Pb = lds + pass_b(slot);
+        auto store = [&](auto in_place) __attribute__((always_inline)) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) { fb[0][0][b] = frag_b(NSB - 1 - slot, h, b); fb[0][0][b] = in ? fb[0][0][b] : z; }
+            for (int c = 0; c < NA; ++c) {
+                const int idx = tid + PT * c, row = idx & (BM - 1), cc = idx / BM;
+                if (c >= NA / 2 && kc <= 32) continue;
+                *reinterpret_cast<uint4*>(Pa + row * 128 + ((cc ^ (row & 7)) << 4)) = in_place(pa[c], ea[c], r0 + cc * 8);
+            }
+#pragma unroll
+            for (int c = 0; c < NB_; ++c) {
+                const int idx = tid + PT * c;
+                if (c >= NB_ / 2 && kc <= 32) continue;
+                if (NN) {
+                    const int k = idx / (BN / 8), nc = idx % (BN / 8);
+                    *reinterpret_cast<uint4*>(Pb + k * BROW + ((((nc >> 1) ^ fkey(k)) << 5) | ((nc & 1) << 4))) = k < kc ? pb[c] : zero4();
+                } else {
+                    const int row = idx & (BN - 1), cc = idx / BN;
+                    *reinterpret_cast<uint4*>(Pb + row * 128 + ((cc ^ (row & 7)) << 4)) = in_place(pb[c], eb[c], r0 + cc * 8);
+                }
+            }
+        };
+        if (r >= 8) store([](uint4 v, int drop, int) { return drop_front(v, drop); });
+        else        store([&](uint4 v, int drop, int at) { return keep_front(drop_front(v, drop), r - at); });
+    };
+    // rows [lo, hi) of the accumulators take the products of the pass in `slot`, then times f.  A half's fragments (128 x 128; else both halves') are read
+    // before its first product and there are no branches: with a wait per row block a pass took 1000 cycles more, and 300 more with the number of halves
+    // decided behind the first one's reads.
+    auto take_pass = [&](int slot, int kc, int lo, int hi, float f) {
+        const bf16x8 z = __builtin_bit_cast(bf16x8, zero4());
+        auto halves = [&](auto count, int h0, float times) __attribute__((always_inline)) {
+            constexpr int H = decltype(count)::value;
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) fb[h][0][b] = frag_b(pass_b(slot), h0 + h, b);
+#pragma unroll
+                for (int a = 0; a < MB; ++a) fa[h][0][a] = frag_a(pass_a(slot), h0 + h, a);
+            }
+            const bool in = (h0 + H - 1) * 32 + 8 * g4 < kc;     // (the first of two halves is whole)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) fb[H - 1][0][b] = in ? fb[H - 1][0][b] : z;
+#pragma unroll
+            for (int a = 0; a < MB; ++a) fa[H - 1][0][a] = in ? fa[H - 1][0][a] : z;
 #pragma unroll
             for (int a = 0; a < MB; ++a) {
                 const int row0 = m0 + wm * WTM + a * 16, row = row0 + l16;
-                if (row0 >= hi || row0 + 16 <= lo) continue;     // (uniform)
-                fa[0][0][a] = frag_a(NSA - 1 - slot, h, a);
-                fa[0][0][a] = in ? fa[0][0][a] : z;
+                if (MB == 4 && (row0 >= hi || row0 + 16 <= lo)) continue;        // (uniform; a pass of few rows has most of its time in the selects below)
                 const bool own = row >= lo && row < hi;
+                f32x4 t[NB];
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const f32x4 t = mfma16(fb[0][0][b], fa[0][0][a], acc[a][b]);
+                for (int b = 0; b < NB; ++b) t[b] = mfma16(fb[0][0][b], fa[0][0][a], acc[a][b]);
+                if (H == 2) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[a][b][q] = own ? fh * t[q] : acc[a][b][q];
+                    for (int b = 0; b < NB; ++b) t[b] = mfma16(fb[H - 1][0][b], fa[H - 1][0][a], t[b]);
                 }
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[a][b][q] = own ? times * t[b][q] : acc[a][b][q];
             }
+        };
+        const std::integral_constant<int, 1> single{};
+        if constexpr (MB * NB == 16) {                   // (registers for one half)
+            for (int h = 0; h * 32 < kc; ++h) halves(single, h, h * 32 + 32 >= kc ? f : 1.0f);
+        } else {
+            if (kc > 32) halves(std::integral_constant<int, 2>{}, 0, f);
+            else         halves(single, 0, f);
         }
     };
 
@@ -280,7 +337,7 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
         const Entry4 tile = g.pv.gemm_tiles[m0 / kGemmTileRows];
         first = tile.c; cand_end = tile.d;
     }
-    uint32_t* const count = reinterpret_cast<uint32_t*>(lds + (NSA - 2) * AT);     // free until the second pass is asked for
+    uint32_t* const count = reinterpret_cast<uint32_t*>(lds + pass_a(1));     // free until the second pass is asked for
 
     // ---- the loading wavefronts ---------------------------------------------------------------------
     // Wavefronts 4 and 5 load the rows.  The weight's lines are the same for the row tiles of a band, on one XCD: asked for by all of them at once, a
@@ -308,9 +365,9 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
         }
         const char* base = uniform_ptr(rows ? g.Aop + (int64_t)m0 * g.lda : NN ? g.Bop : g.Bop + (int64_t)n0 * g.ldb);
         const int64_t lstep = !rows && NN ? (int64_t)64 * g.ldb * 2 : 128;
-        // NUM loads a step, piece(c) the c-th; D steps ahead in a ring of NS
-        auto run = [&](auto num, auto ahead, auto stages, auto piece) __attribute__((always_inline)) {
-            constexpr int NUM = decltype(num)::value, D = decltype(ahead)::value, NS = decltype(stages)::value;
+        // NUM loads a step, piece(c) the c-th; D steps ahead in a ring of NS, FREE of them before the rank extension is through
+        auto run = [&](auto num, auto ahead, auto stages, auto held, auto piece) __attribute__((always_inline)) {
+            constexpr int NUM = decltype(num)::value, D = decltype(ahead)::value, NS = decltype(stages)::value, FREE = NS - decltype(held)::value;
             static_assert(NUM * D < 64 && D <= NS && D <= 16 && D > 1, "vmcnt holds 6 bits; drain steps");
             int slot = 0;
             bool extended = g.skip_lora != 0;
@@ -323,7 +380,7 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
                 }
             };
             for (int t = 0; t < nk; ++t) {
-                if (t == NS - 2 && !extended) extension();               // (it uses the last two slots)
+                if (t == FREE && !extended) extension();
                 if (t >= D) {
                     if (!extended) extension();
                     wait_loads_and_barrier<NUM * (D - 2)>();             // step t - D + 1 has landed, step t - D has been read
@@ -352,8 +409,9 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
             constexpr int P = decltype(p)::value, OWN = CB / P, REST = CB - OWN;
             const int own = tm_in & (P - 1);
             const std::integral_constant<int, NSB> ring{};
-            if (wave == 6) run(std::integral_constant<int, OWN>{}, std::integral_constant<int, (NSB * OWN < 64 ? NSB : 63 / OWN)>{}, ring, [=](int c) { return c * P + own; });
-            else           run(std::integral_constant<int, REST>{}, std::integral_constant<int, D_REST>{}, ring, [=](int c) { return c / (P - 1) * P + ((own + 1 + c % (P - 1)) & (P - 1)); });
+            const std::integral_constant<int, HELD> held{};
+            if (wave == 6) run(std::integral_constant<int, OWN>{}, std::integral_constant<int, (NSB * OWN < 64 ? NSB : 63 / OWN)>{}, ring, held, [=](int c) { return c * P + own; });
+            else           run(std::integral_constant<int, REST>{}, std::integral_constant<int, D_REST>{}, ring, held, [=](int c) { return c / (P - 1) * P + ((own + 1 + c % (P - 1)) & (P - 1)); });
         };
         if (nk == 0) {
             for (int f = first; f < cand_end && !g.skip_lora; f += 64) {
@@ -362,7 +420,7 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
                 for (int q = 0; q <= passes; ++q) lds_barrier();
             }
         } else if (rows) {
-            run(std::integral_constant<int, CA / 2>{}, std::integral_constant<int, NSA>{}, std::integral_constant<int, NSA>{}, [=](int c) { return (wave & 1) * (CA / 2) + c; });
+            run(std::integral_constant<int, CA / 2>{}, std::integral_constant<int, NSA>{}, std::integral_constant<int, NSA>{}, std::integral_constant<int, 0>{}, [=](int c) { return (wave & 1) * (CA / 2) + c; });
         } else if (band_rows >= 8) {
             share(std::integral_constant<int, 8>{});
         } else if (band_rows >= 4) {
@@ -391,7 +449,8 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
                 return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)v, l);
             };
             int r0 = 0;                            // ranks of the lowest adapter in todo that have been asked for
-            int lo = 0, hi = 0, kc = 0;            // of the pass asked for last
+            int lo = 0, hi = 0, kc = 0, pr = 0, pr0 = 0;         // of the pass asked for last; rank of its adapter and first of its ranks
+            bool staged = false;                   // it comes through registers
             float f = 1.0f;
             auto request = [&](int slot) {
                 const int l = (int)__builtin_ctzll(todo);
@@ -402,14 +461,17 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
                 const int64_t so = (int64_t)lane64((uint64_t)v_so, l);
                 const u16* F = global_ptr<const u16>(reinterpret_cast<const void*>(lane64(v_f, l)));
                 const u16* e = g.E + so + (int64_t)(lo - seg0) * r;
-                if ((r & 7) == 0 && (so & 7) == 0) dma_pass(slot, e + r0, r, lo, hi, NN ? F + (int64_t)r0 * g.Ncols : F + (int64_t)n0 * r + r0, NN ? g.Ncols : r, kc);
-                else                               stage_pass(slot, e, lo, hi, F, r, r0, kc);
+                pr = r; pr0 = r0;
+                staged = (r & 7) != 0 || (so & 7) != 0;
+                if (staged) load_pass(e, lo, hi, F, r, r0, kc);
+                else        dma_pass(slot, e + r0, r, lo, hi, NN ? F + (int64_t)r0 * g.Ncols : F + (int64_t)n0 * r + r0, NN ? g.Ncols : r, kc);
                 const bool last = r0 + 64 >= r;
                 f = last ? __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v_sc), l)) : 1.0f;
                 if (last) { todo &= todo - 1; r0 = 0; }
                 else r0 += 64;
             };
             if (todo) request(0);
+            if (passes > 0 && staged) store_pass(0, pr, pr0, kc);
             if (tid == 0) *count = (uint32_t)passes;
             lds_barrier();                         // the loading wavefronts read it
             for (int q = 0; q < passes; ++q) {
@@ -417,7 +479,9 @@ __global__ __launch_bounds__(SG_THREADS) void small_gemm_kernel(GemmArgs g, Besi
                 const float p_f = f;
                 wait_loads_and_barrier<0>();       // pass q is here, everybody is done with pass q - 1
                 if (todo) request(slot ^ 1);
+                if (MB * NB == 16 && q + 1 < passes && staged) store_pass(slot ^ 1, pr, pr0, kc);      // (not enough registers to multiply meanwhile)
                 take_pass(slot, p_kc, p_lo, p_hi, p_f);
+                if (MB * NB < 16 && q + 1 < passes && staged) store_pass(slot ^ 1, pr, pr0, kc);
             }
             lds_barrier();                         // the passes have been read
         }
