@@ -174,7 +174,7 @@ namespace mlora {
 // Whether the plan's tiled shrink (fwd) or gradient shrink deals undivided row blocks out by halves, and into how many shares it divides their
 // contraction: what the launches do and what plan creation holds memory for.
 inline bool shrink_by_halves(const mlora_plan* p, bool fwd) {
-    return p->n_blocks_wide == 0 && 2 * p->n_blocks_narrow <= p->num_cus && !(fwd && !p->ranks_mult8);
+    return p->n_blocks_wide == 0 && 2 * p->n_blocks_narrow <= p->num_cus && !(fwd && !p->ranks_mult8) && (fwd ? p->k : p->n) >= 256;
 }
 inline int shrink_splits(const mlora_plan* p, bool fwd) {
     return shrink_splits((int64_t)p->n_blocks_wide + p->n_blocks_narrow, fwd ? p->k : p->n, p->num_cus, p->n_blocks_wide != 0,

@@ -547,7 +547,9 @@ __global__ __launch_bounds__(64 * SNW) void shrink_tiled_kernel(ShrinkArgs g) {
 // Launches of no more than half as many blocks as there are CUs whose contraction is not divided (ranks up to 64, multiples of 8): a work group
 // takes 32 rows of a block, 12 KB through the CU's load path per step instead of 16, and twice as many CUs load.  A row's sum is the
 // same chain.  us, forward calls with products of 256 columns, 64 rows / 32: 8192 tokens, k = 2560, ranks 8 and 64 33.8 / 31.5; 8192 x 2048 27.2 /
-// 26.3; 4001 x 1792 20.4 / 19.9; 1024 x 1024 14.2 / 13.6.  With sixteen or fewer ranks 0.1-0.3 less.
+// 26.3; 4001 x 1792 20.4 / 19.9; 1024 x 1024 14.2 / 13.6.  With sixteen or fewer ranks 0.1-0.3 less.  Not below four steps, where the loads that only fill the
+// longer ring count: 16 segments of 31 tokens, the launch, k = 64 4.0 / 4.2, 128 4.15 / 4.4, 192 4.4 / 4.65, 512 5.4 / 5.4; 4000 tokens, ranks 8 and 64, 128 4.2 / 4.2,
+// 256 4.9 / 4.5, 512 5.95 / 5.65.
 template <bool FWD>
 __global__ __launch_bounds__(64 * SNW) void shrink_halves_kernel(ShrinkArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[147456];
