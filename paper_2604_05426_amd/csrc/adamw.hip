@@ -9,9 +9,11 @@
 // block with 19.7 M bf16 parameters: 156 us with a table upload per launch and the grid sized by the largest rank, 121 now (4.5 TB/s; a
 // device copy reaches 5.0).
 // The state, 24 of the 28 bytes, goes past the caches (non-temporal): nobody reads it before the next step, and what it pushed out of the Infinity
-// Cache were the frozen weights and activations that the next kernels read.  The launches themselves take the same time, the steps of a block of
-// 79 to 1124 tokens 3 to 6 % less (360 tokens, rank 64: 1074 -> 1021 us); the state of a single layer, 0.1 to 28 MB, updated again and again 9.8 to 14.9 us as
-// before, 226 MB of it 80.8 -> 83.8.
+// Cache were the frozen weights and activations that the next kernels read: the steps of a block of 79 to 3000 tokens take 1 to 5 % less (360 tokens, rank 64:
+// 1222 -> 1164 us).  Not where all of a step has room in the 256 MB of that cache, which a plan can only know of a layer that is by itself: state, operands,
+// gradients, weight and activations below that, and no other plan over its tables.  us, one layer's step, cached / past, state (all of it): 50 MB (134)
+// 120.2 / 124.0 and 114.9 / 118.7, 101 MB (235) 213.8 / 217.4; 113 MB (343) 330 / 324, 142 MB (381) 368 / 349, 201 MB (368) 296 / 290, 453 MB (840) 1062 /
+// 1034.  (The update by itself, over and over, is faster cached up to 226 MB, 74.8 / 84.1; no training does that.)
 #include <cmath>
 #include <cstring>
 
@@ -51,8 +53,8 @@ template <> __device__ inline void stp<uint16_t>(uint16_t* p, float v) {
 typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // INIT: master <- parameter, m = v = 0.  Otherwise one AdamW step.  (All buffers may start at any element: a piece is loaded and
-// stored as bytes, which global memory takes at any alignment.)
-template <typename T, bool INIT>
+// stored as bytes, which global memory takes at any alignment.)  PAST: the state goes past the caches.
+template <typename T, bool INIT, bool PAST = true>
 __global__ __launch_bounds__(256) void adamw_kernel(AdamwBatch batch, int32_t count, int64_t k, int64_t n) {
     const int32_t wg = blockIdx.x;
     int32_t lo = 0, hi = count;              // the first adapter whose matrices end behind this work group
@@ -77,6 +79,14 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamwBatch batch, int32_t co
     };
     const int64_t base = (int64_t)(wg - first) * kRun + threadIdx.x * 4;
     struct T4 { T t[4]; };
+    auto load = [](const float* at) {
+        const f32x4a4* const src = reinterpret_cast<const f32x4a4*>(at);
+        return PAST ? __builtin_nontemporal_load(src) : *src;
+    };
+    auto store = [](f32x4a4 x, float* at) {
+        f32x4a4* const dst = reinterpret_cast<f32x4a4*>(at);
+        if (PAST) __builtin_nontemporal_store(x, dst); else *dst = x;
+    };
     if (base + 3 * 1024 + 4 <= numel) {
         T4 g[4];
         f32x4a4 th[4], m[4], v[4];
@@ -87,9 +97,9 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamwBatch batch, int32_t co
                 __builtin_memcpy(&g[u], param + idx, sizeof(T4));
             } else {
                 __builtin_memcpy(&g[u], grad + idx, sizeof(T4));
-                th[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4a4*>(master + idx));
-                m[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4a4*>(mm + idx));
-                v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4a4*>(vv + idx));
+                th[u] = load(master + idx);
+                m[u] = load(mm + idx);
+                v[u] = load(vv + idx);
             }
         }
 #pragma unroll
@@ -105,9 +115,9 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamwBatch batch, int32_t co
                 th[u][c] = tc; m[u][c] = mc; v[u][c] = vc;
                 stp<T>(&p.t[c], tc);
             }
-            __builtin_nontemporal_store(th[u], reinterpret_cast<f32x4a4*>(master + idx));
-            __builtin_nontemporal_store(m[u], reinterpret_cast<f32x4a4*>(mm + idx));
-            __builtin_nontemporal_store(v[u], reinterpret_cast<f32x4a4*>(vv + idx));
+            store(th[u], master + idx);
+            store(m[u], mm + idx);
+            store(v[u], vv + idx);
             if (!INIT) __builtin_memcpy(param + idx, &p, sizeof(T4));
         }
     } else {
@@ -156,6 +166,10 @@ static int run(mlora_plan* p, void* const* A, void* const* B, const void* const*
             }
         }
     }
+    int64_t params = 0;
+    for (int32_t i = 0; i < p->N; ++i) params += p->ranks[i] * (p->k + p->n);
+    const int64_t element = p->dtype == MLORA_F32 ? 4 : 2, whole_step = params * (12 + 2 * element) + (p->k * p->n + 2 * p->T * (p->k + p->n)) * element;
+    const bool cached = !p->shares_tables && p->blocks.front().use_count() == 1 && whole_step < 256000000;
     auto groups = [](int64_t numel) { return (numel + kRun - 1) / kRun; };
     for (int32_t base = 0; base < p->N;) {
         AdamwBatch batch;
@@ -189,7 +203,9 @@ static int run(mlora_plan* p, void* const* A, void* const* B, const void* const*
         const dim3 grid((unsigned)total);
         if (init && f32)       hipLaunchKernelGGL((adamw_kernel<float, true>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
         else if (init)         hipLaunchKernelGGL((adamw_kernel<uint16_t, true>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
+        else if (f32 && cached) hipLaunchKernelGGL((adamw_kernel<float, false, false>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
         else if (f32)          hipLaunchKernelGGL((adamw_kernel<float, false>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
+        else if (cached)       hipLaunchKernelGGL((adamw_kernel<uint16_t, false, false>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
         else                   hipLaunchKernelGGL((adamw_kernel<uint16_t, false>), grid, dim3(256), 0, st, batch, cnt, p->k, p->n);
     }
     MLORA_HIP_TRY(hipGetLastError());
