@@ -931,7 +931,7 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
 // (534, 6.4) 40.0 / 35.3, 256 x 257 x 256 (105, 0.4) 15.2 / 12.0, 1600 x 2048 x 1001 (1600, 3.5) 47.0 / 41.9, 2000 x 100 x 333 (2000, 1.0) 23.0 / 19.2;
 // not: 2000 x 1001 x 300 (2000, 2.1) 25.9 / 27.9, 3200 x 300 x 777 (1600, 1.1) 27.4 / 29.5, 6000 x 1001 x 2048 (1617, 10.4) 79.6 / 83.2, 6000 x 1001 x 300
 // (1617, 6.4) 39.0 / 42.2, 6000 x 100 x 333 (4241, 0.9) 36.5 / 42.9, 8000 x 1001 x 300 (6444, 8.9) 66.5 / 82.8.  Over 398 shapes a
-// call takes 4.5 % more than the better of the two on average (always apart 14.4 %), and at most 4.5 % more than apart; what the limit of ten work groups a CU
+// call takes 4.0 % more than the better of the two on average (always apart 14.4 %), and at most 4.1 % more than apart; what the limit of ten work groups a CU
 // leaves apart would take up to a third less together (127 x 1232 x 553, 24 adapters 45.0 / 29.6).
 bool beside_product(const mlora_plan* p, const GenWgradArgs<u16>& w, int64_t groups, int64_t K) {
     const int64_t all = groups + (int64_t)w.panels * p->N * ((p->max_rank + 15) / 16);
@@ -990,9 +990,9 @@ int gemm(mlora_plan* p, const void* A, const void* W, void* C, const void* E, ui
         // 128 x 64 tiles (forward) by what both take in us: a work group of 128 x 64, alone on its CU, waits for every pass with nothing else to run.  us, 64 x 64 /
         // 128 x 64, tokens x outputs x contraction (passes a tile of 64, 128 rows): 1500 x 1001 x 2048 (1.2, 1.4) 28.9 / 25.4, 4000 x 1001 x 2048 (1.5,
         // 2.0) 52.5 / 49.8, 2000 x 1001 x 700 (3.8, 6.3) 38.0 / 41.2, 2000 x 2001 x 130 (3.1, 5.3) 32.6 / 45.8, 4000 x 1001 x 700 (3.7, 6.4) 55.4 / 65.3;
-        // without extension 1500 x 1001 x 300 8.6 / 7.5, 4611 x 4018 x 729 77 / 99, 8000 x 1001 x 700 35.4 / 38.7.  Over 500 forward calls the choice takes
-        // 0.4 % longer than the best of these and the others, 12 % at worst (by rounds and steps alone 4.8 and 59 %).  Backward (both operands
-        // from rows that start anywhere) 1500 x 2048 x 1001 20.6 / 25.1, 4000 x 2048 x 1001 46.9 / 48.4.
+        // without extension 1500 x 1001 x 300 8.6 / 7.5, 4611 x 4018 x 729 77 / 99, 8000 x 1001 x 700 35.4 / 38.7.  Over 478 forward calls the choice takes
+        // 0.5 % longer on average than the best of these and the others (by rounds and steps alone 4.8).  Backward (both operands from rows that start
+        // anywhere) 1500 x 2048 x 1001 20.6 / 25.1, 4000 x 2048 x 1001 46.9 / 48.4.
         const int64_t tall = (a.M + 127) / 128 * a.tiles_n;
         auto rounds = [&](int64_t n) { return (double)((n + p->num_cus - 1) / p->num_cus); };
         const bool wide = FWD && rounds(tall) * (3.5 + 0.45 * steps + 0.8 * passes(7)) < 2.5 + rounds(groups) * (0.5 + 0.28 * steps + 0.3 * passes(6));

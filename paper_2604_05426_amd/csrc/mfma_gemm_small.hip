@@ -588,10 +588,11 @@ static void launch_small(GemmArgs g, bool fwd, const WgradArgs* w, int items, in
 // rounds = tiles over CUs, rounded up.  The step times are what the kernels sustain with all CUs busy (64-wide step; the
 // 256 x 256 kernel moves the fewest bytes per product and wins wherever its last round is not too empty).  They are those of the kernel before
 // its wavefronts were divided: with what it sustains now (0.44, 0.275, 0.175) more products went to small tiles, which does not fit launches that
-// leave CUs to the 256 x 256 kernel's clock (2249 x 3840 x 8448 206 -> 232 us, 2927 tokens through an 8B block 2.51 -> 2.83 ms).  Over 192 products
-// (64 .. 16384 tokens, widths 512 .. 14336, both directions) the choice takes 0.1 % longer in all than the best of the four, 11 % at worst.
-// Measured (us, 256 x 256 / 128 x 128 / 64 x 128 / 64 x 64, tokens x outputs x contraction): 1000 x 4096 x 4096  86 / 41 / 56 / 81;
-// 1000 x 1024 x 4096  81 / 34 / 28 / 23;  200 x 512 x 2048  67 / 25 / 18 / 14;  4000 x 4096 x 4096  110 / 157 / 220 / 300.
+// leave CUs to the 256 x 256 kernel's clock (2249 x 3840 x 8448 206 -> 232 us, 2927 tokens through an 8B block 2.51 -> 2.83 ms).  Over 192 products of the
+// present kernels (64 .. 16384 tokens, widths 512 .. 14336, both directions) the choice takes 0.4 % longer on average than the best of the four, 10 % at
+// worst (8192 x 1000 x 1096 backward 34.2 / 37.8).  Measured (us, launches timed singly, about 5 of them the events': 256 x 256 / 128 x 128 / 64 x 128 / 64 x 64, tokens
+// x outputs x contraction, forward): 1000 x 4096 x 4096  82 / 37 / 47 / 65;  1000 x 1024 x 4096  81 / 30 / 23 / 20;  200 x 512 x 2048  67 / 24 / 16 / 13.5;
+// 4000 x 4096 x 4096  103 / 128 / 164 / 230.
 int small_gemm_tile(int64_t M, int64_t N, int64_t K, int num_cus) {
     struct { int bm, bn; double launch, round, step; } const tab[4] = {
         {256, 256, 3.0, 4.5, 1.45}, {128, 128, 4.0, 2.5, 0.48}, {64, 128, 4.0, 2.0, 0.32}, {64, 64, 3.5, 2.0, 0.225}};
