@@ -34,7 +34,7 @@ template <typename T> struct GenShrinkArgs {
     const T* src; int64_t ld;     // X (ld k) or dY (ld n); the contraction has ld elements
     T* out;                       // ragged S or dS
     int32_t rank_items;           // work groups along the ranks, 16 NB each
-    int32_t apart;                // these one after the other instead of side by side
+    int32_t order;                // 0: these side by side, 1: one after the other, 2: side by side, all blocks' first 16 rows before the others
     PlanView pv;
 };
 
@@ -47,12 +47,16 @@ __global__ __launch_bounds__(512) void general_shrink_kernel(GenShrinkArgs<T> g)
     const int l16 = lane & 15, g4 = lane >> 4;
     const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, groups = (int64_t)g.pv.n_row_blocks * 4;
     if (item >= groups * g.rank_items) return;
-    const int64_t wg = g.apart ? item % groups : item / g.rank_items;
-    const Entry4 e = g.pv.row_blocks[wg >> 2];
-    const int sub = (wg & 3) * 16, rows = min(16, e.d - sub);
+    auto quotient = [](int64_t a, int64_t b) { return ((a | b) >> 32) == 0 ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b; };     // (64-bit ones cost 0.2 us a launch)
+    const int64_t over = quotient(item, g.order == 1 ? groups : g.rank_items);
+    const int64_t wg = g.order == 1 ? item - over * groups : over;
+    const int64_t rank_item = g.order == 1 ? over : item - over * g.rank_items;
+    const int64_t place = g.order == 2 ? quotient(wg, g.pv.n_row_blocks) : wg & 3;
+    const Entry4 e = g.pv.row_blocks[g.order == 2 ? wg - place * g.pv.n_row_blocks : wg >> 2];
+    const int sub = (int)place * 16, rows = min(16, e.d - sub);
     if (rows <= 0) return;
     const int i = e.a, row0 = e.c + sub;
-    const int r = g.pv.rank[i], rho0 = (int)(g.apart ? item / groups : item % g.rank_items) * (16 * NB), rl = min(r - rho0, 16 * NB);      // this work group's ranks
+    const int r = g.pv.rank[i], rho0 = (int)rank_item * (16 * NB), rl = min(r - rho0, 16 * NB);      // this work group's ranks
     if (rl <= 0) return;
     const float s = FWD ? 1.0f : g.pv.scale[i];
     const T* F = global_ptr<const T>(FWD ? g.pv.ptrs[i].A : g.pv.ptrs[i].B) + (FWD ? (int64_t)rho0 : rho0 * g.ld);
@@ -906,17 +910,22 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     // time over apart's in 396 shapes (256 .. 8000 tokens, contractions 520 .. 4095, both directions), fp32 and bf16: even, more than half of the items empty
     // 1.11, 1.07 (8 items to 1.65); even and full 1.02, 1.01 (64 MB, ranks 64 0.91); odd and full 1.03, 1.02 (ranks 100, 8 MB 1.14; ranks 33, 33 and 65 MB
     // 0.95, 0.93 of a call); odd, more than half empty 0.98, 0.96 (three items from 0.66).  The rule takes 0.5 % longer than the better of the two, 14 % at worst.
-    auto mostly_full = [&]() {
-        int64_t all = 0, full = 0;
-        for (int32_t i = 0; i < p->N; ++i) {
-            const int64_t rows = p->ranks[i] > 0 ? p->off[i + 1] - p->off[i] : 0;
-            all += rows * a.rank_items;
-            full += rows * ((p->ranks[i] + 16 * nb - 1) / (16 * nb));
-        }
-        return 5 * full >= 3 * all;
-    };
+    // Short segments fill the first of a block's four places alone, and the work groups that have rows would all be on some of the XCDs and of their shader engines:
+    // with no more than half of the places filled the first ones of all blocks stand together, from ten blocks on.  us a call, side by side / apart / so: fp32 forward
+    // 160 tokens, 32 adapters of ranks 16 to 128, contraction 909 27.2 / 28.6 / 21.8, 576, 24, 4 to 33, 2677 23.4 / 23.4 / 17.0; bf16 backward 480, 32, 64, 3279
+    // 82.1 / 82.9 / 67.3; not 104, 8, 32, 524 11.7 / 11.8 / 12.3.  495 such calls, over the best of the three: by the rule above fp32 1.04, bf16 1.02, now
+    // 1.004 and 1.006, 1.05 and 1.06 at worst.
+    int64_t places = 0, all = 0, full = 0;
+    for (int32_t i = 0; i < p->N; ++i) {
+        const int64_t rows = p->ranks[i] > 0 ? p->off[i + 1] - p->off[i] : 0;
+        places += (rows + 15) / 16;
+        all += rows * a.rank_items;
+        full += rows * ((p->ranks[i] + 16 * nb - 1) / (16 * nb));
+    }
+    const bool mostly_full = 5 * full >= 3 * all;
     const int64_t bytes = p->T * a.ld * (int64_t)sizeof(T);
-    a.apart = (a.rank_items & 1) == 0 ? bytes < 50000000 || !mostly_full() : bytes < 30000000 && mostly_full();
+    const bool apart = (a.rank_items & 1) == 0 ? bytes < 50000000 || !mostly_full : bytes < 30000000 && mostly_full;
+    a.order = a.rank_items > 1 && 2 * places <= groups ? (p->n_row_blocks >= 10 ? 2 : 0) : apart ? 1 : 0;
     const dim3 grid = two_dims(groups * a.rank_items);
     if (nb == 1)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1>), grid, dim3(512), 0, st, a);
     else if (nb == 4) hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 4>), grid, dim3(512), 0, st, a);

@@ -31,3 +31,11 @@ def test_order_of_the_rank_items(dtype, rank):
     """Three or seven items of 16 ranks: one after the other where the adapter is alone, side by side with neighbours that leave most of them empty; a
     neighbour whose rank makes their number even."""
     _same_bits(dtype, 391, 520, rank, [([(4, 500)], [(8, 300)]), ([(64 if rank < 64 else 128, 70)], [(3, 150)])], rows=90)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rank", [17, 48, 100])
+def test_order_of_short_segments(dtype, rank):
+    """All blocks' first 16 rows before the others: an adapter with rows in all four places among short ones that have few, and a short one by itself."""
+    _same_bits(dtype, 391, 520, rank, [([(4, 2)] * 10, [(7, 3)] * 10), ([(8, 17)] + [(64, 1)] * 9, [(128, 16)] * 15)], rows=90)
+    _same_bits(dtype, 391, 520, rank, [([(4, 500)], [(8, 300)]), ([], [(rank, 70)])], rows=13)
