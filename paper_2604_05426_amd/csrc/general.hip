@@ -908,7 +908,8 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     // an even number of items the higher ones, empty for most adapters, would all be on the same ones; with ranks that fill them a number of neighbours on an
     // XCD want the same slice of the adapter's matrix, which is worth more as long as the rows' second reading comes from the L2s (32 MB in all).  Side by side's
     // time over apart's in 396 shapes (256 .. 8000 tokens, contractions 520 .. 4095, both directions), fp32 and bf16: even, more than half of the items empty
-    // 1.11, 1.07 (8 items to 1.65); even and full 1.02, 1.01 (64 MB, ranks 64 0.91); odd and full 1.03, 1.02 (ranks 100, 8 MB 1.14; ranks 33, 33 and 65 MB
+    // 1.11, 1.07 (8 items to 1.65); even and full 1.02, 1.01 (64 MB, ranks 64 0.91; backward, where a slice is whole lines of B_i, fp32
+    // to 12 MB 1.02, 24 to 50 MB 0.98: 2880 tokens, 32 adapters of rank 64, 1320 -> 3952 the step 571 / 565 us); odd and full 1.03, 1.02 (ranks 100, 8 MB 1.14; ranks 33, 33 and 65 MB
     // 0.95, 0.93 of a call); odd, more than half empty 0.98, 0.96 (three items from 0.66).  The rule takes 0.5 % longer than the better of the two, 14 % at worst.
     // Short segments fill the first of a block's four places alone: every fourth work group has rows.  (Turning the places so that these are on all XCDs gained nothing.)
     // With no more than half of the places filled the first ones of all blocks stand together, from ten blocks on.  us a call, side by side / apart / so: fp32 forward
@@ -924,7 +925,7 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     }
     const bool mostly_full = 5 * full >= 3 * all;
     const int64_t bytes = p->T * a.ld * (int64_t)sizeof(T);
-    const bool apart = (a.rank_items & 1) == 0 ? bytes < 50000000 || !mostly_full : bytes < 30000000 && mostly_full;
+    const bool apart = (a.rank_items & 1) == 0 ? bytes < (FWD ? 50000000 : 20000000) || !mostly_full : bytes < 30000000 && mostly_full;
     a.order = a.rank_items > 1 && 2 * places <= groups ? (p->n_row_blocks >= 10 ? 2 : 0) : apart ? 1 : 0;
     const dim3 grid = two_dims(groups * a.rank_items);
     if (nb == 1)      hipLaunchKernelGGL((general_shrink_kernel<T, FWD, 1>), grid, dim3(512), 0, st, a);
