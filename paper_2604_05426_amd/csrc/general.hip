@@ -909,8 +909,8 @@ int shrink(mlora_plan* p, const void* src, void* out, hipStream_t st) {
     // XCD want the same slice of the adapter's matrix, which is worth more as long as the rows' second reading comes from the L2s (32 MB in all).  Side by side's
     // time over apart's in 396 shapes (256 .. 8000 tokens, contractions 520 .. 4095, both directions), fp32 and bf16: even, more than half of the items empty
     // 1.11, 1.07 (8 items to 1.65); even and full 1.02, 1.01 (64 MB, ranks 64 0.91; backward, where a slice is whole lines of B_i, fp32
-    // to 12 MB 1.02, 24 to 50 MB 0.98: 2880 tokens, 32 adapters of rank 64, 1320 -> 3952 the step 571 / 565 us); odd and full 1.03, 1.02 (ranks 100, 8 MB 1.14; ranks 33, 33 and 65 MB
-    // 0.95, 0.93 of a call); odd, more than half empty 0.98, 0.96 (three items from 0.66).  The rule takes 0.5 % longer than the better of the two, 14 % at worst.
+    // to 12 MB 1.02, 24 to 50 MB 0.98: 2880 tokens, 32 adapters of rank 64, 1320 -> 3952 the step 565 / 571 us); odd and full 1.03, 1.02 (ranks 100, 8 MB 1.14;
+    // ranks 33, 33 and 65 MB 0.95, 0.93 of a call); odd, more than half empty 0.98, 0.96 (three items from 0.66).  The rule takes 0.5 % longer than the better of the two, 14 % at worst.
     // Short segments fill the first of a block's four places alone: every fourth work group has rows.  (Turning the places so that these are on all XCDs gained nothing.)
     // With no more than half of the places filled the first ones of all blocks stand together, from ten blocks on.  us a call, side by side / apart / so: fp32 forward
     // 160 tokens, 32 adapters of ranks 16 to 128, contraction 909 27.2 / 28.6 / 21.8, 576, 24, 4 to 33, 2677 23.4 / 23.4 / 17.0; bf16 backward 480, 32, 64, 3279
